@@ -1181,7 +1181,7 @@ int check_opts(const celeste_fit_opts* o) {
 int fit_grid(celeste_ctx* ctx, const Packed& P) {
   int bpc = ctx->persistent;
   if (bpc < 0) {
-    HIPCHK(eval_full_blocks_per_cu(ctx->block, full_variant(ctx), P.prof.n_exp, P.prof.n_dev, &bpc));
+    HIPCHK(eval_full_blocks_per_cu(ctx->block, full_variant(ctx), ctx->tile_log2, P.prof.n_exp, P.prof.n_dev, &bpc));
     bpc = std::max(1, bpc);
   }
   ctx->pgrid = ctx->n_cu * bpc;

@@ -17,10 +17,10 @@
 // (e_axis, e_angle, e_scale) once per pixel with per-image coefficients of dW/deta.
 //
 // Work that is exactly zero is skipped, never approximated: a mixture component whose
-// exponent is below -160 on every lane of a wavefront has density exactly 0 in FP32
-// there (2^-160 is far below the smallest subnormal), so all its contributions are
-// exactly 0 and the wavefront branches over it.  Lanes of a tile that fall outside the
-// image evaluate a point far from every component with a zero count and zero
+// exponent is below the exact-zero threshold on every lane of a wavefront has density exactly 0 in
+// FP32 there, so all its contributions are exactly 0.  For the galaxy components of k_eval_full that is
+// decided before any is evaluated, one component per lane, from the tile's box (tiles.h).  Lanes of a
+// tile that fall outside the image evaluate a point far from every component with a zero count and zero
 // background variance, which makes every one of their terms exactly 0 as well.
 //
 // Accumulation: the ELBO value is accumulated per lane in FP64.  The gradient and the
@@ -33,14 +33,13 @@
 #include <algorithm>
 
 #include "celeste_internal.h"
+#include "tiles.h"
 
 namespace celeste {
 
 namespace {
 
 using namespace tab;
-
-__device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // log(1 + u) for u >= 0.  Below u = 1/2: log(1 + u) = 2 atanh(s), s = u / (2 + u) <= 1/5, by the
 // series 2 (s + s^3/3 + s^5/5 + s^7/7 + s^9/9) (the first omitted term is below 1e-8 of the sum),
@@ -85,14 +84,36 @@ __device__ __forceinline__ void zero(GalAcc& A) {
   for (int i = 0; i < 5; ++i) A.b4[i] = 0.f;
 }
 
+// The fields of a galaxy component's record that the Hermite moments read, copied out of the table so
+// that the next component's loads can be issued while one is evaluated.
+struct GalRec {
+  float v[20];
+};
+
+__device__ __forceinline__ GalRec load_rec(const float* __restrict__ r) {
+  GalRec g;
+#pragma unroll
+  for (int i = 0; i < 20; ++i) g.v[i] = r[i];
+  return g;
+}
+
+struct StarRec {
+  float v[9];
+};
+
+__device__ __forceinline__ StarRec load_star(const float* __restrict__ r) {
+  StarRec g;
+#pragma unroll
+  for (int i = 0; i < 9; ++i) g.v[i] = r[i];
+  return g;
+}
+
 // One galaxy component: N and the Hermite polynomials H1..H4 of b = P d,
-// i.e. the derivatives of N with respect to its mean up to order 4.  Returns false (the same
-// on every lane) when the component is exactly 0 on the whole tile and was skipped.
-__device__ __forceinline__ bool gal_comp(const float* __restrict__ r, float dx, float dy, float dxx, float dxy,
-                                         float dyy, float e_zero, GalAcc& A) {
-  const float e = fmaf(r[R_QXX], dxx, fmaf(r[R_QXY], dxy, fmaf(r[R_QYY], dyy, r[R_C0])));
-  if (!wave_any(e >= e_zero)) return false;
-  const float N = ex2(e);
+// i.e. the derivatives of N with respect to its mean up to order 4.
+__device__ __forceinline__ void gal_comp(const GalRec& g, float dx, float dy, float dxx, float dxy, float dyy,
+                                         GalAcc& A) {
+  const float* r = g.v;
+  const float N = ex2(fmaf(r[R_QXX], dxx, fmaf(r[R_QXY], dxy, fmaf(r[R_QYY], dyy, r[R_C0]))));
   const float Pxx = r[R_PXX], Pxy = r[R_PXY], Pyy = r[R_PYY];
   const float bx = fmaf(Pxx, dx, Pxy * dy);
   const float by = fmaf(Pxy, dx, Pyy * dy);
@@ -129,7 +150,6 @@ __device__ __forceinline__ bool gal_comp(const float* __restrict__ r, float dx, 
   A.b4[2] = fmaf(Nn2, h42, A.b4[2]);
   A.b4[3] = fmaf(Nn2, h43, A.b4[3]);
   A.b4[4] = fmaf(Nn2, h44, A.b4[4]);
-  return true;
 }
 
 // acc += density of one component (value path).  No exact-zero skip here: one exp costs less
@@ -138,79 +158,6 @@ __device__ __forceinline__ bool gal_comp(const float* __restrict__ r, float dx, 
 __device__ __forceinline__ void gal_value(const float* __restrict__ r, float dxx, float dxy, float dyy, float& acc) {
   acc += ex2(fmaf(r[R_QXX], dxx, fmaf(r[R_QXY], dxy, fmaf(r[R_QYY], dyy, r[R_C0]))));
 }
-
-// Pixel -> lane layout of a work item.  Unpacked (tile width 16, 32 or 64): a grid of
-// tw x (64 / tw) tiles over the item's rows; lanes past the image edge are dead.  Packed (tile
-// width 8): the item's rows as 8-row bands (the image's last band may be shorter), each band's
-// pixels in column-major order and the bands back to back; a tile is 64 consecutive pixels of
-// that order, an 8 x 8 square except where it wraps from one band into the next, and only the
-// item's last tile has dead lanes.  Bands are row_begin + 8 b for a dense item and the kept
-// blocks kept[row_begin + b] for a subsampled one.
-struct TileMap {
-  bool packed;
-  int w, rb, tw_log2, th_log2, tiles_x, q_log2, row_lim, row_safe, n_tiles;
-  int nb, hl, bw, npx;
-  float inv_bw, inv_hl;
-  const int* kept;
-
-  __device__ __forceinline__ TileMap(const WorkItem& wi, int w_, int h, int tw_log2_, const int* kept_) {
-    w = w_;
-    rb = wi.row_begin;
-    kept = kept_;
-    tw_log2 = tw_log2_;
-    th_log2 = 6 - tw_log2;
-    packed = tw_log2 == 3;
-    row_lim = kept ? h : wi.row_end;
-    row_safe = kept ? 0 : wi.row_begin;
-    tiles_x = (w + (1 << tw_log2) - 1) >> tw_log2;
-    q_log2 = 3 - th_log2;
-    nb = kept ? wi.row_end - wi.row_begin : (wi.row_end - wi.row_begin + 7) >> 3;
-    const int r_last = kept ? kept[wi.row_end - 1] : wi.row_begin + ((nb - 1) << 3);
-    hl = min(8, row_lim - r_last);
-    bw = w << 3;
-    npx = (nb - 1) * bw + hl * w;
-    inv_bw = 1.0f / (float)bw;
-    inv_hl = 1.0f / (float)hl;
-    if (packed) {
-      n_tiles = (npx + 63) >> 6;
-    } else {
-      const int n_rows = kept ? nb << 3 : wi.row_end - wi.row_begin;
-      n_tiles = tiles_x * ((n_rows + (1 << th_log2) - 1) >> th_log2);
-    }
-  }
-
-  // row, column and liveness of this lane's pixel in tile t; dead lanes get an in-image pixel
-  __device__ __forceinline__ void pixel(int t, int lane, int& row, int& col, bool& live) const {
-    if (packed) {
-      const int q = (t << 6) + lane;
-      live = q < npx;
-      const int qc = live ? q : 0;
-      int b = (int)(((float)qc + 0.5f) * inv_bw);   // within one of the true band index
-      b -= (b * bw > qc) ? 1 : 0;
-      b += ((b + 1) * bw <= qc) ? 1 : 0;
-      b = min(b, nb - 1);
-      const int qq = qc - b * bw;
-      const bool full = b < nb - 1;
-      int cl = (int)(((float)qq + 0.5f) * inv_hl);   // within one of qq / hl
-      cl -= (cl * hl > qq) ? 1 : 0;
-      cl += ((cl + 1) * hl <= qq) ? 1 : 0;
-      col = full ? qq >> 3 : cl;
-      const int r = full ? (qq & 7) : qq - cl * hl;
-      row = (kept ? kept[rb + b] : rb + (b << 3)) + r;
-    } else {
-      const int ty = t / tiles_x, tx = t - ty * tiles_x;
-      const int row0 = kept ? kept[rb + (ty >> q_log2)] + ((ty & ((1 << q_log2) - 1)) << th_log2)
-                            : rb + (ty << th_log2);
-      row = row0 + (lane >> tw_log2);
-      col = (tx << tw_log2) + (lane & ((1 << tw_log2) - 1));
-      live = row < row_lim && col < w;
-      if (!live) {
-        row = row_safe;
-        col = 0;
-      }
-    }
-  }
-};
 
 constexpr int tri(int i, int j) { return i * NZ - (i * (i - 1)) / 2 + (j - i); }
 
@@ -279,80 +226,128 @@ __device__ double bright_entry(const float* __restrict__ T, int e, const double*
 // Wavefront sum of 80 lane values by recursive halving (masks 32, 16, 8, 4) and a
 // butterfly over the last 4 lanes: on return the lanes of each quad hold the wavefront
 // sums of the 5 entries starting at quad_base(lane) = 40*b5 + 20*b4 + 10*b3 + 5*b2
-// (b_k = lane bit k).
-template <int N>
-__device__ __forceinline__ void halvef(const float* v, float* o, int mask, bool up) {
-#pragma unroll
-  for (int i = 0; i < N / 2; ++i) {
-    const float send = up ? v[i] : v[i + N / 2];
-    const float keep = up ? v[i + N / 2] : v[i];
-    o[i] = keep + __shfl_xor(send, mask);
-  }
-}
-
+// (b_k = lane bit k).  The exchanges stay in the vector unit: halving over lane bit 5 or 4 is a
+// swap of half registers (v_permlane32_swap, v_permlane16_swap: after it the two registers hold, on
+// every lane, the lane's own value and its partner's of the entry the lane keeps) and one addition,
+// bit 3 a row rotation by 8, bits 1 and 0 quad permutations; only bit 2 goes through the LDS
+// crossbar.  The same additions through __shfl_xor took two selects and an LDS exchange each (about
+// 340 vector and 91 LDS instructions a sum; 190 and 5 now).
 __device__ __forceinline__ int quad_base(int lane) {
   return ((lane >> 5) & 1) * 40 + ((lane >> 4) & 1) * 20 + ((lane >> 3) & 1) * 10 + ((lane >> 2) & 1) * 5;
 }
 
-template <int N>
-__device__ __forceinline__ void halved(const double* v, double* o, int mask, bool up) {
+// a and b with lane bit 5 (M = 32) or 4 (M = 16) exchanged: on lanes with the bit clear a keeps its
+// value and b takes the partner lane's a; on lanes with it set b keeps its value and a takes the
+// partner lane's b.
+template <int M>
+__device__ __forceinline__ void swap_half(unsigned& a, unsigned& b) {
+  if constexpr (M == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+  } else {
+    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+  }
+}
+
+template <int M>
+__device__ __forceinline__ float swap_add(float x, float y) {
+  unsigned a = __float_as_uint(x), b = __float_as_uint(y);
+  swap_half<M>(a, b);
+  return __uint_as_float(a) + __uint_as_float(b);
+}
+
+template <int M>
+__device__ __forceinline__ double swap_add(double x, double y) {
+  unsigned al = __double2loint(x), ah = __double2hiint(x), bl = __double2loint(y), bh = __double2hiint(y);
+  swap_half<M>(al, bl);
+  swap_half<M>(ah, bh);
+  return __hiloint2double((int)ah, (int)al) + __hiloint2double((int)bh, (int)bl);
+}
+
+// the partner lane's value over a DPP control: row_ror:8 (lane ^ 8), quad_perm (lane ^ 2, lane ^ 1)
+constexpr int DPP_XOR8 = 0x128, DPP_XOR2 = 0x4E, DPP_XOR1 = 0xB1;
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xF, 0xF, true);
+  return __hiloint2double(hi, lo);
+}
+
+// 20 values, already halved over bits 5 and 4, to the quad's 5
+template <class F>
+__device__ __forceinline__ void quad_sum20(const F* t20, F* out5) {
+  const int lane = threadIdx.x & 63;
+  const bool up8 = (lane & 8) != 0, up4 = (lane & 4) != 0;
+  F t10[10];
 #pragma unroll
-  for (int i = 0; i < N / 2; ++i) {
-    const double send = up ? v[i] : v[i + N / 2];
-    const double keep = up ? v[i + N / 2] : v[i];
-    o[i] = keep + __shfl_xor(send, mask);
+  for (int i = 0; i < 10; ++i) {
+    const F send = up8 ? t20[i] : t20[i + 10], keep = up8 ? t20[i + 10] : t20[i];
+    t10[i] = keep + dpp<DPP_XOR8>(send);
+  }
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    const F send = up4 ? t10[i] : t10[i + 5], keep = up4 ? t10[i + 5] : t10[i];
+    out5[i] = keep + __shfl_xor(send, 4);
+  }
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    out5[i] += dpp<DPP_XOR2>(out5[i]);
+    out5[i] += dpp<DPP_XOR1>(out5[i]);
   }
 }
 
 // As wave_sum80f with every addition in FP64: the 80 FP32 values of each lane enter FP64
 // before the first exchange.
 __device__ __forceinline__ void wave_sum80d(const float* v, double* out5) {
-  const int lane = threadIdx.x & 63;
-  const bool up = (lane & 32) != 0;
-  double t40[40], t20[20], t10[10];
+  double t20[20];
 #pragma unroll
-  for (int i = 0; i < 40; ++i) {
-    const float send = up ? v[i] : v[i + 40];
-    const float keep = up ? v[i + 40] : v[i];
-    t40[i] = (double)keep + (double)__shfl_xor(send, 32);
+  for (int i = 0; i < 20; ++i) {
+    const double lo = swap_add<32>((double)v[i], (double)v[i + 40]);
+    const double hi = swap_add<32>((double)v[i + 20], (double)v[i + 60]);
+    t20[i] = swap_add<16>(lo, hi);
   }
-  halved<40>(t40, t20, 16, lane & 16);
-  halved<20>(t20, t10, 8, lane & 8);
-  halved<10>(t10, out5, 4, lane & 4);
-#pragma unroll
-  for (int i = 0; i < 5; ++i) {
-    out5[i] += __shfl_xor(out5[i], 2);
-    out5[i] += __shfl_xor(out5[i], 1);
-  }
+  quad_sum20(t20, out5);
 }
 
 __device__ __forceinline__ void wave_sum80f(const float* v, float* out5) {
-  const int lane = threadIdx.x & 63;
-  float t40[40], t20[20], t10[10];
-  halvef<80>(v, t40, 32, lane & 32);
-  halvef<40>(t40, t20, 16, lane & 16);
-  halvef<20>(t20, t10, 8, lane & 8);
-  halvef<10>(t10, out5, 4, lane & 4);
+  float t20[20];
 #pragma unroll
-  for (int i = 0; i < 5; ++i) {
-    out5[i] += __shfl_xor(out5[i], 2);
-    out5[i] += __shfl_xor(out5[i], 1);
-  }
+  for (int i = 0; i < 20; ++i)
+    t20[i] = swap_add<16>(swap_add<32>(v[i], v[i + 40]), swap_add<32>(v[i + 20], v[i + 60]));
+  quad_sum20(t20, out5);
 }
 
-// NE, ND > 0: compile-time component counts (fully unrolled loops); 0: runtime counts.
+// Bound by vector issue: about 1,600 vector instructions per tile step at the start of a fit, three
+// waves per SIMD.  What kept it from its issue rate was waiting: with the components tested one by one
+// in the tile (3 FMAs, a compare and a branch each) every hit began with the loads of its record, and the
+// pixels were flat loads that every wait for a record also waited for.  With the hits known from the
+// tile's box, the next record in flight, global pixel loads, the per-lane index arithmetic replaced by
+// the walk of tiles.h and the derivative sums of the work item held in LDS, one pass over 3.6e8 px of
+// 4,000 uneven sources takes 17.7 ms instead of 23.2 ms (2.0e10 px/s instead of 1.56e10), every bit the
+// same.
+//
+// NE, ND > 0: compile-time component counts; 0: runtime counts.
 // MINW: minimum resident waves per SIMD the register allocation must allow.
 // MF: the J^T W J part on the matrix cores (true) or in the per-lane FP32 sums (false).
 // S64: every tile step's gradient and Hessian terms are summed across the wavefront in FP64
 // (no FP32 sums across pixels; MF must be false).
-template <int BLOCK, int MINW, int NE, int ND, bool MF, bool S64>
+// PK: the packed tile map (tile width 8).
+template <int BLOCK, int MINW, int NE, int ND, bool MF, bool S64, bool PK>
 __global__ __launch_bounds__(BLOCK, MINW) void k_eval_full(const WorkItem* __restrict__ items,
                                                      const ImgDev* __restrict__ imgs,
                                                      const float* __restrict__ tables, int tstride, int n_exp,
                                                      int n_dev, const int* __restrict__ src_flag,
                                                      int tw_log2, float e_zero, const int* __restrict__ kept,
                                                      double* __restrict__ partials, WorkQueue q) {
-  __shared__ double red[BLOCK / 64][80];
+  __shared__ double red[BLOCK / 64][81];   // value, then 80 derivative sums
+  __shared__ SkipTest skip[64];
   // per wavefront: [A rows (dT, dU) | B columns (hT, hU)][T or U part][z index][pixel]
   __shared__ __align__(16) float jbuf[MF ? BLOCK / 64 : 1][2][2][MF ? NZ : 1][MF ? JP : 4];
   __shared__ __align__(16) float zrow[64];   // operand row of zeros for the padding rows 11..15
@@ -374,20 +369,30 @@ __global__ __launch_bounds__(BLOCK, MINW) void k_eval_full(const WorkItem* __res
   const ImgDev& im = imgs[wi.img];
   const float* __restrict__ T = tables + (size_t)wi.img * tstride;
   const int w = im.w, pitch = im.pitch, npitch = im.nbr_pitch, npsf = im.n_psf;
-  const float* __restrict__ pix = im.pix;
-  const float* __restrict__ nbrE = im.nbr_mean;
-  const float* __restrict__ nbrV = im.nbr_var;
+  const GlobalF pix = global(im.pix);
+  const GlobalF nbrE = global(im.nbr_mean);
+  const GlobalF nbrV = global(im.nbr_var);
   const int ne = NE > 0 ? NE : n_exp;
   const int ncomp = NE > 0 ? NE + ND : n_exp + n_dev;
   const float psx = T[PSX], psy = T[PSY], io = T[CALIB], sky = T[SKY];
   const float io2 = io * io, io3 = io2 * io;
 
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const TileMap tm(wi, w, im.h, tw_log2, kept);
-  const int n_tiles = tm.n_tiles;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  TileMap<PK, BLOCK / 64> tm(wi, w, im.h, tw_log2, kept, wv);
+  const int n_gal = npsf * ncomp;   // at most 64
+  const float* __restrict__ G = T + GAL;
+  if (threadIdx.x < n_gal) skip[threadIdx.x] = skip_test_of(T, threadIdx.x, ncomp);
+  __syncthreads();
+  const SkipTest& my_skip = skip[min(lane, n_gal - 1)];
+  const unsigned long long gal_lanes = n_gal >= 64 ? ~0ull : (1ull << n_gal) - 1;
   double val = 0.0;                 // ELBO value, per lane
-  double acc5[5] = {0.0, 0.0, 0.0, 0.0, 0.0};   // wavefront sums of 5 derivative entries (quad-uniform)
-  const int base5 = quad_base(lane);              // first of the 5 entries this lane's quad holds
+  // FP64 wavefront sums of the derivative entries, in LDS between flushes (ten registers a lane
+  // otherwise): the first lane of each quad holds 5 of them
+  double* const sum5 = &red[wv][1 + quad_base(lane)];
+  if ((lane & 3) == 0) {
+#pragma unroll
+    for (int i = 0; i < 5; ++i) sum5[i] = 0.0;
+  }
   float accf[80];                   // per-lane FP32 sums of the derivative entries since the last flush
 #pragma unroll
   for (int i = 0; i < 80; ++i) accf[i] = 0.f;
@@ -407,67 +412,80 @@ __global__ __launch_bounds__(BLOCK, MINW) void k_eval_full(const WorkItem* __res
     if constexpr (S64) {
       double part[5];
       wave_sum80d(accf, part);
+      if ((lane & 3) == 0) {
 #pragma unroll
-      for (int i = 0; i < 5; ++i) acc5[i] += part[i];
+        for (int i = 0; i < 5; ++i) sum5[i] += part[i];
+      }
     } else {
       float part[5];
       wave_sum80f(accf, part);
+      if ((lane & 3) == 0) {
 #pragma unroll
-      for (int i = 0; i < 5; ++i) acc5[i] += (double)part[i];
+        for (int i = 0; i < 5; ++i) sum5[i] += (double)part[i];
+      }
     }
 #pragma unroll
     for (int i = 0; i < 80; ++i) accf[i] = 0.f;
   };
 
-  for (int t = wv; t < n_tiles; t += BLOCK / 64) {
-    int row, col;
+  for (; tm.more(); tm.next()) {
+    int row, col, first;
     bool live;
-    tm.pixel(t, lane, row, col, live);   // (row, col) is inside the image on every lane
-    const float x = live ? pix[(size_t)row * pitch + col] : 0.f;
-    const float ebg = sky + (nbrE && live ? nbrE[(size_t)row * npitch + col] : 0.f);
-    const float vbg = nbrV && live ? nbrV[(size_t)row * npitch + col] : 0.f;
+    tm.pixel(lane, row, col, live, first);   // (row, col) is inside the image on every lane
+    const float xp = pix[(int64_t)row * pitch + col];
+    const float en = nbrE ? nbrE[(int64_t)row * npitch + col] : 0.f;
+    const float vn = nbrV ? nbrV[(int64_t)row * npitch + col] : 0.f;
+    const float x = live ? xp : 0.f, ebg = sky + (live ? en : 0.f), vbg = live ? vn : 0.f;
     const float dx0 = live ? (float)col - psx : FAR, dy0 = live ? (float)row - psy : FAR;
 
-    // ---- star: N, dN/dp, d2N/dp2
-    bool hit = false;   // some component is not exactly 0 on this tile (wavefront-uniform)
-    float s0 = 0.f, s1x = 0.f, s1y = 0.f, s2xx = 0.f, s2xy = 0.f, s2yy = 0.f;
-    for (int k = 0; k < npsf; ++k) {
-      const float* __restrict__ r = T + STAR + k * STAR_REC;
-      const float dx = dx0 - r[S_XIX], dy = dy0 - r[S_XIY];
-      const float e = fmaf(r[R_QXX], dx * dx, fmaf(r[R_QXY], dx * dy, fmaf(r[R_QYY], dy * dy, r[R_C0])));
-      if (!wave_any(e >= e_zero)) continue;
-      hit = true;
-      const float N = ex2(e);
-      const float bx = fmaf(r[R_PXX], dx, r[R_PXY] * dy), by = fmaf(r[R_PXY], dx, r[R_PYY] * dy);
-      s0 += N;
-      s1x = fmaf(N, bx, s1x);
-      s1y = fmaf(N, by, s1y);
-      s2xx = fmaf(N, fmaf(bx, bx, -r[R_PXX]), s2xx);
-      s2xy = fmaf(N, fmaf(bx, by, -r[R_PXY]), s2xy);
-      s2yy = fmaf(N, fmaf(by, by, -r[R_PYY]), s2yy);
+    unsigned long long hits;   // galaxy components that may be non-zero on the tile
+    {
+      bool more;
+      hits = __ballot(may_hit(my_skip, tm.box(col, first, false, &more), psx, psy, e_zero));
+      if (more) hits |= __ballot(may_hit(my_skip, tm.box(col, first, true, &more), psx, psy, e_zero));
+      hits &= gal_lanes;
     }
+    bool hit = hits != 0ull;   // some component is not exactly 0 on this tile (wavefront-uniform)
 
-    // ---- galaxy: Hermite moments per profile type
+    // ---- star: N, dN/dp, d2N/dp2; galaxy: Hermite moments per profile type.  The galaxy's hits are
+    // taken in table order (PSF component by PSF component, exp before dev).  The next hit's record
+    // and the next star component's are loaded while one is evaluated.
+    float s0 = 0.f, s1x = 0.f, s1y = 0.f, s2xx = 0.f, s2xy = 0.f, s2yy = 0.f;
     GalAcc X, D;
     zero(X);
     zero(D);
-    for (int k = 0; k < npsf; ++k) {
-      const float* __restrict__ sr = T + STAR + k * STAR_REC;
-      const float dx = dx0 - sr[S_XIX], dy = dy0 - sr[S_XIY];
-      const float dxx = dx * dx, dxy = dx * dy, dyy = dy * dy;
-      // the whole galaxy group is exactly 0 on the tile when its bound is (a margin of 1 covers the
-      // FP32 rounding of the bound and of the components' exponents)
-      if (!wave_any(fmaf(sr[S_GMU], dxx + dyy, sr[S_GC0]) >= e_zero - 1.f)) continue;
-      const float* __restrict__ base = T + GAL + k * ncomp * GAL_REC;
-      if constexpr (NE > 0) {
-#pragma unroll
-        for (int j = 0; j < NE; ++j) hit |= gal_comp(base + j * GAL_REC, dx, dy, dxx, dxy, dyy, e_zero, X);
-#pragma unroll
-        for (int j = NE; j < NE + ND; ++j) hit |= gal_comp(base + j * GAL_REC, dx, dy, dxx, dxy, dyy, e_zero, D);
-      } else {
-        for (int j = 0; j < ne; ++j) hit |= gal_comp(base + j * GAL_REC, dx, dy, dxx, dxy, dyy, e_zero, X);
-        for (int j = ne; j < ncomp; ++j) hit |= gal_comp(base + j * GAL_REC, dx, dy, dxx, dxy, dyy, e_zero, D);
+    int c = low_bit(hits);
+    GalRec nx = load_rec(G + (hits ? c : 0) * GAL_REC);
+    StarRec ns = load_star(T + STAR);
+    auto evaluate = [&](int lim, float dx, float dy, float dxx, float dxy, float dyy, GalAcc& acc) {
+      while (c < lim) {
+        const GalRec cur = nx;
+        hits &= hits - 1;
+        c = low_bit(hits);
+        nx = load_rec(G + (hits ? c : 0) * GAL_REC);
+        gal_comp(cur, dx, dy, dxx, dxy, dyy, acc);
       }
+    };
+    for (int k = 0; k < npsf; ++k) {
+      const StarRec sr = ns;
+      const float* r = sr.v;
+      ns = load_star(T + STAR + min(k + 1, npsf - 1) * STAR_REC);
+      const float dx = dx0 - r[S_XIX], dy = dy0 - r[S_XIY];
+      const float dxx = dx * dx, dxy = dx * dy, dyy = dy * dy;
+      const float e = fmaf(r[R_QXX], dxx, fmaf(r[R_QXY], dxy, fmaf(r[R_QYY], dyy, r[R_C0])));
+      if (wave_any(e >= e_zero)) {
+        hit = true;
+        const float N = ex2(e);
+        const float bx = fmaf(r[R_PXX], dx, r[R_PXY] * dy), by = fmaf(r[R_PXY], dx, r[R_PYY] * dy);
+        s0 += N;
+        s1x = fmaf(N, bx, s1x);
+        s1y = fmaf(N, by, s1y);
+        s2xx = fmaf(N, fmaf(bx, bx, -r[R_PXX]), s2xx);
+        s2xy = fmaf(N, fmaf(bx, by, -r[R_PXY]), s2xy);
+        s2yy = fmaf(N, fmaf(by, by, -r[R_PYY]), s2yy);
+      }
+      evaluate(k * ncomp + ne, dx, dy, dxx, dxy, dyy, X);
+      evaluate((k + 1) * ncomp, dx, dy, dxx, dxy, dyy, D);
     }
     if (!hit) {
       // No component reaches the tile: T, U and all their derivatives are exactly 0, so the
@@ -763,11 +781,6 @@ __global__ __launch_bounds__(BLOCK, MINW) void k_eval_full(const WorkItem* __res
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) val += __shfl_xor(val, o);
   if (lane == 0) red[wv][0] = val;
-  if ((lane & 3) == 0) {
-#pragma unroll
-    for (int i = 0; i < 5; ++i)
-      if (base5 + i < NACC - 1) red[wv][1 + base5 + i] = acc5[i];
-  }
   if constexpr (MF) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -799,7 +812,7 @@ __global__ __launch_bounds__(BLOCK, MINW) void k_eval_full(const WorkItem* __res
   }   // items
 }
 
-template <int BLOCK, int NE, int ND>
+template <int BLOCK, int NE, int ND, bool PK>
 __global__ __launch_bounds__(BLOCK) void k_eval_value(const WorkItem* __restrict__ items,
                                                       const ImgDev* __restrict__ imgs,
                                                       const float* __restrict__ tables, int tstride, int n_exp_rt,
@@ -813,24 +826,24 @@ __global__ __launch_bounds__(BLOCK) void k_eval_value(const WorkItem* __restrict
   const ImgDev& im = imgs[wi.img];
   const float* __restrict__ T = tables + (size_t)wi.img * tstride;
   const int w = im.w, pitch = im.pitch, npitch = im.nbr_pitch, npsf = im.n_psf;
-  const float* __restrict__ pix = im.pix;
-  const float* __restrict__ nbrE = im.nbr_mean;
-  const float* __restrict__ nbrV = im.nbr_var;
+  const GlobalF pix = global(im.pix);
+  const GlobalF nbrE = global(im.nbr_mean);
+  const GlobalF nbrV = global(im.nbr_var);
   const int ncomp = n_exp + n_dev;
   const float psx = T[PSX], psy = T[PSY], io = T[CALIB], sky = T[SKY];
   const float ed = T[EDEV];
   const float cs = T[CS], cg = T[CG], Ks = T[KS], Kg = T[KG], Ksg = T[KSG];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const TileMap tm(wi, w, im.h, tw_log2, kept);
-  const int n_tiles = tm.n_tiles;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  TileMap<PK, BLOCK / 64> tm(wi, w, im.h, tw_log2, kept, wv);
   double acc = 0.0;
-  for (int t = wv; t < n_tiles; t += BLOCK / 64) {
-    int row, col;
+  for (; tm.more(); tm.next()) {
+    int row, col, first;
     bool live;
-    tm.pixel(t, lane, row, col, live);   // (row, col) is inside the image on every lane
-    const float x = live ? pix[(size_t)row * pitch + col] : 0.f;
-    const float ebg = sky + (nbrE && live ? nbrE[(size_t)row * npitch + col] : 0.f);
-    const float vbg = nbrV && live ? nbrV[(size_t)row * npitch + col] : 0.f;
+    tm.pixel(lane, row, col, live, first);   // (row, col) is inside the image on every lane
+    const float xp = pix[(int64_t)row * pitch + col];
+    const float en = nbrE ? nbrE[(int64_t)row * npitch + col] : 0.f;
+    const float vn = nbrV ? nbrV[(int64_t)row * npitch + col] : 0.f;
+    const float x = live ? xp : 0.f, ebg = sky + (live ? en : 0.f), vbg = live ? vn : 0.f;
     const float dx0 = live ? (float)col - psx : FAR, dy0 = live ? (float)row - psy : FAR;
     float Gs = 0.f, gx = 0.f, gd = 0.f;
     for (int k = 0; k < npsf; ++k) {
@@ -901,7 +914,7 @@ constexpr int NG = NGRAD;   // entries of a gradient partial: value and the 11 z
 // with first-order moments only (6 sums per galaxy component instead of 18) and no second-
 // order terms; value and gradient accumulated per lane in FP64.  One partial of NG doubles per
 // work item.  Exactly-zero components, galaxy groups and tiles are skipped as in k_eval_full.
-template <int BLOCK, int NE, int ND>
+template <int BLOCK, int NE, int ND, bool PK>
 __global__ __launch_bounds__(BLOCK) void k_eval_grad(const WorkItem* __restrict__ items,
                                                      const ImgDev* __restrict__ imgs,
                                                      const float* __restrict__ tables, int tstride, int n_exp_rt,
@@ -916,23 +929,24 @@ __global__ __launch_bounds__(BLOCK) void k_eval_grad(const WorkItem* __restrict_
   const ImgDev& im = imgs[wi.img];
   const float* __restrict__ T = tables + (size_t)wi.img * tstride;
   const int w = im.w, pitch = im.pitch, npitch = im.nbr_pitch, npsf = im.n_psf;
-  const float* __restrict__ pix = im.pix;
-  const float* __restrict__ nbrE = im.nbr_mean;
-  const float* __restrict__ nbrV = im.nbr_var;
+  const GlobalF pix = global(im.pix);
+  const GlobalF nbrE = global(im.nbr_mean);
+  const GlobalF nbrV = global(im.nbr_var);
   const float psx = T[PSX], psy = T[PSY], io = T[CALIB], sky = T[SKY];
   const float io2 = io * io;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const TileMap tm(wi, w, im.h, tw_log2, kept);
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  TileMap<PK, BLOCK / 64> tm(wi, w, im.h, tw_log2, kept, wv);
   double acc[NG];
 #pragma unroll
   for (int j = 0; j < NG; ++j) acc[j] = 0.0;
-  for (int t = wv; t < tm.n_tiles; t += BLOCK / 64) {
-    int row, col;
+  for (; tm.more(); tm.next()) {
+    int row, col, first;
     bool live;
-    tm.pixel(t, lane, row, col, live);   // (row, col) is inside the image on every lane
-    const float x = live ? pix[(size_t)row * pitch + col] : 0.f;
-    const float ebg = sky + (nbrE && live ? nbrE[(size_t)row * npitch + col] : 0.f);
-    const float vbg = nbrV && live ? nbrV[(size_t)row * npitch + col] : 0.f;
+    tm.pixel(lane, row, col, live, first);   // (row, col) is inside the image on every lane
+    const float xp = pix[(int64_t)row * pitch + col];
+    const float en = nbrE ? nbrE[(int64_t)row * npitch + col] : 0.f;
+    const float vn = nbrV ? nbrV[(int64_t)row * npitch + col] : 0.f;
+    const float x = live ? xp : 0.f, ebg = sky + (live ? en : 0.f), vbg = live ? vn : 0.f;
     const float dx0 = live ? (float)col - psx : FAR, dy0 = live ? (float)row - psy : FAR;
 
     bool hit = false;
@@ -1039,34 +1053,32 @@ __global__ __launch_bounds__(BLOCK) void k_eval_grad(const WorkItem* __restrict_
 }  // namespace
 
 namespace {
-using FullKernel = decltype(&k_eval_full<256, 1, 6, 8, false, false>);
+using FullKernel = decltype(&k_eval_full<256, 1, 6, 8, false, false, true>);
 
-// The value+gradient+Hessian kernel instance for (block, variant). Variant bits: 0 = the higher
-// occupancy register budget (3 resident waves per SIMD for the vector kernels, 2 with the
+// The value+gradient+Hessian kernel instance for (block, variant, tile width). Variant bits: 0 = the
+// higher occupancy register budget (3 resident waves per SIMD for the vector kernels, 2 with the
 // matrix-core J^T W J; otherwise the compiler's choice, 2 waves per SIMD for this kernel), 1 =
 // mixture loops unrolled for 6 exp + 8 dev components, 2 = J^T W J on the matrix cores, 3 = FP64
 // lane sums.
-FullKernel full_kernel(int block, int variant, int n_exp, int n_dev) {
+template <int B, bool PK>
+FullKernel full_kernel_of(bool hi, bool unroll, bool s64, bool mf) {
+  if (s64) {
+    if (unroll) return hi ? &k_eval_full<B, 3, 6, 8, false, true, PK> : &k_eval_full<B, 1, 6, 8, false, true, PK>;
+    return hi ? &k_eval_full<B, 3, 0, 0, false, true, PK> : &k_eval_full<B, 1, 0, 0, false, true, PK>;
+  }
+  if (mf) return hi ? &k_eval_full<B, 2, 6, 8, true, false, PK> : &k_eval_full<B, 1, 6, 8, true, false, PK>;
+  if (unroll) return hi ? &k_eval_full<B, 3, 6, 8, false, false, PK> : &k_eval_full<B, 1, 6, 8, false, false, PK>;
+  return hi ? &k_eval_full<B, 3, 0, 0, false, false, PK> : &k_eval_full<B, 1, 0, 0, false, false, PK>;
+}
+
+FullKernel full_kernel(int block, int variant, int tw_log2, int n_exp, int n_dev) {
   const bool hi = (variant & 1) != 0;
   const bool unroll = (variant & 2) != 0 && n_exp == 6 && n_dev == 8;
   const bool s64 = (variant & 8) != 0;
   const bool mf = (variant & 4) != 0 && unroll && !s64;
-  if (block == 128) {
-    if (s64) {
-      if (unroll) return hi ? &k_eval_full<128, 3, 6, 8, false, true> : &k_eval_full<128, 1, 6, 8, false, true>;
-      return hi ? &k_eval_full<128, 3, 0, 0, false, true> : &k_eval_full<128, 1, 0, 0, false, true>;
-    }
-    if (mf) return hi ? &k_eval_full<128, 2, 6, 8, true, false> : &k_eval_full<128, 1, 6, 8, true, false>;
-    if (unroll) return hi ? &k_eval_full<128, 3, 6, 8, false, false> : &k_eval_full<128, 1, 6, 8, false, false>;
-    return hi ? &k_eval_full<128, 3, 0, 0, false, false> : &k_eval_full<128, 1, 0, 0, false, false>;
-  }
-  if (s64) {
-    if (unroll) return hi ? &k_eval_full<256, 3, 6, 8, false, true> : &k_eval_full<256, 1, 6, 8, false, true>;
-    return hi ? &k_eval_full<256, 3, 0, 0, false, true> : &k_eval_full<256, 1, 0, 0, false, true>;
-  }
-  if (mf) return hi ? &k_eval_full<256, 2, 6, 8, true, false> : &k_eval_full<256, 1, 6, 8, true, false>;
-  if (unroll) return hi ? &k_eval_full<256, 3, 6, 8, false, false> : &k_eval_full<256, 1, 6, 8, false, false>;
-  return hi ? &k_eval_full<256, 3, 0, 0, false, false> : &k_eval_full<256, 1, 0, 0, false, false>;
+  if (block == 128)
+    return tw_log2 == 3 ? full_kernel_of<128, true>(hi, unroll, s64, mf) : full_kernel_of<128, false>(hi, unroll, s64, mf);
+  return tw_log2 == 3 ? full_kernel_of<256, true>(hi, unroll, s64, mf) : full_kernel_of<256, false>(hi, unroll, s64, mf);
 }
 }  // namespace
 
@@ -1077,15 +1089,15 @@ hipError_t launch_eval_full(const WorkItem* items, int n_items, const ImgDev* im
   if (n_items <= 0) return hipSuccess;
   const WorkQueue q = queue ? *queue : WorkQueue{};
   const dim3 g(queue ? std::min(n_items, persistent_grid) : n_items);
-  const FullKernel k = full_kernel(block == 128 ? 128 : 256, variant, n_exp, n_dev);
+  const FullKernel k = full_kernel(block == 128 ? 128 : 256, variant, tw_log2, n_exp, n_dev);
   hipLaunchKernelGGL(k, g, dim3(block == 128 ? 128 : 256), 0, st, items, imgs, tables, tstride, n_exp, n_dev,
                      src_flag, tw_log2, e_zero, kept, partials, q);
   return hipGetLastError();
 }
 
-hipError_t eval_full_blocks_per_cu(int block, int variant, int n_exp, int n_dev, int* blocks) {
+hipError_t eval_full_blocks_per_cu(int block, int variant, int tw_log2, int n_exp, int n_dev, int* blocks) {
   const int b = block == 128 ? 128 : 256;
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, full_kernel(b, variant, n_exp, n_dev), b, 0);
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, full_kernel(b, variant, tw_log2, n_exp, n_dev), b, 0);
 }
 
 hipError_t launch_eval_grad(const WorkItem* items, int n_items, const ImgDev* imgs, const float* tables, int tstride,
@@ -1095,7 +1107,9 @@ hipError_t launch_eval_grad(const WorkItem* items, int n_items, const ImgDev* im
   const bool unroll = (variant & 2) != 0 && n_exp == 6 && n_dev == 8;
   const dim3 g(n_items);
 #define CELESTE_LAUNCH_GRAD(B, E, D) \
-  hipLaunchKernelGGL((k_eval_grad<B, E, D>), g, dim3(B), 0, st, items, imgs, tables, tstride, n_exp, n_dev, \
+  if (tw_log2 == 3) CELESTE_LAUNCH_GRAD_(B, E, D, true); else CELESTE_LAUNCH_GRAD_(B, E, D, false)
+#define CELESTE_LAUNCH_GRAD_(B, E, D, PK) \
+  hipLaunchKernelGGL((k_eval_grad<B, E, D, PK>), g, dim3(B), 0, st, items, imgs, tables, tstride, n_exp, n_dev, \
                      src_flag, tw_log2, e_zero, kept, partials)
   if (block == 128) {
     if (unroll) CELESTE_LAUNCH_GRAD(128, 6, 8); else CELESTE_LAUNCH_GRAD(128, 0, 0);
@@ -1103,6 +1117,7 @@ hipError_t launch_eval_grad(const WorkItem* items, int n_items, const ImgDev* im
     if (unroll) CELESTE_LAUNCH_GRAD(256, 6, 8); else CELESTE_LAUNCH_GRAD(256, 0, 0);
   }
 #undef CELESTE_LAUNCH_GRAD
+#undef CELESTE_LAUNCH_GRAD_
   return hipGetLastError();
 }
 
@@ -1126,7 +1141,9 @@ hipError_t launch_eval_value(const WorkItem* items, int n_items, const ImgDev* i
   const bool unroll = (variant & 2) != 0 && n_exp == 6 && n_dev == 8;
   const dim3 g(n_items);
 #define CELESTE_LAUNCH_VALUE(B, E, D) \
-  hipLaunchKernelGGL((k_eval_value<B, E, D>), g, dim3(B), 0, st, items, imgs, tables, tstride, n_exp, n_dev, \
+  if (tw_log2 == 3) CELESTE_LAUNCH_VALUE_(B, E, D, true); else CELESTE_LAUNCH_VALUE_(B, E, D, false)
+#define CELESTE_LAUNCH_VALUE_(B, E, D, PK) \
+  hipLaunchKernelGGL((k_eval_value<B, E, D, PK>), g, dim3(B), 0, st, items, imgs, tables, tstride, n_exp, n_dev, \
                      src_flag, tw_log2, kept, partials)
   if (block == 128) {
     if (unroll) CELESTE_LAUNCH_VALUE(128, 6, 8); else CELESTE_LAUNCH_VALUE(128, 0, 0);
@@ -1134,6 +1151,7 @@ hipError_t launch_eval_value(const WorkItem* items, int n_items, const ImgDev* i
     if (unroll) CELESTE_LAUNCH_VALUE(256, 6, 8); else CELESTE_LAUNCH_VALUE(256, 0, 0);
   }
 #undef CELESTE_LAUNCH_VALUE
+#undef CELESTE_LAUNCH_VALUE_
   return hipGetLastError();
 }
 

@@ -1,0 +1,208 @@
+// Pixel tiles of the mixture kernels: the pixel -> lane layout of a work item, and the test that
+// decides for a whole tile which mixture components can be non-zero on it.
+#pragma once
+
+#include "celeste_internal.h"
+
+namespace celeste {
+namespace {
+
+__device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// Pixel box of a tile: columns [x0, x1], rows [y0, y1] (wave-uniform).
+struct TileBox {
+  int x0, x1, y0, y1;
+};
+
+// A pointer read from a metadata record, known to be device memory: its loads are global loads.  (Through
+// a plain pointer they are flat loads, which count as scalar-memory operations too, so that every wait
+// for a table record also waits for the pixels.)
+typedef const __attribute__((address_space(1))) float* GlobalF;
+__device__ __forceinline__ GlobalF global(const float* p) { return (GlobalF)p; }
+
+// Pixel -> lane layout of a work item, walked by the wavefronts of a block (wave wv takes every WAVES-th
+// tile from the wv-th on; the tile, and all state here, is wave-uniform).
+//
+// Packed (PK, tile width 8): the item's rows as 8-row bands (the image's last band may be shorter),
+// each band's pixels in column-major order and the bands back to back; a tile is 64 consecutive
+// pixels of that order, an 8 x 8 square except where it wraps from one band into the next, and only
+// the item's last tile has dead lanes.  Bands are row_begin + 8 b for a dense item and the kept
+// blocks kept[row_begin + b] for a subsampled one.  The walk keeps the tile's band and its place in
+// it, so that a lane finds its pixel with one comparison per band of the tile (dividing the pixel's
+// index by the band's size, per lane and tile, took 45 vector instructions, five of them quarter-rate
+// integer products).
+//
+// Unpacked (tile width 16, 32 or 64): a grid of tw x (64 / tw) tiles over the item's rows; lanes past
+// the image edge are dead.
+template <bool PK, int WAVES>
+struct TileMap {
+  int w, row_lim, n_tiles, t;
+  const int* kept;
+  int rb;
+  // packed: bands, rows of the last band, pixels of a full band and of the item; the tile's band
+  // and its first pixel's place in the band
+  int nb, hl, bw, npx, b0, q0;
+  float inv_hl;
+  // unpacked
+  int tw_log2, th_log2, tiles_x, q_log2, row_safe;
+
+  __device__ __forceinline__ TileMap(const WorkItem& wi, int w_, int h, int tw_log2_, const int* kept_, int wv) {
+    w = w_;
+    rb = wi.row_begin;
+    kept = kept_;
+    row_lim = kept ? h : wi.row_end;
+    t = wv;
+    nb = kept ? wi.row_end - wi.row_begin : (wi.row_end - wi.row_begin + 7) >> 3;
+    if constexpr (PK) {
+      hl = min(8, row_lim - band_row(nb - 1));
+      bw = w << 3;
+      npx = (nb - 1) * bw + hl * w;
+      inv_hl = 1.0f / (float)hl;
+      n_tiles = (npx + 63) >> 6;
+      b0 = 0;
+      q0 = wv << 6;
+      settle();
+    } else {
+      tw_log2 = tw_log2_;
+      th_log2 = 6 - tw_log2;
+      row_safe = kept ? 0 : wi.row_begin;
+      tiles_x = (w + (1 << tw_log2) - 1) >> tw_log2;
+      q_log2 = 3 - th_log2;
+      const int n_rows = kept ? nb << 3 : wi.row_end - wi.row_begin;
+      n_tiles = tiles_x * ((n_rows + (1 << th_log2) - 1) >> th_log2);
+    }
+  }
+
+  __device__ __forceinline__ bool more() const { return t < n_tiles; }
+  __device__ __forceinline__ void next() {
+    t += WAVES;
+    if constexpr (PK) {
+      q0 += WAVES << 6;
+      settle();
+    }
+  }
+  __device__ __forceinline__ void settle() {
+    while (q0 >= bw && b0 < nb - 1) {
+      q0 -= bw;
+      ++b0;
+    }
+  }
+  __device__ __forceinline__ int band_row(int b) const { return kept ? kept[rb + b] : rb + (b << 3); }
+
+  // row, column and liveness of this lane's pixel in the tile; dead lanes get an in-image pixel.
+  // first: the first row of the pixel's band (packed) or of the tile.
+  __device__ __forceinline__ void pixel(int lane, int& row, int& col, bool& live, int& first) const {
+    if constexpr (PK) {
+      live = (t << 6) + lane < npx;
+      int q = q0 + (live ? lane : 0);
+      int b = b0;
+      first = band_row(b0);
+      for (int k = b0 + 1, lim = bw; k < nb && lim < q0 + 64; ++k, lim += bw) {   // one step where bw >= 64
+        const int rk = band_row(k);
+        if (q0 + lane >= lim && live) {
+          q -= bw;
+          b = k;
+          first = rk;
+        }
+      }
+      const bool full = b < nb - 1 || hl == 8;
+      // q / hl in the last band: (q + 1/2) / hl is at least 1/14 from an integer, so its floor is
+      // exact where the quotient's FP32 rounding is below that
+      int cl = (int)(((float)q + 0.5f) * inv_hl);
+      if (w > 65536) {
+        cl -= (cl * hl > q) ? 1 : 0;
+        cl += ((cl + 1) * hl <= q) ? 1 : 0;
+      }
+      col = full ? q >> 3 : cl;
+      row = first + (full ? (q & 7) : q - cl * hl);
+    } else {
+      const int ty = t / tiles_x, tx = t - ty * tiles_x;
+      const int row0 = kept ? kept[rb + (ty >> q_log2)] + ((ty & ((1 << q_log2) - 1)) << th_log2)
+                            : rb + (ty << th_log2);
+      first = row0;
+      row = row0 + (lane >> tw_log2);
+      col = (tx << tw_log2) + (lane & ((1 << tw_log2) - 1));
+      live = row < row_lim && col < w;
+      if (!live) {
+        row = row_safe;
+        col = 0;
+      }
+    }
+  }
+
+  // Box of the tile's live pixels, from this lane's column and band row.  second: a packed tile that
+  // runs from the end of one band into the start of the next has a box in each; the first or the
+  // second one is returned, and *two says that there is a second.  (A tile spans more than two bands
+  // only where a band holds fewer than 64 pixels; its one box is then all columns of its bands.)
+  __device__ __forceinline__ TileBox box(int col, int first, bool second, bool* two) const {
+    if constexpr (!PK) {
+      const int r0 = __builtin_amdgcn_readfirstlane(first);
+      const int x0 = (t % tiles_x) << tw_log2;
+      *two = false;
+      return TileBox{x0, min(w - 1, x0 + (1 << tw_log2) - 1), r0, max(r0, min(row_lim, r0 + (1 << th_log2)) - 1)};
+    }
+    const int last = min(63, npx - 1 - (t << 6));
+    const int c0 = __builtin_amdgcn_readfirstlane(col), s0 = __builtin_amdgcn_readfirstlane(first);
+    const int c1 = __builtin_amdgcn_readlane(col, last), s1 = __builtin_amdgcn_readlane(first, last);
+    const bool one = s0 == s1, wide = w < 8;
+    *two = !one && !wide;
+    TileBox b;
+    b.x0 = (!one && (wide || second)) ? 0 : c0;
+    b.x1 = (one || (second && !wide)) ? c1 : w - 1;
+    b.y0 = (*two && second) ? s1 : s0;
+    b.y1 = (*two && !second) ? s0 + 7 : min(row_lim, s1 + 8) - 1;
+    return b;
+  }
+};
+
+// Which components of an image's galaxy mixture (npsf groups of ncomp, at most 64) can be non-zero on
+// a tile.  One component per lane: the lane holds the component's exponent
+//   e(d) = c0 - (A dx^2 + B dx dy + C dy^2)   (log2 of its density at offset d)
+// and bounds e over the tile's box from above; a component whose bound is below the exact-zero
+// threshold is exactly 0 on every pixel of the tile.  The quadratic form is positive definite with
+// its minimum at the origin, so its minimum over the box lies on a box edge that faces the origin
+// (the segment from any point of the box to the origin leaves the box through such an edge, the
+// form falling along it): the nearest edge in x with the best y on it, or the nearest edge in y with
+// the best x.  The box's edges are formed by the pixels' own FP32 operations, whose rounding is
+// monotonic, so every pixel's computed offset lies in the box; what remains is the rounding of the
+// exponents themselves, covered by a slack of 16 ulp of the largest terms on the box plus 0.01.
+//
+// Against a test of every component's exponent on the tile's pixels (3 FMAs, a compare and a branch
+// each) this takes about 30 vector instructions for all components, and the hits are known before
+// their records are read, so the next hit's scalar loads are in flight while one is evaluated.
+struct SkipTest {
+  float4 form;     // c0, A, B, C
+  float4 geo;      // centre offset x, y (the PSF component's), B / 2C, B / 2A
+};
+
+__device__ __forceinline__ SkipTest skip_test_of(const float* __restrict__ T, int c, int ncomp) {
+  using namespace tab;
+  const float* r = T + GAL + c * GAL_REC;
+  const float* sr = T + STAR + (c / ncomp) * STAR_REC;
+  SkipTest s;
+  s.form = make_float4(r[R_C0], -r[R_QXX], -r[R_QXY], -r[R_QYY]);
+  s.geo = make_float4(sr[S_XIX], sr[S_XIY], s.form.w > 0.f ? 0.5f * s.form.z / s.form.w : 0.f,
+                      s.form.y > 0.f ? 0.5f * s.form.z / s.form.y : 0.f);
+  return s;
+}
+
+// True on the lanes whose component may be non-zero on the box (psx, psy: the source's position).
+__device__ __forceinline__ bool may_hit(const SkipTest& s, const TileBox& b, float psx, float psy, float e_zero) {
+  const float xl = ((float)b.x0 - psx) - s.geo.x, xh = ((float)b.x1 - psx) - s.geo.x;
+  const float yl = ((float)b.y0 - psy) - s.geo.y, yh = ((float)b.y1 - psy) - s.geo.y;
+  const float A = s.form.y, B = s.form.z, C = s.form.w;
+  const float xn = __builtin_amdgcn_fmed3f(xl, 0.f, xh), yn = __builtin_amdgcn_fmed3f(yl, 0.f, yh);
+  const float ys = __builtin_amdgcn_fmed3f(-s.geo.z * xn, yl, yh);
+  const float xs = __builtin_amdgcn_fmed3f(-s.geo.w * yn, xl, xh);
+  const float q1 = fmaf(A * xn, xn, ys * fmaf(B, xn, C * ys));
+  const float q2 = fmaf(C * yn, yn, xs * fmaf(B, yn, A * xs));
+  const float X = fmaxf(fabsf(xl), fabsf(xh)), Y = fmaxf(fabsf(yl), fabsf(yh));
+  const float M = fmaf(X, fmaf(A, X, fabsf(B) * Y), C * Y * Y);
+  return (s.form.x - fminf(q1, q2)) + fmaf(M, 0x1p-20f, 0.01f) >= e_zero;
+}
+
+// Index of the lowest set bit of m, or 64 if there is none.
+__device__ __forceinline__ int low_bit(unsigned long long m) { return m ? __builtin_ctzll(m) : 64; }
+
+}  // namespace
+}  // namespace celeste
