@@ -93,13 +93,13 @@ enum {                          /* context options (celeste_ctx_set_option) */
                                    kernel takes per step: 8, 16, 32 or 64 (default 8) */
   CELESTE_OPT_VALUE_BLOCK = 7,  /* threads per value-kernel block: 128 or 256 (default 256) */
   CELESTE_OPT_VALUE_TILE_W = 8, /* tile width of the value kernel: 8, 16, 32 or 64 (default 8) */
-  CELESTE_OPT_EXACT_ZERO = 9,   /* skip threshold of the value+gradient+Hessian kernel: a mixture
+  CELESTE_OPT_EXACT_ZERO = 9,   /* skip threshold of the pixel kernels: a mixture
                                    component whose density is below 2^-v on a whole tile is skipped.
                                    160 (always exact: below the smallest FP32 subnormal), 127 (exact
                                    where the device's exp2 flushes results below 2^-126 to zero, which
                                    the context checks at creation; E_UNSUPPORTED elsewhere), 0 for
                                    the context's choice (127 where exact, else 160; the default), or
-                                   1 to skip nothing: every component, galaxy group and tile is
+                                   1 to skip nothing: every component and tile is
                                    evaluated (the reference the skips are tested against) */
   CELESTE_OPT_PERSISTENT = 10,  /* trust-region fits (celeste_newton_fit, celeste_batch_fit): before
                                    each value+gradient+Hessian pass the work items of the sources

@@ -1000,7 +1000,7 @@ int eval_impl(celeste_ctx* ctx, const celeste_batch* b, const double* theta, dou
     ctx->stats.grad_launches += 1;
   } else {
     HIPCHK(launch_eval_value(B.items, P.n_items, B.imgs, B.tables, P.tstride, P.prof.n_exp, P.prof.n_dev, nullptr,
-                             B.partials, ctx->vblock, ctx->variant, ctx->vtile_log2, st, kept));
+                             B.partials, ctx->vblock, ctx->variant, ctx->vtile_log2, ctx->e_zero, st, kept));
     T.mark(2, st);
     HIPCHK(launch_reduce_value(B.srcs, P.n_src, B.imgs, B.partials, B.img_const, th_dev, P.prior, nullptr, d_elbo,
                                ctr_value(ctx), st, px_weight));
@@ -1223,7 +1223,7 @@ int enqueue_iteration(celeste_ctx* ctx, const Packed& P, const FitDev& F, const 
   HIPCHK(launch_setup(imgs, P.n_img, F.theta_trial, F.active, P.prof, tables, P.tstride, st));
   T->mark(5, st);
   HIPCHK(launch_eval_value(items, P.n_items, imgs, tables, P.tstride, P.prof.n_exp, P.prof.n_dev, F.active, parts,
-                           ctx->vblock, ctx->variant, ctx->vtile_log2, st));
+                           ctx->vblock, ctx->variant, ctx->vtile_log2, ctx->e_zero, st));
   T->mark(6, st);
   HIPCHK(launch_reduce_value(srcs, P.n_src, imgs, parts, ic, F.theta_trial, P.prior, F.active, F.f_trial,
                              ctr_value(ctx), st));
@@ -1366,7 +1366,7 @@ int fit_begin(celeste_ctx* ctx, const celeste_batch* b, const double* theta_inou
       HIPCHK(launch_setup(imgs0, P.n_img, tk, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st));
       HIPCHK(launch_eval_value(as<WorkItem>(ctx->items), P.n_items, imgs0, as<float>(ctx->tables), P.tstride,
                                P.prof.n_exp, P.prof.n_dev, nullptr, as<double>(ctx->partials), ctx->vblock, ctx->variant,
-                             ctx->vtile_log2, st));
+                             ctx->vtile_log2, ctx->e_zero, st));
       HIPCHK(launch_reduce_value(as<SrcDev>(ctx->srcs), S, imgs0, as<double>(ctx->partials),
                                  as<double>(ctx->img_const), tk, P.prior, nullptr, k == 0 ? F.f : F.f_trial,
                                  ctr_value(ctx), st));
@@ -1385,7 +1385,7 @@ int fit_begin(celeste_ctx* ctx, const celeste_batch* b, const double* theta_inou
     HIPCHK(launch_setup(imgs, P.n_img, F.theta, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st));
     HIPCHK(launch_eval_value(as<WorkItem>(ctx->items), P.n_items, imgs, as<float>(ctx->tables), P.tstride,
                              P.prof.n_exp, P.prof.n_dev, nullptr, as<double>(ctx->partials), ctx->vblock,
-                             ctx->variant, ctx->vtile_log2, st));
+                             ctx->variant, ctx->vtile_log2, ctx->e_zero, st));
     HIPCHK(launch_reduce_value(as<SrcDev>(ctx->srcs), S, imgs, as<double>(ctx->partials),
                                as<double>(ctx->img_const), F.theta, P.prior, nullptr, F.f, ctr_value(ctx), st));
     ctx->stats.value_launches += 1;
@@ -1636,7 +1636,7 @@ int run_fit_sampled(celeste_ctx* ctx, const celeste_batch* b, double* theta_inou
   HIPCHK(launch_split(F.active, F.samp, F.fa, F.fb, S, st));
   HIPCHK(launch_setup(imgs, P.n_img, F.theta, F.fb, P.prof, tables, P.tstride, st));
   HIPCHK(launch_eval_value(items_s, Ps.n_items, imgs_s, tables, P.tstride, P.prof.n_exp, P.prof.n_dev, F.fb, parts_s,
-                           ctx->vblock, ctx->variant, ctx->vtile_log2, st, kept));
+                           ctx->vblock, ctx->variant, ctx->vtile_log2, ctx->e_zero, st, kept));
   HIPCHK(launch_reduce_value(srcs_s, S, imgs_s, parts_s, ic, F.theta, P.prior, F.fb, F.f, ctr_value(ctx), st, w));
   stage(ctx->stats.ms_start, st);
   PhaseTimer T;
@@ -1662,9 +1662,9 @@ int run_fit_sampled(celeste_ctx* ctx, const celeste_batch* b, double* theta_inou
     HIPCHK(launch_setup(imgs, P.n_img, F.theta_trial, F.active, P.prof, tables, P.tstride, st));
     t->mark(5, st);
     HIPCHK(launch_eval_value(items, P.n_items, imgs, tables, P.tstride, P.prof.n_exp, P.prof.n_dev, F.fa, parts,
-                             ctx->vblock, ctx->variant, ctx->vtile_log2, st));
+                             ctx->vblock, ctx->variant, ctx->vtile_log2, ctx->e_zero, st));
     HIPCHK(launch_eval_value(items_s, Ps.n_items, imgs_s, tables, P.tstride, P.prof.n_exp, P.prof.n_dev, F.fb, parts_s,
-                             ctx->vblock, ctx->variant, ctx->vtile_log2, st, kept));
+                             ctx->vblock, ctx->variant, ctx->vtile_log2, ctx->e_zero, st, kept));
     t->mark(6, st);
     HIPCHK(launch_reduce_value(srcs, S, imgs, parts, ic, F.theta_trial, P.prior, F.fa, F.f_trial, ctr_value(ctx), st));
     HIPCHK(launch_reduce_value(srcs_s, S, imgs_s, parts_s, ic, F.theta_trial, P.prior, F.fb, F.f_trial,
@@ -1784,7 +1784,7 @@ int run_lbfgs(celeste_ctx* ctx, const celeste_batch* b, double* theta_inout, con
     HIPCHK(launch_setup(imgs, P.n_img, F.theta_trial, X.in_ls, P.prof, tables, P.tstride, st));
     t->mark(5, st);
     HIPCHK(launch_eval_value(items, P.n_items, imgs, tables, P.tstride, P.prof.n_exp, P.prof.n_dev, X.in_ls, parts,
-                             ctx->vblock, ctx->variant, ctx->vtile_log2, st));
+                             ctx->vblock, ctx->variant, ctx->vtile_log2, ctx->e_zero, st));
     t->mark(6, st);
     HIPCHK(launch_reduce_value(srcs, P.n_src, imgs, parts, ic, F.theta_trial, P.prior, X.in_ls, F.f_trial,
                                ctr_value(ctx), st));
@@ -2453,7 +2453,8 @@ int autotune(celeste_ctx* ctx, const celeste_batch* b, const double* theta, int6
         double ms = 0.0;
         CHK(time_min(st, 3, [&]() {
           return launch_eval_value(as<WorkItem>(ctx->items), P.n_items, di, tables, P.tstride, P.prof.n_exp,
-                                   P.prof.n_dev, nullptr, as<double>(ctx->partials), vblock, r.variant, tl, st);
+                                   P.prof.n_dev, nullptr, as<double>(ctx->partials), vblock, r.variant, tl,
+                                   ctx->e_zero, st);
         }, &ms));
         r.n_candidates += 1;
         if (vblock == 256 && tl == 3 && r.chunk_px == 4096) r.default_value_ms = ms;
@@ -2476,7 +2477,7 @@ int autotune(celeste_ctx* ctx, const celeste_batch* b, const double* theta, int6
     HIPCHK(launch_setup(di, P.n_img, th_dev, nullptr, P.prof, tables, P.tstride, st));
     CHK(time_min(st, 3, [&]() {
       return launch_eval_value(as<WorkItem>(ctx->items), P.n_items, di, tables, P.tstride, P.prof.n_exp,
-                               P.prof.n_dev, nullptr, as<double>(ctx->partials), 256, 3, 3, st);
+                               P.prof.n_dev, nullptr, as<double>(ctx->partials), 256, 3, 3, ctx->e_zero, st);
     }, &r.default_value_ms));
   }
   guard.saved = r.chunk_px;  // the guard leaves the chosen size on the context

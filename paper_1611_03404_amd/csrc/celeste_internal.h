@@ -72,22 +72,24 @@ constexpr int W4 = 73;                   // [6 pairs][5]: B4 contraction
 constexpr int W2 = 103;                  // [6 pairs][3]: (W_xx/2, W_xy, W_yy/2) of d2W/deta deta'
 constexpr int STAR = 128;                // [CELESTE_MAX_PSF][16]
 constexpr int STAR_REC = 16;
-constexpr int GAL = 192;                 // [n_psf][n_exp + n_dev][GAL_REC]
-constexpr int GAL_REC = 24;
-// galaxy record fields
+// galaxy components [n_psf][n_exp + n_dev]: first the exponents' constants of all of them (c0, qxx, qxy,
+// qyy: all that the value kernel and the whole-tile skip read, 16 bytes each, side by side), then
+// their records, which hold the exponents' constants again (one record is one run of scalar loads; with the
+// exponents left out of it the value+gradient+Hessian kernel took 18.7 instead of 17.7 ms)
+constexpr int EXPO = 192;
+constexpr int EXPO_REC = 4;
+constexpr int GAL_REC = 20;
+constexpr int gal_at(int n_gal) { return EXPO + EXPO_REC * n_gal; }
+// record fields; star records: c0, qxx, qxy, qyy, Pxx, Pxy, Pyy, xi_x, xi_y
 constexpr int R_C0 = 0, R_QXX = 1, R_QXY = 2, R_QYY = 3, R_PXX = 4, R_PXY = 5, R_PYY = 6, R_NU = 7;
 constexpr int R_3PXX = 8, R_3PYY = 9, R_2PXY = 10, R_6PXX = 11, R_6PYY = 12, R_3PXY = 13, R_4PXY = 14;
 constexpr int R_K4A = 15, R_K4B = 16, R_K4C = 17, R_K4D = 18, R_K4E = 19;
-// star record fields: c0, qxx, qxy, qyy, Pxx, Pxy, Pyy, xi_x, xi_y
 constexpr int S_XIX = 7, S_XIY = 8;
-// bound of the galaxy components of one PSF component: each has log2 density at most
-// S_GC0 + S_GMU |d|^2 at offset d from the PSF component's centre (S_GMU < 0)
-constexpr int S_GC0 = 9, S_GMU = 10;
 }  // namespace tab
 
 inline int table_stride(int max_psf, int n_exp, int n_dev) {
-  int n = tab::GAL + max_psf * (n_exp + n_dev) * tab::GAL_REC;
-  return (n + 15) & ~15;
+  const int n = max_psf * (n_exp + n_dev);
+  return (tab::gal_at(n) + n * tab::GAL_REC + 15) & ~15;
 }
 
 // ---------------------------------------------------------------- device work queue
@@ -151,7 +153,7 @@ hipError_t launch_eval_grad(const WorkItem* items, int n_items, const ImgDev* im
 hipError_t launch_exp2_probe(const float* in, float* out, int n, hipStream_t st);
 hipError_t launch_eval_value(const WorkItem* items, int n_items, const ImgDev* imgs, const float* tables,
                              int tstride, int n_exp, int n_dev, const int* src_flag, double* partials,
-                             int block, int variant, int tw_log2, hipStream_t st,
+                             int block, int variant, int tw_log2, float e_zero, hipStream_t st,
                              const int* kept = nullptr);
 // px_weight scales every image's pixel partials (not its theta-free constant): 1/p for a
 // pixel subsample whose work items cover only the kept rows.

@@ -34,9 +34,9 @@ __device__ __noinline__ void source_rate(const float* __restrict__ T, float dx0,
     const float dx = dx0 - sr[S_XIX], dy = dy0 - sr[S_XIY];
     const float dxx = dx * dx, dxy = dx * dy, dyy = dy * dy;
     Gs += comp(sr, dxx, dxy, dyy);
-    const float* __restrict__ base = T + GAL + k * ncomp * GAL_REC;
-    for (int j = 0; j < ne; ++j) gx += comp(base + j * GAL_REC, dxx, dxy, dyy);
-    for (int j = ne; j < ncomp; ++j) gd += comp(base + j * GAL_REC, dxx, dxy, dyy);
+    const float* __restrict__ base = T + EXPO + k * ncomp * EXPO_REC;
+    for (int j = 0; j < ne; ++j) gx += comp(base + j * EXPO_REC, dxx, dxy, dyy);
+    for (int j = ne; j < ncomp; ++j) gd += comp(base + j * EXPO_REC, dxx, dxy, dyy);
   }
   const float ed = T[EDEV];
   const float Gg = fmaf(ed, gd - gx, gx);

@@ -84,16 +84,16 @@ __device__ __forceinline__ void zero(GalAcc& A) {
   for (int i = 0; i < 5; ++i) A.b4[i] = 0.f;
 }
 
-// The fields of a galaxy component's record that the Hermite moments read, copied out of the table so
-// that the next component's loads can be issued while one is evaluated.
+// A galaxy component's record, copied out of the table so that the next component's loads can be
+// issued while one is evaluated.
 struct GalRec {
-  float v[20];
+  float v[GAL_REC];
 };
 
 __device__ __forceinline__ GalRec load_rec(const float* __restrict__ r) {
   GalRec g;
 #pragma unroll
-  for (int i = 0; i < 20; ++i) g.v[i] = r[i];
+  for (int i = 0; i < GAL_REC; ++i) g.v[i] = r[i];
   return g;
 }
 
@@ -152,11 +152,33 @@ __device__ __forceinline__ void gal_comp(const GalRec& g, float dx, float dy, fl
   A.b4[4] = fmaf(Nn2, h44, A.b4[4]);
 }
 
-// acc += density of one component (value path).  No exact-zero skip here: one exp costs less
-// than the wavefront test and branch (measured: 24.7 ms without, 29.7 ms as a select, 42.4 ms as
-// a branch, for one value pass over 1.9e9 pixels).
-__device__ __forceinline__ void gal_value(const float* __restrict__ r, float dxx, float dxy, float dyy, float& acc) {
-  acc += ex2(fmaf(r[R_QXX], dxx, fmaf(r[R_QXY], dxy, fmaf(r[R_QYY], dyy, r[R_C0]))));
+// The exponent's constants of a component (value path).
+struct ValRec {
+  float c0, qxx, qxy, qyy;
+};
+
+__device__ __forceinline__ ValRec load_val(const float* __restrict__ r) {
+  return ValRec{r[R_C0], r[R_QXX], r[R_QXY], r[R_QYY]};
+}
+
+// The exponents' constants of N consecutive components in scalar registers, loaded together.
+template <int N>
+struct ExpoBlock {
+  typedef float V4 __attribute__((ext_vector_type(4), aligned(16)));
+  V4 v[N];
+  __device__ __forceinline__ void load(const float* __restrict__ e) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) v[j] = *reinterpret_cast<const V4*>(e + j * EXPO_REC);
+    // used here: sunk to the conditional uses that follow, each would wait for a load of its own
+#pragma unroll
+    for (int j = 0; j < N; ++j) asm volatile("" ::"s"(v[j]));
+  }
+  __device__ __forceinline__ ValRec rec(int j) const { return ValRec{v[j].x, v[j].y, v[j].z, v[j].w}; }
+};
+
+// acc += density of one component (value path).
+__device__ __forceinline__ void comp_value(const ValRec& r, float dxx, float dxy, float dyy, float& acc) {
+  acc += ex2(fmaf(r.qxx, dxx, fmaf(r.qxy, dxy, fmaf(r.qyy, dyy, r.c0))));
 }
 
 constexpr int tri(int i, int j) { return i * NZ - (i * (i - 1)) / 2 + (j - i); }
@@ -368,10 +390,8 @@ __global__ __launch_bounds__(BLOCK, MINW) void k_eval_full(const WorkItem* __res
   if (!q.items && src_flag && !src_flag[wi.src]) break;
   const ImgDev& im = imgs[wi.img];
   const float* __restrict__ T = tables + (size_t)wi.img * tstride;
-  const int w = im.w, pitch = im.pitch, npitch = im.nbr_pitch, npsf = im.n_psf;
-  const GlobalF pix = global(im.pix);
-  const GlobalF nbrE = global(im.nbr_mean);
-  const GlobalF nbrV = global(im.nbr_var);
+  const int w = im.w, npsf = im.n_psf;
+  const Pixels pix(im);
   const int ne = NE > 0 ? NE : n_exp;
   const int ncomp = NE > 0 ? NE + ND : n_exp + n_dev;
   const float psx = T[PSX], psy = T[PSY], io = T[CALIB], sky = T[SKY];
@@ -380,11 +400,12 @@ __global__ __launch_bounds__(BLOCK, MINW) void k_eval_full(const WorkItem* __res
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   TileMap<PK, BLOCK / 64> tm(wi, w, im.h, tw_log2, kept, wv);
   const int n_gal = npsf * ncomp;   // at most 64
-  const float* __restrict__ G = T + GAL;
+  const float* __restrict__ G = T + gal_at(n_gal);
   if (threadIdx.x < n_gal) skip[threadIdx.x] = skip_test_of(T, threadIdx.x, ncomp);
+  touch_table(T, gal_at(n_gal) + n_gal * GAL_REC);
   __syncthreads();
   const SkipTest& my_skip = skip[min(lane, n_gal - 1)];
-  const unsigned long long gal_lanes = n_gal >= 64 ? ~0ull : (1ull << n_gal) - 1;
+  const unsigned long long gal_lanes = lane_mask(n_gal);
   double val = 0.0;                 // ELBO value, per lane
   // FP64 wavefront sums of the derivative entries, in LDS between flushes (ten registers a lane
   // otherwise): the first lane of each quad holds 5 of them
@@ -432,19 +453,13 @@ __global__ __launch_bounds__(BLOCK, MINW) void k_eval_full(const WorkItem* __res
     int row, col, first;
     bool live;
     tm.pixel(lane, row, col, live, first);   // (row, col) is inside the image on every lane
-    const float xp = pix[(int64_t)row * pitch + col];
-    const float en = nbrE ? nbrE[(int64_t)row * npitch + col] : 0.f;
-    const float vn = nbrV ? nbrV[(int64_t)row * npitch + col] : 0.f;
+    float xp, en, vn;
+    pix.load(row, col, xp, en, vn);
     const float x = live ? xp : 0.f, ebg = sky + (live ? en : 0.f), vbg = live ? vn : 0.f;
     const float dx0 = live ? (float)col - psx : FAR, dy0 = live ? (float)row - psy : FAR;
 
-    unsigned long long hits;   // galaxy components that may be non-zero on the tile
-    {
-      bool more;
-      hits = __ballot(may_hit(my_skip, tm.box(col, first, false, &more), psx, psy, e_zero));
-      if (more) hits |= __ballot(may_hit(my_skip, tm.box(col, first, true, &more), psx, psy, e_zero));
-      hits &= gal_lanes;
-    }
+    // galaxy components that may be non-zero on the tile
+    unsigned long long hits = tile_hits(my_skip, tm, col, first, psx, psy, e_zero) & gal_lanes;
     bool hit = hits != 0ull;   // some component is not exactly 0 on this tile (wavefront-uniform)
 
     // ---- star: N, dN/dp, d2N/dp2; galaxy: Hermite moments per profile type.  The galaxy's hits are
@@ -812,54 +827,86 @@ __global__ __launch_bounds__(BLOCK, MINW) void k_eval_full(const WorkItem* __res
   }   // items
 }
 
+// ELBO value only.  Bound by vector issue (a quarter-rate exponential, three FMAs, a move and an addition
+// per component); components that are exactly 0 on the tile are known from its box (tiles.h), so the
+// exponents' constants of a PSF component's group are loaded in two blocks and its components evaluated
+// in pairs, a pair where either may be non-zero, by scalar tests of the hit bits.  (Testing components one by
+// one on the tile's pixels, and a loop over the hits with a load each, were no faster than evaluating
+// every component.)  One pass over 1.4e8 px of 1,500 uneven sources with neighbour arrays: 1.23 ms, 1.72 ms
+// with every component evaluated.
 template <int BLOCK, int NE, int ND, bool PK>
 __global__ __launch_bounds__(BLOCK) void k_eval_value(const WorkItem* __restrict__ items,
                                                       const ImgDev* __restrict__ imgs,
                                                       const float* __restrict__ tables, int tstride, int n_exp_rt,
                                                       int n_dev_rt, const int* __restrict__ src_flag,
-                                                      int tw_log2, const int* __restrict__ kept,
+                                                      int tw_log2, float e_zero, const int* __restrict__ kept,
                                                       double* __restrict__ partials) {
   const int n_exp = NE > 0 ? NE : n_exp_rt, n_dev = NE > 0 ? ND : n_dev_rt;
   __shared__ double red[BLOCK / 64];
+  __shared__ SkipTest skip[64];
   const WorkItem wi = items[blockIdx.x];
   if (src_flag && !src_flag[wi.src]) return;
   const ImgDev& im = imgs[wi.img];
   const float* __restrict__ T = tables + (size_t)wi.img * tstride;
-  const int w = im.w, pitch = im.pitch, npitch = im.nbr_pitch, npsf = im.n_psf;
-  const GlobalF pix = global(im.pix);
-  const GlobalF nbrE = global(im.nbr_mean);
-  const GlobalF nbrV = global(im.nbr_var);
+  const int w = im.w, npsf = im.n_psf;
+  const Pixels pix(im);
   const int ncomp = n_exp + n_dev;
-  const float psx = T[PSX], psy = T[PSY], io = T[CALIB], sky = T[SKY];
-  const float ed = T[EDEV];
-  const float cs = T[CS], cg = T[CG], Ks = T[KS], Kg = T[KG], Ksg = T[KSG];
+  float psx = T[PSX], psy = T[PSY], io = T[CALIB], sky = T[SKY], ed = T[EDEV];
+  float cs = T[CS], cg = T[CG], Ks = T[KS], Kg = T[KG], Ksg = T[KSG];
+  for (float* c : {&psx, &psy, &io, &sky, &ed, &cs, &cg, &Ks, &Kg, &Ksg}) to_vector(*c);
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   TileMap<PK, BLOCK / 64> tm(wi, w, im.h, tw_log2, kept, wv);
+  const int n_gal = npsf * ncomp;   // at most 64
+  const float* __restrict__ E = T + EXPO;
+  if (threadIdx.x < n_gal) skip[threadIdx.x] = skip_test_of(T, threadIdx.x, ncomp);
+  touch_table(T, gal_at(n_gal));
+  __syncthreads();
+  const SkipTest my_skip = skip[min(lane, n_gal - 1)];
+  const unsigned long long gal_lanes = lane_mask(n_gal);
   double acc = 0.0;
   for (; tm.more(); tm.next()) {
     int row, col, first;
     bool live;
     tm.pixel(lane, row, col, live, first);   // (row, col) is inside the image on every lane
-    const float xp = pix[(int64_t)row * pitch + col];
-    const float en = nbrE ? nbrE[(int64_t)row * npitch + col] : 0.f;
-    const float vn = nbrV ? nbrV[(int64_t)row * npitch + col] : 0.f;
+    float xp, en, vn;
+    pix.load(row, col, xp, en, vn);
     const float x = live ? xp : 0.f, ebg = sky + (live ? en : 0.f), vbg = live ? vn : 0.f;
     const float dx0 = live ? (float)col - psx : FAR, dy0 = live ? (float)row - psy : FAR;
+    unsigned long long hits = tile_hits(my_skip, tm, col, first, psx, psy, e_zero) & gal_lanes;
     float Gs = 0.f, gx = 0.f, gd = 0.f;
     for (int k = 0; k < npsf; ++k) {
       const float* __restrict__ r = T + STAR + k * STAR_REC;
+      const float* __restrict__ Ek = E + k * ncomp * EXPO_REC;
+      const unsigned hk = (unsigned)(hits >> (k * ncomp));   // bits from ncomp on: the next groups'
       const float dx = dx0 - r[S_XIX], dy = dy0 - r[S_XIY];
       const float dxx = dx * dx, dxy = dx * dy, dyy = dy * dy;
-      gal_value(r, dxx, dxy, dyy, Gs);
-      const float* __restrict__ base = T + GAL + k * ncomp * GAL_REC;
+      comp_value(load_val(r), dxx, dxy, dyy, Gs);
       if constexpr (NE > 0) {
+        constexpr int NC = NE + ND;
+        if ((hk & ((1u << NC) - 1)) == 0) continue;
+        {
+          ExpoBlock<NE> v;
+          v.load(Ek);
 #pragma unroll
-        for (int j = 0; j < NE; ++j) gal_value(base + j * GAL_REC, dxx, dxy, dyy, gx);
+          for (int j = 0; j < NE; j += 2)
+            if (hk & (3u << j)) {
+              comp_value(v.rec(j), dxx, dxy, dyy, gx);
+              if (j + 1 < NE) comp_value(v.rec(j + 1), dxx, dxy, dyy, gx);
+            }
+        }
+        {
+          ExpoBlock<ND> v;
+          v.load(Ek + NE * EXPO_REC);
 #pragma unroll
-        for (int j = NE; j < NE + ND; ++j) gal_value(base + j * GAL_REC, dxx, dxy, dyy, gd);
+          for (int j = 0; j < ND; j += 2)
+            if ((hk >> NE) & (3u << j)) {
+              comp_value(v.rec(j), dxx, dxy, dyy, gd);
+              if (j + 1 < ND) comp_value(v.rec(j + 1), dxx, dxy, dyy, gd);
+            }
+        }
       } else {
-        for (int j = 0; j < n_exp; ++j) gal_value(base + j * GAL_REC, dxx, dxy, dyy, gx);
-        for (int j = n_exp; j < ncomp; ++j) gal_value(base + j * GAL_REC, dxx, dxy, dyy, gd);
+        for (int j = 0; j < ncomp; ++j)
+          if ((hk >> j) & 1u) comp_value(load_val(Ek + j * EXPO_REC), dxx, dxy, dyy, j < n_exp ? gx : gd);
       }
     }
     const float Gg = fmaf(ed, gd - gx, gx);
@@ -889,12 +936,22 @@ struct GalAcc1 {
   float b2xx, b2xy, b2yy;
 };
 
-// One galaxy component, first order only; false (on every lane) when it is exactly 0 on the tile.
-__device__ __forceinline__ bool gal_comp1(const float* __restrict__ r, float dx, float dy, float dxx, float dxy,
-                                          float dyy, float e_zero, GalAcc1& A) {
-  const float e = fmaf(r[R_QXX], dxx, fmaf(r[R_QXY], dxy, fmaf(r[R_QYY], dyy, r[R_C0])));
-  if (!wave_any(e >= e_zero)) return false;
-  const float N = ex2(e);
+struct GradRec {
+  float v[8];
+};
+
+__device__ __forceinline__ GradRec load_grad(const float* __restrict__ r) {
+  GradRec g;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) g.v[i] = r[i];
+  return g;
+}
+
+// One galaxy component, first order only.
+__device__ __forceinline__ void gal_comp1(const GradRec& g, float dx, float dy, float dxx, float dxy, float dyy,
+                                          GalAcc1& A) {
+  const float* r = g.v;
+  const float N = ex2(fmaf(r[R_QXX], dxx, fmaf(r[R_QXY], dxy, fmaf(r[R_QYY], dyy, r[R_C0]))));
   const float Pxx = r[R_PXX], Pxy = r[R_PXY], Pyy = r[R_PYY];
   const float bx = fmaf(Pxx, dx, Pxy * dy);
   const float by = fmaf(Pxy, dx, Pyy * dy);
@@ -905,7 +962,6 @@ __device__ __forceinline__ bool gal_comp1(const float* __restrict__ r, float dx,
   A.b2xx = fmaf(Nn, fmaf(bx, bx, -Pxx), A.b2xx);
   A.b2xy = fmaf(Nn, fmaf(bx, by, -Pxy), A.b2xy);
   A.b2yy = fmaf(Nn, fmaf(by, by, -Pyy), A.b2yy);
-  return true;
 }
 
 constexpr int NG = NGRAD;   // entries of a gradient partial: value and the 11 z-gradient entries
@@ -913,7 +969,8 @@ constexpr int NG = NGRAD;   // entries of a gradient partial: value and the 11 z
 // Value and z-gradient of the pixel sum (no Hessian): the same per-pixel model as k_eval_full
 // with first-order moments only (6 sums per galaxy component instead of 18) and no second-
 // order terms; value and gradient accumulated per lane in FP64.  One partial of NG doubles per
-// work item.  Exactly-zero components, galaxy groups and tiles are skipped as in k_eval_full.
+// work item.  Exactly-zero components and tiles are skipped as in k_eval_full (100 sources of 21..61
+// px sides, 500 work items: 63 us, 80 us with a test per component).
 template <int BLOCK, int NE, int ND, bool PK>
 __global__ __launch_bounds__(BLOCK) void k_eval_grad(const WorkItem* __restrict__ items,
                                                      const ImgDev* __restrict__ imgs,
@@ -922,20 +979,26 @@ __global__ __launch_bounds__(BLOCK) void k_eval_grad(const WorkItem* __restrict_
                                                      float e_zero, const int* __restrict__ kept,
                                                      double* __restrict__ partials) {
   __shared__ double red[BLOCK / 64][NG];
+  __shared__ SkipTest skip[64];
   const WorkItem wi = items[blockIdx.x];
   if (src_flag && !src_flag[wi.src]) return;
   const int ne = NE > 0 ? NE : n_exp_rt;
   const int ncomp = NE > 0 ? NE + ND : n_exp_rt + n_dev_rt;
   const ImgDev& im = imgs[wi.img];
   const float* __restrict__ T = tables + (size_t)wi.img * tstride;
-  const int w = im.w, pitch = im.pitch, npitch = im.nbr_pitch, npsf = im.n_psf;
-  const GlobalF pix = global(im.pix);
-  const GlobalF nbrE = global(im.nbr_mean);
-  const GlobalF nbrV = global(im.nbr_var);
+  const int w = im.w, npsf = im.n_psf;
+  const Pixels pix(im);
   const float psx = T[PSX], psy = T[PSY], io = T[CALIB], sky = T[SKY];
   const float io2 = io * io;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   TileMap<PK, BLOCK / 64> tm(wi, w, im.h, tw_log2, kept, wv);
+  const int n_gal = npsf * ncomp;   // at most 64
+  const float* __restrict__ G = T + gal_at(n_gal);
+  if (threadIdx.x < n_gal) skip[threadIdx.x] = skip_test_of(T, threadIdx.x, ncomp);
+  touch_table(T, gal_at(n_gal) + n_gal * GAL_REC);
+  __syncthreads();
+  const SkipTest& my_skip = skip[min(lane, n_gal - 1)];
+  const unsigned long long gal_lanes = lane_mask(n_gal);
   double acc[NG];
 #pragma unroll
   for (int j = 0; j < NG; ++j) acc[j] = 0.0;
@@ -943,41 +1006,43 @@ __global__ __launch_bounds__(BLOCK) void k_eval_grad(const WorkItem* __restrict_
     int row, col, first;
     bool live;
     tm.pixel(lane, row, col, live, first);   // (row, col) is inside the image on every lane
-    const float xp = pix[(int64_t)row * pitch + col];
-    const float en = nbrE ? nbrE[(int64_t)row * npitch + col] : 0.f;
-    const float vn = nbrV ? nbrV[(int64_t)row * npitch + col] : 0.f;
+    float xp, en, vn;
+    pix.load(row, col, xp, en, vn);
     const float x = live ? xp : 0.f, ebg = sky + (live ? en : 0.f), vbg = live ? vn : 0.f;
     const float dx0 = live ? (float)col - psx : FAR, dy0 = live ? (float)row - psy : FAR;
 
-    bool hit = false;
+    unsigned long long hits = tile_hits(my_skip, tm, col, first, psx, psy, e_zero) & gal_lanes;
+    bool hit = hits != 0ull;
     float s0 = 0.f, s1x = 0.f, s1y = 0.f;
-    for (int k = 0; k < npsf; ++k) {
-      const float* __restrict__ r = T + STAR + k * STAR_REC;
-      const float dx = dx0 - r[S_XIX], dy = dy0 - r[S_XIY];
-      const float e = fmaf(r[R_QXX], dx * dx, fmaf(r[R_QXY], dx * dy, fmaf(r[R_QYY], dy * dy, r[R_C0])));
-      if (!wave_any(e >= e_zero)) continue;
-      hit = true;
-      const float N = ex2(e);
-      s0 += N;
-      s1x = fmaf(N, fmaf(r[R_PXX], dx, r[R_PXY] * dy), s1x);
-      s1y = fmaf(N, fmaf(r[R_PXY], dx, r[R_PYY] * dy), s1y);
-    }
     GalAcc1 X = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, D = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int k = 0; k < npsf; ++k) {
-      const float* __restrict__ sr = T + STAR + k * STAR_REC;
-      const float dx = dx0 - sr[S_XIX], dy = dy0 - sr[S_XIY];
-      const float dxx = dx * dx, dxy = dx * dy, dyy = dy * dy;
-      if (!wave_any(fmaf(sr[S_GMU], dxx + dyy, sr[S_GC0]) >= e_zero - 1.f)) continue;
-      const float* __restrict__ base = T + GAL + k * ncomp * GAL_REC;
-      if constexpr (NE > 0) {
-#pragma unroll
-        for (int j = 0; j < NE; ++j) hit |= gal_comp1(base + j * GAL_REC, dx, dy, dxx, dxy, dyy, e_zero, X);
-#pragma unroll
-        for (int j = NE; j < NE + ND; ++j) hit |= gal_comp1(base + j * GAL_REC, dx, dy, dxx, dxy, dyy, e_zero, D);
-      } else {
-        for (int j = 0; j < ne; ++j) hit |= gal_comp1(base + j * GAL_REC, dx, dy, dxx, dxy, dyy, e_zero, X);
-        for (int j = ne; j < ncomp; ++j) hit |= gal_comp1(base + j * GAL_REC, dx, dy, dxx, dxy, dyy, e_zero, D);
+    int c = low_bit(hits);
+    GradRec nx = load_grad(G + (hits ? c : 0) * GAL_REC);
+    StarRec ns = load_star(T + STAR);
+    auto evaluate = [&](int lim, float dx, float dy, float dxx, float dxy, float dyy, GalAcc1& acc) {
+      while (c < lim) {
+        const GradRec cur = nx;
+        hits &= hits - 1;
+        c = low_bit(hits);
+        nx = load_grad(G + (hits ? c : 0) * GAL_REC);
+        gal_comp1(cur, dx, dy, dxx, dxy, dyy, acc);
       }
+    };
+    for (int k = 0; k < npsf; ++k) {
+      const StarRec sr = ns;
+      const float* r = sr.v;
+      ns = load_star(T + STAR + min(k + 1, npsf - 1) * STAR_REC);
+      const float dx = dx0 - r[S_XIX], dy = dy0 - r[S_XIY];
+      const float dxx = dx * dx, dxy = dx * dy, dyy = dy * dy;
+      const float e = fmaf(r[R_QXX], dxx, fmaf(r[R_QXY], dxy, fmaf(r[R_QYY], dyy, r[R_C0])));
+      if (wave_any(e >= e_zero)) {
+        hit = true;
+        const float N = ex2(e);
+        s0 += N;
+        s1x = fmaf(N, fmaf(r[R_PXX], dx, r[R_PXY] * dy), s1x);
+        s1y = fmaf(N, fmaf(r[R_PXY], dx, r[R_PYY] * dy), s1y);
+      }
+      evaluate(k * ncomp + ne, dx, dy, dxx, dxy, dyy, X);
+      evaluate((k + 1) * ncomp, dx, dy, dxx, dxy, dyy, D);
     }
     if (!hit) {
       // no component reaches the tile: only the neighbour-variance part of the pixel term
@@ -1106,18 +1171,17 @@ hipError_t launch_eval_grad(const WorkItem* items, int n_items, const ImgDev* im
   if (n_items <= 0) return hipSuccess;
   const bool unroll = (variant & 2) != 0 && n_exp == 6 && n_dev == 8;
   const dim3 g(n_items);
-#define CELESTE_LAUNCH_GRAD(B, E, D) \
-  if (tw_log2 == 3) CELESTE_LAUNCH_GRAD_(B, E, D, true); else CELESTE_LAUNCH_GRAD_(B, E, D, false)
-#define CELESTE_LAUNCH_GRAD_(B, E, D, PK) \
-  hipLaunchKernelGGL((k_eval_grad<B, E, D, PK>), g, dim3(B), 0, st, items, imgs, tables, tstride, n_exp, n_dev, \
-                     src_flag, tw_log2, e_zero, kept, partials)
-  if (block == 128) {
-    if (unroll) CELESTE_LAUNCH_GRAD(128, 6, 8); else CELESTE_LAUNCH_GRAD(128, 0, 0);
-  } else {
-    if (unroll) CELESTE_LAUNCH_GRAD(256, 6, 8); else CELESTE_LAUNCH_GRAD(256, 0, 0);
-  }
-#undef CELESTE_LAUNCH_GRAD
-#undef CELESTE_LAUNCH_GRAD_
+  using Kernel = decltype(&k_eval_grad<256, 6, 8, true>);
+  const bool pk = tw_log2 == 3;
+  Kernel k;
+  if (block == 128)
+    k = unroll ? (pk ? &k_eval_grad<128, 6, 8, true> : &k_eval_grad<128, 6, 8, false>)
+               : (pk ? &k_eval_grad<128, 0, 0, true> : &k_eval_grad<128, 0, 0, false>);
+  else
+    k = unroll ? (pk ? &k_eval_grad<256, 6, 8, true> : &k_eval_grad<256, 6, 8, false>)
+               : (pk ? &k_eval_grad<256, 0, 0, true> : &k_eval_grad<256, 0, 0, false>);
+  hipLaunchKernelGGL(k, g, dim3(block == 128 ? 128 : 256), 0, st, items, imgs, tables, tstride, n_exp, n_dev,
+                     src_flag, tw_log2, e_zero, kept, partials);
   return hipGetLastError();
 }
 
@@ -1136,22 +1200,21 @@ hipError_t launch_exp2_probe(const float* in, float* out, int n, hipStream_t st)
 
 hipError_t launch_eval_value(const WorkItem* items, int n_items, const ImgDev* imgs, const float* tables, int tstride,
                              int n_exp, int n_dev, const int* src_flag, double* partials, int block, int variant,
-                             int tw_log2, hipStream_t st, const int* kept) {
+                             int tw_log2, float e_zero, hipStream_t st, const int* kept) {
   if (n_items <= 0) return hipSuccess;
   const bool unroll = (variant & 2) != 0 && n_exp == 6 && n_dev == 8;
   const dim3 g(n_items);
-#define CELESTE_LAUNCH_VALUE(B, E, D) \
-  if (tw_log2 == 3) CELESTE_LAUNCH_VALUE_(B, E, D, true); else CELESTE_LAUNCH_VALUE_(B, E, D, false)
-#define CELESTE_LAUNCH_VALUE_(B, E, D, PK) \
-  hipLaunchKernelGGL((k_eval_value<B, E, D, PK>), g, dim3(B), 0, st, items, imgs, tables, tstride, n_exp, n_dev, \
-                     src_flag, tw_log2, kept, partials)
-  if (block == 128) {
-    if (unroll) CELESTE_LAUNCH_VALUE(128, 6, 8); else CELESTE_LAUNCH_VALUE(128, 0, 0);
-  } else {
-    if (unroll) CELESTE_LAUNCH_VALUE(256, 6, 8); else CELESTE_LAUNCH_VALUE(256, 0, 0);
-  }
-#undef CELESTE_LAUNCH_VALUE
-#undef CELESTE_LAUNCH_VALUE_
+  using Kernel = decltype(&k_eval_value<256, 6, 8, true>);
+  const bool pk = tw_log2 == 3;
+  Kernel k;
+  if (block == 128)
+    k = unroll ? (pk ? &k_eval_value<128, 6, 8, true> : &k_eval_value<128, 6, 8, false>)
+               : (pk ? &k_eval_value<128, 0, 0, true> : &k_eval_value<128, 0, 0, false>);
+  else
+    k = unroll ? (pk ? &k_eval_value<256, 6, 8, true> : &k_eval_value<256, 6, 8, false>)
+               : (pk ? &k_eval_value<256, 0, 0, true> : &k_eval_value<256, 0, 0, false>);
+  hipLaunchKernelGGL(k, g, dim3(block == 128 ? 128 : 256), 0, st, items, imgs, tables, tstride, n_exp, n_dev,
+                     src_flag, tw_log2, e_zero, kept, partials);
   return hipGetLastError();
 }
 

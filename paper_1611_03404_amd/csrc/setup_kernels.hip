@@ -72,31 +72,37 @@ __device__ ShapeDerivs shape_derivs(double q, double t, double s, const double* 
   return o;
 }
 
-__device__ inline void write_component(float* rec, double w, Sym2 C, bool galaxy, double nu) {
+// The exponent's constants of w N(0, C) and its precision.
+__device__ inline Sym2 write_gaussian(float* rec, double w, Sym2 C) {
   const double det = C.xx * C.yy - C.xy * C.xy;
   const double inv = 1.0 / det;
-  const double Pxx = C.yy * inv, Pxy = -C.xy * inv, Pyy = C.xx * inv;
+  const Sym2 P = {C.yy * inv, -C.xy * inv, C.xx * inv};
   rec[tab::R_C0] = (float)(log2(w) - log2(kTwoPi) - 0.5 * log2(det));
-  rec[tab::R_QXX] = (float)(-0.5 * kLog2e * Pxx);
-  rec[tab::R_QXY] = (float)(-kLog2e * Pxy);
-  rec[tab::R_QYY] = (float)(-0.5 * kLog2e * Pyy);
-  rec[tab::R_PXX] = (float)Pxx;
-  rec[tab::R_PXY] = (float)Pxy;
-  rec[tab::R_PYY] = (float)Pyy;
-  if (!galaxy) return;
+  rec[tab::R_QXX] = (float)(-0.5 * kLog2e * P.xx);
+  rec[tab::R_QXY] = (float)(-kLog2e * P.xy);
+  rec[tab::R_QYY] = (float)(-0.5 * kLog2e * P.yy);
+  rec[tab::R_PXX] = (float)P.xx;
+  rec[tab::R_PXY] = (float)P.xy;
+  rec[tab::R_PYY] = (float)P.yy;
+  return P;
+}
+
+__device__ inline void write_galaxy(float* expo, float* rec, double w, Sym2 C, double nu) {
+  const Sym2 P = write_gaussian(rec, w, C);
+  for (int i = 0; i < tab::EXPO_REC; ++i) expo[i] = rec[i];
   rec[tab::R_NU] = (float)nu;
-  rec[tab::R_3PXX] = (float)(3.0 * Pxx);
-  rec[tab::R_3PYY] = (float)(3.0 * Pyy);
-  rec[tab::R_2PXY] = (float)(2.0 * Pxy);
-  rec[tab::R_6PXX] = (float)(6.0 * Pxx);
-  rec[tab::R_6PYY] = (float)(6.0 * Pyy);
-  rec[tab::R_3PXY] = (float)(3.0 * Pxy);
-  rec[tab::R_4PXY] = (float)(4.0 * Pxy);
-  rec[tab::R_K4A] = (float)(3.0 * Pxx * Pxx);
-  rec[tab::R_K4B] = (float)(3.0 * Pxx * Pxy);
-  rec[tab::R_K4C] = (float)(2.0 * Pxy * Pxy);
-  rec[tab::R_K4D] = (float)(3.0 * Pyy * Pxy);
-  rec[tab::R_K4E] = (float)(3.0 * Pyy * Pyy);
+  rec[tab::R_3PXX] = (float)(3.0 * P.xx);
+  rec[tab::R_3PYY] = (float)(3.0 * P.yy);
+  rec[tab::R_2PXY] = (float)(2.0 * P.xy);
+  rec[tab::R_6PXX] = (float)(6.0 * P.xx);
+  rec[tab::R_6PYY] = (float)(6.0 * P.yy);
+  rec[tab::R_3PXY] = (float)(3.0 * P.xy);
+  rec[tab::R_4PXY] = (float)(4.0 * P.xy);
+  rec[tab::R_K4A] = (float)(3.0 * P.xx * P.xx);
+  rec[tab::R_K4B] = (float)(3.0 * P.xx * P.xy);
+  rec[tab::R_K4C] = (float)(2.0 * P.xy * P.xy);
+  rec[tab::R_K4D] = (float)(3.0 * P.yy * P.xy);
+  rec[tab::R_K4E] = (float)(3.0 * P.yy * P.yy);
 }
 
 // One 64-thread block per image: thread 0 writes the header and the shape
@@ -194,34 +200,18 @@ __global__ __launch_bounds__(64) void k_setup(const ImgDev* __restrict__ imgs, c
   if (t < im.n_psf) {
     const double* ps = im.psf[t];
     float* rec = T + tab::STAR + t * tab::STAR_REC;
-    write_component(rec, ps[0], Sym2{ps[3], ps[4], ps[5]}, false, 0.0);
+    write_gaussian(rec, ps[0], Sym2{ps[3], ps[4], ps[5]});
     rec[tab::S_XIX] = (float)ps[1];
     rec[tab::S_XIY] = (float)ps[2];
-    // bound of this PSF component's galaxy group: C_j = nu_j W + Sigma_k has
-    // lambda_max(C_j) <= nu_max lambda_max(W) + lambda_max(Sigma_k) and det C_j >= det Sigma_k, so
-    // each component's log2 density is at most log2(w_k amp_max / (2 pi sqrt(det Sigma_k))) -
-    // log2(e) |d|^2 / (2 (nu_max lambda_max(W) + lambda_max(Sigma_k))); both rounded up
-    double amp_max = 0.0, nu_max = 0.0;
-    for (int j = 0; j < ncomp; ++j) {
-      amp_max = fmax(amp_max, prof.amp[j]);
-      nu_max = fmax(nu_max, prof.var[j]);
-    }
-    auto lam_max = [](double a, double b, double c) { return 0.5 * (a + c) + sqrt(0.25 * (a - c) * (a - c) + b * b); };
-    const double lmax = nu_max * lam_max(sd.W.xx, sd.W.xy, sd.W.yy) + lam_max(ps[3], ps[4], ps[5]);
-    const double c0b = log2(ps[0] * amp_max) - log2(kTwoPi) - 0.5 * log2(ps[3] * ps[5] - ps[4] * ps[4]);
-    const double mub = -0.5 * kLog2e / lmax;
-    float c0f = (float)c0b, muf = (float)mub;
-    if ((double)c0f < c0b) c0f = nextafterf(c0f, INFINITY);
-    if ((double)muf < mub) muf = nextafterf(muf, INFINITY);
-    rec[tab::S_GC0] = c0f;
-    rec[tab::S_GMU] = muf;
   }
-  for (int c = t; c < im.n_psf * ncomp; c += blockDim.x) {
+  const int n_gal = im.n_psf * ncomp;
+  float* G = T + tab::gal_at(n_gal);
+  for (int c = t; c < n_gal; c += blockDim.x) {
     const int k = c / ncomp, j = c - k * ncomp;
     const double* ps = im.psf[k];
     const double nu = prof.var[j];
     Sym2 C = {nu * sd.W.xx + ps[3], nu * sd.W.xy + ps[4], nu * sd.W.yy + ps[5]};
-    write_component(T + tab::GAL + c * tab::GAL_REC, ps[0] * prof.amp[j], C, true, nu);
+    write_galaxy(T + tab::EXPO + c * tab::EXPO_REC, G + c * tab::GAL_REC, ps[0] * prof.amp[j], C, nu);
   }
 }
 

@@ -20,6 +20,26 @@ struct TileBox {
 typedef const __attribute__((address_space(1))) float* GlobalF;
 __device__ __forceinline__ GlobalF global(const float* p) { return (GlobalF)p; }
 
+// The pixels of an image and, where given, its neighbour arrays.  (A second address form for images whose
+// byte offsets fit in 32 bits, one 24-bit multiply-add instead of a 64-bit product, was slower: the
+// scalars it holds cost the value+gradient+Hessian kernel more in spills, 18.1 against 17.4 ms.)
+struct Pixels {
+  GlobalF pix, nbr_mean, nbr_var;
+  int pitch, nbr_pitch;
+  __device__ __forceinline__ explicit Pixels(const ImgDev& im)
+      : pix(global(im.pix)), nbr_mean(global(im.nbr_mean)), nbr_var(global(im.nbr_var)), pitch(im.pitch),
+        nbr_pitch(im.nbr_pitch) {}
+  // count, neighbour mean and neighbour variance at (row, col), 0 where there is no array
+  __device__ __forceinline__ void load(int row, int col, float& x, float& mean, float& var) const {
+    x = pix[(int64_t)row * pitch + col];
+    mean = nbr_mean ? nbr_mean[(int64_t)row * nbr_pitch + col] : 0.f;
+    var = nbr_var ? nbr_var[(int64_t)row * nbr_pitch + col] : 0.f;
+  }
+};
+
+// x in a vector register (a wave-uniform value that would otherwise hold a scalar one across the tile loop).
+__device__ __forceinline__ void to_vector(float& x) { asm volatile("" : "+v"(x)); }
+
 // Pixel -> lane layout of a work item, walked by the wavefronts of a block (wave wv takes every WAVES-th
 // tile from the wv-th on; the tile, and all state here, is wave-uniform).
 //
@@ -41,7 +61,7 @@ struct TileMap {
   int rb;
   // packed: bands, rows of the last band, pixels of a full band and of the item; the tile's band
   // and its first pixel's place in the band
-  int nb, hl, bw, npx, b0, q0;
+  int nb, hl, bw, npx, b0, q0, first0;
   float inv_hl;
   // unpacked
   int tw_log2, th_log2, tiles_x, q_log2, row_safe;
@@ -60,6 +80,7 @@ struct TileMap {
       inv_hl = 1.0f / (float)hl;
       n_tiles = (npx + 63) >> 6;
       b0 = 0;
+      first0 = band_row(0);
       q0 = wv << 6;
       settle();
     } else {
@@ -84,8 +105,12 @@ struct TileMap {
   __device__ __forceinline__ void settle() {
     while (q0 >= bw && b0 < nb - 1) {
       q0 -= bw;
-      ++b0;
+      first0 = band_row(++b0);
     }
+  }
+  // The tile lies in one band of 8 rows: the common case, whose pixels and box need no per-lane search.
+  __device__ __forceinline__ bool plain() const {
+    return b0 < nb - 1 ? q0 + 64 <= bw : hl == 8;
   }
   __device__ __forceinline__ int band_row(int b) const { return kept ? kept[rb + b] : rb + (b << 3); }
 
@@ -95,8 +120,14 @@ struct TileMap {
     if constexpr (PK) {
       live = (t << 6) + lane < npx;
       int q = q0 + (live ? lane : 0);
+      if (plain()) {
+        first = first0;
+        col = q >> 3;
+        row = first0 + (q & 7);
+        return;
+      }
       int b = b0;
-      first = band_row(b0);
+      first = first0;
       for (int k = b0 + 1, lim = bw; k < nb && lim < q0 + 64; ++k, lim += bw) {   // one step where bw >= 64
         const int rk = band_row(k);
         if (q0 + lane >= lim && live) {
@@ -142,6 +173,10 @@ struct TileMap {
       return TileBox{x0, min(w - 1, x0 + (1 << tw_log2) - 1), r0, max(r0, min(row_lim, r0 + (1 << th_log2)) - 1)};
     }
     const int last = min(63, npx - 1 - (t << 6));
+    if (plain()) {
+      *two = false;
+      return TileBox{q0 >> 3, (q0 + last) >> 3, first0, first0 + 7};
+    }
     const int c0 = __builtin_amdgcn_readfirstlane(col), s0 = __builtin_amdgcn_readfirstlane(first);
     const int c1 = __builtin_amdgcn_readlane(col, last), s1 = __builtin_amdgcn_readlane(first, last);
     const bool one = s0 == s1, wide = w < 8;
@@ -177,7 +212,7 @@ struct SkipTest {
 
 __device__ __forceinline__ SkipTest skip_test_of(const float* __restrict__ T, int c, int ncomp) {
   using namespace tab;
-  const float* r = T + GAL + c * GAL_REC;
+  const float* r = T + EXPO + c * EXPO_REC;
   const float* sr = T + STAR + (c / ncomp) * STAR_REC;
   SkipTest s;
   s.form = make_float4(r[R_C0], -r[R_QXX], -r[R_QXY], -r[R_QYY]);
@@ -201,8 +236,32 @@ __device__ __forceinline__ bool may_hit(const SkipTest& s, const TileBox& b, flo
   return (s.form.x - fminf(q1, q2)) + fmaf(M, 0x1p-20f, 0.01f) >= e_zero;
 }
 
+// Brings an image's whole table (n floats) into the cache behind the scalar loads that will read it,
+// 128 bytes per lane of the block's second wavefront, while the first one forms the skip tests.  The
+// tables of a large batch come from HBM, and a record's first scalar load would wait for it hit by hit.
+__device__ __forceinline__ void touch_table(const float* __restrict__ T, int n) {
+  for (int i = ((int)threadIdx.x - 64) * 32; i >= 0 && i < n; i += 64 * 32) {
+    const float v = T[i];
+    asm volatile("" ::"v"(v));
+  }
+}
+
 // Index of the lowest set bit of m, or 64 if there is none.
 __device__ __forceinline__ int low_bit(unsigned long long m) { return m ? __builtin_ctzll(m) : 64; }
+
+// The lanes below n (n <= 64).
+__device__ __forceinline__ unsigned long long lane_mask(int n) { return n >= 64 ? ~0ull : (1ull << n) - 1; }
+
+// Components (bit = the lane holding the component's test) that may be non-zero on tm's tile; col and
+// first are this lane's from tm.pixel.
+template <class MAP>
+__device__ __forceinline__ unsigned long long tile_hits(const SkipTest& s, const MAP& tm, int col, int first,
+                                                        float psx, float psy, float e_zero) {
+  bool two;
+  unsigned long long hits = __ballot(may_hit(s, tm.box(col, first, false, &two), psx, psy, e_zero));
+  if (two) hits |= __ballot(may_hit(s, tm.box(col, first, true, &two), psx, psy, e_zero));
+  return hits;
+}
 
 }  // namespace
 }  // namespace celeste
