@@ -10,6 +10,7 @@
 #include <math.h>
 
 #include "celeste_internal.h"
+#include "tiles.h"
 
 namespace celeste {
 
@@ -233,63 +234,159 @@ __global__ __launch_bounds__(256) void k_lfact(double* __restrict__ t) {
   if (i < LFACT_N) t[i] = lgamma((double)i + 1.0);
 }
 
+// Index of a count's log x! in the table, or -1 where it has none (a fractional, large, negative or
+// non-finite value).
+__device__ __forceinline__ int table_index(float x) {
+  const int n = (int)x;   // truncated
+  return (float)n == x && (unsigned)n < (unsigned)LFACT_N ? n : -1;
+}
+
 // One pass over every pixel of an image (one block per image): flags any negative or
 // non-finite pixel / neighbour value, and sums the theta-independent part of the pixel term,
 // x log E_bg - E_bg - log x!, E_bg = sky + neighbour mean.  log x! of an integer count below
 // LFACT_N is read from the table (the same value lgamma gives); without neighbour arrays E_bg
 // is the sky at every pixel, so the first two terms are log(sky) sum x - n sky.
-__global__ __launch_bounds__(256) void k_check_const(const ImgDev* __restrict__ imgs, const double* __restrict__ lfact,
+//
+// An image of the usual sizes is one or two passes of the block, so the loads of a pass are issued
+// together: rows that follow each other without gaps are read as one run of 16-byte pieces (4,096 px at
+// once; 1,024 px and their neighbour arrays), which need the 4-byte alignment of the pixels only; others pixel by
+// pixel, their row and column carried along instead of divided out.  What the table does not hold is
+// left to a second pass over the image, taken only where there is such a pixel (the library's lgamma
+// inside the unrolled loops took 219 registers), which also finds the negative and non-finite ones.
+// The registers are held to eight waves per SIMD (176 and two waves otherwise, for the second pass's lgamma,
+// whose spills only that pass meets: 1,180 us).  3.6e8 px of 4,000 uneven sources: 436 us; 1,950 us with 4
+// pixels per thread in flight, a division each and lgamma in the loop; 310 us at the rate of a large
+// copy.  1.4e8 px with neighbour arrays: 507 us (1,580).
+__global__ __launch_bounds__(256, 8) void k_check_const(const ImgDev* __restrict__ imgs, const double* __restrict__ lfact,
                                                      double* __restrict__ out, int* __restrict__ bad) {
+  typedef float V4 __attribute__((ext_vector_type(4), aligned(4)));
+  typedef const __attribute__((address_space(1))) V4* GlobalV4;
   __shared__ double sh[4];
   const ImgDev& im = imgs[blockIdx.x];
-  const int n = im.h * im.w;
-  double acc = 0.0, sx = 0.0;
-  int cnt = 0, flag = 0;
-  // four pixels per thread and step, their loads issued before any is used (the pass is bound by
-  // memory latency, not bandwidth)
-  constexpr int U = 4;
-  for (int m0 = threadIdx.x; m0 < n; m0 += U * 256) {
-    float xs[U], es[U], vs[U];
+  const int w = im.w, n = im.h * w, pitch = im.pitch, npitch = im.nbr_pitch;
+  const GlobalF px = global(im.pix), ne = global(im.nbr_mean), nv = global(im.nbr_var);
+  const double sky = im.sky;
+  const int t = threadIdx.x;
+  double acc = 0.0;      // - log x!, and with neighbour arrays x log E_bg - E_bg
+  double sx = 0.0;       // without a neighbour mean: sum of x over the counts of the table
+  bool rare = false;     // a pixel that is no count of the table
+  bool flag = false;     // a pixel or neighbour value out of range
+  if (!ne && !nv) {
+    auto term = [&](float x, unsigned& sum) {
+      const int k = table_index(x);
+      rare |= k < 0;
+      const int i = max(k, 0);
+      acc -= lfact[i];
+      sum += (unsigned)i;
+    };
+    if (pitch == w) {
+      constexpr int U = 4;
+      const int n4 = n >> 2;
+      for (int m0 = t; m0 < n4; m0 += U * 256) {
+        V4 x[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int m = min(m0 + u * 256, n - 1);
-      const int r = m / im.w, c = m - r * im.w;
-      const size_t o = (size_t)r * im.pitch + c;
-      const size_t on = (size_t)r * im.nbr_pitch + c;
-      xs[u] = im.pix[o];
-      es[u] = im.nbr_mean ? im.nbr_mean[on] : 0.f;
-      vs[u] = im.nbr_var ? im.nbr_var[on] : 0.f;
-    }
+        for (int u = 0; u < U; ++u) x[u] = ((GlobalV4)px)[min(m0 + u * 256, n4 - 1)];
+        unsigned sum = 0;   // at most 16 counts below LFACT_N
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (m0 + u * 256 >= n) break;
-      const float xf = xs[u];
-      if (!(xf >= 0.0f) || !isfinite(xf)) flag = 1;
-      const double x = xf;
-      double lg;
-      if (x >= 0.0 && x < (double)LFACT_N && x == (double)(int)x)
-        lg = lfact[(int)x];
-      else
-        lg = lgamma(x + 1.0);
-      if (im.nbr_mean) {
-        const float e = es[u];
-        if (!(e >= 0.0f) || !isfinite(e)) flag = 1;
-        const double ebg = im.sky + (double)e;
-        acc += x * log(ebg) - ebg - lg;
-      } else {
-        sx += x;
-        ++cnt;
-        acc -= lg;
+        for (int u = 0; u < U; ++u) {
+          if (m0 + u * 256 >= n4) break;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) term(x[u][j], sum);
+        }
+        sx += (double)sum;
       }
-      if (im.nbr_var) {
-        const float v = vs[u];
-        if (!(v >= 0.0f) || !isfinite(v)) flag = 1;
+      const int m = 4 * n4 + t;   // at most three pixels are left
+      if (m < n) {
+        unsigned sum = 0;
+        term(px[m], sum);
+        sx += (double)sum;
+      }
+    } else {
+      constexpr int U = 8;
+      const int dr = 256 / w, dc = 256 - dr * w;
+      int r = t / w, c = t - r * w;
+      for (int m0 = t; m0 < n; m0 += U * 256) {
+        float x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          x[u] = px[m0 + u * 256 < n ? (int64_t)r * pitch + c : 0];
+          r += dr;
+          c += dc;
+          if (c >= w) {
+            c -= w;
+            ++r;
+          }
+        }
+        unsigned sum = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (m0 + u * 256 >= n) break;
+          term(x[u], sum);
+        }
+        sx += (double)sum;
+      }
+    }
+  } else {
+    auto term = [&](float x, float e, float v) {
+      const int k = table_index(x);
+      rare |= k < 0;
+      flag |= !(e >= 0.f) || !(e < INFINITY) || !(v >= 0.f) || !(v < INFINITY);
+      const double ebg = sky + (double)e;
+      acc += (k < 0 ? 0.0 : (double)x) * log(ebg) - ebg - lfact[max(k, 0)];
+    };
+    if (pitch == w && npitch == w) {
+      const int n4 = n >> 2;
+      for (int m = t; m < n4; m += 256) {
+        const V4 x = ((GlobalV4)px)[m], e = ne ? ((GlobalV4)ne)[m] : V4{0.f, 0.f, 0.f, 0.f};
+        const V4 v = nv ? ((GlobalV4)nv)[m] : V4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) term(x[j], e[j], v[j]);
+      }
+      const int m = 4 * n4 + t;
+      if (m < n) term(px[m], ne ? ne[m] : 0.f, nv ? nv[m] : 0.f);
+    } else {
+      constexpr int U = 4;
+      const int dr = 256 / w, dc = 256 - dr * w;
+      int r = t / w, c = t - r * w;
+      for (int m0 = t; m0 < n; m0 += U * 256) {
+        float x[U], e[U], v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const bool in = m0 + u * 256 < n;
+          const int64_t o = in ? (int64_t)r * pitch + c : 0, on = in ? (int64_t)r * npitch + c : 0;
+          x[u] = px[o];
+          e[u] = ne ? ne[on] : 0.f;
+          v[u] = nv ? nv[on] : 0.f;
+          r += dr;
+          c += dc;
+          if (c >= w) {
+            c -= w;
+            ++r;
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (m0 + u * 256 >= n) break;
+          term(x[u], e[u], v[u]);
+        }
       }
     }
   }
-  if (!im.nbr_mean) acc += log(im.sky) * sx - (double)cnt * im.sky;
+  const bool one_sky = !ne && !nv;
+  if (one_sky) acc += log(sky) * sx;
+  if (__syncthreads_or(rare)) {
+#pragma unroll 1
+    for (int m = t; m < n; m += 256) {
+      const int r = m / w, c = m - r * w;
+      const float x = px[(int64_t)r * pitch + c];
+      if (table_index(x) >= 0) continue;
+      flag |= !(x >= 0.f) || !(x < INFINITY);
+      const double ebg = sky + (ne ? (double)ne[(int64_t)r * npitch + c] : 0.0);
+      acc += (double)x * log(ebg) - lgamma((double)x + 1.0);
+    }
+  }
   const double tot = block_sum<256>(acc, sh);
-  if (threadIdx.x == 0) out[blockIdx.x] = tot;
+  if (t == 0) out[blockIdx.x] = one_sky ? tot - (double)n * sky : tot;
   if (flag) atomicOr(bad, 1);
 }
 

@@ -94,3 +94,54 @@ def test_kept_blocks_skips(env, shape):
     finally:
         ctx.set_option(cb.OPT_CHUNK_PX, 4096)
         ctx.set_option(cb.OPT_EXACT_ZERO, 0)
+
+
+@pytest.mark.parametrize("pitch", [0, 5])
+@pytest.mark.parametrize("nbr", [False, True])
+@pytest.mark.parametrize("kind", ["counts", "fractional", "large"])
+@pytest.mark.parametrize("shape", [(9, 1), (31, 5), (40, 23), (65, 66)])
+def test_pixel_constants(env, shape, kind, nbr, pitch):
+    """The theta-independent sums over runs, remainders and strided rows, counts of the log n! table and
+    others, against the oracle; a bad value anywhere is found."""
+    cb, ctx = env
+    h, w = shape
+    sb = _one(h, w, seed=h + w, far=0)
+    rng = np.random.default_rng(h * w + len(kind))
+    x = rng.poisson(100.0, (5, h, w)).astype(np.float32)
+    if kind == "fractional":
+        x += rng.random((5, h, w)).astype(np.float32)
+    if kind == "large":
+        x[:, h // 2, w // 2] = [65535.0, 65536.0, 65537.0, 1e6, 0.0]
+    e, v = rng.uniform(0, 20, (2, 5, h, w)).astype(np.float32)
+    th = perturb_theta(sb.theta_truth, 6)
+
+    def batch(x, e, v):
+        buf = np.full((3, 5, h, w + pitch), np.nan, np.float32)   # the gaps between rows are never read
+        for k, a in enumerate((x, e, v)):
+            buf[k, :, :, :w] = a
+        buf[:, :, -1, w:] = 0
+        n = h * (w + pitch)
+        off = np.arange(5, dtype=np.int64) * n
+        kw = dict(nbr_mean=buf[1].ravel(), nbr_var=buf[2].ravel(), nbr_pitch=w + pitch) if nbr else {}
+        return cb.Batch(sb.src_img_off, sb.img_band, sb.img_h, sb.img_w, sb.img_w + pitch, sb.img_origin, sb.img_wcs,
+                        sb.img_sky, sb.img_calib, sb.img_psf, sb.img_npsf, _device(buf[0]), off, sb.prior,
+                        sb.profiles, **{k: _device(a) if k != "nbr_pitch" else a for k, a in kw.items()})
+
+    sb.pixels = x.ravel()
+    onbr = {i: (e[i], v[i]) for i in range(5)} if nbr else None
+    ref = oracle_eval(sb, 0, th[0], nbr=onbr, want="value")[0]
+    print("constants", shape, kind, nbr, pitch, flush=True)
+    el = ctx.elbo_eval(batch(x, e, v), th, want="value")[0]
+    # FP64 sums of the same terms: what differs is the FP32 theta-dependent rest
+    assert_elbo_close(float(el[0]), ref, rtol=1e-6)
+    for k, bad in ((0, -1.0), (0, np.nan), (0, np.inf)) + (((1, -1.0), (2, np.inf), (1, np.nan)) if nbr else ()):
+        a = [x.copy(), e.copy(), v.copy()]
+        a[k][4, h - 1, w - 1] = bad
+        with pytest.raises(cb.CelesteError) as err:
+            ctx.elbo_eval(batch(*a), th, want="value")
+        assert err.value.code == cb.E_INVALID
+
+
+def _device(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a).ravel()).cuda()
