@@ -34,6 +34,7 @@
 
 #include "celeste_internal.h"
 #include "tiles.h"
+#include "wave.h"
 
 namespace celeste {
 
@@ -256,50 +257,6 @@ __device__ double bright_entry(const float* __restrict__ T, int e, const double*
 // 340 vector and 91 LDS instructions a sum; 190 and 5 now).
 __device__ __forceinline__ int quad_base(int lane) {
   return ((lane >> 5) & 1) * 40 + ((lane >> 4) & 1) * 20 + ((lane >> 3) & 1) * 10 + ((lane >> 2) & 1) * 5;
-}
-
-// a and b with lane bit 5 (M = 32) or 4 (M = 16) exchanged: on lanes with the bit clear a keeps its
-// value and b takes the partner lane's a; on lanes with it set b keeps its value and a takes the
-// partner lane's b.
-template <int M>
-__device__ __forceinline__ void swap_half(unsigned& a, unsigned& b) {
-  if constexpr (M == 32) {
-    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-    a = r[0];
-    b = r[1];
-  } else {
-    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
-    a = r[0];
-    b = r[1];
-  }
-}
-
-template <int M>
-__device__ __forceinline__ float swap_add(float x, float y) {
-  unsigned a = __float_as_uint(x), b = __float_as_uint(y);
-  swap_half<M>(a, b);
-  return __uint_as_float(a) + __uint_as_float(b);
-}
-
-template <int M>
-__device__ __forceinline__ double swap_add(double x, double y) {
-  unsigned al = __double2loint(x), ah = __double2hiint(x), bl = __double2loint(y), bh = __double2hiint(y);
-  swap_half<M>(al, bl);
-  swap_half<M>(ah, bh);
-  return __hiloint2double((int)ah, (int)al) + __hiloint2double((int)bh, (int)bl);
-}
-
-// the partner lane's value over a DPP control: row_ror:8 (lane ^ 8), quad_perm (lane ^ 2, lane ^ 1)
-constexpr int DPP_XOR8 = 0x128, DPP_XOR2 = 0x4E, DPP_XOR1 = 0xB1;
-template <int CTRL>
-__device__ __forceinline__ float dpp(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp(double x) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xF, 0xF, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xF, 0xF, true);
-  return __hiloint2double(hi, lo);
 }
 
 // 20 values, already halved over bits 5 and 4, to the quad's 5

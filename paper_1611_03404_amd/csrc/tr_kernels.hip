@@ -14,6 +14,7 @@
 
 #include "celeste_internal.h"
 #include "psi_map.h"
+#include "wave.h"
 
 namespace celeste {
 
@@ -88,29 +89,113 @@ __global__ void k_fit_start(FitDev st, int n_src) {
   }
 }
 
-__device__ inline void pair_of(int round, int k, int* p, int* q) {
-  // circle method over NPAD players: player NPAD-1 fixed, the rest rotate
-  const int m = NPAD - 1;
-  if (k == 0) {
-    *p = m;
-    *q = round;
-  } else {
-    *p = (round + k) % m;
-    *q = (round - k + m) % m;
-  }
-}
+// The circle method over NPAD players (player M = NPAD - 1 fixed, the rest rotating): pair k of round r
+// is (M, r) for k = 0 and (r + k, r - k) mod M otherwise.
+constexpr unsigned PM = NPAD - 1;
+__device__ __forceinline__ unsigned wrap(unsigned x) { return min(x, x - PM); }          // x in [0, 2 PM)
+__device__ __forceinline__ unsigned player_u(unsigned r, unsigned k) { return k == 0 ? PM : wrap(r + k); }
+__device__ __forceinline__ unsigned player_v(unsigned r, unsigned k) { return wrap(r + (k == 0 ? 0 : PM - k)); }
 
-__global__ __launch_bounds__(64) void k_tr(FitDev st, FitParams fp) {
-  __shared__ double B[NPAD][NPAD + 1];
-  __shared__ double V[NPAD][NPAD + 1];   // eigenvectors; the Cholesky paths' factor before that
-  __shared__ double g[NPAD], gt[NPAD], lam[NPAD], pt[NPAD], d1s[NP];
-  // a round's rotations: (p, q) and (cos, sin) side by side so that a reader loads each pair at once
-  __shared__ double2 rcs[NPAD / 2];
-  __shared__ int2 rpq[NPAD / 2];
-  __shared__ int done;
+// Where the lane of pair k of round r finds what its rotation needs, for r > 0 in the copy of B before round
+// r - 1: pair k joins one player of pair a and one of pair b of that round (a < b), so its entry is one
+// element of that 2x2 block after it.  x: the block's four entries (flat indices), p and q: the pair.
+// Round 0 reads its pivots from B.
+struct NextPivot {
+  unsigned short x00, x01, x10, x11;
+  unsigned char p, q, a, b, row_q, col_q, pad[2];
+};
+struct NextPivots {
+  NextPivot e[NPAD - 1][NPAD / 2];
+  unsigned first_u[NPAD - 1];
+};
+constexpr NextPivots make_next_pivots() {
+  NextPivots t{};
+  const int M = NPAD - 1;
+  for (int r = 0; r < M; ++r)
+    for (int k = 0; k < NPAD / 2; ++k) {
+      const int u = k == 0 ? M : (r + k) % M, v = k == 0 ? r : (r + M - k) % M;
+      NextPivot& e = t.e[r][k];
+      e.p = (unsigned char)(u < v ? u : v);
+      e.q = (unsigned char)(u < v ? v : u);
+      if (r == 0) continue;
+      // the pairs of round r - 1 that hold players u and v
+      int pair[2] = {0, 0};
+      for (int w = 0; w < 2; ++w) {
+        const int x = w == 0 ? u : v, d = (x - (r - 1) + M) % M;
+        pair[w] = x == M || d == 0 ? 0 : (d <= M / 2 ? d : M - d);
+      }
+      const int first = pair[0] < pair[1] ? 0 : 1;
+      const int a = pair[first], b = pair[1 - first], row = first == 0 ? u : v, col = first == 0 ? v : u;
+      int lo[2] = {0, 0}, hi[2] = {0, 0};
+      for (int w = 0; w < 2; ++w) {
+        const int k2 = w == 0 ? a : b;
+        const int u2 = k2 == 0 ? M : (r - 1 + k2) % M, v2 = k2 == 0 ? r - 1 : (r - 1 + M - k2) % M;
+        lo[w] = u2 < v2 ? u2 : v2;
+        hi[w] = u2 < v2 ? v2 : u2;
+      }
+      e.a = (unsigned char)a;
+      e.b = (unsigned char)b;
+      e.row_q = row == hi[0];
+      e.col_q = col == hi[1];
+      int x[4] = {0, 0, 0, 0};
+      for (int w = 0; w < 4; ++w) {
+        const int i = w < 2 ? lo[0] : hi[0], j = w % 2 == 0 ? lo[1] : hi[1];
+        x[w] = (i < j ? i : j) * (NPAD + 1) + (i < j ? j : i);
+      }
+      e.x00 = (unsigned short)x[0];
+      e.x01 = (unsigned short)x[1];
+      e.x10 = (unsigned short)x[2];
+      e.x11 = (unsigned short)x[3];
+    }
+  // bit k of first_u[r]: the first player of pair k is the smaller one
+  for (int r = 0; r < M; ++r)
+    for (int k = 1; k < NPAD / 2; ++k)
+      if ((r + k) % M < (r + M - k) % M) t.first_u[r] |= 1u << k;
+  return t;
+}
+__device__ const NextPivots kNextPivots = make_next_pivots();
+
+// A rotation of the plane (p, q): the entries of a row (or column) pair after it.  Written out so that
+// every use rounds alike.
+__device__ __forceinline__ double rot_p(double c, double sn, double xp, double xq) { return fma(c, xp, -(sn * xq)); }
+__device__ __forceinline__ double rot_q(double c, double sn, double xp, double xq) { return fma(sn, xp, c * xq); }
+
+// flat index of (i, j) in the LDS matrices
+constexpr int LDP = NPAD + 1;
+__device__ __forceinline__ int at(int i, int j) { return (int)__umul24((unsigned)i, (unsigned)LDP) + j; }
+// ... of (i, j) in the upper triangle
+__device__ __forceinline__ int upper(int i, int j) { return at(min(i, j), max(i, j)); }
+
+// The trust-region subproblem of one source: one block of four wavefronts.  A solve is a chain of short
+// dependent steps (27 rounds a Jacobi sweep, 27 columns a factorisation), so its time is their latency
+// and, with a few hundred sources or fewer, the launch's time is one solve's.  The work of a step is
+// spread over the wavefronts, and in a Jacobi round the one long chain (three divisions and two square
+// roots per rotation) runs ahead of the rest: wavefront 0 forms the next round's rotations from
+// the few entries they need, which it rotates itself, while 1 and 2 rotate B's upper triangle by this
+// round's (from one LDS copy into the other) and 3 rotates V, a row per lane in registers: one barrier a
+// round, each wavefront in its own loop so that only V's holds V's registers.  (V in LDS took over
+// half of a round's LDS accesses, which bound large launches: 12,000 sources' fits spent 32.5 ms here.)
+// Sums over the wavefront stay in the vector unit; triangular solves keep their vector in the lanes of
+// one wavefront.  Every entry of B, V and the factors sees the operations of a one-wavefront solve in the
+// same order.  One source, mean of 23 solves: 68 us (138 us on one wavefront); slowest of 1,000 sources,
+// mean of 48 launches: 126 us (229 us); fits of 12,000 sources: 21.4 ms in all (26.8 ms);
+// registers held to six waves per SIMD (three otherwise, and 26.2 ms).
+constexpr int TRT = 256;
+
+__global__ __launch_bounds__(TRT, 6) void k_tr(FitDev st, FitParams fp) {
+  __shared__ double Bm[2][NPAD * LDP];   // B; the Jacobi rounds go from one to the other
+  __shared__ double V[NPAD][LDP];        // eigenvectors; the Cholesky paths' factor before that
+  double (*B)[LDP] = reinterpret_cast<double (*)[LDP]>(Bm[0]);
+  __shared__ double g[NPAD], gt[NPAD], pt[NPAD], pst[NPAD], y[NPAD], d1s[NP], d2s[NP];
+  __shared__ double2 rcs[2][NPAD / 2];   // (cos, sin) of a round's rotations, of this round and the next
+  __shared__ double rtt[2][NPAD / 2];    // tangents, 0 where there is no rotation
+  __shared__ double dg[NPAD];            // wavefront 0: diagonal of B
+  __shared__ double red[2][TRT / 64];
+  __shared__ double s_a, s_b;
+  __shared__ int s_curv, done;
   const int s = blockIdx.x;
   if (!st.active[s]) return;
-  const int t = threadIdx.x;
+  const int t = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
   if (t == 0 && st.need_full[s]) {
     st.n_full[s] += 1;
     st.need_full[s] = 0;
@@ -120,7 +205,6 @@ __global__ __launch_bounds__(64) void k_tr(FitDev st, FitParams fp) {
   const double* Hn = st.H + (size_t)s * NP * NP;
   const double* u0 = st.u0 + 2 * s;
   // transform to unconstrained coordinates: g = t' g_n, B = -(D H D + diag(t'' g_n))
-  __shared__ double d2s[NP];
   if (t < NP) {
     double d1, d2;
     to_theta1(ps[t], box_of(t, u0, fp.u_box), &d1, &d2);
@@ -128,7 +212,7 @@ __global__ __launch_bounds__(64) void k_tr(FitDev st, FitParams fp) {
     d2s[t] = d2;
   }
   __syncthreads();
-  for (int k = t; k < NPAD * NPAD; k += 64) {
+  for (int k = t; k < NPAD * NPAD; k += TRT) {
     const int i = k / NPAD, j = k - i * NPAD;
     double b = 0.0;
     if (i < NP && j < NP) {
@@ -139,15 +223,11 @@ __global__ __launch_bounds__(64) void k_tr(FitDev st, FitParams fp) {
   }
   if (t < NPAD) g[t] = t < NP ? d1s[t] * gn[t] : 0.0;
   __syncthreads();
-  auto wsum = [](double x) {
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-    return __shfl(x, 0);
-  };
   const double delta = st.delta[s];
-  // psi step; predicted gain; whether B is positive semi-definite to the curvature tolerance
-  __shared__ double pst[NPAD], y[NPAD];
+  // the step goes to pst, its predicted gain to pred (thread 0), whether B is positive semi-definite to
+  // the curvature tolerance to s_curv
   double pred = 0.0;
-  bool curv_ok = true;
+  if (t == 0) s_curv = 1;
 
   // ---- Cholesky paths.  Where B is positive definite, the subproblem's solution is
   // p(lam) = (B + lam I)^{-1} g with lam = 0 if |p(0)| <= Delta (the interior Newton step), and
@@ -162,107 +242,140 @@ __global__ __launch_bounds__(64) void k_tr(FitDev st, FitParams fp) {
   // steps, takes the eigendecomposition below.
   int path = 2;   // 0: interior step by Cholesky, 1: boundary step by Cholesky, 2: eigendecomposition
   if (fp.tr_chol) {
-    double dmax = t < NP ? B[t][t] : -INFINITY;
+    double dmax = lane < NP ? B[lane][lane] : -INFINITY;   // the same on every wavefront
     for (int o = 32; o > 0; o >>= 1) dmax = fmax(dmax, __shfl_xor(dmax, o));
-    dmax = __shfl(dmax, 0);
-    // V <- the Cholesky factor L of B + lam I (lower triangle), pst <- (B + lam I)^{-1} g (V holds
-    // the eigenvectors only in the eigendecomposition path, which loads them afresh)
-    auto factor_solve = [&](double lam) -> bool {
-      for (int k = t; k < NP * NP; k += 64) {
+    dmax = wave_uniform(dmax);
+    // V <- the Cholesky factor L of B + lam I (lower triangle), pst <- (B + lam I)^{-1} g and its
+    // squared norm (V holds the eigenvectors only in the eigendecomposition path, which loads them afresh).
+    // All threads; the decisions are made on values that every thread reads.
+    const int cj = t & 31, ch = t >> 5;   // trailing update: column cj, rows cj + ch, cj + ch + 8, ...
+    auto factor_solve = [&](double lam, double* pn2) -> bool {
+      for (int k = t; k < NP * NP; k += TRT) {
         const int i = k / NP, j = k - i * NP;
         V[i][j] = B[i][j] + (i == j ? lam : 0.0);
       }
       if (t < NPAD) y[t] = g[t];
       __syncthreads();
+#pragma unroll 1
       for (int k = 0; k < NP; ++k) {
-        const double piv = V[k][k];   // the same value on every lane: the decision is uniform
-        if (!(piv > 1e-12 * (dmax + lam))) return false;
+        const double piv = V[k][k];   // the same value on every thread: the decision is uniform
+        if (!(piv > 1e-12 * (dmax + lam))) {
+          __syncthreads();
+          return false;
+        }
         const double lkk = sqrt(piv);
-        // (V[k][k] is read above by every lane and written only after the barrier)
+        // (V[k][k] is read above by every thread and written only after the barrier)
         if (t > k && t < NP) V[t][k] /= lkk;
         if (t == k) y[k] /= lkk;
         __syncthreads();
-        // trailing update of the lower triangle: lane (h, j) = (t / 32, t % 32) takes column j,
-        // rows j + h, j + h + 2, ... (each entry updated by one lane)
-        {
-          const int j = t & 31;
-          if (j > k && j < NP) {
-            const double ljk = V[j][k];
-            for (int i = j + (t >> 5); i < NP; i += 2) V[i][j] -= V[i][k] * ljk;
+        if (cj > k && cj < NP && ch < 8) {
+          const double ljk = V[cj][k];
+          double a[4], l[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int i = min(cj + ch + 8 * u, NP - 1);
+            l[u] = V[i][k];
+            a[u] = V[i][cj];
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int i = cj + ch + 8 * u;
+            if (i < NP) V[i][cj] = a[u] - l[u] * ljk;
           }
         }
         if (t > k && t < NP) y[t] -= V[t][k] * y[k];
         if (t == k) V[k][k] = lkk;
         __syncthreads();
       }
-      // back substitution L' p = y, one unknown per step
-      for (int k = NP - 1; k >= 0; --k) {
-        const double yk = y[k] / V[k][k];
-        if (t == k) pst[k] = yk;
-        if (t < k) y[t] -= V[k][t] * yk;
-        __syncthreads();
+      // back substitution L' p = y, one unknown per step, lane k of wavefront 0 keeping p_k
+      if (wv == 0) {
+        double yt = lane < NP ? y[lane] : 0.0, pk = 0.0;
+        const double dt = lane < NP ? V[lane][lane] : 1.0;
+        double row = V[NP - 1][min(lane, NP - 1)];
+#pragma unroll 1
+        for (int k = NP - 1; k >= 0; --k) {
+          const double cur = row;
+          row = V[max(k - 1, 0)][min(lane, NP - 1)];
+          const double yk = lane_value(yt, k) / lane_value(dt, k);
+          if (lane == k) pk = yk;
+          if (lane < k) yt -= cur * yk;
+        }
+        if (lane < NP) pst[lane] = pk;
+        const double n2 = wave_sum(lane < NP ? pk * pk : 0.0);
+        if (lane == 0) s_a = n2;
       }
+      __syncthreads();
+      *pn2 = s_a;
       return true;
     };
-    if (dmax > 0.0 && factor_solve(0.0)) {
-      double pn2 = wsum(t < NP ? pst[t] * pst[t] : 0.0);
-      if (pn2 <= delta * delta) {
+    double pn2 = 0.0, lam = 0.0;
+    bool first = true;
+    int it = 0;
+#pragma unroll 1
+    while (dmax > 0.0 && factor_solve(lam, &pn2)) {
+      if (first && pn2 <= delta * delta) {
         path = 0;
-        pred = 0.5 * wsum(t < NP ? g[t] * pst[t] : 0.0);
-      } else {
-        double lam = 0.0;
-        int it = 0;
-        for (; it < 30; ++it) {
-          const double pn = sqrt(pn2);
-          if (fabs(pn - delta) <= 1e-9 * delta) {
-            path = 1;
-            break;
-          }
-          // q = L^{-1} p by forward substitution, lane k keeping q_k
-          if (t < NPAD) y[t] = t < NP ? pst[t] : 0.0;
-          __syncthreads();
-          double qk = 0.0;
-          for (int k = 0; k < NP; ++k) {
-            const double yk = y[k] / V[k][k];
-            if (t == k) qk = yk;
-            if (t > k && t < NP) y[t] -= V[t][k] * yk;
-            __syncthreads();
-          }
-          const double qn2 = wsum(qk * qk);
-          lam += (pn2 / qn2) * (pn - delta) / delta;
-          if (!(lam >= 0.0)) lam = 0.0;   // only by rounding: |p(0)| > Delta
-          if (!factor_solve(lam)) break;
-          pn2 = wsum(t < NP ? pst[t] * pst[t] : 0.0);
-        }
-        if (t == 0 && fp.tr_ctr) atomicAdd(fp.tr_ctr + 5, (unsigned long long)it);
-        // predicted gain g'p - p'Bp/2 with (B + lam I) p = g
-        if (path == 1) pred = 0.5 * (wsum(t < NP ? g[t] * pst[t] : 0.0) + lam * pn2);
+        break;
       }
+      it += first ? 0 : 1;
+      first = false;
+      if (it >= 30) break;
+      const double pn = sqrt(pn2);
+      if (fabs(pn - delta) <= 1e-9 * delta) {
+        path = 1;
+        break;
+      }
+      // q = L^{-1} p by forward substitution, lane k of wavefront 0 keeping q_k
+      if (wv == 0) {
+        double yt = lane < NP ? pst[lane] : 0.0, qk = 0.0;
+        const double dt = lane < NP ? V[lane][lane] : 1.0;
+        double col = V[min(lane, NP - 1)][0];
+#pragma unroll 1
+        for (int k = 0; k < NP; ++k) {
+          const double cur = col;
+          col = V[min(lane, NP - 1)][min(k + 1, NP - 1)];
+          const double yk = lane_value(yt, k) / lane_value(dt, k);
+          if (lane == k) qk = yk;
+          if (lane > k && lane < NP) yt -= cur * yk;
+        }
+        const double n2 = wave_sum(qk * qk);
+        if (lane == 0) s_b = n2;
+      }
+      __syncthreads();
+      const double qn2 = s_b;
+      lam += (pn2 / qn2) * (pn - delta) / delta;
+      if (!(lam >= 0.0)) lam = 0.0;   // only by rounding: |p(0)| > Delta
+    }
+    if (t == 0 && !first && fp.tr_ctr) atomicAdd(fp.tr_ctr + 5, (unsigned long long)it);
+    if (path != 2 && wv == 0) {
+      // predicted gain: g'p / 2 inside, g'p - p'Bp/2 with (B + lam I) p = g on the boundary
+      const double gp = wave_sum(lane < NP ? g[lane] * pst[lane] : 0.0);
+      pred = path == 0 ? 0.5 * gp : 0.5 * (gp + lam * pn2);
     }
     __syncthreads();
   }
 
   if (path == 2) {
   // warm start: the eigenvectors of the previous model (identity at the first iteration)
-  for (int k = t; k < NPAD * NPAD; k += 64) {
+  for (int k = t; k < NPAD * NPAD; k += TRT) {
     const int i = k / NPAD, j = k - i * NPAD;
     V[i][j] = (i < NP && j < NP) ? st.V[(size_t)s * NP * NP + i * NP + j] : (i == j ? 1.0 : 0.0);
   }
   __syncthreads();
   // B <- V^T B V, nearly diagonal when the model changed little since the previous iteration;
   // the Jacobi rotations below accumulate into V, so V ends as the eigenvectors of the model.
-  // Lane (h, j) = (t / 32, t % 32), j < NPAD, forms column j of each product for the rows
-  // NPAD/2 h .. NPAD/2 h + NPAD/2 - 1 in registers (one LDS read of its own column and broadcast
-  // reads of the other operand per r; every entry summed over r in increasing order) and stores
-  // them after the barrier.
+  // Thread (h, j) = (t / 32, t % 32), h < 7, j < NPAD, forms column j of each product for rows 4 h ..
+  // 4 h + 3 in registers (one LDS read of its own column and broadcast reads of the other operand per
+  // r; every entry summed over r in increasing order) and stores them after the barrier.
   {
-    constexpr int HR = NPAD / 2;
+    constexpr int HR = 4;
     const int cj = t & 31, r0 = (t >> 5) * HR;
-    const bool cl = cj < NPAD;
+    const bool cl = cj < NPAD && r0 < NPAD;
     double acc[HR];
 #pragma unroll
     for (int i = 0; i < HR; ++i) acc[i] = 0.0;
     if (cl)
+#pragma unroll 4
       for (int r = 0; r < NPAD; ++r) {
         const double v = V[r][cj];
 #pragma unroll
@@ -276,6 +389,7 @@ __global__ __launch_bounds__(64) void k_tr(FitDev st, FitParams fp) {
 #pragma unroll
     for (int i = 0; i < HR; ++i) acc[i] = 0.0;
     if (cl)
+#pragma unroll 4
       for (int r = 0; r < NPAD; ++r) {
         const double b = B[r][cj];
 #pragma unroll
@@ -288,7 +402,7 @@ __global__ __launch_bounds__(64) void k_tr(FitDev st, FitParams fp) {
     __syncthreads();
   }
   // symmetrise (the Hessian is assembled symmetrically; this removes rounding asymmetry)
-  for (int k = t; k < NPAD * NPAD; k += 64) {
+  for (int k = t; k < NPAD * NPAD; k += TRT) {
     const int i = k / NPAD, j = k - i * NPAD;
     if (i < j) {
       const double m = 0.5 * (B[i][j] + B[j][i]);
@@ -299,116 +413,172 @@ __global__ __launch_bounds__(64) void k_tr(FitDev st, FitParams fp) {
   __syncthreads();
 
   // ---- cyclic Jacobi, round-robin parallel ordering
-  // A lane updates the same off-diagonal 2x2 blocks of B (by pair indices a < b) and the same
-  // entries of V in every round, so their indices are decoded once here.
   constexpr int NPR = NPAD / 2;                     // disjoint rotations per round
-  constexpr int NBLK = NPR * (NPR - 1) / 2;         // off-diagonal 2x2 blocks of B per round
-  constexpr int BPL = (NBLK + 63) / 64, VPL = (NPR * NPAD + 63) / 64;
-  int blk_a[BPL], blk_b[BPL];   // blk_a < 0: no block
-#pragma unroll
-  for (int u = 0; u < BPL; ++u) {
-    const int k = t + 64 * u;
-    blk_a[u] = -1;
-    blk_b[u] = -1;
-    if (k >= NBLK) continue;
-    int a = 0, idx = k;
-    while (idx >= NPR - 1 - a) {
-      idx -= NPR - 1 - a;
-      ++a;
+  constexpr int NBLK = NPR * (NPR - 1) / 2;         // off-diagonal 2x2 blocks of B per round (91)
+  // wavefronts 1 and 2: one block of B each thread, an off-diagonal one (pairs a < b) or a pair's own
+  int blk_a = -1, blk_b = -1;
+  if (wv == 1 || wv == 2) {
+    int idx = t - 64, a = 0;
+    if (idx < NBLK) {
+      while (idx >= NPR - 1 - a) {
+        idx -= NPR - 1 - a;
+        ++a;
+      }
+      blk_a = a;
+      blk_b = a + 1 + idx;
+    } else if (idx < NBLK + NPR) {
+      blk_a = blk_b = idx - NBLK;
     }
-    blk_a[u] = a;
-    blk_b[u] = a + 1 + idx;
   }
-  int v_pr[VPL], v_r[VPL];      // rotation and row of the lane's entries of V (v_pr < 0: none)
-#pragma unroll
-  for (int u = 0; u < VPL; ++u) {
-    const int k = t + 64 * u;
-    v_pr[u] = k < NPR * NPAD ? k / NPAD : -1;
-    v_r[u] = k - (k / NPAD) * NPAD;
-  }
-  int sweeps = 0;
-  for (; sweeps < 40; ++sweeps) {
+  auto rotate_b = [&](unsigned r, const double* from, double* to, const double2* cs, const double* tn) {
+    const unsigned ua = player_u(r, blk_a), va = player_v(r, blk_a), ub = player_u(r, blk_b), vb = player_v(r, blk_b);
+    const int p1 = min(ua, va), q1 = max(ua, va), p2 = min(ub, vb), q2 = max(ub, vb);
+    const int i00 = upper(p1, p2), i01 = upper(p1, q2), i10 = upper(q1, p2), i11 = upper(q1, q2);
+    const double x00 = from[i00], x01 = from[i01], x10 = from[i10], x11 = from[i11];
+    const double2 a = cs[blk_a], b = cs[blk_b];
+    if (blk_a != blk_b) {
+      // columns first, then rows
+      const double y00 = rot_p(b.x, b.y, x00, x01), y01 = rot_q(b.x, b.y, x00, x01);
+      const double y10 = rot_p(b.x, b.y, x10, x11), y11 = rot_q(b.x, b.y, x10, x11);
+      to[i00] = rot_p(a.x, a.y, y00, y10);
+      to[i01] = rot_p(a.x, a.y, y01, y11);
+      to[i10] = rot_q(a.x, a.y, y00, y10);
+      to[i11] = rot_q(a.x, a.y, y01, y11);
+    } else {
+      // a pair's own block takes the rotated eigenvalue estimates and an exact zero
+      const double tt = tn[blk_a];
+      to[i00] = tt != 0.0 ? fma(-tt, x01, x00) : x00;
+      to[i11] = tt != 0.0 ? fma(tt, x01, x11) : x11;
+      to[i01] = tt != 0.0 ? 0.0 : x01;
+    }
+  };
+  // one barrier that every wavefront reaches from its own loop
+  auto sync = []() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  };
+  int sweeps = 0, cur = 0;   // cur: the copy of B that holds it
+  // whether another sweep is taken (the same on every thread; two barriers)
+  auto another = [&]() -> bool {
     double off = 0.0, fro = 0.0;
-    for (int k = t; k < NPAD * NPAD; k += 64) {
+    for (int k = t; k < NPAD * NPAD; k += TRT) {
       const int i = k / NPAD, j = k - i * NPAD;
-      const double v = B[i][j] * B[i][j];
-      fro += v;
-      if (i != j) off += v;
+      if (i > j) continue;
+      const double x = Bm[cur][at(i, j)], v = x * x;
+      fro += i == j ? v : 2.0 * v;
+      off += i == j ? 0.0 : 2.0 * v;
     }
-    for (int o = 32; o > 0; o >>= 1) {
-      off += __shfl_xor(off, o);
-      fro += __shfl_xor(fro, o);
+    off = wave_sum(off);
+    fro = wave_sum(fro);
+    if (lane == 0) {
+      red[0][wv] = off;
+      red[1][wv] = fro;
     }
-    if (off <= 1e-30 * fro || fro == 0.0) break;
-    for (int round = 0; round < NPAD - 1; ++round) {
-      if (t < NPR) {
-        int p, q;
-        pair_of(round, t, &p, &q);
-        if (p > q) {
-          const int x = p;
-          p = q;
-          q = x;
-        }
-        const double apq = B[p][q], app = B[p][p], aqq = B[q][q];
-        double c = 1.0, sn = 0.0, tt = 0.0;
-        if (fabs(apq) > 1e-300 && fabs(apq) > 1e-18 * sqrt(fabs(app * aqq))) {
+    sync();
+    off = fro = 0.0;
+#pragma unroll
+    for (int w = 0; w < TRT / 64; ++w) {
+      off += red[0][w];
+      fro += red[1][w];
+    }
+    sync();
+    return sweeps < 40 && !(off <= 1e-30 * fro || fro == 0.0);
+  };
+  // a sweep is NPAD slots of one barrier each: in slot r wavefront 0 forms round r's rotations (r < NPAD - 1)
+  // and the others apply round r - 1's (r > 0)
+  if (wv == 0) {
+    const int kk = min(lane, NPR - 1);
+    for (; another(); ++sweeps) {
+      NextPivot np = kNextPivots.e[0][kk];
+      for (int r = 0; r < NPAD; ++r) {
+        if (r < NPAD - 1 && lane < NPR) {
+          const NextPivot e = np;
+          np = kNextPivots.e[min(r + 1, NPAD - 2)][kk];   // in flight during this slot
+          const double* from = Bm[cur];
+          const int p = e.p, q = e.q;
+          double apq, app, aqq;
+          if (r == 0) {
+            apq = from[at(p, q)];
+            app = from[at(p, p)];
+            aqq = from[at(q, q)];
+          } else {
+            // the pair's entry after round r - 1, as rotate_b forms it
+            const double x00 = from[e.x00], x01 = from[e.x01], x10 = from[e.x10], x11 = from[e.x11];
+            const double2 a = rcs[(r - 1) & 1][e.a], b = rcs[(r - 1) & 1][e.b];
+            app = dg[p];
+            aqq = dg[q];
+            const double y0 = e.col_q ? rot_q(b.x, b.y, x00, x01) : rot_p(b.x, b.y, x00, x01);
+            const double y1 = e.col_q ? rot_q(b.x, b.y, x10, x11) : rot_p(b.x, b.y, x10, x11);
+            apq = e.row_q ? rot_q(a.x, a.y, y0, y1) : rot_p(a.x, a.y, y0, y1);
+          }
+          // (the test runs beside the chain, whose result a negligible entry's lane drops)
+          const bool rotate = (fabs(apq) > 1e-300) & (fabs(apq) > 1e-18 * sqrt(fabs(app * aqq)));
           const double th = (aqq - app) / (2.0 * apq);
-          tt = (th >= 0.0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
-          c = 1.0 / sqrt(tt * tt + 1.0);
-          sn = tt * c;
+          double tt = (th >= 0.0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
+          double c = 1.0 / sqrt(tt * tt + 1.0), sn = tt * c;
+          c = rotate ? c : 1.0;
+          sn = rotate ? sn : 0.0;
+          tt = rotate ? tt : 0.0;
+          rcs[r & 1][lane] = make_double2(c, sn);
+          rtt[r & 1][lane] = tt;
+          dg[p] = tt != 0.0 ? fma(-tt, apq, app) : app;
+          dg[q] = tt != 0.0 ? fma(tt, apq, aqq) : aqq;
         }
-        rpq[t] = make_int2(p, q);
-        rcs[t] = make_double2(c, sn);
-        // the pair's own 2x2 block takes the rotated eigenvalue estimates and exact zeros; no other
-        // lane reads these four entries in this round
-        if (tt != 0.0) {
-          B[p][p] = app - tt * apq;
-          B[q][q] = aqq + tt * apq;
-          B[p][q] = 0.0;
-          B[q][p] = 0.0;
-        }
+        sync();
+        if (r > 0) cur ^= 1;
       }
-      __syncthreads();
-      // B <- J^T B J and V <- V J in one pass: the off-diagonal 2x2 blocks of B (pair a's rows x
-      // pair b's columns, a < b), each read and written by one lane, so no entry is touched twice;
-      // a block is transformed columns first, then rows, and mirrored
-#pragma unroll
-      for (int u = 0; u < BPL; ++u) {
-        const int a = blk_a[u], b = blk_b[u];
-        if (a < 0) continue;
-        const int2 pq1 = rpq[a], pq2 = rpq[b];
-        const double2 cs1 = rcs[a], cs2 = rcs[b];
-        const int p1 = pq1.x, q1 = pq1.y, p2 = pq2.x, q2 = pq2.y;
-        const double c1 = cs1.x, s1 = cs1.y, c2 = cs2.x, s2 = cs2.y;
-        const double x00 = B[p1][p2], x01 = B[p1][q2], x10 = B[q1][p2], x11 = B[q1][q2];
-        const double y00 = c2 * x00 - s2 * x01, y01 = s2 * x00 + c2 * x01;
-        const double y10 = c2 * x10 - s2 * x11, y11 = s2 * x10 + c2 * x11;
-        const double z00 = c1 * y00 - s1 * y10, z10 = s1 * y00 + c1 * y10;
-        const double z01 = c1 * y01 - s1 * y11, z11 = s1 * y01 + c1 * y11;
-        B[p1][p2] = z00;
-        B[p1][q2] = z01;
-        B[q1][p2] = z10;
-        B[q1][q2] = z11;
-        B[p2][p1] = z00;
-        B[q2][p1] = z01;
-        B[p2][q1] = z10;
-        B[q2][q1] = z11;
-      }
-#pragma unroll
-      for (int u = 0; u < VPL; ++u) {
-        const int pr = v_pr[u], r = v_r[u];
-        if (pr < 0) continue;
-        const int2 pq = rpq[pr];
-        const double2 cs = rcs[pr];
-        const int p = pq.x, q = pq.y;
-        const double c = cs.x, sn = cs.y;
-        const double vp = V[r][p], vq = V[r][q];
-        V[r][p] = c * vp - sn * vq;
-        V[r][q] = sn * vp + c * vq;
-      }
-      __syncthreads();
     }
+  } else if (wv == 3) {
+    // lane = row; register j holds the column of player (r + j) mod PM, j < PM, and x[PM] that of player PM: pair
+    // k of every round is registers k and PM - k, and a rotation's results go one register down
+    const int row = min(lane, NPAD - 1);
+    double x[NPAD];
+#pragma unroll
+    for (int j = 0; j < NPAD; ++j) x[j] = V[row][j];
+    for (; another(); ++sweeps)
+      for (int r = 0; r < NPAD; ++r) {
+        if (r > 0) {
+          const double2* cs = rcs[(r - 1) & 1];
+          const unsigned first = kNextPivots.first_u[r - 1];
+          constexpr int M = NPAD - 1;
+          double2 c = cs[0];
+          double carry = rot_p(c.x, c.y, x[0], x[M]);   // player M is the larger one; goes to register M - 1
+          x[M] = rot_q(c.x, c.y, x[0], x[M]);
+#pragma unroll
+          for (int k = 1; k < NPR; ++k) {
+            c = cs[k];
+            const double xu = x[k], xv = x[M - k];
+            double nu, nv;
+            if ((first >> k) & 1u) {
+              nu = rot_p(c.x, c.y, xu, xv);
+              nv = rot_q(c.x, c.y, xu, xv);
+            } else {
+              nu = rot_q(c.x, c.y, xv, xu);
+              nv = rot_p(c.x, c.y, xv, xu);
+            }
+            x[k - 1] = nu;
+            x[M - k] = carry;
+            carry = nv;
+          }
+          x[NPR - 1] = carry;   // register M - 1 - (NPR - 1)
+        }
+        sync();
+        if (r > 0) cur ^= 1;
+      }
+    if (lane < NPAD)
+#pragma unroll
+      for (int j = 0; j < NPAD; ++j) V[lane][j] = x[j];
+  } else {
+    for (; another(); ++sweeps)
+      for (int r = 0; r < NPAD; ++r) {
+        if (r > 0 && blk_a >= 0) rotate_b(r - 1, Bm[cur], Bm[cur ^ 1], rcs[(r - 1) & 1], rtt[(r - 1) & 1]);
+        sync();
+        if (r > 0) cur ^= 1;
+      }
   }
+  __syncthreads();
+  B = reinterpret_cast<double (*)[LDP]>(Bm[cur]);
 
   if (t == 0 && fp.tr_ctr) {
     atomicAdd(fp.tr_ctr + 3, (unsigned long long)sweeps);
@@ -417,26 +587,25 @@ __global__ __launch_bounds__(64) void k_tr(FitDev st, FitParams fp) {
 
   // ---- eigen-coordinates of g; the eigenvectors are kept for the next iteration's start
   if (t < NP) {
-    lam[t] = B[t][t];
     double a = 0.0;
     for (int r = 0; r < NP; ++r) a += V[r][t] * g[r];
     gt[t] = a;
   }
-  for (int k = t; k < NP * NP; k += 64) st.V[(size_t)s * NP * NP + k] = V[k / NP][k % NP];
-  __syncthreads();
+  for (int k = t; k < NP * NP; k += TRT) st.V[(size_t)s * NP * NP + k] = V[k / NP][k % NP];
 
-  // ---- secular equation, one eigen-coordinate per lane (lanes >= NP hold neutral values);
-  // every reduction is broadcast from lane 0 so all lanes take the same decisions
-  {
-    const bool on = t < NP;
-    const double li = on ? lam[t] : 0.0, gi = on ? gt[t] : 0.0;
+  // ---- secular equation, one eigen-coordinate per lane of wavefront 0 (lanes >= NP hold neutral values);
+  // every reduction is the same on all lanes, so all take the same decisions
+  if (wv == 0) {
+    const bool on = lane < NP;
+    const double li = on ? B[lane][lane] : 0.0, gi = on ? gt[lane] : 0.0;
+    auto wsum = [](double x) { return wave_uniform(wave_sum(x)); };
     auto wmin = [](double x) {
       for (int o = 32; o > 0; o >>= 1) x = fmin(x, __shfl_xor(x, o));
-      return __shfl(x, 0);
+      return wave_uniform(x);
     };
     auto wmax = [](double x) {
       for (int o = 32; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o));
-      return __shfl(x, 0);
+      return wave_uniform(x);
     };
     const double lam0 = wmin(on ? li : INFINITY);
     // first index holding the smallest eigenvalue
@@ -460,7 +629,7 @@ __global__ __launch_bounds__(64) void k_tr(FitDev st, FitParams fp) {
         hard = true;
         sv = slo;
         pti = bottom ? 0.0 : qrest;
-        if (t == i0) pti += sqrt(fmax(delta * delta - prest2, 0.0));
+        if (lane == i0) pti += sqrt(fmax(delta * delta - prest2, 0.0));
       } else {
         double lo = slo, hi = slo + sqrt(gn2) / delta + 1.0;
         sv = (slo > 0.0) ? slo + 1e-12 * scale : 0.0;
@@ -484,9 +653,9 @@ __global__ __launch_bounds__(64) void k_tr(FitDev st, FitParams fp) {
       }
     }
     if (!hard) pti = on ? gi / (li + sv) : 0.0;
-    if (on) pt[t] = pti;
+    if (on) pt[lane] = pti;
     pred = wsum(on ? gi * pti - 0.5 * li * pti * pti : 0.0);
-    curv_ok = lam0 >= -fp.curv_tol * scale;
+    if (lane == 0) s_curv = lam0 >= -fp.curv_tol * scale ? 1 : 0;
   }
   __syncthreads();
   // the step back in psi coordinates
@@ -497,6 +666,7 @@ __global__ __launch_bounds__(64) void k_tr(FitDev st, FitParams fp) {
   }
   }   // eigendecomposition
 
+  if (wv != 0) return;   // the rest is one wavefront's: thread 0's decision, then one coordinate a lane
   if (t == 0) {
     if (fp.tr_ctr) atomicAdd(fp.tr_ctr + path, 1ull);
     // convergence and iteration cap; on the subsampled objective, the switch to the full one
@@ -511,7 +681,7 @@ __global__ __launch_bounds__(64) void k_tr(FitDev st, FitParams fp) {
         st.status[s] = CELESTE_MAX_ITER;
         d = 1;
       }
-    } else if (pred <= fp.pred_rtol * fmax(1.0, fabs(f)) && curv_ok) {
+    } else if (pred <= fp.pred_rtol * fmax(1.0, fabs(f)) && s_curv) {
       st.status[s] = CELESTE_CONVERGED;
       d = 1;
     } else if (st.iter[s] >= fp.max_iter) {
@@ -522,7 +692,9 @@ __global__ __launch_bounds__(64) void k_tr(FitDev st, FitParams fp) {
     if (d == 1) st.active[s] = 0;
     done = d;
   }
-  __syncthreads();
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   if (done == 2) {
     // the switch: the trial point is the current point, whose ELBO on the full objective the
     // value pass evaluates (k_accept takes it as the current value)
@@ -541,7 +713,7 @@ __global__ __launch_bounds__(64) void k_tr(FitDev st, FitParams fp) {
     tht[t] = to_theta1(ps[t] + a, box_of(t, u0, fp.u_box), &d1, &d2);
     pn2 = a * a;
   }
-  for (int o = 32; o > 0; o >>= 1) pn2 += __shfl_xor(pn2, o);
+  pn2 = wave_sum(pn2);
   if (t == 0) st.pnorm[s] = sqrt(pn2);
 }
 
@@ -746,7 +918,7 @@ hipError_t launch_fit_start(FitDev st, int n_src, hipStream_t s) {
 }
 
 hipError_t launch_tr_step(FitDev st, int n_src, FitParams fp, hipStream_t s) {
-  hipLaunchKernelGGL(k_tr, dim3(n_src), dim3(64), 0, s, st, fp);
+  hipLaunchKernelGGL(k_tr, dim3(n_src), dim3(TRT), 0, s, st, fp);
   return hipGetLastError();
 }
 
