@@ -2073,7 +2073,8 @@ int celeste_render_fields(celeste_ctx* ctx, const celeste_batch* b, const double
   const ImgDev* imgs = as<ImgDev>(ctx->imgs);
   HIPCHK(launch_setup(imgs, P.n_img, th, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st));
   HIPCHK(launch_render(as<int>(ctx->tile_off), as<int>(ctx->tile_img), n_tiles, imgs, as<float>(ctx->tables),
-                       P.tstride, P.prof.n_exp, P.prof.n_dev, f->height, f->width, tx, tpf, f->mean, f->var, st));
+                       P.tstride, P.prof.n_exp, P.prof.n_dev, f->height, f->width, tx, tpf, ctx->e_zero, f->mean,
+                       f->var, st));
   HIPCHK(hipStreamSynchronize(st));
   return CELESTE_OK;
 }
@@ -2098,8 +2099,8 @@ int celeste_neighbour_arrays(celeste_ctx* ctx, const celeste_batch* b, const dou
   const ImgDev* imgs = as<ImgDev>(ctx->imgs);
   HIPCHK(launch_setup(imgs, P.n_img, th, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st));
   HIPCHK(launch_neighbours(imgs, P.n_img, as<int>(ctx->img_field), as<float>(ctx->tables), P.tstride, P.prof.n_exp,
-                           P.prof.n_dev, f->height, f->width, f->mean, f->var, as<long long>(ctx->nbr_off), nbr_mean,
-                           nbr_var, st));
+                           P.prof.n_dev, f->height, f->width, ctx->e_zero, f->mean, f->var,
+                           as<long long>(ctx->nbr_off), nbr_mean, nbr_var, st));
   HIPCHK(hipStreamSynchronize(st));
   return CELESTE_OK;
 }
@@ -2157,7 +2158,7 @@ int celeste_update_fields(celeste_ctx* ctx, const celeste_batch* b, const double
   HIPCHK(launch_setup(imgs, P.n_img, th_new, nullptr, P.prof, as<float>(ctx->tables2), P.tstride, st));
   HIPCHK(launch_update_fields(imgs, P.n_img, as<int>(ctx->img_field), as<float>(ctx->tables),
                               as<float>(ctx->tables2), P.tstride, P.prof.n_exp, P.prof.n_dev, f->height, f->width,
-                              f->mean, f->var, st));
+                              ctx->e_zero, f->mean, f->var, st));
   HIPCHK(hipStreamSynchronize(st));
   return CELESTE_OK;
 }

@@ -173,14 +173,14 @@ hipError_t launch_reduce_value(const SrcDev* srcs, int n_src, const ImgDev* imgs
 
 hipError_t launch_render(const int* tile_off, const int* tile_img, int n_tiles, const ImgDev* imgs,
                          const float* tables, int tstride, int n_exp, int n_dev, int H, int W, int tiles_x,
-                         int tiles_per_field, float* mean, float* var, hipStream_t st);
+                         int tiles_per_field, float e_zero, float* mean, float* var, hipStream_t st);
 hipError_t launch_neighbours(const ImgDev* imgs, int n_img, const int* img_field, const float* tables, int tstride,
-                             int n_exp, int n_dev, int H, int W, const float* mean, const float* var,
+                             int n_exp, int n_dev, int H, int W, float e_zero, const float* mean, const float* var,
                              const long long* nbr_off, float* nbr_mean, float* nbr_var, hipStream_t st);
 
 hipError_t launch_update_fields(const ImgDev* imgs, int n_img, const int* img_field, const float* t_old,
-                                const float* t_new, int tstride, int n_exp, int n_dev, int H, int W, float* mean,
-                                float* var, hipStream_t st);
+                                const float* t_new, int tstride, int n_exp, int n_dev, int H, int W,
+                                float e_zero, float* mean, float* var, hipStream_t st);
 hipError_t launch_field_terms(const float* x, const float* mean, const float* var, const double* sky, int H, int W,
                               int n_fields, int per_block, int n_blocks, double* partials, hipStream_t st);
 hipError_t launch_prior_term(const double* theta, int n_src, PriorDev prior, double* out, hipStream_t st);

@@ -153,35 +153,6 @@ __device__ __forceinline__ void gal_comp(const GalRec& g, float dx, float dy, fl
   A.b4[4] = fmaf(Nn2, h44, A.b4[4]);
 }
 
-// The exponent's constants of a component (value path).
-struct ValRec {
-  float c0, qxx, qxy, qyy;
-};
-
-__device__ __forceinline__ ValRec load_val(const float* __restrict__ r) {
-  return ValRec{r[R_C0], r[R_QXX], r[R_QXY], r[R_QYY]};
-}
-
-// The exponents' constants of N consecutive components in scalar registers, loaded together.
-template <int N>
-struct ExpoBlock {
-  typedef float V4 __attribute__((ext_vector_type(4), aligned(16)));
-  V4 v[N];
-  __device__ __forceinline__ void load(const float* __restrict__ e) {
-#pragma unroll
-    for (int j = 0; j < N; ++j) v[j] = *reinterpret_cast<const V4*>(e + j * EXPO_REC);
-    // used here: sunk to the conditional uses that follow, each would wait for a load of its own
-#pragma unroll
-    for (int j = 0; j < N; ++j) asm volatile("" ::"s"(v[j]));
-  }
-  __device__ __forceinline__ ValRec rec(int j) const { return ValRec{v[j].x, v[j].y, v[j].z, v[j].w}; }
-};
-
-// acc += density of one component (value path).
-__device__ __forceinline__ void comp_value(const ValRec& r, float dxx, float dxy, float dyy, float& acc) {
-  acc += ex2(fmaf(r.qxx, dxx, fmaf(r.qxy, dxy, fmaf(r.qyy, dyy, r.c0))));
-}
-
 constexpr int tri(int i, int j) { return i * NZ - (i * (i - 1)) / 2 + (j - i); }
 
 // Brightness entries from product sums. The brightness z-derivatives of T and U are per-image

@@ -190,6 +190,35 @@ struct TileMap {
   }
 };
 
+// The exponent's constants of a component (value path).
+struct ValRec {
+  float c0, qxx, qxy, qyy;
+};
+
+__device__ __forceinline__ ValRec load_val(const float* __restrict__ r) {
+  return ValRec{r[tab::R_C0], r[tab::R_QXX], r[tab::R_QXY], r[tab::R_QYY]};
+}
+
+// The exponents' constants of N consecutive components in scalar registers, loaded together.
+template <int N>
+struct ExpoBlock {
+  typedef float V4 __attribute__((ext_vector_type(4), aligned(16)));
+  V4 v[N];
+  __device__ __forceinline__ void load(const float* __restrict__ e) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) v[j] = *reinterpret_cast<const V4*>(e + j * tab::EXPO_REC);
+    // used here: sunk to the conditional uses that follow, each would wait for a load of its own
+#pragma unroll
+    for (int j = 0; j < N; ++j) asm volatile("" ::"s"(v[j]));
+  }
+  __device__ __forceinline__ ValRec rec(int j) const { return ValRec{v[j].x, v[j].y, v[j].z, v[j].w}; }
+};
+
+// acc += density of one component (value path).
+__device__ __forceinline__ void comp_value(const ValRec& r, float dxx, float dxy, float dyy, float& acc) {
+  acc += ex2(fmaf(r.qxx, dxx, fmaf(r.qxy, dxy, fmaf(r.qyy, dyy, r.c0))));
+}
+
 // Which components of an image's galaxy mixture (npsf groups of ncomp, at most 64) can be non-zero on
 // a tile.  One component per lane: the lane holds the component's exponent
 //   e(d) = c0 - (A dx^2 + B dx dy + C dy^2)   (log2 of its density at offset d)
@@ -210,15 +239,20 @@ struct SkipTest {
   float4 geo;      // centre offset x, y (the PSF component's), B / 2C, B / 2A
 };
 
-__device__ __forceinline__ SkipTest skip_test_of(const float* __restrict__ T, int c, int ncomp) {
+// Test of the component with the constants at r, of the PSF component with the star record sr.
+__device__ __forceinline__ SkipTest skip_test(const float* __restrict__ r, const float* __restrict__ sr) {
   using namespace tab;
-  const float* r = T + EXPO + c * EXPO_REC;
-  const float* sr = T + STAR + (c / ncomp) * STAR_REC;
   SkipTest s;
   s.form = make_float4(r[R_C0], -r[R_QXX], -r[R_QXY], -r[R_QYY]);
   s.geo = make_float4(sr[S_XIX], sr[S_XIY], s.form.w > 0.f ? 0.5f * s.form.z / s.form.w : 0.f,
                       s.form.y > 0.f ? 0.5f * s.form.z / s.form.y : 0.f);
   return s;
+}
+
+// ... of galaxy component c
+__device__ __forceinline__ SkipTest skip_test_of(const float* __restrict__ T, int c, int ncomp) {
+  using namespace tab;
+  return skip_test(T + EXPO + c * EXPO_REC, T + STAR + (c / ncomp) * STAR_REC);
 }
 
 // True on the lanes whose component may be non-zero on the box (psx, psy: the source's position).

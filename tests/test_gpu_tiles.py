@@ -142,6 +142,86 @@ def test_pixel_constants(env, shape, kind, nbr, pitch):
         assert err.value.code == cb.E_INVALID
 
 
+@pytest.mark.parametrize("shape,n,n_psf,n_proto", [((1, 1), 70, 3, (6, 8)), ((7, 9), 130, 2, (6, 8)),
+                                                   ((8, 8), 64, 1, (6, 8)), ((33, 5), 65, 3, (6, 8)),
+                                                   ((70, 75), 5, 3, (6, 8)), ((17, 31), 20, 4, (6, 8)),
+                                                   ((33, 17), 20, 4, (8, 8)), ((16, 40), 9, 2, (2, 3))])
+def test_field_rendering(env, shape, n, n_psf, n_proto):
+    """Rendering, neighbour arrays and updates over patches that end inside squares and tiles, with more
+    sources than one pass over a tile's list takes and other component counts: the skips change no bit, and the
+    field meets the FP64 oracle."""
+    import torch
+    from oracle import model
+    cb, ctx = env
+    h, w = shape
+    H, W, NF = 70, 75, 2
+    sb = _one(h, w, seed=h, far=0)
+    rng = np.random.default_rng(h * w + n)
+    th = perturb_theta(np.repeat(sb.theta_truth, n, axis=0), 8)
+    th[:, 0:2] = rng.uniform(-3, [W + 3, H + 3], (n, 2))
+    th2 = perturb_theta(th, 9, scale=0.1)
+    ox = rng.integers(0, [W - w + 1, H - h + 1], (n, 2))
+    img = np.tile(np.arange(NF), n)
+    prof = {k: tuple(np.asarray(x)[np.arange(m) % len(x)] for x in sb.profiles[k])
+            for k, m in zip(("exp", "dev"), n_proto)}
+    psf = np.tile(sb.img_psf[:1, :1], (n * NF, 4, 1))
+    psf[:, :, 0] = 1.0 / n_psf
+    psf[:, :, 3:] *= np.array([1.0, 2.0, 4.0, 9.0])[:, None]
+    psf[:, n_psf:] = 0.0
+    npx, wcs = n * NF * h * w, np.tile([1.0, 0, 0, 1.0, 0, 0], (n * NF, 1))
+    b = cb.Batch(np.arange(n + 1, dtype=np.int64) * NF, img.astype(np.int32), np.full(n * NF, h, np.int32),
+                 np.full(n * NF, w, np.int32), np.full(n * NF, w, np.int32), np.repeat(ox, NF, axis=0).astype(float),
+                 wcs, np.full(n * NF, 90.0), np.ones(n * NF), psf, np.full(n * NF, n_psf, np.int32),
+                 torch.ones(npx, device="cuda"), np.arange(n * NF, dtype=np.int64) * h * w, sb.prior, prof)
+    td, td2 = torch.from_numpy(th).cuda(), torch.from_numpy(th2).cuda()
+    meta, off = (img.astype(np.int32), NF, H, W), np.arange(n * NF, dtype=np.int64) * h * w
+    one, i1 = b.subset([n - 1])
+    out = []
+    try:
+        for skip in (1, 0):
+            print("field", shape, n, n_psf, n_proto, "skip option", skip, flush=True)
+            ctx.set_option(cb.OPT_EXACT_ZERO, skip)
+            f = ctx.render_fields(b, td, *meta)
+            nb = [torch.empty(npx, device="cuda") for _ in range(2)]
+            ctx.neighbour_arrays(b, td, *meta, f, off, *nb)
+            g = [x.clone() for x in f]
+            ctx.update_fields(one, td[-1:], td2[-1:], meta[0][i1], NF, H, W, g)
+            out.append([x.cpu().numpy() for x in (*f, *nb, *g)])
+    finally:
+        ctx.set_option(cb.OPT_EXACT_ZERO, 0)
+    for x, y in zip(*out):
+        assert np.array_equal(x, y)
+    yy, xx = np.mgrid[0:h, 0:w]
+
+    def rendered(t):
+        ref, own = np.zeros((2, NF, H, W)), []
+        for s in range(n):
+            for f in range(NF):
+                z = model.image_z(t[s], f, wcs[0])
+                d = np.stack([(xx + ox[s, 0]).ravel() - z[5], (yy + ox[s, 1]).ravel() - z[6]], axis=1).astype(float)
+                Gs, p = model.star_value(d, psf[0][:n_psf]), psf[0][:n_psf]
+                Gg = model.galaxy_value(d, p, t[s][3], t[s][4], t[s][5], t[s][6], prof, np.eye(2))
+                ev = np.stack(model.rate_values(z, Gs, Gg, 0.0, 1.0, 0.0, 0.0)).reshape(2, h, w)
+                ref[:, f, ox[s, 1]:ox[s, 1] + h, ox[s, 0]:ox[s, 0] + w] += ev
+                own.append(ev)
+        return ref, own
+
+    ref, own = rendered(th)
+    moved = rendered(np.concatenate([th[:-1], th2[-1:]]))[0]
+    mean, var, nm, nv, um, uv = out[1]
+    # the tolerances of the field's own test at every pixel; differences get the total's
+    for got, want, rt in ((mean, ref[0], 1e-5), (var, ref[1], 1e-4), (um, moved[0], 1e-5), (uv, moved[1], 1e-4)):
+        tot = np.maximum(want, ref[0] if rt == 1e-5 else ref[1])
+        assert np.all(np.abs(got.reshape(want.shape) - want) <= rt * np.maximum(tot, 1e-3) + 1e-6)
+    for i in range(n * NF):
+        s, f = divmod(i, NF)
+        for got, k, rt in ((nm, 0, 1e-5), (nv, 1, 1e-4)):
+            tot = ref[k, f, ox[s, 1]:ox[s, 1] + h, ox[s, 0]:ox[s, 0] + w]
+            want = np.maximum(tot - own[i][k], 0.0)
+            assert np.all(np.abs(got[i * h * w:(i + 1) * h * w].reshape(h, w) - want)
+                          <= rt * np.maximum(tot, 1e-3) + 1e-6)
+
+
 def _device(a):
     import torch
     return torch.from_numpy(np.ascontiguousarray(a).ravel()).cuda()
