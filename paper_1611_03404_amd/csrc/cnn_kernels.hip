@@ -41,6 +41,10 @@ constexpr int TM = 64, TK = 32, TKP = TK + 8;
 // convolution operands built from images, 8 consecutive n at one k (b8n; kRunN true): n is a
 // multiple of 8 and the images are square with a power-of-two width of at least 8, so the 8
 // pixels lie in one image row and the tap and channel decomposition is done once per run.
+// Likewise for A: 8 consecutive k at one m (a8; kRunM false) or 8 consecutive m at one k (a8m; kRunM
+// true).  An operand stored with its other index running is read in runs of that one: 16-byte loads
+// where element loads along k would touch a line each (256 x 2048 weight gradient over 256 images:
+// 33 us by elements, 10 us by runs).
 
 // kk -> (ky, kx) of a 3x3 kernel tap
 __device__ __forceinline__ int tap_y(int kk) { return (kk * 11) >> 5; }   // kk / 3 for kk < 9
@@ -120,6 +124,8 @@ struct RunState {
 
 struct LdConvFwd {        // Y[co][img*HW+p] = sum_{ci,kk} W[co][ci*9+kk] X[img][ci][p + off(kk)]
   static constexpr bool kRunN = true;
+  static constexpr bool kRunM = false;
+  static constexpr int kTileN = 128;
   const bf16* W;
   const bf16* X;
   int Cin, hwl, wl;       // image side 2^wl, HW = 2^hwl
@@ -143,9 +149,11 @@ struct LdConvFwd {        // Y[co][img*HW+p] = sum_{ci,kk} W[co][ci*9+kk] X[img]
 // The same product with K ordered tap-major, k = kk*Cin + ci, for Cin a power of two of at least
 // 32: a 32-deep K step (K splits start at multiples of 32) then lies within one tap, so the tap's
 // row and column shift are the same on every lane.  W is the layer's weights re-laid as
-// W[co][kk*Cin + ci] (k_wf).
+// W[co][kk*Cin + ci] (k_tap_major).
 struct LdConvFwdT {
   static constexpr bool kRunN = true;
+  static constexpr bool kRunM = false;
+  static constexpr int kTileN = 128;
   const bf16* W;
   const bf16* X;
   int Cin, cl, hwl, wl;   // Cin = 2^cl
@@ -167,7 +175,9 @@ struct LdConvFwdT {
 
 struct LdConvDgrad {      // dX[ci][img*HW+p] = sum_{co,kk} W[co][ci][kk] dY[img][co][p - off(kk)]
   static constexpr bool kRunN = true;
-  const bf16* Wt;         // the layer's weights as Wt[ci][kk*Cout+co] (k_wt)
+  static constexpr bool kRunM = false;
+  static constexpr int kTileN = 128;
+  const bf16* Wt;         // the layer's weights as Wt[ci][kk*Cout+co] (k_tap_major)
   const bf16* dY;
   int Cin, Cout, col, hwl, wl;   // K ordered tap-major, k = kk*Cout + co, Cout = 2^col >= 32 (as LdConvFwdT)
   __device__ bf16x8_t a8(int m, int k, int kend) const {
@@ -188,6 +198,8 @@ struct LdConvDgrad {      // dX[ci][img*HW+p] = sum_{co,kk} W[co][ci][kk] dY[img
 
 struct LdConvWgrad {      // dW[co][ci*9+kk] = sum_{img,p} dY[img][co][p] X[img][ci][p + off(kk)]
   static constexpr bool kRunN = false;
+  static constexpr bool kRunM = false;
+  static constexpr int kTileN = 64;
   const bf16* dY;
   const bf16* X;
   int Cin, Cout, hwl, wl;   // image side 2^wl, HW = 2^hwl
@@ -208,6 +220,8 @@ struct LdConvWgrad {      // dW[co][ci*9+kk] = sum_{img,p} dY[img][co][p] X[img]
 
 struct LdFcFwd {          // Y[o][b] = sum_i W[o][i] X[b][i]
   static constexpr bool kRunN = false;
+  static constexpr bool kRunM = false;
+  static constexpr int kTileN = 64;
   const bf16* W;
   const bf16* X;
   int In;
@@ -221,15 +235,13 @@ struct LdFcFwd {          // Y[o][b] = sum_i W[o][i] X[b][i]
 
 struct LdFcDgrad {        // dX[i][b] = sum_o W[o][i] dY[b][o]
   static constexpr bool kRunN = false;
+  static constexpr bool kRunM = true;
+  static constexpr int kTileN = 64;
   const bf16* W;
   const bf16* dY;
   int In, Out;
-  __device__ bf16x8_t a8(int m, int k, int kend) const {
-    bf16x8_t v = zero8();
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (k + j < kend) v[j] = W[(size_t)(k + j) * In + m];
-    return v;
+  __device__ bf16x8_t a8m(int m, int k, int M) const {
+    return load8(W + (size_t)k * In + m, M - m, (In & 7) == 0);
   }
   __device__ bf16x8_t b8(int k, int n, int kend) const {
     return load8(dY + (size_t)n * Out + k, kend - k, ((size_t)n * Out + k) % 8 == 0);
@@ -237,23 +249,18 @@ struct LdFcDgrad {        // dX[i][b] = sum_o W[o][i] dY[b][o]
 };
 
 struct LdFcWgrad {        // dW[o][i] = sum_b dY[b][o] X[b][i]
-  static constexpr bool kRunN = false;
+  static constexpr bool kRunN = true;
+  static constexpr bool kRunM = true;
+  static constexpr int kTileN = 64;
   const bf16* dY;
   const bf16* X;
-  int In, Out;
-  __device__ bf16x8_t a8(int m, int k, int kend) const {
-    bf16x8_t v = zero8();
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (k + j < kend) v[j] = dY[(size_t)(k + j) * Out + m];
-    return v;
+  int In, Out;            // In a multiple of 8
+  __device__ bf16x8_t a8m(int m, int k, int M) const {
+    return load8(dY + (size_t)k * Out + m, M - m, (Out & 7) == 0);
   }
-  __device__ bf16x8_t b8(int k, int n, int kend) const {
-    bf16x8_t v = zero8();
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (k + j < kend) v[j] = X[(size_t)(k + j) * In + n];
-    return v;
+  __device__ RunState run(int n) const { return RunState{X + n, 0, 0}; }
+  __device__ bf16x8_t b8n(int k0, int kb, const RunState& r) const {
+    return load8(r.plane0 + (size_t)(k0 + kb) * In, 8, true);
   }
 };
 
@@ -265,10 +272,10 @@ struct EpConvFwd {
   int hwl;                // HW = 2^hwl pixels per image
 };
 
-// Tile width in N: 128 for the convolution operands built from images (n-runs), 64 otherwise
+// Tile width in N: 128 for the convolution operands built from images, 64 otherwise
 // (the dense layers and the weight gradients, whose N is small).
 template <class LD>
-constexpr int tile_n() { return LD::kRunN ? 128 : 64; }
+constexpr int tile_n() { return LD::kTileN; }
 
 // C[z][m][n] = sum over the z-th K split of A(m,k) B(k,n).  Block 256 = 4 waves in a 2x2
 // arrangement over a 64 x TNB tile, each wave a 32 x TNB/2 sub-tile of 2 x TNB/32 MFMA
@@ -295,7 +302,7 @@ __global__ __launch_bounds__(256) void k_gemm(LD ld, int M, int N, int K, int kc
   // (TNB = 128): k = t % 32, columns 8 (t / 32) .. + 7 and the same + 64 (the 32 lanes of one
   // n-run write 32 consecutive k of a row of Bs, so the transposed stores spread over the banks).
   const int ar = t >> 2, ak = (t & 3) * 8;
-  const int nb = 8 * (t >> 5), kb = t & 31;
+  const int nb = 8 * (t >> 5), kb = t & 31;   // of A's m-runs too
   bf16x8_t an, bn[NR];
   // n-run states (fixed over the K loop; unused for k-run operands)
   RunState rs[NR];
@@ -309,7 +316,10 @@ __global__ __launch_bounds__(256) void k_gemm(LD ld, int M, int N, int K, int kc
     }
   }
   auto fetch = [&](int k0) {
-    {
+    if constexpr (LD::kRunM) {
+      const int m = m0 + nb, k = k0 + kb;
+      an = (m < M && k < kend) ? ld.a8m(m, k, M) : zero8();
+    } else {
       const int m = m0 + ar, k = k0 + ak;
       an = (m < M && k < kend) ? ld.a8(m, k, kend) : zero8();
     }
@@ -330,7 +340,12 @@ __global__ __launch_bounds__(256) void k_gemm(LD ld, int M, int N, int K, int kc
   fetch(kbeg);
   const int r16 = lane & 15, kq = (lane >> 4) * 8;
   for (int k0 = kbeg; k0 < kend; k0 += TK) {
-    *reinterpret_cast<bf16x8_t*>(&As[ar][ak]) = an;
+    if constexpr (LD::kRunM) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) As[nb + j][kb] = an[j];
+    } else {
+      *reinterpret_cast<bf16x8_t*>(&As[ar][ak]) = an;
+    }
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       if constexpr (LD::kRunN) {
@@ -389,16 +404,72 @@ __device__ __forceinline__ float split_sum(const float* C, int S, size_t MN, siz
 
 // ------------------------------------------------------------------ epilogues and elementwise
 
-// conv forward: act[img][co][p] = bf16(relu(C[co][img*HW+p] + bias[co]))
-__global__ void k_ep_conv_fwd(const float* __restrict__ C, int S, int Cout, int B, int HW,
-                              const float* __restrict__ bias, bf16* __restrict__ act) {
-  const size_t total = (size_t)B * Cout * HW;
+// The elementwise passes over images work on units of 2 rows x 8 columns of one channel of one image (image
+// side 2^wl >= 8): 16-byte loads and stores, four whole pooling windows, and shifts instead of divisions by
+// the image's shape.
+struct Unit {
+  size_t plane;   // first element of the channel's image
+  int p, q;       // the unit's first pixel in it, and in the pooled image
+};
+__device__ __forceinline__ Unit unit_at(size_t plane_index, int u, int wl) {
+  const int y2 = u >> (wl - 3), x8 = u & ((1 << (wl - 3)) - 1);
+  return Unit{plane_index << (2 * wl), (y2 << (wl + 1)) + 8 * x8, (y2 << (wl - 1)) + 4 * x8};
+}
+
+__device__ __forceinline__ bf16x8_t ld8(const bf16* p) { return *reinterpret_cast<const bf16x8_t*>(p); }
+__device__ __forceinline__ void st8(bf16* p, const bf16x8_t& v) { *reinterpret_cast<bf16x8_t*>(p) = v; }
+
+// split_sum of 4 consecutive elements (idx a multiple of 4)
+__device__ __forceinline__ f32x4_t split_sum4(const float* C, int S, size_t MN, size_t idx) {
+  f32x4_t s = *reinterpret_cast<const f32x4_t*>(C + idx);
+  int z = 1;
+  for (; z + 4 <= S; z += 4) {
+    f32x4_t v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const f32x4_t*>(C + (size_t)(z + j) * MN + idx);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s += v[j];
+  }
+  for (; z < S; ++z) s += *reinterpret_cast<const f32x4_t*>(C + (size_t)z * MN + idx);
+  return s;
+}
+
+// 2x2 max-pool of a unit's rows
+__device__ __forceinline__ void pool_store(const bf16x8_t& a, const bf16x8_t& b, bf16* out) {
+  typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
+  bf16x4_t o;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    o[j] = to_bf16(fmaxf(fmaxf(from_bf16(a[2 * j]), from_bf16(a[2 * j + 1])),
+                         fmaxf(from_bf16(b[2 * j]), from_bf16(b[2 * j + 1]))));
+  *reinterpret_cast<bf16x4_t*>(out) = o;
+}
+
+// conv forward from split products: act[img][co][p] = bf16(relu(sum of C[co][img*HW+p] + bias[co])), and
+// its 2x2 max-pool (pool may be null)
+__global__ __launch_bounds__(256) void k_ep_conv_fwd(const float* __restrict__ C, int S, int Cout, int B, int wl,
+                                                     const float* __restrict__ bias, bf16* __restrict__ act,
+                                                     bf16* __restrict__ pool) {
+  const int ul = 2 * wl - 4;   // log2 of the units of an image
+  const size_t total = ((size_t)B * Cout) << ul, MN = ((size_t)Cout * B) << (2 * wl);
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-    const int p = i % HW;
-    const int co = (i / HW) % Cout;
-    const int img = i / ((size_t)HW * Cout);
-    const float v = split_sum(C, S, (size_t)Cout * B * HW, (size_t)co * B * HW + (size_t)img * HW + p) + bias[co];
-    act[i] = to_bf16(fmaxf(v, 0.f));
+    const size_t pl = i >> ul;
+    const int co = (int)(pl % Cout), img = (int)(pl / Cout);
+    const Unit u = unit_at(pl, (int)(i & ((1u << ul) - 1)), wl);
+    const size_t src = (((size_t)co * B + img) << (2 * wl)) + u.p;
+    const float bc = bias[co];
+    bf16x8_t o[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const f32x4_t v = split_sum4(C, S, MN, src + ((size_t)r << wl) + 4 * h);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[r][4 * h + j] = to_bf16(fmaxf(v[j] + bc, 0.f));
+      }
+    st8(act + u.plane + u.p, o[0]);
+    st8(act + u.plane + u.p + (1 << wl), o[1]);
+    if (pool) pool_store(o[0], o[1], pool + (u.plane >> 2) + u.q);
   }
 }
 
@@ -414,65 +485,168 @@ __global__ void k_ep_fc_fwd(const float* __restrict__ C, int S, int Out, int B, 
   }
 }
 
-// weight gradient: dW[m][n] = sum_z C[z][m][n]
-__global__ void k_ep_sum(const float* __restrict__ C, int S, int MN, float* __restrict__ out) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < MN; i += gridDim.x * blockDim.x)
-    out[i] = split_sum(C, S, MN, i);
+// Convolution weight gradient dW[m][n] = sum_z C[z][m][n] over S splits, in order, and, in the last blocks, a
+// bias gradient per thread from its channel's slices.  The smallest layer has 1,440 entries and up to
+// 1,024 splits, so its time is the chain of loads: a block takes 32 consecutive entries, all its threads load
+// (128 splits at a time, the next ones in flight) and one per entry adds, from LDS.  256 images, mean of the
+// four layers: 7.4 us (a thread per entry, 8 loads in flight, and a launch for the biases: 14.1 and 4.5 us).
+constexpr int BP_PARTS = 64;   // slices of a channel's bias gradient
+constexpr int GS_COLS = 32, GS_GROUPS = 8, GS_DEPTH = 16;
+__global__ __launch_bounds__(256) void k_grad_sum(const float* __restrict__ C, int S, int MN, int n_blocks_w,
+                                                  float* __restrict__ gw, const float* __restrict__ bpart, int Cch,
+                                                  float* __restrict__ gb) {
+  const int t = threadIdx.x;
+  if ((int)blockIdx.x >= n_blocks_w) {
+    const int c = ((int)blockIdx.x - n_blocks_w) * 256 + t;
+    if (c >= Cch) return;
+    float s = 0.f;
+#pragma unroll 16
+    for (int q = 0; q < BP_PARTS; ++q) s += bpart[c * BP_PARTS + q];
+    gb[c] = s;
+    return;
+  }
+  constexpr int STEP = GS_GROUPS * GS_DEPTH;
+  __shared__ float sh[2][STEP][GS_COLS];
+  const int col = t & (GS_COLS - 1), g = t / GS_COLS, idx = (int)blockIdx.x * GS_COLS + col;
+  const float* src = C + min(idx, MN - 1);
+  float v[GS_DEPTH], s = -0.f;   // -0 + x is x
+  auto fetch = [&](int z0) {
+#pragma unroll
+    for (int k = 0; k < GS_DEPTH; ++k) v[k] = src[(size_t)min(z0 + g + GS_GROUPS * k, S - 1) * MN];
+  };
+  fetch(0);
+  for (int z0 = 0, b = 0; z0 < S; z0 += STEP, b ^= 1) {
+#pragma unroll
+    for (int k = 0; k < GS_DEPTH; ++k) sh[b][g + GS_GROUPS * k][col] = v[k];
+    __syncthreads();   // one a step: the other buffer is written only after every sum over it
+    if (z0 + STEP < S) fetch(z0 + STEP);
+    if (g == 0) {
+      const int n = min(STEP, S - z0);
+      int k = 0;
+      for (; k + 16 <= n; k += 16) {
+        float w[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) w[j] = sh[b][k + j][col];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) s += w[j];
+      }
+      for (; k < n; ++k) s += sh[b][k][col];
+    }
+  }
+  if (g == 0 && idx < MN) gw[idx] = s;
 }
 
-// 2x2 max-pool (BF16)
-__global__ void k_pool_fwd(const bf16* __restrict__ in, int BC, int H, int W, bf16* __restrict__ out) {
-  const int Ho = H / 2, Wo = W / 2;
-  const size_t total = (size_t)BC * Ho * Wo;
+// 2x2 max-pool (BF16) of n_planes images of side 2^wl
+__global__ __launch_bounds__(256) void k_pool_fwd(const bf16* __restrict__ in, int n_planes, int wl,
+                                                  bf16* __restrict__ out) {
+  const int ul = 2 * wl - 4;
+  const size_t total = (size_t)n_planes << ul;
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-    const int x = i % Wo, y = (i / Wo) % Ho;
-    const size_t bc = i / ((size_t)Ho * Wo);
-    const bf16* q = in + bc * H * W + (2 * y) * W + 2 * x;
-    const float v = fmaxf(fmaxf(from_bf16(q[0]), from_bf16(q[1])), fmaxf(from_bf16(q[W]), from_bf16(q[W + 1])));
-    out[i] = to_bf16(v);
+    const Unit u = unit_at(i >> ul, (int)(i & ((1u << ul) - 1)), wl);
+    const bf16* q = in + u.plane + u.p;
+    pool_store(ld8(q), ld8(q + (1 << wl)), out + (u.plane >> 2) + u.q);
   }
 }
 
 // Backward through (optional) 2x2 max-pool and ReLU.  g comes from a GEMM as C[c*Hg*Wg + q][img]
-// (dense) or C[c][img*Hg*Wg + q] (convolution), summed over splits; r is the post-ReLU
-// activation at full resolution (H x W).  The pooled gradient goes to the first maximal
-// input of its window (row-major), then is masked by r > 0.
-__global__ void k_pool_relu_bwd(const float* __restrict__ C, int S, int dense_layout, int B, int Cch, int H, int W,
-                                int pooled, const bf16* __restrict__ r, float* __restrict__ dz,
-                                bf16* __restrict__ dzb) {
-  const int Hg = pooled ? H / 2 : H, Wg = pooled ? W / 2 : W;
-  const size_t MN = (size_t)Cch * Hg * Wg * B;
-  const size_t total = (size_t)B * Cch * H * W;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-    const int x = i % W, y = (i / W) % H;
-    const int c = (i / ((size_t)W * H)) % Cch;
-    const int img = i / ((size_t)W * H * Cch);
-    const bf16* rr = r + ((size_t)img * Cch + c) * H * W;
-    const float rv = from_bf16(rr[y * W + x]);
-    float g = 0.f;
-    if (rv > 0.f) {
-      int gy = y, gx = x;
-      bool take = true;
-      if (pooled) {
-        gy = y / 2;
-        gx = x / 2;
-        const int y0 = 2 * gy, x0 = 2 * gx;
-        const float a0 = from_bf16(rr[y0 * W + x0]), a1 = from_bf16(rr[y0 * W + x0 + 1]);
-        const float a2 = from_bf16(rr[(y0 + 1) * W + x0]), a3 = from_bf16(rr[(y0 + 1) * W + x0 + 1]);
-        const float mx = fmaxf(fmaxf(a0, a1), fmaxf(a2, a3));
-        const int first = (a0 == mx) ? 0 : (a1 == mx) ? 1 : (a2 == mx) ? 2 : 3;
-        take = first == (y - y0) * 2 + (x - x0);
-      }
-      if (take) {
-        const int q = gy * Wg + gx;
-        const size_t idx = dense_layout ? ((size_t)(c * Hg * Wg + q) * B + img)
-                                        : ((size_t)c * B * Hg * Wg + (size_t)img * Hg * Wg + q);
-        g = split_sum(C, S, MN, idx);
-      }
+// (DENSE) or C[c][img*Hg*Wg + q] (convolution), summed over splits; r is the post-ReLU
+// activation at full resolution (side 2^wl).  The pooled gradient goes to the first maximal
+// input of its window (row-major), then is masked by r > 0.  A wavefront takes the q-th of BP_PARTS
+// slices of a channel's pixels (over images and positions) in runs of 1,024, a unit per lane, and
+// sums the FP32 gradient over the slice for the bias: 256 strided sums, then a tree.
+// Bound by memory: the gradient and the activation read, the BF16 result written.  256 images, mean of the four
+// layers: 14 us (39 us with an element per thread, its FP32 gradient written for a pass of 12 us over it).
+constexpr int PRB_RUN = 1024;
+
+template <bool POOLED, bool DENSE>
+__device__ __forceinline__ void pool_relu_unit(const float* __restrict__ C, int S, int B, size_t MN, int c, int img,
+                                               int gl, int wl, const Unit& u, const bf16x8_t& a0, const bf16x8_t& a1,
+                                               float (&d)[2][8]) {
+  if constexpr (POOLED) {
+    f32x4_t g;
+    if constexpr (DENSE) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) g[j] = split_sum(C, S, MN, ((((size_t)c << gl) + u.q + j)) * B + img);
+    } else {
+      g = split_sum4(C, S, MN, (((size_t)c * B + img) << gl) + u.q);
     }
-    dz[i] = g;
-    dzb[i] = to_bf16(g);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float v[4] = {from_bf16(a0[2 * j]), from_bf16(a0[2 * j + 1]), from_bf16(a1[2 * j]),
+                          from_bf16(a1[2 * j + 1])};
+      const float mx = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
+      const int first = v[0] == mx ? 0 : v[1] == mx ? 1 : v[2] == mx ? 2 : 3;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) d[m >> 1][2 * j + (m & 1)] = (first == m && v[m] > 0.f) ? g[j] : 0.f;
+    }
+  } else {
+    static_assert(!DENSE, "the dense layer follows a pooled one");
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const f32x4_t g = split_sum4(C, S, MN, (((size_t)c * B + img) << gl) + u.p + (y << wl) + 4 * h);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) d[y][4 * h + j] = from_bf16((y ? a1 : a0)[4 * h + j]) > 0.f ? g[j] : 0.f;
+      }
   }
+}
+
+template <bool POOLED, bool DENSE>
+__global__ __launch_bounds__(256) void k_pool_relu_bwd(const float* __restrict__ C, int S, int B, int Cch, int wl,
+                                                       const bf16* __restrict__ r, bf16* __restrict__ dzb,
+                                                       float* __restrict__ bpart) {
+  __shared__ float run[4][PRB_RUN];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int c = blockIdx.y, slice = (int)blockIdx.x * 4 + wv;
+  const int gl = POOLED ? 2 * wl - 2 : 2 * wl, xl = wl - 3;   // 2^xl units per pair of rows
+  const size_t MN = ((size_t)Cch * B) << gl;
+  const int n = B << (2 * wl), per = (n + BP_PARTS - 1) / BP_PARTS;
+  const int i0 = min(n, slice * per), i1 = min(n, i0 + per);
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};   // strided sums lane, lane + 64, + 128, + 192
+  for (int a = i0; a < i1; a += PRB_RUN) {
+    const int b = min(i1, a + PRB_RUN);   // pixels [a, b): units of the row pairs they lie in
+    const int u0 = (a >> (wl + 1)) << xl, u1 = (((b - 1) >> (wl + 1)) + 1) << xl;
+    for (int k = u0 + lane; k < u1; k += 64) {
+      const int ul = 2 * wl - 4, img = k >> ul;
+      const Unit u = unit_at((size_t)img * Cch + c, k & ((1 << ul) - 1), wl);
+      const size_t o0 = u.plane + u.p, o1 = o0 + (1 << wl);
+      const bf16x8_t a0 = ld8(r + o0), a1 = ld8(r + o1);
+      float d[2][8];
+      pool_relu_unit<POOLED, DENSE>(C, S, B, MN, c, img, gl, wl, u, a0, a1, d);
+      const int at = (img << (2 * wl)) + u.p;   // the unit's first pixel in the channel
+      if (at >= a && at < b) {                  // a unit's pixels may lie in two runs: one of them stores it
+        bf16x8_t b0, b1;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          b0[j] = to_bf16(d[0][j]);
+          b1[j] = to_bf16(d[1][j]);
+        }
+        st8(dzb + o0, b0);
+        st8(dzb + o1, b1);
+      }
+#pragma unroll
+      for (int y = 0; y < 2; ++y)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int i = at + (y << wl) + j - a;
+          if (i >= 0 && i < b - a) run[wv][i] = d[y][j];
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int j = 0; j < PRB_RUN / 64; ++j)
+      if (64 * j + lane < b - a) acc[j & 3] += run[wv][64 * j + lane];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  float s = (acc[0] + acc[2]) + (acc[1] + acc[3]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o);   // lane i < o: entry i + entry i + o
+  if (lane == 0) bpart[c * BP_PARTS + slice] = s;
 }
 
 // dense hidden-layer backward: dz[b][i] = C[i][b] * (h[b][i] > 0)
@@ -504,38 +678,6 @@ __global__ __launch_bounds__(256) void k_bias_grad(const float* __restrict__ dz,
     __syncthreads();
   }
   if (threadIdx.x == 0) db[c] = sh[0];
-}
-
-// Conv-layer bias gradient in two fixed-order passes: block (c, q) sums the q-th of BP_PARTS
-// slices of channel c over images and positions; then one thread per channel sums its slices.
-constexpr int BP_PARTS = 64;
-
-__global__ __launch_bounds__(256) void k_bias_part(const float* __restrict__ dz, int B, int Cch, int HW,
-                                                   float* __restrict__ part) {
-  __shared__ float sh[256];
-  const int c = blockIdx.x, q = blockIdx.y;
-  const int n = B * HW, per = (n + BP_PARTS - 1) / BP_PARTS;
-  const int i0 = q * per, i1 = min(n, i0 + per);
-  float s = 0.f;
-  for (int i = i0 + threadIdx.x; i < i1; i += 256) {
-    const int img = i / HW, p = i - img * HW;
-    s += dz[((size_t)img * Cch + c) * HW + p];
-  }
-  sh[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[c * BP_PARTS + q] = sh[0];
-}
-
-__global__ __launch_bounds__(128) void k_bias_fin(const float* __restrict__ part, int Cch, float* __restrict__ db) {
-  const int c = blockIdx.x * 128 + threadIdx.x;
-  if (c >= Cch) return;
-  float s = 0.f;
-  for (int q = 0; q < BP_PARTS; ++q) s += part[c * BP_PARTS + q];
-  db[c] = s;
 }
 
 // MSE loss over the batch: dy = 2 (y - t) / (B*27); loss written by one block
@@ -575,23 +717,22 @@ __global__ void k_adam(float* __restrict__ w, float* __restrict__ m, float* __re
   }
 }
 
-// One convolution layer's weights re-laid for the data-gradient product, tap-major:
-// Wt[ci][kk*Cout+co] = W[co][ci*9+kk].
-__global__ void k_wt(const bf16* __restrict__ W, int Cin, int Cout, bf16* __restrict__ Wt) {
-  const int n = Cin * Cout * 9;
+// The tap-major weights of the convolution layers 1 .. 3, a layer per blockIdx.y (one launch instead of
+// one per layer and direction, 4.6 us each): Wf[co][kk*Cin+ci] = W[co][ci*9+kk] for the forward products (y < 3) and
+// Wt[ci][kk*Cout+co] = W[co][ci*9+kk] for the data-gradient ones.
+struct ConvWeights {
+  int off[3], cin[3], cout[3];
+};
+__global__ void k_tap_major(const bf16* __restrict__ wb, ConvWeights L, bf16* __restrict__ wf, bf16* __restrict__ wt) {
+  const int l = blockIdx.y % 3, Cin = L.cin[l], Cout = L.cout[l], n = Cin * Cout * 9;
+  const bool fwd = blockIdx.y < 3;
+  const bf16* W = wb + L.off[l];
+  bf16* out = (fwd ? wf : wt) + L.off[l];
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    const int ci = i / (Cout * 9), r = i - ci * Cout * 9, kk = r / Cout, co = r - kk * Cout;
-    Wt[i] = W[((size_t)co * Cin + ci) * 9 + kk];
-  }
-}
-
-// One convolution layer's weights re-laid for the tap-major forward product:
-// Wf[co][kk*Cin+ci] = W[co][ci*9+kk].
-__global__ void k_wf(const bf16* __restrict__ W, int Cin, int Cout, bf16* __restrict__ Wf) {
-  const int n = Cin * Cout * 9;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    const int co = i / (Cin * 9), r = i - co * Cin * 9, kk = r / Cin, ci = r - kk * Cin;
-    Wf[i] = W[((size_t)co * Cin + ci) * 9 + kk];
+    const int inner = fwd ? Cin : Cout;
+    const int a = i / (inner * 9), r = i - a * inner * 9, kk = r / inner, b = r - kk * inner;
+    const int co = fwd ? a : b, ci = fwd ? b : a;
+    out[i] = W[((size_t)co * Cin + ci) * 9 + kk];
   }
 }
 
@@ -666,6 +807,20 @@ hipError_t gemm(LD ld, int M, int N, int K, float* C, int& splits, hipStream_t s
   return hipGetLastError();
 }
 
+// A weight gradient: the product's splits summed into gw (one split is written there directly), and, for a
+// convolution (bpart), the bias gradient of its M channels from their slices.
+template <class LD>
+hipError_t gemm_sum(LD ld, int M, int N, int K, float* C, int splits, float* gw, hipStream_t st,
+                    const float* bpart = nullptr, float* gb = nullptr) {
+  const bool direct = splits == 1;
+  const hipError_t e = gemm(ld, M, N, K, direct ? gw : C, splits, st);
+  if (e != hipSuccess) return e;
+  const int bw = direct ? 0 : (M * N + GS_COLS - 1) / GS_COLS, bb = bpart ? (M + 255) / 256 : 0;
+  if (bw + bb > 0)
+    hipLaunchKernelGGL(k_grad_sum, dim3(bw + bb), dim3(256), 0, st, C, splits, M * N, bw, gw, bpart, M, gb);
+  return hipGetLastError();
+}
+
 inline int nblk(size_t n) { return (int)std::min<size_t>((n + 255) / 256, 16384); }
 
 inline int ilog2(int v) {
@@ -720,7 +875,7 @@ struct NetState {
   int cap_batch = 0;
   // activations (BF16) and gradients for cap_batch images
   bf16 *x = nullptr, *r[4] = {}, *p[4] = {}, *h = nullptr, *dyb = nullptr, *dzb = nullptr, *dhb = nullptr;
-  float *y = nullptr, *t = nullptr, *dy = nullptr, *dz = nullptr, *dh = nullptr, *C = nullptr, *loss = nullptr;
+  float *y = nullptr, *t = nullptr, *dy = nullptr, *dh = nullptr, *C = nullptr, *loss = nullptr;
   float* bpart = nullptr;   // conv bias-gradient slices (128 channels x BP_PARTS)
   size_t c_cap = 0;
 };
@@ -746,12 +901,12 @@ void net_free_work(NetState* n) {
                 n->dzb, n->dhb};
   for (bf16* q : bb)
     if (q) (void)hipFree(q);
-  float* ff[] = {n->y, n->t, n->dy, n->dz, n->dh, n->C};
+  float* ff[] = {n->y, n->t, n->dy, n->dh, n->C};
   for (float* q : ff)
     if (q) (void)hipFree(q);
   n->x = n->h = n->dyb = n->dzb = n->dhb = nullptr;
   for (int l = 0; l < 4; ++l) n->r[l] = n->p[l] = nullptr;
-  n->y = n->t = n->dy = n->dz = n->dh = n->C = nullptr;
+  n->y = n->t = n->dy = n->dh = n->C = nullptr;
   n->cap_batch = 0;
 }
 
@@ -790,7 +945,6 @@ hipError_t net_reserve(NetState* n, int B) {
   ALLOC(n->y, (size_t)B * 27 * 4);
   ALLOC(n->t, (size_t)B * 27 * 4);
   ALLOC(n->dy, (size_t)B * 27 * 4);
-  ALLOC(n->dz, maxact * 4);
   ALLOC(n->dh, (size_t)B * 2048 * 4);
   // split-K partial products: the largest M*N times the split count
   n->c_cap = std::max(maxact * 2, (size_t)8 << 20);
@@ -807,10 +961,20 @@ static int splits_for(size_t M, size_t N, size_t K, size_t cap, size_t tn = 64) 
   return s;
 }
 
-// Forward pass of B images at x_in (BF16, B x 5 x 32 x 32); leaves y (FP32, B x 27).
-hipError_t net_forward(NetState* n, const bf16* x_in, int B, hipStream_t st) {
+// Forward pass of B images at x_in (BF16, B x 5 x 32 x 32); leaves y (FP32, B x 27), and the weights that
+// net_backward reads in n->wt where it follows (backward).
+hipError_t net_forward(NetState* n, const bf16* x_in, int B, hipStream_t st, bool backward) {
   const NetLayout& L = n->L;
   hipError_t e;
+  ConvWeights cw;
+  for (int l = 1; l < 4; ++l) {
+    if (!tap_major(L.cin[l]) || !tap_major(L.cout[l])) return hipErrorInvalidValue;
+    cw.off[l - 1] = (int)L.off[2 * l];
+    cw.cin[l - 1] = L.cin[l];
+    cw.cout[l - 1] = L.cout[l];
+  }
+  hipLaunchKernelGGL(k_tap_major, dim3(nblk((size_t)128 * 64 * 9), backward ? 6 : 3), dim3(256), 0, st, n->wb, cw,
+                     n->wf, n->wt);
   const bf16* in = x_in;
   for (int l = 0; l < 4; ++l) {
     const int HW = L.hw[l] * L.hw[l];
@@ -818,9 +982,7 @@ hipError_t net_forward(NetState* n, const bf16* x_in, int B, hipStream_t st) {
     int S = splits_for(M, N, K, n->c_cap, tile_n<LdConvFwd>());
     const int wl = ilog2(L.hw[l]);
     const EpConvFwd ep{n->w + L.off[2 * l + 1], n->r[l], 2 * wl};
-    if (tap_major(L.cin[l])) {
-      hipLaunchKernelGGL(k_wf, dim3(nblk((size_t)L.cin[l] * L.cout[l] * 9)), dim3(256), 0, st, n->wb + L.off[2 * l],
-                         L.cin[l], L.cout[l], n->wf + L.off[2 * l]);
+    if (l > 0) {
       LdConvFwdT ld{n->wf + L.off[2 * l], in, L.cin[l], ilog2(L.cin[l]), 2 * wl, wl};
       if ((e = gemm(ld, (int)M, (int)N, (int)K, n->C, S, st, ep)) != hipSuccess) return e;
     } else {
@@ -828,15 +990,12 @@ hipError_t net_forward(NetState* n, const bf16* x_in, int B, hipStream_t st) {
       if ((e = gemm(ld, (int)M, (int)N, (int)K, n->C, S, st, ep)) != hipSuccess) return e;
     }
     if (S > 1)   // split products: the epilogue sums the splits
-      hipLaunchKernelGGL(k_ep_conv_fwd, dim3(nblk(M * N)), dim3(256), 0, st, n->C, S, L.cout[l], B, HW,
-                         n->w + L.off[2 * l + 1], n->r[l]);
-    if (L.pool[l]) {
-      hipLaunchKernelGGL(k_pool_fwd, dim3(nblk((size_t)B * L.cout[l] * HW / 4)), dim3(256), 0, st, n->r[l],
-                         B * L.cout[l], L.hw[l], L.hw[l], n->p[l]);
-      in = n->p[l];
-    } else {
-      in = n->r[l];
-    }
+      hipLaunchKernelGGL(k_ep_conv_fwd, dim3(nblk(M * N / 16)), dim3(256), 0, st, n->C, S, L.cout[l], B, wl,
+                         n->w + L.off[2 * l + 1], n->r[l], L.pool[l] ? n->p[l] : nullptr);
+    else if (L.pool[l])
+      hipLaunchKernelGGL(k_pool_fwd, dim3(nblk((size_t)B * L.cout[l] * HW / 16)), dim3(256), 0, st, n->r[l],
+                         B * L.cout[l], wl, n->p[l]);
+    in = L.pool[l] ? n->p[l] : n->r[l];
   }
   {
     int S = splits_for(256, B, 2048, n->c_cap);
@@ -865,8 +1024,7 @@ hipError_t net_backward(NetState* n, const bf16* x_in, int B, hipStream_t st) {
   {
     int S = splits_for(27, 256, B, n->c_cap);
     LdFcWgrad ld{n->dyb, n->h, 256, 27};
-    if ((e = gemm(ld, 27, 256, B, n->C, S, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_ep_sum, dim3(nblk(27 * 256)), dim3(256), 0, st, n->C, S, 27 * 256, n->g + L.off[10]);
+    if ((e = gemm_sum(ld, 27, 256, B, n->C, S, n->g + L.off[10], st)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_bias_grad, dim3(27), dim3(256), 0, st, n->dy, B, 27, 1, n->g + L.off[11]);
     int S2 = splits_for(256, B, 27, n->c_cap);
     LdFcDgrad ld2{n->wb + L.off[10], n->dyb, 256, 27};
@@ -878,15 +1036,14 @@ hipError_t net_backward(NetState* n, const bf16* x_in, int B, hipStream_t st) {
   {
     int S = splits_for(256, 2048, B, n->c_cap);
     LdFcWgrad ld{n->dhb, n->p[3], 2048, 256};
-    if ((e = gemm(ld, 256, 2048, B, n->C, S, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_ep_sum, dim3(nblk(256 * 2048)), dim3(256), 0, st, n->C, S, 256 * 2048, n->g + L.off[8]);
+    if ((e = gemm_sum(ld, 256, 2048, B, n->C, S, n->g + L.off[8], st)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_bias_grad, dim3(256), dim3(256), 0, st, n->dh, B, 256, 1, n->g + L.off[9]);
     int S2 = splits_for(2048, B, 256, n->c_cap);
     LdFcDgrad ld2{n->wb + L.off[8], n->dhb, 2048, 256};
     if ((e = gemm(ld2, 2048, B, 256, n->C, S2, st)) != hipSuccess) return e;
     // into conv4's post-ReLU activation through its pool (dense layout C[c*16+q][img])
-    hipLaunchKernelGGL(k_pool_relu_bwd, dim3(nblk((size_t)B * 128 * 64)), dim3(256), 0, st, n->C, S2, 1, B, 128, 8, 8,
-                       1, n->r[3], n->dz, n->dzb);
+    hipLaunchKernelGGL((k_pool_relu_bwd<true, true>), dim3(BP_PARTS / 4, 128), dim3(256), 0, st, n->C, S2, B, 128,
+                       3, n->r[3], n->dzb, n->bpart);
   }
   for (int l = 3; l >= 0; --l) {
     const int HW = L.hw[l] * L.hw[l];
@@ -897,27 +1054,22 @@ hipError_t net_backward(NetState* n, const bf16* x_in, int B, hipStream_t st) {
       int S = splits_for(M, N, K, n->c_cap);
       const int wl = ilog2(L.hw[l]);
       LdConvWgrad ld{n->dzb, xin, L.cin[l], L.cout[l], 2 * wl, wl};
-      if ((e = gemm(ld, (int)M, (int)N, (int)K, n->C, S, st)) != hipSuccess) return e;
-      hipLaunchKernelGGL(k_ep_sum, dim3(nblk(M * N)), dim3(256), 0, st, n->C, S, (int)(M * N), n->g + L.off[2 * l]);
-      hipLaunchKernelGGL(k_bias_part, dim3(L.cout[l], BP_PARTS), dim3(256), 0, st, n->dz, B, L.cout[l], HW,
-                         n->bpart);
-      hipLaunchKernelGGL(k_bias_fin, dim3((L.cout[l] + 127) / 128), dim3(128), 0, st, n->bpart, L.cout[l],
-                         n->g + L.off[2 * l + 1]);
+      if ((e = gemm_sum(ld, (int)M, (int)N, (int)K, n->C, S, n->g + L.off[2 * l], st, n->bpart,
+                        n->g + L.off[2 * l + 1])) != hipSuccess)
+        return e;
     }
     if (l == 0) break;
     // data gradient into the previous layer's post-ReLU activation (through its pool)
     {
       const size_t M = L.cin[l], N = (size_t)B * HW, K = (size_t)L.cout[l] * 9;
       int S = splits_for(M, N, K, n->c_cap, tile_n<LdConvDgrad>());
-      hipLaunchKernelGGL(k_wt, dim3(nblk((size_t)L.cin[l] * L.cout[l] * 9)), dim3(256), 0, st, n->wb + L.off[2 * l],
-                         L.cin[l], L.cout[l], n->wt + L.off[2 * l]);
       const int wl = ilog2(L.hw[l]);
-      if (!tap_major(L.cout[l])) return hipErrorInvalidValue;   // the layout has Cout >= 32 here
       LdConvDgrad ld{n->wt + L.off[2 * l], n->dzb, L.cin[l], L.cout[l], ilog2(L.cout[l]), 2 * wl, wl};
       if ((e = gemm(ld, (int)M, (int)N, (int)K, n->C, S, st)) != hipSuccess) return e;
-      const int Hp = L.hw[l - 1];
-      hipLaunchKernelGGL(k_pool_relu_bwd, dim3(nblk((size_t)B * L.cout[l - 1] * Hp * Hp)), dim3(256), 0, st, n->C, S,
-                         0, B, L.cout[l - 1], Hp, Hp, L.pool[l - 1], n->r[l - 1], n->dz, n->dzb);
+      const int wlp = ilog2(L.hw[l - 1]);
+      const auto k = L.pool[l - 1] ? &k_pool_relu_bwd<true, false> : &k_pool_relu_bwd<false, false>;
+      hipLaunchKernelGGL(k, dim3(BP_PARTS / 4, L.cout[l - 1]), dim3(256), 0, st, n->C, S, B, L.cout[l - 1], wlp,
+                         n->r[l - 1], n->dzb, n->bpart);
     }
   }
   return hipGetLastError();
@@ -1015,7 +1167,7 @@ int surrogate_predict(celeste_net* net, const SrcDev* srcs, int n_src, const Img
   NETCHK(net_reserve(&net->s, std::min(chunk, n_src)), "network workspace");
   for (int a = 0; a < n_src; a += chunk) {
     const int B = std::min(chunk, n_src - a);
-    NETCHK(net_forward(&net->s, (const bf16*)net->patches + (size_t)a * 5 * 1024, B, st), "network forward");
+    NETCHK(net_forward(&net->s, (const bf16*)net->patches + (size_t)a * 5 * 1024, B, st, false), "network forward");
     NETCHK(net_destandardise(net->s.y, net->psi_mean, net->psi_std, B * 27, psi_out + (size_t)a * 27, st),
            "destandardise");
   }
@@ -1090,7 +1242,7 @@ int celeste_net_loss_grad(celeste_net* net, const void* x, const float* t, int b
   hipStream_t st = net->stream;
   NETCHK(celeste::net_reserve(&net->s, batch), "network workspace");
   NETCHK(hipMemcpyAsync(net->s.t, t, (size_t)batch * 27 * 4, hipMemcpyDeviceToDevice, st), "targets");
-  NETCHK(celeste::net_forward(&net->s, (const celeste::bf16*)x, batch, st), "forward");
+  NETCHK(celeste::net_forward(&net->s, (const celeste::bf16*)x, batch, st, true), "forward");
   NETCHK(celeste::net_backward(&net->s, (const celeste::bf16*)x, batch, st), "backward");
   NETCHK(hipMemcpyAsync(loss, net->s.loss, 4, hipMemcpyDeviceToHost, st), "loss");
   if (grad) NETCHK(hipMemcpyAsync(grad, net->s.g, net->s.L.total * 4, hipMemcpyDeviceToHost, st), "gradient");
@@ -1107,7 +1259,7 @@ int celeste_net_forward(celeste_net* net, const void* x, int64_t n, float* y) {
   NETCHK(celeste::net_reserve(&net->s, (int)std::min<int64_t>(chunk, n)), "network workspace");
   for (int64_t a = 0; a < n; a += chunk) {
     const int B = (int)std::min<int64_t>(chunk, n - a);
-    NETCHK(celeste::net_forward(&net->s, (const celeste::bf16*)x + a * 5 * 1024, B, st), "forward");
+    NETCHK(celeste::net_forward(&net->s, (const celeste::bf16*)x + a * 5 * 1024, B, st, false), "forward");
     NETCHK(hipMemcpyAsync(y + a * 27, net->s.y, (size_t)B * 27 * 4, hipMemcpyDeviceToDevice, st), "output");
   }
   NETCHK(hipStreamSynchronize(st), "sync");
@@ -1133,7 +1285,7 @@ int celeste_net_train(celeste_net* net, const void* x, const float* t, int64_t n
     for (int64_t b = 0; b < nb; ++b) {
       const int B = (int)std::min<int64_t>(batch, n - b * batch);
       NETCHK(celeste::net_gather(&net->s, x, t, (const int*)orders + (size_t)e * n + b * batch, B, st), "gather");
-      NETCHK(celeste::net_forward(&net->s, net->s.x, B, st), "forward");
+      NETCHK(celeste::net_forward(&net->s, net->s.x, B, st, true), "forward");
       NETCHK(celeste::net_backward(&net->s, net->s.x, B, st), "backward");
       NETCHK(celeste::net_adam(&net->s, lr, st), "adam");
       NETCHK(celeste::net_acc_loss(&net->s, net->acc + e, st), "loss");
