@@ -4,11 +4,11 @@
 // standardised unconstrained coordinates) so that the trust-region fit starts
 // closer to the optimum; the plain start remains the fallback.  Layers: four
 // 3x3 same convolutions (5->32->64->64->128, ReLU, 2x2 max-pool after the last
-// three) and dense 2048->256 (ReLU) -> 27.  Every matrix product (convolution
-// forward, data gradient and weight gradient as implicit GEMMs, dense layers)
-// runs on one gather-GEMM kernel on the BF16 matrix cores (16x16x32 MFMA, FP32
-// accumulation, split-K partials summed in a fixed order; the convolution forward's bias,
-// ReLU and BF16 store fused into the product where it needs no split).  Activations and
+// three) and dense 2048->256 (ReLU) -> 27.  Every matrix product runs on the BF16 matrix
+// cores (16x16x32 MFMA, FP32 accumulation): the convolutions' forward and data-gradient products on
+// kernels that stage an image's pixels once for all taps (k_conv1, k_conv3: bias, ReLU, pooling and the
+// sum of K splits in them), their weight gradients and the dense layers on a
+// gather-GEMM (k_gemm, split-K partials summed in a fixed order).  Activations and
 // gradients feeding a product are BF16; master weights, Adam moments, biases and
 // all reductions are FP32.
 #include <math.h>
@@ -20,6 +20,7 @@
 #include <string>
 
 #include "celeste_internal.h"
+#include "wave.h"
 
 namespace celeste {
 
@@ -33,14 +34,12 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 __device__ __forceinline__ bf16 to_bf16(float x) { return (bf16)x; }
 __device__ __forceinline__ float from_bf16(bf16 x) { return (float)x; }
 
-constexpr int TM = 64, TK = 32, TKP = TK + 8;
+constexpr int TM = 64, TN = 64, TK = 32, TKP = TK + 8;
 
 // ------------------------------------------------------------------ gather loaders
 // A loader gives 8 consecutive k of A(m, k) (a8), zero for k >= kend or an index out of range.
-// For B(k, n) it gives either 8 consecutive k at one n (b8; kRunN false) or, for the
-// convolution operands built from images, 8 consecutive n at one k (b8n; kRunN true): n is a
-// multiple of 8 and the images are square with a power-of-two width of at least 8, so the 8
-// pixels lie in one image row and the tap and channel decomposition is done once per run.
+// For B(k, n) it gives either 8 consecutive k at one n (b8; kRunN false) or 8 consecutive n at one k
+// (b8n; kRunN true), n a multiple of 8.
 // Likewise for A: 8 consecutive k at one m (a8; kRunM false) or 8 consecutive m at one k (a8m; kRunM
 // true).  An operand stored with its other index running is read in runs of that one: 16-byte loads
 // where element loads along k would touch a line each (256 x 2048 weight gradient over 256 images:
@@ -91,115 +90,9 @@ __device__ __forceinline__ bf16x8_t row8(const bf16* __restrict__ row, int px, i
   return __builtin_bit_cast(bf16x8_t, o);
 }
 
-// row8 for a shift sh that is the same on every lane: one scalar branch instead of per-lane selects
-// (the same 8 values as row8).
-__device__ __forceinline__ bf16x8_t row8u(const bf16* __restrict__ row, int px, int sh, int wd) {
-  typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
-  const u32x4_t zero = {0u, 0u, 0u, 0u};
-  const u32x4_t mid = *reinterpret_cast<const u32x4_t*>(row + px);
-  if (sh == 0) return __builtin_bit_cast(bf16x8_t, mid);
-  u32x4_t o;
-  if (sh < 0) {
-    const u32x4_t lo = px > 0 ? *reinterpret_cast<const u32x4_t*>(row + px - 8) : zero;
-    o[0] = __builtin_amdgcn_alignbit(mid.x, lo.w, 16u);
-    o[1] = __builtin_amdgcn_alignbit(mid.y, mid.x, 16u);
-    o[2] = __builtin_amdgcn_alignbit(mid.z, mid.y, 16u);
-    o[3] = __builtin_amdgcn_alignbit(mid.w, mid.z, 16u);
-  } else {
-    const u32x4_t hi = px + 8 < wd ? *reinterpret_cast<const u32x4_t*>(row + px + 8) : zero;
-    o[0] = __builtin_amdgcn_alignbit(mid.y, mid.x, 16u);
-    o[1] = __builtin_amdgcn_alignbit(mid.z, mid.y, 16u);
-    o[2] = __builtin_amdgcn_alignbit(mid.w, mid.z, 16u);
-    o[3] = __builtin_amdgcn_alignbit(hi.x, mid.w, 16u);
-  }
-  return __builtin_bit_cast(bf16x8_t, o);
-}
-
-// Per-thread state of an n-run of a convolution operand: the run's image plane 0 and its first
-// pixel (row py, column px, a multiple of 8); fixed over the K loop.
-struct RunState {
-  const bf16* plane0;
-  int py, px;
-};
-
-struct LdConvFwd {        // Y[co][img*HW+p] = sum_{ci,kk} W[co][ci*9+kk] X[img][ci][p + off(kk)]
-  static constexpr bool kRunN = true;
-  static constexpr bool kRunM = false;
-  static constexpr int kTileN = 128;
-  const bf16* W;
-  const bf16* X;
-  int Cin, hwl, wl;       // image side 2^wl, HW = 2^hwl
-  __device__ bf16x8_t a8(int m, int k, int kend) const {
-    const size_t o = (size_t)m * Cin * 9 + k;
-    return load8(W + o, kend - k, (o & 7) == 0);
-  }
-  __device__ RunState run(int n) const {
-    const int img = n >> hwl, p = n & ((1 << hwl) - 1);
-    return RunState{X + (((size_t)img * Cin) << hwl), p >> wl, p & ((1 << wl) - 1)};
-  }
-  __device__ bf16x8_t b8n(int k0, int kb, const RunState& r) const {
-    const int k = k0 + kb;
-    const int ci = k / 9, kk = k - ci * 9;
-    const int y = r.py + tap_y(kk) - 1;
-    if (y < 0 || y >= (1 << wl)) return zero8();
-    return row8(r.plane0 + ((size_t)ci << hwl) + ((size_t)y << wl), r.px, tap_x(kk) - 1, 1 << wl);
-  }
-};
-
-// The same product with K ordered tap-major, k = kk*Cin + ci, for Cin a power of two of at least
-// 32: a 32-deep K step (K splits start at multiples of 32) then lies within one tap, so the tap's
-// row and column shift are the same on every lane.  W is the layer's weights re-laid as
-// W[co][kk*Cin + ci] (k_tap_major).
-struct LdConvFwdT {
-  static constexpr bool kRunN = true;
-  static constexpr bool kRunM = false;
-  static constexpr int kTileN = 128;
-  const bf16* W;
-  const bf16* X;
-  int Cin, cl, hwl, wl;   // Cin = 2^cl
-  __device__ bf16x8_t a8(int m, int k, int kend) const {
-    const size_t o = (size_t)m * Cin * 9 + k;
-    return load8(W + o, kend - k, (o & 7) == 0);
-  }
-  __device__ RunState run(int n) const {
-    const int img = n >> hwl, p = n & ((1 << hwl) - 1);
-    return RunState{X + (((size_t)img * Cin) << hwl), p >> wl, p & ((1 << wl) - 1)};
-  }
-  __device__ bf16x8_t b8n(int k0, int kb, const RunState& r) const {
-    const int kk = k0 >> cl, ci = (k0 & (Cin - 1)) + kb;
-    const int y = r.py + tap_y(kk) - 1;
-    if (y < 0 || y >= (1 << wl)) return zero8();
-    return row8u(r.plane0 + ((size_t)ci << hwl) + ((size_t)y << wl), r.px, tap_x(kk) - 1, 1 << wl);
-  }
-};
-
-struct LdConvDgrad {      // dX[ci][img*HW+p] = sum_{co,kk} W[co][ci][kk] dY[img][co][p - off(kk)]
-  static constexpr bool kRunN = true;
-  static constexpr bool kRunM = false;
-  static constexpr int kTileN = 128;
-  const bf16* Wt;         // the layer's weights as Wt[ci][kk*Cout+co] (k_tap_major)
-  const bf16* dY;
-  int Cin, Cout, col, hwl, wl;   // K ordered tap-major, k = kk*Cout + co, Cout = 2^col >= 32 (as LdConvFwdT)
-  __device__ bf16x8_t a8(int m, int k, int kend) const {
-    const size_t o = (size_t)m * Cout * 9 + k;
-    return load8(Wt + o, kend - k, (o & 7) == 0);
-  }
-  __device__ RunState run(int n) const {
-    const int img = n >> hwl, p = n & ((1 << hwl) - 1);
-    return RunState{dY + (((size_t)img * Cout) << hwl), p >> wl, p & ((1 << wl) - 1)};
-  }
-  __device__ bf16x8_t b8n(int k0, int kb, const RunState& r) const {
-    const int kk = k0 >> col, co = (k0 & (Cout - 1)) + kb;
-    const int y = r.py - tap_y(kk) + 1;
-    if (y < 0 || y >= (1 << wl)) return zero8();
-    return row8u(r.plane0 + ((size_t)co << hwl) + ((size_t)y << wl), r.px, 1 - tap_x(kk), 1 << wl);
-  }
-};
-
 struct LdConvWgrad {      // dW[co][ci*9+kk] = sum_{img,p} dY[img][co][p] X[img][ci][p + off(kk)]
   static constexpr bool kRunN = false;
   static constexpr bool kRunM = false;
-  static constexpr int kTileN = 64;
   const bf16* dY;
   const bf16* X;
   int Cin, Cout, hwl, wl;   // image side 2^wl, HW = 2^hwl
@@ -221,7 +114,6 @@ struct LdConvWgrad {      // dW[co][ci*9+kk] = sum_{img,p} dY[img][co][p] X[img]
 struct LdFcFwd {          // Y[o][b] = sum_i W[o][i] X[b][i]
   static constexpr bool kRunN = false;
   static constexpr bool kRunM = false;
-  static constexpr int kTileN = 64;
   const bf16* W;
   const bf16* X;
   int In;
@@ -236,7 +128,6 @@ struct LdFcFwd {          // Y[o][b] = sum_i W[o][i] X[b][i]
 struct LdFcDgrad {        // dX[i][b] = sum_o W[o][i] dY[b][o]
   static constexpr bool kRunN = false;
   static constexpr bool kRunM = true;
-  static constexpr int kTileN = 64;
   const bf16* W;
   const bf16* dY;
   int In, Out;
@@ -251,70 +142,39 @@ struct LdFcDgrad {        // dX[i][b] = sum_o W[o][i] dY[b][o]
 struct LdFcWgrad {        // dW[o][i] = sum_b dY[b][o] X[b][i]
   static constexpr bool kRunN = true;
   static constexpr bool kRunM = true;
-  static constexpr int kTileN = 64;
   const bf16* dY;
   const bf16* X;
   int In, Out;            // In a multiple of 8
   __device__ bf16x8_t a8m(int m, int k, int M) const {
     return load8(dY + (size_t)k * Out + m, M - m, (Out & 7) == 0);
   }
-  __device__ RunState run(int n) const { return RunState{X + n, 0, 0}; }
-  __device__ bf16x8_t b8n(int k0, int kb, const RunState& r) const {
-    return load8(r.plane0 + (size_t)(k0 + kb) * In, 8, true);
-  }
+  __device__ bf16x8_t b8n(int k, int n) const { return load8(X + (size_t)k * In + n, 8, true); }
 };
-
-// Optional fused epilogue of a product with one K split: the convolution forward's
-// act[img][co][p] = bf16(relu(C[co][img*HW+p] + bias[co])) instead of storing C.
-struct EpConvFwd {
-  const float* bias;
-  bf16* act;
-  int hwl;                // HW = 2^hwl pixels per image
-};
-
-// Tile width in N: 128 for the convolution operands built from images, 64 otherwise
-// (the dense layers and the weight gradients, whose N is small).
-template <class LD>
-constexpr int tile_n() { return LD::kTileN; }
 
 // C[z][m][n] = sum over the z-th K split of A(m,k) B(k,n).  Block 256 = 4 waves in a 2x2
-// arrangement over a 64 x TNB tile, each wave a 32 x TNB/2 sub-tile of 2 x TNB/32 MFMA
-// 16x16x32 tiles.  Operand runs of 8 BF16 go to LDS (k-runs as 16-byte stores, n-runs
+// arrangement over a 64 x 64 tile, each wave a 32 x 32 sub-tile of 2 x 2 MFMA
+// 16x16x32 tiles.  Operand runs of 8 BF16 go to LDS (k-runs as 16-byte stores, m- and n-runs
 // transposed element by element) and come back as single 16-byte reads; the next K step's
-// operands are loaded into registers while the current step's products run.  With ep.act set
-// (and one split) the convolution forward epilogue is applied in place of the C store.
+// operands are loaded into registers while the current step's products run.
 template <class LD>
-__global__ __launch_bounds__(256) void k_gemm(LD ld, int M, int N, int K, int kchunk, float* __restrict__ C,
-                                              EpConvFwd ep) {
-  constexpr int TNB = tile_n<LD>(), NJ = TNB / 32, NR = TNB / 64;
+__global__ __launch_bounds__(256) void k_gemm(LD ld, int M, int N, int K, int kchunk, float* __restrict__ C) {
+  constexpr int NJ = TN / 32;
   __shared__ __align__(16) bf16 As[TM][TKP];
-  __shared__ __align__(16) bf16 Bs[TNB][TKP];
-  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TNB;
+  __shared__ __align__(16) bf16 Bs[TN][TKP];
+  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
   const int kbeg = blockIdx.z * kchunk, kend = min(K, kbeg + kchunk);
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int wm = (wv >> 1) * 32, wn = (wv & 1) * (TNB / 2);
+  const int wm = (wv >> 1) * 32, wn = (wv & 1) * (TN / 2);
   f32x4_t acc[2][NJ];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  // A: row t / 4, k-run (t % 4) * 8.  B k-runs: rows t / 4 (+ 64), k-run (t % 4) * 8.  B n-runs
-  // (TNB = 128): k = t % 32, columns 8 (t / 32) .. + 7 and the same + 64 (the 32 lanes of one
-  // n-run write 32 consecutive k of a row of Bs, so the transposed stores spread over the banks).
+  // k-runs: row t / 4, k-run (t % 4) * 8.  m- and n-runs: k = t % 32, rows 8 (t / 32) .. + 7 (the 32
+  // lanes of one run write 32 consecutive k of an LDS row, so the transposed stores spread over the banks).
   const int ar = t >> 2, ak = (t & 3) * 8;
-  const int nb = 8 * (t >> 5), kb = t & 31;   // of A's m-runs too
-  bf16x8_t an, bn[NR];
-  // n-run states (fixed over the K loop; unused for k-run operands)
-  RunState rs[NR];
-  bool rv[NR];
-  if constexpr (LD::kRunN) {
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      const int n = n0 + nb + 64 * r;
-      rv[r] = n < N;
-      rs[r] = ld.run(rv[r] ? n : 0);
-    }
-  }
+  const int nb = 8 * (t >> 5), kb = t & 31;
+  bf16x8_t an, bn;
   auto fetch = [&](int k0) {
     if constexpr (LD::kRunM) {
       const int m = m0 + nb, k = k0 + kb;
@@ -324,16 +184,11 @@ __global__ __launch_bounds__(256) void k_gemm(LD ld, int M, int N, int K, int kc
       an = (m < M && k < kend) ? ld.a8(m, k, kend) : zero8();
     }
     if constexpr (LD::kRunN) {
-      const int k = k0 + kb;
-#pragma unroll
-      for (int r = 0; r < NR; ++r) bn[r] = (rv[r] && k < kend) ? ld.b8n(k0, kb, rs[r]) : zero8();
+      const int n = n0 + nb, k = k0 + kb;
+      bn = (n < N && k < kend) ? ld.b8n(k, n) : zero8();
     } else {
-      const int k = k0 + ak;
-#pragma unroll
-      for (int r = 0; r < NR; ++r) {
-        const int n = n0 + ar + 64 * r;
-        bn[r] = (n < N && k < kend) ? ld.b8(k, n, kend) : zero8();
-      }
+      const int n = n0 + ar, k = k0 + ak;
+      bn = (n < N && k < kend) ? ld.b8(k, n, kend) : zero8();
     }
   };
   bf16x8_t a[2], b[NJ];
@@ -346,14 +201,11 @@ __global__ __launch_bounds__(256) void k_gemm(LD ld, int M, int N, int K, int kc
     } else {
       *reinterpret_cast<bf16x8_t*>(&As[ar][ak]) = an;
     }
+    if constexpr (LD::kRunN) {
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      if constexpr (LD::kRunN) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) Bs[nb + 64 * r + j][kb] = bn[r][j];
-      } else {
-        *reinterpret_cast<bf16x8_t*>(&Bs[ar + 64 * r][ak]) = bn[r];
-      }
+      for (int j = 0; j < 8; ++j) Bs[nb + j][kb] = bn[j];
+    } else {
+      *reinterpret_cast<bf16x8_t*>(&Bs[ar][ak]) = bn;
     }
     __syncthreads();
     if (k0 + TK < kend) fetch(k0 + TK);   // next step's operands, in flight during the products
@@ -376,15 +228,252 @@ __global__ __launch_bounds__(256) void k_gemm(LD ld, int M, int N, int K, int kc
       for (int r = 0; r < 4; ++r) {
         const int mm = m0 + wm + i * 16 + (lane >> 4) * 4 + r;
         const int nn = n0 + wn + j * 16 + (lane & 15);
-        if (mm < M && nn < N) {
-          if (ep.act) {
-            const int img = nn >> ep.hwl, p = nn & ((1 << ep.hwl) - 1);
-            ep.act[((((size_t)img * M + mm) << ep.hwl) + p)] = to_bf16(fmaxf(acc[i][j][r] + ep.bias[mm], 0.f));
-          } else {
-            Cz[(size_t)mm * N + nn] = acc[i][j][r];
-          }
-        }
+        if (mm < M && nn < N) Cz[(size_t)mm * N + nn] = acc[i][j][r];
       }
+}
+
+// ------------------------------------------------------------------ convolutions
+// The convolution kernels' wavefronts work on 16-pixel fragments of 2 rows x 8 pixels, whole pooling windows; after
+// the products lane (px = lane & 15, kq = lane >> 4) holds channels 4 kq .. 4 kq + 3 of the fragment's px-th pixel.
+// Storing those one value at a time (64 two-byte stores per 64 x 64 outputs) took longer than the
+// products; here a quad of lanes exchanges its 4 channels x 4 pixels first.
+struct FragStore {
+  int px;
+  unsigned sel0, sel1;
+  __device__ __forceinline__ explicit FragStore(int px_) : px(px_) {
+    constexpr unsigned kLo = 0x05040100u, kHi = 0x07060302u, kLoR = 0x01000504u, kHiR = 0x03020706u;
+    sel0 = px & 2 ? (px & 1 ? kHiR : kHi) : (px & 1 ? kLoR : kLo);
+    sel1 = px & 2 ? (px & 1 ? kLoR : kLo) : (px & 1 ? kHiR : kHi);
+  }
+  // bf16(relu(v + b)) of the four channels; this lane stores channel px & 3 of its quad's 4 pixels at dst
+  __device__ __forceinline__ void act(const f32x4_t& v, const f32x4_t& b, bf16* dst) const {
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+    unsigned w[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      w[h] = __builtin_bit_cast(unsigned, bf16x2_t{to_bf16(fmaxf(v[2 * h] + b[2 * h], 0.f)),
+                                                   to_bf16(fmaxf(v[2 * h + 1] + b[2 * h + 1], 0.f))});
+    const bool b1 = px & 2, b0 = px & 1;
+    const unsigned keep = b1 ? w[1] : w[0], got2 = dpp_u<DPP_XOR2>(b1 ? w[0] : w[1]);   // 2 channels, pixels px, px ^ 2
+    const unsigned lo = __builtin_amdgcn_perm(got2, keep, 0x05040100u), hi = __builtin_amdgcn_perm(got2, keep, 0x07060302u);
+    const unsigned mine = b0 ? hi : lo, got1 = dpp_u<DPP_XOR1>(b0 ? lo : hi);           // 1 channel, px ^ 1, px ^ 3
+    const uint2 o = make_uint2(__builtin_amdgcn_perm(got1, mine, sel0), __builtin_amdgcn_perm(got1, mine, sel1));
+    *reinterpret_cast<uint2*>(dst) = o;
+  }
+  // the channel of four whose pooled value this lane stores
+  __device__ __forceinline__ int pool_channel() const { return (px & 1) + ((px >> 2) & 2); }
+  // 2x2 max-pool of bf16(relu(v + b)): relu, the addition and the rounding keep order, so the largest v is taken first.
+  // This lane stores its window's value of pool_channel(), whose bias is bc, at dst.
+  __device__ __forceinline__ void pool(const f32x4_t& v, float bc, bf16* dst) const {
+    float m[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      m[r] = fmaxf(v[r], dpp<DPP_XOR1>(v[r]));
+      m[r] = fmaxf(m[r], dpp<DPP_XOR8>(m[r]));
+    }
+    const float a = px & 1 ? m[1] : m[0], c = px & 1 ? m[3] : m[2];
+    *dst = to_bf16(fmaxf((px & 8 ? c : a) + bc, 0.f));
+  }
+  template <int CTRL>
+  static __device__ __forceinline__ unsigned dpp_u(unsigned x) {
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
+  }
+};
+
+// First convolution: 5 channels of 32 x 32 images to 32, k = ci*9+kk (45, two 32-deep steps), act = bf16(relu(. + bias)).
+// A block takes 8 rows of an image, 64 pixels a wavefront; the image's rows and border are staged as they lie and
+// a lane gathers its 8 k of a step by per-lane offsets, fixed over the fragments.  Bound by the activation it
+// writes (64 KB an image): 4,000 images 100 us (365 us as a gather-GEMM with a transposing LDS
+// store per element and half its rows unused).
+constexpr int C1_IN = 5, C1_OUT = 32, C1_K = 45;
+__global__ __launch_bounds__(256) void k_conv1(const bf16* __restrict__ wfrag, const bf16* __restrict__ X,
+                                               const float* __restrict__ bias, bf16* __restrict__ act) {
+  constexpr int W = 32, R = 8, LP = 48, X0 = 8;   // LDS row pitch; column of pixel 0 (16-byte aligned)
+  constexpr int NF = 4, MF = C1_OUT / 16;
+  __shared__ __align__(16) bf16 lds[C1_IN][R + 2][LP];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int img = blockIdx.x >> 2, y0 = (blockIdx.x & 3) * R;
+  for (int i = t; i < C1_IN * (R + 2) * (LP / 8); i += 256) {
+    const int x8 = i % (LP / 8), row = i / (LP / 8), ci = row / (R + 2), r = row - ci * (R + 2), y = y0 + r - 1;
+    const bool in = x8 >= 1 && x8 <= W / 8 && y >= 0 && y < W;
+    *reinterpret_cast<bf16x8_t*>(&lds[ci][r][8 * x8]) =
+        in ? *reinterpret_cast<const bf16x8_t*>(X + ((((size_t)img * C1_IN + ci) * W + y) * W + 8 * (x8 - 1))) : zero8();
+  }
+  const int px = lane & 15, kq = lane >> 4;
+  bf16x8_t a[2][MF];
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int i = 0; i < MF; ++i) a[s][i] = *reinterpret_cast<const bf16x8_t*>(wfrag + ((s * MF + i) * 64 + lane) * 8);
+  int off[2][8];      // element offset of k from the pixel's own place
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int k = min(s * 32 + kq * 8 + j, C1_K - 1), ci = k / 9, kk = k - ci * 9;
+      off[s][j] = ci * ((R + 2) * LP) + tap_y(kk) * LP + tap_x(kk) - 1;
+    }
+  const FragStore st(px);
+  f32x4_t b4[MF];
+#pragma unroll
+  for (int i = 0; i < MF; ++i) b4[i] = *reinterpret_cast<const f32x4_t*>(bias + 16 * i + 4 * kq);
+  __syncthreads();
+  const bf16* flat = &lds[0][0][0];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    const int g = wv * NF + f, y = 2 * (g >> 2) + (px >> 3), x = 8 * (g & 3) + (px & 7);
+    const bf16* at = flat + y * LP + X0 + x;
+    bf16x8_t b[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const bf16 v = at[off[s][j]];
+        b[s][j] = s == 0 || 32 + kq * 8 + j < C1_K ? v : (bf16)0.f;
+      }
+#pragma unroll
+    for (int i = 0; i < MF; ++i) {
+      f32x4_t acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][i], b[0], f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1][i], b[1], acc, 0, 0, 0);
+      const int m = 16 * i + 4 * kq + (px & 3);
+      st.act(acc, b4[i], act + (((size_t)img * C1_OUT + m) * W + y0 + y) * W + (x & ~3));
+    }
+  }
+}
+
+// 3x3 same convolution of images of side 2^WL with 2^CL channels (layers 1 .. 3), forward and data gradient
+// (FLIP: the taps mirrored), as an implicit product over k = tap * 2^CL + channel in 32-deep steps.
+// A block of four wavefronts takes 64 NF pixels (rows of one image, or whole images) of 16 MF output channels.  It
+// stages every channel of its pixels and their border once, pixel-major with a zero border, so that the operand of
+// each tap is the same LDS data at a constant offset: the K loop has neither barriers nor addresses,
+// only the weights' fragments (k_conv_weights) to load from cache.  A wavefront's 16-pixel
+// fragments are 2 rows x 8 pixels, whole pooling windows, so the pooled image is formed from the
+// accumulators.  LDS pitch: 16 bytes more than a pixel's channels, 4 banks apart modulo 32, so that the
+// 16-byte reads of 8 neighbouring pixels do not collide.
+// Sums stay those of the K splits that the layer's size asks for (chunk: steps of one split), added in order.
+// Bound by the matrix cores and the LDS reads that feed them (16 MF NF products' operands come
+// from MF + NF reads).  4,000 images, the three forward products with pooling: 438 us; 256 images,
+// data gradients: 20 us each.  (Gathering each tap's operand anew, transposed through LDS element by
+// element with two barriers a step: 1,110 us and 224 us more for the pooling; 37 us each.)
+template <int CL, int WL, int MF, int NF, bool FLIP>
+__global__ __launch_bounds__(256) void k_conv3(const bf16* __restrict__ wfrag, const bf16* __restrict__ X, int B, int M,
+                                               int chunk, const float* __restrict__ bias, bf16* __restrict__ act,
+                                               bf16* __restrict__ pool, float* __restrict__ out) {
+  constexpr int CH = 1 << CL, W = 1 << WL, NPX = 64 * NF;
+  constexpr int R = W * W < NPX ? W : NPX / W, NI = NPX / (R * W);   // rows of an image, images
+  constexpr int WP = W + 2, RP = R + 2, PB = CH * 2 + 16;            // with border; bytes per pixel
+  __shared__ __align__(16) unsigned char lds[NI * RP * WP * PB];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int first = (int)blockIdx.x * (NPX / 64);        // in runs of 64 pixels
+  const int img0 = first >> (2 * WL - 6), y0 = ((first & ((1 << (2 * WL - 6)) - 1)) << 6) >> WL;
+  // ---- stage: 4 channels x 8 pixels per thread and turn, channels fastest over the lanes
+  constexpr int CG = CH / 4, XG = W / 8, ROWS = NI * RP;
+  typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
+  for (int i = t; i < ROWS * XG * CG; i += 256) {
+    const int cg = i & (CG - 1), x8 = (i / CG) & (XG - 1), row = i / (CG * XG);
+    const int ni = row / RP, y = y0 + (row - ni * RP) - 1;
+    bf16x8_t v[4];
+    const bool in = y >= 0 && y < W && img0 + ni < B;
+    const bf16* src = X + ((((size_t)(img0 + ni) * CH + 4 * cg) << (2 * WL)) + ((size_t)(in ? y : 0) << WL) + 8 * x8);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] = in ? *reinterpret_cast<const bf16x8_t*>(src + ((size_t)c << (2 * WL))) : zero8();
+    unsigned char* dst = lds + (row * WP + 1 + 8 * x8) * PB + cg * 8;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) *reinterpret_cast<bf16x4_t*>(dst + j * PB) = bf16x4_t{v[0][j], v[1][j], v[2][j], v[3][j]};
+  }
+  constexpr int CV = CH / 8;
+  for (int i = t; i < ROWS * 2 * CV; i += 256) {
+    const int c = i & (CV - 1), side = (i / CV) & 1, row = i / (2 * CV);
+    *reinterpret_cast<bf16x8_t*>(lds + (row * WP + side * (W + 1)) * PB + c * 16) = zero8();
+  }
+  __syncthreads();
+  // ---- products
+  const int px = lane & 15, kq = lane >> 4;
+  int at[NF];         // LDS byte of this lane's pixel of each fragment, at the first tap
+  int py[NF], pi[NF], pxx[NF];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    const int g = wv * NF + f, x8 = g & (XG - 1), r2 = 2 * (g / XG), ni = r2 / R, r = r2 - ni * R;
+    py[f] = r + (px >> 3);
+    pxx[f] = 8 * x8 + (px & 7);
+    pi[f] = ni;
+    at[f] = ((ni * RP + py[f]) * WP + pxx[f]) * PB + kq * 16;
+  }
+  const int m16 = M >> 4, mb0 = blockIdx.y * MF;
+  const bf16* wl = wfrag + ((size_t)mb0 * 64 + lane) * 8;
+  constexpr int CB = CH / 32, STEPS = 9 * CB;
+  f32x4_t acc[MF][NF], sum[MF][NF];
+#pragma unroll
+  for (int i = 0; i < MF; ++i)
+#pragma unroll
+    for (int j = 0; j < NF; ++j) {
+      acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      if constexpr (NF < 4) sum[i][j] = f32x4_t{-0.f, -0.f, -0.f, -0.f};   // -0 + x is x
+    }
+  bf16x8_t a[2][MF];
+  auto weights = [&](int step, bf16x8_t (&d)[MF]) {
+#pragma unroll
+    for (int i = 0; i < MF; ++i) d[i] = *reinterpret_cast<const bf16x8_t*>(wl + ((size_t)step * m16 + i) * 512);
+  };
+  weights(0, a[0]);
+  int left = chunk;
+#pragma unroll
+  for (int s = 0; s < STEPS; ++s) {
+    const int kk = s / CB, ty = FLIP ? 2 - kk / 3 : kk / 3, tx = FLIP ? 2 - kk % 3 : kk % 3;
+    const int tap = (ty * WP + tx) * PB + (s % CB) * 64;
+    bf16x8_t b[NF];
+#pragma unroll
+    for (int j = 0; j < NF; ++j) b[j] = *reinterpret_cast<const bf16x8_t*>(lds + at[j] + tap);
+    if (s + 1 < STEPS) weights(s + 1, a[(s + 1) & 1]);
+#pragma unroll
+    for (int i = 0; i < MF; ++i)
+#pragma unroll
+      for (int j = 0; j < NF; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s & 1][i], b[j], acc[i][j], 0, 0, 0);
+    if constexpr (NF < 4) {
+      if (--left == 0 || s + 1 == STEPS) {   // the end of a split
+        left = chunk;
+#pragma unroll
+        for (int i = 0; i < MF; ++i)
+#pragma unroll
+          for (int j = 0; j < NF; ++j) {
+            sum[i][j] += acc[i][j];
+            acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+          }
+      }
+    }
+  }
+  // ---- results
+  const FragStore st(px);
+  f32x4_t b4[MF];
+  float bc[MF];
+#pragma unroll
+  for (int i = 0; i < MF; ++i)
+    if constexpr (!FLIP) {
+      const float* bm = bias + (mb0 + i) * 16 + 4 * kq;
+      b4[i] = *reinterpret_cast<const f32x4_t*>(bm);
+      bc[i] = bm[st.pool_channel()];
+    }
+#pragma unroll
+  for (int j = 0; j < NF; ++j) {
+    const int img = img0 + pi[j];
+    if (img >= B) continue;   // the same on the lanes of a fragment
+    const int y = y0 + py[j], x = pxx[j];
+#pragma unroll
+    for (int i = 0; i < MF; ++i) {
+      f32x4_t v;
+      if constexpr (NF < 4) v = sum[i][j]; else v = acc[i][j];
+      const int m = (mb0 + i) * 16 + 4 * kq;
+      if constexpr (FLIP) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) out[((size_t)(m + r) * B + img) * (W * W) + y * W + x] = v[r];
+      } else {
+        const size_t plane = (size_t)img * M + m;
+        if (act) st.act(v, b4[i], act + ((plane + (px & 3)) << (2 * WL)) + y * W + (x & ~3));
+        st.pool(v, bc[i], pool + ((plane + st.pool_channel()) << (2 * WL - 2)) + (y >> 1) * (W / 2) + (x >> 1));
+      }
+    }
+  }
 }
 
 // Sum over the K splits in split order; 8 loads in flight at a time.
@@ -418,60 +507,6 @@ __device__ __forceinline__ Unit unit_at(size_t plane_index, int u, int wl) {
 
 __device__ __forceinline__ bf16x8_t ld8(const bf16* p) { return *reinterpret_cast<const bf16x8_t*>(p); }
 __device__ __forceinline__ void st8(bf16* p, const bf16x8_t& v) { *reinterpret_cast<bf16x8_t*>(p) = v; }
-
-// split_sum of 4 consecutive elements (idx a multiple of 4)
-__device__ __forceinline__ f32x4_t split_sum4(const float* C, int S, size_t MN, size_t idx) {
-  f32x4_t s = *reinterpret_cast<const f32x4_t*>(C + idx);
-  int z = 1;
-  for (; z + 4 <= S; z += 4) {
-    f32x4_t v[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const f32x4_t*>(C + (size_t)(z + j) * MN + idx);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) s += v[j];
-  }
-  for (; z < S; ++z) s += *reinterpret_cast<const f32x4_t*>(C + (size_t)z * MN + idx);
-  return s;
-}
-
-// 2x2 max-pool of a unit's rows
-__device__ __forceinline__ void pool_store(const bf16x8_t& a, const bf16x8_t& b, bf16* out) {
-  typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
-  bf16x4_t o;
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    o[j] = to_bf16(fmaxf(fmaxf(from_bf16(a[2 * j]), from_bf16(a[2 * j + 1])),
-                         fmaxf(from_bf16(b[2 * j]), from_bf16(b[2 * j + 1]))));
-  *reinterpret_cast<bf16x4_t*>(out) = o;
-}
-
-// conv forward from split products: act[img][co][p] = bf16(relu(sum of C[co][img*HW+p] + bias[co])), and
-// its 2x2 max-pool (pool may be null)
-__global__ __launch_bounds__(256) void k_ep_conv_fwd(const float* __restrict__ C, int S, int Cout, int B, int wl,
-                                                     const float* __restrict__ bias, bf16* __restrict__ act,
-                                                     bf16* __restrict__ pool) {
-  const int ul = 2 * wl - 4;   // log2 of the units of an image
-  const size_t total = ((size_t)B * Cout) << ul, MN = ((size_t)Cout * B) << (2 * wl);
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-    const size_t pl = i >> ul;
-    const int co = (int)(pl % Cout), img = (int)(pl / Cout);
-    const Unit u = unit_at(pl, (int)(i & ((1u << ul) - 1)), wl);
-    const size_t src = (((size_t)co * B + img) << (2 * wl)) + u.p;
-    const float bc = bias[co];
-    bf16x8_t o[2];
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const f32x4_t v = split_sum4(C, S, MN, src + ((size_t)r << wl) + 4 * h);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) o[r][4 * h + j] = to_bf16(fmaxf(v[j] + bc, 0.f));
-      }
-    st8(act + u.plane + u.p, o[0]);
-    st8(act + u.plane + u.p + (1 << wl), o[1]);
-    if (pool) pool_store(o[0], o[1], pool + (u.plane >> 2) + u.q);
-  }
-}
 
 // dense forward: out[b][o] = C[o][b] + bias[o], ReLU + BF16 (hidden) or FP32 (output)
 __global__ void k_ep_fc_fwd(const float* __restrict__ C, int S, int Out, int B, const float* __restrict__ bias,
@@ -536,20 +571,8 @@ __global__ __launch_bounds__(256) void k_grad_sum(const float* __restrict__ C, i
   if (g == 0 && idx < MN) gw[idx] = s;
 }
 
-// 2x2 max-pool (BF16) of n_planes images of side 2^wl
-__global__ __launch_bounds__(256) void k_pool_fwd(const bf16* __restrict__ in, int n_planes, int wl,
-                                                  bf16* __restrict__ out) {
-  const int ul = 2 * wl - 4;
-  const size_t total = (size_t)n_planes << ul;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-    const Unit u = unit_at(i >> ul, (int)(i & ((1u << ul) - 1)), wl);
-    const bf16* q = in + u.plane + u.p;
-    pool_store(ld8(q), ld8(q + (1 << wl)), out + (u.plane >> 2) + u.q);
-  }
-}
-
 // Backward through (optional) 2x2 max-pool and ReLU.  g comes from a GEMM as C[c*Hg*Wg + q][img]
-// (DENSE) or C[c][img*Hg*Wg + q] (convolution), summed over splits; r is the post-ReLU
+// (DENSE, summed over splits) or C[c][img*Hg*Wg + q] (convolution); r is the post-ReLU
 // activation at full resolution (side 2^wl).  The pooled gradient goes to the first maximal
 // input of its window (row-major), then is masked by r > 0.  A wavefront takes the q-th of BP_PARTS
 // slices of a channel's pixels (over images and positions) in runs of 1,024, a unit per lane, and
@@ -568,7 +591,7 @@ __device__ __forceinline__ void pool_relu_unit(const float* __restrict__ C, int 
 #pragma unroll
       for (int j = 0; j < 4; ++j) g[j] = split_sum(C, S, MN, ((((size_t)c << gl) + u.q + j)) * B + img);
     } else {
-      g = split_sum4(C, S, MN, (((size_t)c * B + img) << gl) + u.q);
+      g = *reinterpret_cast<const f32x4_t*>(C + (((size_t)c * B + img) << gl) + u.q);
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -585,7 +608,7 @@ __device__ __forceinline__ void pool_relu_unit(const float* __restrict__ C, int 
     for (int y = 0; y < 2; ++y)
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const f32x4_t g = split_sum4(C, S, MN, (((size_t)c * B + img) << gl) + u.p + (y << wl) + 4 * h);
+        const f32x4_t g = *reinterpret_cast<const f32x4_t*>(C + (((size_t)c * B + img) << gl) + u.p + (y << wl) + 4 * h);
 #pragma unroll
         for (int j = 0; j < 4; ++j) d[y][4 * h + j] = from_bf16((y ? a1 : a0)[4 * h + j]) > 0.f ? g[j] : 0.f;
       }
@@ -686,6 +709,7 @@ __global__ __launch_bounds__(256) void k_mse(const float* __restrict__ y, const 
                                              float* __restrict__ loss) {
   __shared__ float sh[256];
   float s = 0.f;
+#pragma unroll 8
   for (int i = threadIdx.x; i < n; i += 256) {
     const float d = y[i] - t[i];
     s += d * d;
@@ -717,21 +741,34 @@ __global__ void k_adam(float* __restrict__ w, float* __restrict__ m, float* __re
   }
 }
 
-// The tap-major weights of the convolution layers 1 .. 3, a layer per blockIdx.y (one launch instead of
-// one per layer and direction, 4.6 us each): Wf[co][kk*Cin+ci] = W[co][ci*9+kk] for the forward products (y < 3) and
-// Wt[ci][kk*Cout+co] = W[co][ci*9+kk] for the data-gradient ones.
+// The weights of the convolution layers 1 .. 3 as k_conv3's fragments, a layer per blockIdx.y (one launch for
+// all, 4.6 us each): for the forward products (y < 3) A[m][k] = W[co = m][ci*9+kk], k = kk*Cin + ci,
+// and for the data-gradient ones A[m][k] = W[co][ci = m][kk], k = kk*Cout + co; stored so that the 16 x 32
+// fragment of K step s and row block b is one run of 512 values, 8 per lane, at (s * rows/16 + b) * 512.
 struct ConvWeights {
   int off[3], cin[3], cout[3];
+  int off1;   // of the first layer's fragments in wf
 };
-__global__ void k_tap_major(const bf16* __restrict__ wb, ConvWeights L, bf16* __restrict__ wf, bf16* __restrict__ wt) {
+constexpr int C1_FRAG = 2 * (C1_OUT / 16) * 512;
+__global__ void k_conv_weights(const bf16* __restrict__ wb, ConvWeights L, bf16* __restrict__ wf,
+                               bf16* __restrict__ wt) {
+  if (blockIdx.y == 0) {   // the first layer's: k = ci*9+kk, zeros from 45 to 63
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < C1_FRAG; i += gridDim.x * blockDim.x) {
+      const int frag = i >> 9, lane = (i >> 3) & 63, m = (frag & 1) * 16 + (lane & 15);
+      const int k = (frag >> 1) * 32 + (lane >> 4) * 8 + (i & 7);
+      wf[L.off1 + i] = k < C1_K ? wb[m * C1_K + k] : (bf16)0.f;
+    }
+  }
   const int l = blockIdx.y % 3, Cin = L.cin[l], Cout = L.cout[l], n = Cin * Cout * 9;
   const bool fwd = blockIdx.y < 3;
+  const int rows = fwd ? Cout : Cin, inner = fwd ? Cin : Cout;
   const bf16* W = wb + L.off[l];
   bf16* out = (fwd ? wf : wt) + L.off[l];
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    const int inner = fwd ? Cin : Cout;
-    const int a = i / (inner * 9), r = i - a * inner * 9, kk = r / inner, b = r - kk * inner;
-    const int co = fwd ? a : b, ci = fwd ? b : a;
+    const int frag = i >> 9, lane = (i >> 3) & 63, step = frag / (rows >> 4), blk = frag - step * (rows >> 4);
+    const int m = blk * 16 + (lane & 15), k = step * 32 + (lane >> 4) * 8 + (i & 7);
+    const int kk = k / inner, c = k - kk * inner;
+    const int co = fwd ? m : c, ci = fwd ? c : m;
     out[i] = W[((size_t)co * Cin + ci) * 9 + kk];
   }
 }
@@ -795,15 +832,13 @@ __global__ __launch_bounds__(256) void k_patches(const SrcDev* __restrict__ srcs
 
 // Launches the product with at most `splits` K-splits; *splits is set to the number used
 // (the count the epilogue must sum).
-// ep (optional): the convolution forward epilogue, applied in the product when it has one split.
 template <class LD>
-hipError_t gemm(LD ld, int M, int N, int K, float* C, int& splits, hipStream_t st, EpConvFwd ep = EpConvFwd{}) {
+hipError_t gemm(LD ld, int M, int N, int K, float* C, int& splits, hipStream_t st) {
   const int kchunk = ((K + splits - 1) / splits + TK - 1) / TK * TK;
   const int S = (K + kchunk - 1) / kchunk;
   splits = S;
-  if (S != 1) ep.act = nullptr;
-  dim3 grid((N + tile_n<LD>() - 1) / tile_n<LD>(), (M + TM - 1) / TM, S);
-  hipLaunchKernelGGL(k_gemm<LD>, grid, dim3(256), 0, st, ld, M, N, K, kchunk, C, ep);
+  dim3 grid((N + TN - 1) / TN, (M + TM - 1) / TM, S);
+  hipLaunchKernelGGL(k_gemm<LD>, grid, dim3(256), 0, st, ld, M, N, K, kchunk, C);
   return hipGetLastError();
 }
 
@@ -829,8 +864,28 @@ inline int ilog2(int v) {
   return l;
 }
 
-// a convolution product over c channels may order K tap-major: c a power of two of at least 32
-inline bool tap_major(int c) { return c >= 32 && (c & (c - 1)) == 0; }
+// A k_conv3 product of M output channels over B images, its sums in `splits` K splits (the rule of gemm).
+// Blocks of 256 pixels where that leaves two blocks or more per compute unit, else (and where
+// the sums of splits must be kept beside the running ones, or 128 channels would take 109 KB of LDS)
+// of 128.
+template <int CL, int WL, int MF, bool FLIP>
+hipError_t conv3(const bf16* wfrag, const bf16* X, int B, int M, int splits, const float* bias, bf16* act, bf16* pool,
+                 float* out, hipStream_t st) {
+  constexpr int K = 9 << CL;
+  const int chunk = ((K + splits - 1) / splits + TK - 1) / TK;
+  const int64_t n = (int64_t)B << (2 * WL);
+  const int rows = M / (16 * MF);
+  if (M != rows * 16 * MF) return hipErrorInvalidValue;
+  if constexpr (CL < 7)
+    if (splits == 1 && (n + 255) / 256 * rows >= 512) {
+      hipLaunchKernelGGL((k_conv3<CL, WL, MF, 4, FLIP>), dim3((n + 255) / 256, rows), dim3(256), 0, st, wfrag, X, B, M,
+                         chunk, bias, act, pool, out);
+      return hipGetLastError();
+    }
+  hipLaunchKernelGGL((k_conv3<CL, WL, MF, 2, FLIP>), dim3((n + 127) / 128, rows), dim3(256), 0, st, wfrag, X, B, M, chunk,
+                     bias, act, pool, out);
+  return hipGetLastError();
+}
 
 }  // namespace
 
@@ -870,7 +925,7 @@ struct NetState {
   float* g = nullptr;     // gradient
   bf16* wb = nullptr;     // BF16 weights
   bf16* wt = nullptr;     // convolution weights re-laid for the data-gradient products (conv offsets)
-  bf16* wf = nullptr;     // convolution weights re-laid for the tap-major forward products (conv offsets)
+  bf16* wf = nullptr;     // ... for the forward products (conv offsets; the first layer's after the others)
   int step = 0;
   int cap_batch = 0;
   // activations (BF16) and gradients for cap_batch images
@@ -889,7 +944,7 @@ hipError_t net_alloc(NetState* n) {
   if ((e = hipMalloc(&n->g, P * 4)) != hipSuccess) return e;
   if ((e = hipMalloc(&n->wb, P * 2)) != hipSuccess) return e;
   if ((e = hipMalloc(&n->wt, n->L.off[8] * 2)) != hipSuccess) return e;
-  if ((e = hipMalloc(&n->wf, n->L.off[8] * 2)) != hipSuccess) return e;
+  if ((e = hipMalloc(&n->wf, (n->L.off[8] + C1_FRAG) * 2)) != hipSuccess) return e;
   if ((e = hipMemset(n->m, 0, P * 4)) != hipSuccess) return e;
   if ((e = hipMemset(n->v, 0, P * 4)) != hipSuccess) return e;
   if ((e = hipMalloc(&n->bpart, sizeof(float) * 128 * BP_PARTS)) != hipSuccess) return e;
@@ -967,36 +1022,30 @@ hipError_t net_forward(NetState* n, const bf16* x_in, int B, hipStream_t st, boo
   const NetLayout& L = n->L;
   hipError_t e;
   ConvWeights cw;
+  cw.off1 = (int)L.off[8];
   for (int l = 1; l < 4; ++l) {
-    if (!tap_major(L.cin[l]) || !tap_major(L.cout[l])) return hipErrorInvalidValue;
     cw.off[l - 1] = (int)L.off[2 * l];
     cw.cin[l - 1] = L.cin[l];
     cw.cout[l - 1] = L.cout[l];
   }
-  hipLaunchKernelGGL(k_tap_major, dim3(nblk((size_t)128 * 64 * 9), backward ? 6 : 3), dim3(256), 0, st, n->wb, cw,
+  hipLaunchKernelGGL(k_conv_weights, dim3(nblk((size_t)128 * 64 * 9), backward ? 6 : 3), dim3(256), 0, st, n->wb, cw,
                      n->wf, n->wt);
-  const bf16* in = x_in;
-  for (int l = 0; l < 4; ++l) {
-    const int HW = L.hw[l] * L.hw[l];
-    const size_t M = L.cout[l], N = (size_t)B * HW, K = (size_t)L.cin[l] * 9;
-    int S = splits_for(M, N, K, n->c_cap, tile_n<LdConvFwd>());
-    const int wl = ilog2(L.hw[l]);
-    const EpConvFwd ep{n->w + L.off[2 * l + 1], n->r[l], 2 * wl};
-    if (l > 0) {
-      LdConvFwdT ld{n->wf + L.off[2 * l], in, L.cin[l], ilog2(L.cin[l]), 2 * wl, wl};
-      if ((e = gemm(ld, (int)M, (int)N, (int)K, n->C, S, st, ep)) != hipSuccess) return e;
-    } else {
-      LdConvFwd ld{n->wb + L.off[2 * l], in, L.cin[l], 2 * wl, wl};
-      if ((e = gemm(ld, (int)M, (int)N, (int)K, n->C, S, st, ep)) != hipSuccess) return e;
-    }
-    if (S > 1)   // split products: the epilogue sums the splits
-      hipLaunchKernelGGL(k_ep_conv_fwd, dim3(nblk(M * N / 16)), dim3(256), 0, st, n->C, S, L.cout[l], B, wl,
-                         n->w + L.off[2 * l + 1], n->r[l], L.pool[l] ? n->p[l] : nullptr);
-    else if (L.pool[l])
-      hipLaunchKernelGGL(k_pool_fwd, dim3(nblk((size_t)B * L.cout[l] * HW / 16)), dim3(256), 0, st, n->r[l],
-                         B * L.cout[l], wl, n->p[l]);
-    in = L.pool[l] ? n->p[l] : n->r[l];
-  }
+  const auto splits = [&](int l) {
+    return splits_for(L.cout[l], (size_t)B * L.hw[l] * L.hw[l], (size_t)L.cin[l] * 9, n->c_cap, 128);
+  };
+  const auto act = [&](int l) { return backward || !L.pool[l] ? n->r[l] : nullptr; };   // the backward pass reads it
+  const auto bias = [&](int l) { return n->w + L.off[2 * l + 1]; };
+  hipLaunchKernelGGL(k_conv1, dim3(4 * B), dim3(256), 0, st, n->wf + cw.off1, x_in, bias(0), n->r[0]);
+  if ((e = conv3<5, 5, 4, false>(n->wf + L.off[2], n->r[0], B, 64, splits(1), bias(1), act(1), n->p[1], nullptr, st)) !=
+      hipSuccess)
+    return e;
+  if ((e = conv3<6, 4, 4, false>(n->wf + L.off[4], n->p[1], B, 64, splits(2), bias(2), act(2), n->p[2], nullptr, st)) !=
+      hipSuccess)
+    return e;
+  if ((e = conv3<6, 3, 4, false>(n->wf + L.off[6], n->p[2], B, 128, splits(3), bias(3), act(3), n->p[3], nullptr, st)) !=
+      hipSuccess)
+    return e;
+  const bf16* in = n->p[3];
   {
     int S = splits_for(256, B, 2048, n->c_cap);
     LdFcFwd ld{n->wb + L.off[8], in, 2048};
@@ -1061,14 +1110,16 @@ hipError_t net_backward(NetState* n, const bf16* x_in, int B, hipStream_t st) {
     if (l == 0) break;
     // data gradient into the previous layer's post-ReLU activation (through its pool)
     {
-      const size_t M = L.cin[l], N = (size_t)B * HW, K = (size_t)L.cout[l] * 9;
-      int S = splits_for(M, N, K, n->c_cap, tile_n<LdConvDgrad>());
-      const int wl = ilog2(L.hw[l]);
-      LdConvDgrad ld{n->wt + L.off[2 * l], n->dzb, L.cin[l], L.cout[l], ilog2(L.cout[l]), 2 * wl, wl};
-      if ((e = gemm(ld, (int)M, (int)N, (int)K, n->C, S, st)) != hipSuccess) return e;
+      const int M = L.cin[l];
+      const int S = splits_for(M, (size_t)B * HW, (size_t)L.cout[l] * 9, n->c_cap, 128);
+      const bf16* wt = n->wt + L.off[2 * l];
+      e = l == 3   ? conv3<7, 3, 4, true>(wt, n->dzb, B, M, S, nullptr, nullptr, nullptr, n->C, st)
+          : l == 2 ? conv3<6, 4, 4, true>(wt, n->dzb, B, M, S, nullptr, nullptr, nullptr, n->C, st)
+                   : conv3<6, 5, 2, true>(wt, n->dzb, B, M, S, nullptr, nullptr, nullptr, n->C, st);
+      if (e != hipSuccess) return e;
       const int wlp = ilog2(L.hw[l - 1]);
       const auto k = L.pool[l - 1] ? &k_pool_relu_bwd<true, false> : &k_pool_relu_bwd<false, false>;
-      hipLaunchKernelGGL(k, dim3(BP_PARTS / 4, L.cout[l - 1]), dim3(256), 0, st, n->C, S, B, L.cout[l - 1], wlp,
+      hipLaunchKernelGGL(k, dim3(BP_PARTS / 4, L.cout[l - 1]), dim3(256), 0, st, n->C, 1, B, L.cout[l - 1], wlp,
                          n->r[l - 1], n->dzb, n->bpart);
     }
   }
