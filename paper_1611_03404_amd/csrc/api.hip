@@ -4,13 +4,16 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <string>
+#include <system_error>
 #include <thread>
 #include <unordered_map>
 #include <vector>
@@ -76,7 +79,9 @@ struct celeste_ctx {
   bool exp2_flushes = false;   // the device's exp2 returns 0 below 2^-126 (checked at creation)
   int vblock = 256;      // value kernel block size
   int vtile_log2 = 3;    // log2 tile width of the value kernel
-  DevBuf imgs, items, srcs, tables, partials, img_const, staging, theta, o_elbo, o_grad, o_hess, flag;
+  DevBuf meta, items_kept;                // packed metadata (one upload); a subsample's work items
+  DevBuf imgs, items, srcs, flag;         // where the last pack's parts lie in them (views, not owned)
+  DevBuf tables, partials, img_const, staging, theta, o_elbo, o_grad, o_hess;
   DevBuf st_buf;   // all trust-region state in one allocation
   DevBuf ctr;      // device counters: pixel evaluations [full, value, grad], subproblem paths and work [3..8]
   int profile = 0;
@@ -84,7 +89,7 @@ struct celeste_ctx {
 
   celeste_net* net = nullptr;   // surrogate network (not owned)
   DevBuf sur;                   // surrogate predictions (float, S x 27)
-  DevBuf tile_off, tile_img, img_field, nbr_off;   // crowded-field index buffers
+  DevBuf tile_off, img_field, nbr_off;             // crowded-field index buffers
   DevBuf tables2, fsky;                            // second setup table (field updates), field skies
   DevBuf kept;                                     // first rows of the kept blocks of a pixel subsample
   DevBuf lr_in, lr_cov, lr_status, lr_eval;        // linear-response covariance staging
@@ -100,7 +105,8 @@ struct celeste_ctx {
   int n_cu = 0;                                    // compute units of the device
   DevBuf qbuf;                                     // the fits' device work queue
   bool lfact_ready = false;
-  DevBuf h_imgs, h_items, h_srcs;                  // pinned host staging of the packed metadata
+  DevBuf h_meta, h_items, h_out, h_pix, h_theta;   // pinned host staging: packed metadata, a subsample's items,
+                                                   // results, pixels of host batches, estimates
 };
 
 namespace {
@@ -278,48 +284,112 @@ int check_theta(const double* th, int64_t s) {
   return CELESTE_OK;
 }
 
-// Host-side packed metadata; the arrays live in the context's pinned staging buffers (valid
-// until the context packs the next batch).
-// Host storage of the packed metadata from the process heap (the no-allocation entry point),
-// instead of the context's pinned buffers.
-struct HostPack {
-  std::vector<ImgDev> imgs;
-  std::vector<WorkItem> items;
-  std::vector<SrcDev> srcs;
-};
+size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
+// Host-side packed metadata: one block [images | sources | work items | 4 zeros (the check's flags)], uploaded
+// as it is.  It lives in the context's pinned staging buffer (valid until the context packs the next
+// batch), or, for the no-allocation entry point, on the process heap.
 struct Packed {
   ImgDev* imgs = nullptr;
-  WorkItem* items = nullptr;
   SrcDev* srcs = nullptr;
+  WorkItem* items = nullptr;
+  unsigned char* block = nullptr;
+  size_t o_srcs = 0, o_items = 0, o_flag = 0, bytes = 0;   // parts of the block
+  bool own_items = false;                                  // the items lie outside it (a pixel subsample)
   PriorDev prior;
   ProfDev prof;
   int tstride = 0;
   int n_src = 0, n_img = 0, n_items = 0;
 };
+typedef std::vector<unsigned char> HostPack;
 
-// fn(begin, end) over [0, n) in contiguous slices on up to 16 host threads (serial when small).
-template <class F>
-void parallel_for(int64_t n, F fn) {
-  const int64_t per_thread_min = 8192;
-  int nt = (int)std::min<int64_t>(16, std::max<int64_t>(1, n / per_thread_min));
-  nt = std::min<int>(nt, std::max(1u, std::thread::hardware_concurrency()));
-  if (nt <= 1) {
-    fn((int64_t)0, n);
-    return;
+// Host threads of one pass over a batch: fn(t, n, barrier) on n threads, the calling one among them.  A pass
+// costs about 50 ns an item and a thread about 10 us to start, so a thread is taken for every 2,048 items,
+// up to 16 (20,000 images packed: 10 threads; with one per 8,192, two).  Where a thread
+// cannot be started the pass runs on those that were.
+class Barrier {
+ public:
+  void wait() {
+    const int g = gen_.load(std::memory_order_acquire);
+    if (in_.fetch_add(1, std::memory_order_acq_rel) + 1 == total_) {
+      in_.store(0, std::memory_order_relaxed);
+      gen_.fetch_add(1, std::memory_order_release);
+    } else {
+      while (gen_.load(std::memory_order_acquire) == g) std::this_thread::yield();
+    }
   }
+  void set(int n) { total_ = n; }
+
+ private:
+  int total_ = 1;
+  std::atomic<int> in_{0}, gen_{0};
+};
+
+int team_size(int64_t n) {
+  const int nt = (int)std::min<int64_t>(16, std::max<int64_t>(1, n / 2048));
+  return std::min<int>(nt, std::max(1u, std::thread::hardware_concurrency()));
+}
+
+template <class F>
+void team(int nt, F fn) {
+  Barrier bar;
+  std::atomic<int> go{0};   // the number of threads, once all have been started
   std::vector<std::thread> th;
-  for (int t = 0; t < nt; ++t) th.emplace_back(fn, n * t / nt, n * (t + 1) / nt);
+  th.reserve(nt);
+  for (int t = 1; t < nt; ++t) {
+    try {
+      th.emplace_back([&, t] {
+        int n;
+        while ((n = go.load(std::memory_order_acquire)) == 0) std::this_thread::yield();
+        fn(t, n, bar);
+      });
+    } catch (const std::system_error&) {
+      break;
+    }
+  }
+  const int n = (int)th.size() + 1;
+  bar.set(n);
+  go.store(n, std::memory_order_release);
+  fn(0, n, bar);
   for (auto& x : th) x.join();
 }
 
+// The first index of [0, n) for which ok(i) is false, or n.
+template <class F>
+int64_t first_failure(int64_t n, F ok) {
+  std::atomic<int64_t> bad{n};
+  team(team_size(n), [&](int t, int nt, Barrier&) {
+    for (int64_t i = n * t / nt; i < n * (t + 1) / nt; ++i)
+      if (!ok(i)) {
+        int64_t cur = bad.load();
+        while (i < cur && !bad.compare_exchange_weak(cur, i)) {
+        }
+        break;
+      }
+  });
+  return bad.load();
+}
+
+int check_thetas(const double* th, int64_t n) {
+  const int64_t bad = first_failure(n, [&](int64_t s) { return check_theta(th + s * NP, s) == CELESTE_OK; });
+  return bad < n ? check_theta(th + bad * NP, bad) : CELESTE_OK;
+}
+
+// Rows of a work item: whole 8-row tile rows holding about `chunk` pixels.
+int band_rows(const celeste_image& im, int chunk) { return std::max(TILE, (chunk / std::max(1, im.w)) / TILE * TILE); }
 int items_of(const celeste_image& im, int chunk) {
-  // bands of whole 8-row tile rows holding about `chunk` pixels
-  const int band = std::max(TILE, (chunk / std::max(1, im.w)) / TILE * TILE);
+  const int band = band_rows(im, chunk);
   return (im.h + band - 1) / band;
 }
 
-int validate_and_pack(celeste_ctx* ctx, const celeste_batch* b, Packed* P, HostPack* hp = nullptr) {
+// What validate_and_pack leaves: everything, all but the work items (a subsample builds its own, calls that
+// evaluate no pixels read none), or nothing but the checks and counts.
+enum class Pack { kAll, kNoItems, kCheck };
+
+// Checks the batch and packs its metadata in one pass of the host threads, each over whole sources: checks and
+// counts, then (the block allocated) the records.
+int validate_and_pack(celeste_ctx* ctx, const celeste_batch* b, Packed* P, HostPack* hp = nullptr,
+                      Pack what = Pack::kAll) {
   if (!ctx) return fail(CELESTE_E_INVALID, "context is NULL");
   if (!b) return fail(CELESTE_E_INVALID, "batch is NULL");
   if (b->n_sources < 1) return fail(CELESTE_E_INVALID, "n_sources must be >= 1");
@@ -337,100 +407,111 @@ int validate_and_pack(celeste_ctx* ctx, const celeste_batch* b, Packed* P, HostP
   if (n_img > (int64_t)1 << 30) return fail(CELESTE_E_INVALID, "too many images");
   CHK(make_prior(b->prior, &P->prior));
   CHK(make_profiles(b->profiles, &P->prof));
-  // image checks in parallel; the message comes from re-checking the first bad image here
-  const int nslot = 16;
-  std::vector<int64_t> first_bad(nslot, INT64_MAX);
-  std::vector<int> slot_psf(nslot, 1);
-  {
-    parallel_for(n_img, [&](int64_t i0, int64_t i1) {
-      const int slot = (int)((i0 * nslot) / std::max<int64_t>(1, n_img));
-      int64_t bad = INT64_MAX;
-      int mp = 1;
-      for (int64_t i = i0; i < i1; ++i) {
-        if (check_image(b->images[i], i) != CELESTE_OK) {
-          bad = i;
-          break;
-        }
-        mp = std::max(mp, b->images[i].n_psf);
-      }
-      first_bad[slot] = std::min(first_bad[slot], bad);
-      slot_psf[slot] = std::max(slot_psf[slot], mp);
-    });
-  }
-  const int64_t bad = *std::min_element(first_bad.begin(), first_bad.end());
-  if (bad != INT64_MAX) return check_image(b->images[bad], bad);
-  const int max_psf = *std::max_element(slot_psf.begin(), slot_psf.end());
-  P->tstride = table_stride(max_psf, P->prof.n_exp, P->prof.n_dev);
-  P->n_src = b->n_sources;
-  P->n_img = (int)n_img;
-  if (hp) {
-    hp->imgs.resize((size_t)n_img);
-    hp->srcs.resize((size_t)b->n_sources);
-    P->imgs = hp->imgs.data();
-    P->srcs = hp->srcs.data();
-  } else {
-    CHK(ensure_host(ctx->h_imgs, sizeof(ImgDev) * n_img));
-    CHK(ensure_host(ctx->h_srcs, sizeof(SrcDev) * b->n_sources));
-    P->imgs = as<ImgDev>(ctx->h_imgs);
-    P->srcs = as<SrcDev>(ctx->h_srcs);
-  }
   const int chunk = std::max(64, ctx->chunk_px);
-  // work-item offsets per image (items in image order, so per source contiguous)
-  std::vector<int64_t> first_item(n_img + 1, 0);
-  for (int64_t i = 0; i < n_img; ++i) first_item[i + 1] = first_item[i] + items_of(b->images[i], chunk);
-  if (first_item[n_img] > (int64_t)INT32_MAX / 2) return fail(CELESTE_E_INVALID, "too many work items");
-  if (hp) {
-    hp->items.resize((size_t)first_item[n_img]);
-    P->items = hp->items.data();
-  } else {
-    CHK(ensure_host(ctx->h_items, sizeof(WorkItem) * first_item[n_img]));
-    P->items = as<WorkItem>(ctx->h_items);
-  }
-  std::vector<int> src_of(n_img);
-  for (int s = 0; s < b->n_sources; ++s)
-    for (int64_t i = b->image_offsets[s]; i < b->image_offsets[s + 1]; ++i) src_of[i] = s;
-  parallel_for(n_img, [&](int64_t i0, int64_t i1) {
-    for (int64_t i = i0; i < i1; ++i) {
-      const celeste_image& im = b->images[i];
-      const int s = src_of[i];
-      ImgDev& d = P->imgs[i];
-      std::memset(&d, 0, sizeof(d));
-      d.pix = im.pixels;
-      d.nbr_mean = im.nbr_mean;
-      d.nbr_var = im.nbr_var;
-      d.h = im.h;
-      d.w = im.w;
-      d.pitch = im.pitch;
-      d.nbr_pitch = im.nbr_pitch ? im.nbr_pitch : im.pitch;
-      d.band = im.band;
-      d.n_psf = im.n_psf;
-      d.src = s;
-      d.origin[0] = im.origin[0];
-      d.origin[1] = im.origin[1];
-      for (int k = 0; k < 6; ++k) d.wcs[k] = im.wcs[k];
-      d.sky = im.sky;
-      d.calib = im.calib;
-      for (int k = 0; k < CELESTE_MAX_PSF; ++k)
-        for (int j = 0; j < 6; ++j) d.psf[k][j] = k < im.n_psf ? im.psf[k][j] : 0.0;
-      d.item_begin = (int)first_item[i];
-      d.item_end = (int)first_item[i + 1];
-      const int band = std::max(TILE, (chunk / std::max(1, im.w)) / TILE * TILE);
-      int64_t it = first_item[i];
-      for (int r = 0; r < im.h; r += band) P->items[it++] = WorkItem{(int)i, s, r, std::min(im.h, r + band)};
+  const int S = b->n_sources;
+  P->n_src = S;
+  P->n_img = (int)n_img;
+  struct Slice {
+    int64_t bad = INT64_MAX, items = 0;
+    int max_psf = 1;
+  };
+  Slice sl[16];
+  int rc = CELESTE_OK;
+  int64_t bad = INT64_MAX, n_items = 0;
+  team(team_size(n_img), [&](int t, int nt, Barrier& bar) {
+    // sources whose first image lies in this thread's share of the images
+    const auto first_src = [&](int k) {
+      return k == nt ? S : (int)(std::lower_bound(b->image_offsets, b->image_offsets + S, n_img * k / nt) - b->image_offsets);
+    };
+    const int s0 = first_src(t), s1 = first_src(t + 1);
+    Slice me;
+    for (int64_t i = b->image_offsets[s0]; i < b->image_offsets[s1]; ++i) {
+      if (check_image(b->images[i], i) != CELESTE_OK) {
+        me.bad = i;
+        break;
+      }
+      me.max_psf = std::max(me.max_psf, b->images[i].n_psf);
+      me.items += items_of(b->images[i], chunk);
+    }
+    sl[t] = me;
+    bar.wait();
+    if (t == 0) {
+      int max_psf = 1;
+      for (int k = 0; k < nt; ++k) {
+        bad = std::min(bad, sl[k].bad);
+        max_psf = std::max(max_psf, sl[k].max_psf);
+        n_items += sl[k].items;
+      }
+      if (bad == INT64_MAX && n_items > (int64_t)INT32_MAX / 2) rc = fail(CELESTE_E_INVALID, "too many work items");
+      P->tstride = table_stride(max_psf, P->prof.n_exp, P->prof.n_dev);
+      if (bad == INT64_MAX && rc == CELESTE_OK && what != Pack::kCheck) {
+        P->n_items = what == Pack::kAll ? (int)n_items : 0;
+        P->o_srcs = align256(sizeof(ImgDev) * n_img);
+        P->o_items = P->o_srcs + align256(sizeof(SrcDev) * S);
+        P->o_flag = P->o_items + align256(sizeof(WorkItem) * P->n_items);
+        P->bytes = P->o_flag + sizeof(int) * 4;
+        if (hp) {
+          try {
+            hp->resize(P->bytes);
+          } catch (const std::bad_alloc&) {
+            rc = fail(CELESTE_E_NOMEM, "host allocation of %zu bytes failed", P->bytes);
+          }
+          P->block = hp->data();
+        } else {
+          rc = ensure_host(ctx->h_meta, P->bytes);
+          P->block = as<unsigned char>(ctx->h_meta);
+        }
+        P->imgs = reinterpret_cast<ImgDev*>(P->block);
+        P->srcs = reinterpret_cast<SrcDev*>(P->block + P->o_srcs);
+        P->items = reinterpret_cast<WorkItem*>(P->block + P->o_items);
+        if (rc == CELESTE_OK) std::memset(P->block + P->o_flag, 0, sizeof(int) * 4);
+      }
+    }
+    bar.wait();
+    if (bad != INT64_MAX || rc != CELESTE_OK || what == Pack::kCheck) return;
+    int64_t it = 0;
+    for (int k = 0; k < t; ++k) it += sl[k].items;
+    for (int s = s0; s < s1; ++s) {
+      SrcDev sd;
+      sd.img_begin = (int)b->image_offsets[s];
+      sd.img_end = (int)b->image_offsets[s + 1];
+      sd.item_begin = what == Pack::kAll ? (int)it : 0;
+      sd.npix = 0;
+      for (int64_t i = sd.img_begin; i < sd.img_end; ++i) {
+        const celeste_image& im = b->images[i];
+        ImgDev& d = P->imgs[i];
+        std::memset(&d, 0, sizeof(d));
+        d.pix = im.pixels;
+        d.nbr_mean = im.nbr_mean;
+        d.nbr_var = im.nbr_var;
+        d.h = im.h;
+        d.w = im.w;
+        d.pitch = im.pitch;
+        d.nbr_pitch = im.nbr_pitch ? im.nbr_pitch : im.pitch;
+        d.band = im.band;
+        d.n_psf = im.n_psf;
+        d.src = s;
+        d.origin[0] = im.origin[0];
+        d.origin[1] = im.origin[1];
+        for (int k = 0; k < 6; ++k) d.wcs[k] = im.wcs[k];
+        d.sky = im.sky;
+        d.calib = im.calib;
+        for (int k = 0; k < im.n_psf; ++k)
+          for (int j = 0; j < 6; ++j) d.psf[k][j] = im.psf[k][j];
+        sd.npix += (int64_t)im.h * im.w;
+        if (what == Pack::kAll) {
+          d.item_begin = (int)it;
+          const int band = band_rows(im, chunk);
+          for (int r = 0; r < im.h; r += band) P->items[it++] = WorkItem{(int)i, s, r, std::min(im.h, r + band)};
+          d.item_end = (int)it;
+        }
+      }
+      sd.item_end = what == Pack::kAll ? (int)it : 0;
+      P->srcs[s] = sd;
     }
   });
-  for (int s = 0; s < b->n_sources; ++s) {
-    SrcDev sd;
-    sd.img_begin = (int)b->image_offsets[s];
-    sd.img_end = (int)b->image_offsets[s + 1];
-    sd.item_begin = (int)first_item[sd.img_begin];
-    sd.item_end = (int)first_item[sd.img_end];
-    sd.npix = 0;
-    for (int64_t i = sd.img_begin; i < sd.img_end; ++i) sd.npix += (int64_t)b->images[i].h * b->images[i].w;
-    P->srcs[s] = sd;
-  }
-  P->n_items = (int)first_item[n_img];
-  return CELESTE_OK;
+  if (bad != INT64_MAX) return check_image(b->images[bad], bad);   // again, for its message
+  return rc;
 }
 
 // Pixel subsample: the work items are rebuilt over the kept 8-row blocks only.  kept_rows
@@ -441,79 +522,148 @@ int validate_and_pack(celeste_ctx* ctx, const celeste_batch* b, Packed* P, HostP
 int subsample_items(celeste_ctx* ctx, const celeste_batch* b, Packed* P, const uint8_t* keep,
                     const int64_t* keep_off, std::vector<int>& kept_rows) {
   if (keep_off[0] != 0) return fail(CELESTE_E_INVALID, "keep_off[0] must be 0");
-  for (int i = 0; i < P->n_img; ++i)
-    if (keep_off[i + 1] - keep_off[i] != (b->images[i].h + 7) / 8)
-      return fail(CELESTE_E_INVALID, "image %d: keep_off must give (h + 7) / 8 blocks", i);
-  const int chunk = std::max(64, ctx->chunk_px);
-  std::vector<WorkItem> items;
-  std::vector<int64_t> kept_px(P->n_img, 0);
-  kept_rows.clear();
-  for (int i = 0; i < P->n_img; ++i) {
-    const celeste_image& im = b->images[i];
-    const uint8_t* k = keep + keep_off[i];
-    const int nb = (im.h + 7) / 8;
-    const int per_item = std::max(TILE, (chunk / std::max(1, im.w)) / TILE * TILE) / TILE;   // blocks
-    ImgDev& d = P->imgs[i];
-    const size_t first = kept_rows.size();
-    for (int j = 0; j < nb; ++j)
-      if (k[j]) {
-        kept_rows.push_back(TILE * j);
-        kept_px[i] += (int64_t)(std::min(im.h, TILE * (j + 1)) - TILE * j) * im.w;
+  const int64_t off_bad = first_failure(
+      P->n_img, [&](int64_t i) { return keep_off[i + 1] - keep_off[i] == (b->images[i].h + 7) / 8; });
+  if (off_bad < P->n_img)
+    return fail(CELESTE_E_INVALID, "image %lld: keep_off must give (h + 7) / 8 blocks", (long long)off_bad);
+  const int chunk = std::max(64, ctx->chunk_px), S = P->n_src;
+  const int64_t n_img = P->n_img;
+  struct Slice {
+    int64_t rows = 0, items = 0;
+  };
+  Slice sl[16];
+  int rc = CELESTE_OK;
+  team(team_size(n_img), [&](int t, int nt, Barrier& bar) {
+    const auto first_src = [&](int k) {
+      return k == nt ? S : (int)(std::lower_bound(b->image_offsets, b->image_offsets + S, n_img * k / nt) - b->image_offsets);
+    };
+    const int s0 = first_src(t), s1 = first_src(t + 1);
+    const auto blocks_per_item = [&](const celeste_image& im) { return band_rows(im, chunk) / TILE; };
+    Slice me;
+    for (int64_t i = b->image_offsets[s0]; i < b->image_offsets[s1]; ++i) {
+      const uint8_t* k = keep + keep_off[i];
+      const int nb = (b->images[i].h + 7) / 8, per = blocks_per_item(b->images[i]);
+      int64_t n = 0;
+      for (int j = 0; j < nb; ++j) n += k[j] ? 1 : 0;
+      me.rows += n;
+      me.items += (n + per - 1) / per;
+    }
+    sl[t] = me;
+    bar.wait();
+    Slice base;
+    for (int k = 0; k < t; ++k) {
+      base.rows += sl[k].rows;
+      base.items += sl[k].items;
+    }
+    if (t == 0) {
+      Slice all;
+      for (int k = 0; k < nt; ++k) {
+        all.rows += sl[k].rows;
+        all.items += sl[k].items;
       }
-    if (kept_rows.size() > (size_t)INT32_MAX / 2) return fail(CELESTE_E_INVALID, "too many kept blocks");
-    d.item_begin = (int)items.size();
-    for (size_t e = first; e < kept_rows.size(); e += per_item)
-      items.push_back(WorkItem{i, d.src, (int)e, (int)std::min(kept_rows.size(), e + per_item)});
-    if (items.size() > (size_t)INT32_MAX / 2) return fail(CELESTE_E_INVALID, "too many work items");
-    d.item_end = (int)items.size();
-  }
-  CHK(ensure_host(ctx->h_items, sizeof(WorkItem) * std::max<size_t>(1, items.size())));
-  P->items = as<WorkItem>(ctx->h_items);
-  if (!items.empty()) std::memcpy(P->items, items.data(), sizeof(WorkItem) * items.size());
-  for (int s = 0; s < P->n_src; ++s) {
-    SrcDev& sd = P->srcs[s];
-    sd.item_begin = P->imgs[sd.img_begin].item_begin;
-    sd.item_end = P->imgs[sd.img_end - 1].item_end;
-    sd.npix = 0;
-    for (int i = sd.img_begin; i < sd.img_end; ++i) sd.npix += kept_px[i];
-  }
-  P->n_items = (int)items.size();
-  return CELESTE_OK;
+      if (all.rows > (int64_t)INT32_MAX / 2)
+        rc = fail(CELESTE_E_INVALID, "too many kept blocks");
+      else if (all.items > (int64_t)INT32_MAX / 2)
+        rc = fail(CELESTE_E_INVALID, "too many work items");
+      else
+        rc = ensure_host(ctx->h_items, sizeof(WorkItem) * std::max<int64_t>(1, all.items));
+      if (rc == CELESTE_OK) {
+        try {
+          kept_rows.resize((size_t)all.rows);
+        } catch (const std::bad_alloc&) {
+          rc = fail(CELESTE_E_NOMEM, "host allocation of the kept blocks failed");
+        }
+      }
+      P->items = as<WorkItem>(ctx->h_items);
+      P->own_items = true;
+      P->n_items = (int)all.items;
+    }
+    bar.wait();
+    if (rc != CELESTE_OK) return;
+    int64_t row = base.rows, it = base.items;
+    for (int s = s0; s < s1; ++s) {
+      SrcDev& sd = P->srcs[s];
+      sd.npix = 0;
+      sd.item_begin = (int)it;
+      for (int i = sd.img_begin; i < sd.img_end; ++i) {
+        const celeste_image& im = b->images[i];
+        const uint8_t* k = keep + keep_off[i];
+        const int nb = (im.h + 7) / 8, per = blocks_per_item(im);
+        ImgDev& d = P->imgs[i];
+        const int64_t first = row;
+        for (int j = 0; j < nb; ++j)
+          if (k[j]) {
+            kept_rows[row++] = TILE * j;
+            sd.npix += (int64_t)(std::min(im.h, TILE * (j + 1)) - TILE * j) * im.w;
+          }
+        d.item_begin = (int)it;
+        for (int64_t e = first; e < row; e += per)
+          P->items[it++] = WorkItem{i, d.src, (int)e, (int)std::min<int64_t>(row, e + per)};
+        d.item_end = (int)it;
+      }
+      sd.item_end = (int)it;
+    }
+  });
+  return rc;
 }
 
-// Copies host pixel arrays into one device staging buffer and repoints the images.
+// Copies host pixel arrays into one device staging buffer and repoints the images, through a pinned buffer
+// of at most PIX_STAGE bytes (a larger batch in as many turns).
+constexpr size_t PIX_STAGE = (size_t)64 << 20;
+
 int stage_host_pixels(celeste_ctx* ctx, const celeste_batch* b, Packed* P, hipStream_t st) {
+  // the arrays in their order, each as h rows of w pixels
+  struct Part {
+    const float* src;
+    size_t pitch, off;   // off: first pixel in the staging buffer
+    int h, w;
+  };
+  std::vector<Part> parts;
+  parts.reserve((size_t)P->n_img);
   size_t total = 0;
-  for (int i = 0; i < P->n_img; ++i) {
-    const celeste_image& im = b->images[i];
-    const size_t n = (size_t)im.h * im.w;
-    total += n * (1 + (im.nbr_mean ? 1 : 0) + (im.nbr_var ? 1 : 0));
-  }
-  std::vector<float> host(total);
-  size_t off = 0;
-  std::vector<size_t> offs(3 * P->n_img, (size_t)-1);
   for (int i = 0; i < P->n_img; ++i) {
     const celeste_image& im = b->images[i];
     const float* srcs[3] = {im.pixels, im.nbr_mean, im.nbr_var};
     for (int k = 0; k < 3; ++k) {
       if (!srcs[k]) continue;
-      offs[3 * i + k] = off;
-      const size_t rp = k == 0 ? (size_t)im.pitch : (size_t)(im.nbr_pitch ? im.nbr_pitch : im.pitch);
-      for (int r = 0; r < im.h; ++r) std::memcpy(&host[off + (size_t)r * im.w], srcs[k] + (size_t)r * rp, sizeof(float) * im.w);
-      off += (size_t)im.h * im.w;
+      parts.push_back(Part{srcs[k], k == 0 ? (size_t)im.pitch : (size_t)(im.nbr_pitch ? im.nbr_pitch : im.pitch), total,
+                           im.h, im.w});
+      total += (size_t)im.h * im.w;
     }
   }
   CHK(ensure(ctx->staging, total * sizeof(float)));
-  HIPCHK(hipMemcpyAsync(ctx->staging.p, host.data(), total * sizeof(float), hipMemcpyHostToDevice, st));
-  HIPCHK(hipStreamSynchronize(st));
   float* base = as<float>(ctx->staging);
+  const size_t cap = std::min(total, PIX_STAGE / sizeof(float));   // pixels per turn
+  CHK(ensure_host(ctx->h_pix, cap * sizeof(float)));
+  float* pin = as<float>(ctx->h_pix);
+  for (size_t p0 = 0; p0 < total; p0 += cap) {
+    const size_t p1 = std::min(total, p0 + cap);
+    if (p0 > 0) HIPCHK(hipStreamSynchronize(st));   // the pinned buffer is free again
+    team(team_size((int64_t)((p1 - p0) / 64)), [&](int t, int nt, Barrier&) {
+      const size_t a = p0 + (p1 - p0) * t / nt, e = p0 + (p1 - p0) * (t + 1) / nt;   // this thread's pixels
+      size_t k = std::upper_bound(parts.begin(), parts.end(), a, [](size_t v, const Part& p) { return v < p.off; }) -
+                 parts.begin() - 1;
+      for (size_t at = a; at < e; ++k) {
+        const Part& p = parts[k];
+        const size_t end = std::min(e, p.off + (size_t)p.h * p.w);
+        while (at < end) {
+          const size_t r = (at - p.off) / p.w, c = (at - p.off) - r * p.w, n = std::min(end - at, (size_t)p.w - c);
+          std::memcpy(pin + (at - p0), p.src + r * p.pitch + c, sizeof(float) * n);
+          at += n;
+        }
+      }
+    });
+    HIPCHK(hipMemcpyAsync(base + p0, pin, (p1 - p0) * sizeof(float), hipMemcpyHostToDevice, st));
+  }
+  size_t k = 0;
   for (int i = 0; i < P->n_img; ++i) {
+    const celeste_image& im = b->images[i];
     ImgDev& d = P->imgs[i];
     d.pitch = d.w;
     d.nbr_pitch = d.w;
-    d.pix = base + offs[3 * i];
-    d.nbr_mean = offs[3 * i + 1] != (size_t)-1 ? base + offs[3 * i + 1] : nullptr;
-    d.nbr_var = offs[3 * i + 2] != (size_t)-1 ? base + offs[3 * i + 2] : nullptr;
+    d.pix = base + parts[k++].off;
+    d.nbr_mean = im.nbr_mean ? base + parts[k++].off : nullptr;
+    d.nbr_var = im.nbr_var ? base + parts[k++].off : nullptr;
   }
   return CELESTE_OK;
 }
@@ -530,62 +680,68 @@ struct EvalBufs {
   int* flag = nullptr;
   double* lfact = nullptr;
   bool lfact_ready = false;   // the table holds its values (else it is filled before use)
+  // the parts of the metadata block, copied to base
+  void place(const Packed& P, unsigned char* base) {
+    imgs = reinterpret_cast<ImgDev*>(base);
+    srcs = reinterpret_cast<SrcDev*>(base + P.o_srcs);
+    items = reinterpret_cast<WorkItem*>(base + P.o_items);
+    flag = reinterpret_cast<int*>(base + P.o_flag);
+  }
 };
 
 // The context's own buffers, grown to the batch.
 int ctx_bufs(celeste_ctx* ctx, const Packed* P, EvalBufs* B) {
-  CHK(ensure(ctx->imgs, sizeof(ImgDev) * P->n_img));
-  CHK(ensure(ctx->items, sizeof(WorkItem) * P->n_items));
-  CHK(ensure(ctx->srcs, sizeof(SrcDev) * P->n_src));
+  CHK(ensure(ctx->meta, P->bytes));
+  if (P->own_items) CHK(ensure(ctx->items_kept, sizeof(WorkItem) * P->n_items));
   CHK(ensure(ctx->img_const, sizeof(double) * P->n_img));
   CHK(ensure(ctx->tables, sizeof(float) * (size_t)P->tstride * P->n_img));
   CHK(ensure(ctx->partials, sizeof(double) * (size_t)NACC * P->n_items));
-  CHK(ensure(ctx->flag, sizeof(int) * 4));
   if (!ctx->lfact_ready) CHK(ensure(ctx->lfact, sizeof(double) * LFACT_N));
-  B->imgs = as<ImgDev>(ctx->imgs);
-  B->items = as<WorkItem>(ctx->items);
-  B->srcs = as<SrcDev>(ctx->srcs);
+  B->place(*P, as<unsigned char>(ctx->meta));
+  if (P->own_items) B->items = as<WorkItem>(ctx->items_kept);
+  ctx->imgs.p = B->imgs;
+  ctx->srcs.p = B->srcs;
+  ctx->items.p = B->items;
+  ctx->flag.p = B->flag;
   B->img_const = as<double>(ctx->img_const);
   B->tables = as<float>(ctx->tables);
   B->partials = as<double>(ctx->partials);
-  B->flag = as<int>(ctx->flag);
   B->lfact = as<double>(ctx->lfact);
   B->lfact_ready = ctx->lfact_ready;
   return CELESTE_OK;
 }
 
-// Metadata upload + pixel validation + per-image constants (the last two only when the
-// call reads pixels) into the buffers B.  Synchronous.  Host batches are staged in the
-// context's staging buffer first.
-int prepare_in(celeste_ctx* ctx, const celeste_batch* b, Packed* P, EvalBufs* B, hipStream_t st, bool pixels) {
+// The metadata into the buffers B (host batches' pixels are staged first), and, where the call reads pixels, the
+// launch of their check and of the per-image constants.  Nothing here waits: B.flag tells once the stream has run
+// (FLAG_PIXELS, and FLAG_THETA where theta, device memory, is given to be checked).
+int upload_in(celeste_ctx* ctx, const celeste_batch* b, Packed* P, EvalBufs* B, hipStream_t st, bool pixels,
+              const double* theta = nullptr) {
   if (b->mem_kind == CELESTE_MEM_HOST) CHK(stage_host_pixels(ctx, b, P, st));
-  HIPCHK(hipMemcpyAsync(B->imgs, P->imgs, sizeof(ImgDev) * P->n_img, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(B->items, P->items, sizeof(WorkItem) * P->n_items, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(B->srcs, P->srcs, sizeof(SrcDev) * P->n_src, hipMemcpyHostToDevice, st));
-  if (!pixels) {
-    HIPCHK(hipStreamSynchronize(st));
-    return CELESTE_OK;
-  }
+  HIPCHK(hipMemcpyAsync(B->imgs, P->block, P->bytes, hipMemcpyHostToDevice, st));
+  if (P->own_items && P->n_items > 0)
+    HIPCHK(hipMemcpyAsync(B->items, P->items, sizeof(WorkItem) * P->n_items, hipMemcpyHostToDevice, st));
+  if (!pixels) return CELESTE_OK;
   if (!B->lfact_ready) {
     HIPCHK(launch_lfact(B->lfact, st));
-    B->lfact_ready = true;   // complete before first use: the check below synchronises the stream
+    B->lfact_ready = true;   // complete before first use, on this stream and, once the call has waited, on every other
   }
-  HIPCHK(launch_zero_int(B->flag, 4, st));
-  HIPCHK(launch_check_const(B->imgs, P->n_img, B->lfact, B->img_const, B->flag, st));
-  int bad = 0;
-  HIPCHK(hipMemcpyAsync(&bad, B->flag, sizeof(int), hipMemcpyDeviceToHost, st));
-  HIPCHK(hipStreamSynchronize(st));
-  if (bad) return fail(CELESTE_E_INVALID, "pixel or neighbour arrays hold negative or non-finite values");
+  HIPCHK(launch_check_const(B->imgs, P->n_img, B->lfact, B->img_const, B->flag, st, theta, theta ? P->n_src : 0));
   return CELESTE_OK;
 }
 
-// prepare_in on the context's own buffers.
+int pixel_error() { return fail(CELESTE_E_INVALID, "pixel or neighbour arrays hold negative or non-finite values"); }
+
+// upload_in on the context's own buffers; waits for the check of the pixels.
 int prepare(celeste_ctx* ctx, const celeste_batch* b, Packed* P, hipStream_t st, bool pixels = true) {
   EvalBufs B;
   CHK(ctx_bufs(ctx, P, &B));
-  const int rc = prepare_in(ctx, b, P, &B, st, pixels);
+  CHK(upload_in(ctx, b, P, &B, st, pixels));
+  if (!pixels) return CELESTE_OK;
+  int bad = 0;
+  HIPCHK(hipMemcpyAsync(&bad, B.flag, sizeof(int), hipMemcpyDeviceToHost, st));
+  HIPCHK(hipStreamSynchronize(st));
   ctx->lfact_ready = ctx->lfact_ready || B.lfact_ready;
-  return rc;
+  return bad ? pixel_error() : CELESTE_OK;
 }
 
 hipStream_t pick(celeste_ctx* ctx, void* stream) { return stream ? (hipStream_t)stream : ctx->stream; }
@@ -729,14 +885,14 @@ void celeste_ctx_destroy(celeste_ctx* c) {
   if (!c) return;
   (void)hipSetDevice(c->device);
   (void)hipStreamSynchronize(c->stream);
-  DevBuf* bufs[] = {&c->imgs, &c->items, &c->srcs, &c->tables, &c->partials, &c->img_const, &c->staging,
-                    &c->theta, &c->o_elbo, &c->o_grad, &c->o_hess, &c->flag, &c->st_buf, &c->ctr, &c->sur,
-                    &c->tile_off, &c->tile_img, &c->img_field, &c->nbr_off, &c->tables2, &c->fsky,
+  DevBuf* bufs[] = {&c->meta, &c->items_kept, &c->tables, &c->partials, &c->img_const, &c->staging,
+                    &c->theta, &c->o_elbo, &c->o_grad, &c->o_hess, &c->st_buf, &c->ctr, &c->sur,
+                    &c->tile_off, &c->img_field, &c->nbr_off, &c->tables2, &c->fsky,
                     &c->kept, &c->lr_in, &c->lr_cov, &c->lr_status, &c->lr_eval,
                     &c->lfact, &c->lb_buf, &c->imgs_s, &c->items_s, &c->srcs_s, &c->partials_s, &c->qbuf};
   for (DevBuf* b : bufs)
     if (b->p) (void)hipFree(b->p);
-  for (DevBuf* b : {&c->h_imgs, &c->h_items, &c->h_srcs})
+  for (DevBuf* b : {&c->h_meta, &c->h_items, &c->h_out, &c->h_pix, &c->h_theta})
     if (b->p) (void)hipHostFree(b->p);
   (void)hipStreamDestroy(c->stream);
   delete c;
@@ -913,6 +1069,7 @@ int celeste_lr_covariance(celeste_ctx* ctx, const celeste_batch* b, const double
 namespace {
 
 int scratch_bufs(celeste_ctx* ctx, const Packed* P, int per_item, EvalBufs* B);
+constexpr size_t OUT_STAGE = (size_t)16 << 20;
 void scratch_lfact_filled(int device);
 
 int eval_impl(celeste_ctx* ctx, const celeste_batch* b, const double* theta, double* elbo, double* grad,
@@ -920,26 +1077,32 @@ int eval_impl(celeste_ctx* ctx, const celeste_batch* b, const double* theta, dou
               bool noalloc) {
   Packed P;
   HostPack hp;
-  CHK(validate_and_pack(ctx, b, &P, noalloc ? &hp : nullptr));
+  CHK(validate_and_pack(ctx, b, &P, noalloc ? &hp : nullptr, keep ? Pack::kNoItems : Pack::kAll));
   if (!theta || !elbo) return fail(CELESTE_E_INVALID, "theta and elbo must not be NULL");
   if (hess && !grad) return fail(CELESTE_E_INVALID, "hess requires grad");
-  if (noalloc && b->mem_kind != CELESTE_MEM_DEVICE)
+  const bool on_host = b->mem_kind == CELESTE_MEM_HOST;
+  if (noalloc && on_host)
     return fail(CELESTE_E_INVALID, "the no-allocation evaluation takes device batches only (mem_kind DEVICE)");
   HIPCHK(hipSetDevice(ctx->device));
   const hipStream_t st = pick(ctx, stream);
   const size_t S = P.n_src;
-  std::vector<double> th_host;
+  // The checks of pixels and of estimates on the device run in the same stream as the evaluation, whose reductions
+  // write nothing once one has failed; one wait at the end tells (with a wait after each check, one source's
+  // evaluation took 154 us instead of 115).  A subsample's list is checked on the host
+  // after the estimates, so there they are read back first.
   const double* th_dev = theta;
-  if (b->mem_kind == CELESTE_MEM_HOST) {
-    for (size_t s = 0; s < S; ++s) CHK(check_theta(theta + s * NP, (int64_t)s));
+  const bool check_on_device = !on_host && !keep;
+  std::vector<double> th_host;
+  if (on_host) {
+    CHK(check_thetas(theta, (int64_t)S));
     CHK(ensure(ctx->theta, sizeof(double) * NP * S));
     HIPCHK(hipMemcpyAsync(ctx->theta.p, theta, sizeof(double) * NP * S, hipMemcpyHostToDevice, st));
     th_dev = as<double>(ctx->theta);
-  } else {
+  } else if (keep) {
     th_host.resize(NP * S);
     HIPCHK(hipMemcpyAsync(th_host.data(), theta, sizeof(double) * NP * S, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    for (size_t s = 0; s < S; ++s) CHK(check_theta(th_host.data() + s * NP, (int64_t)s));
+    CHK(check_thetas(th_host.data(), (int64_t)S));
   }
   double px_weight = 1.0;
   std::vector<int> kept_rows;
@@ -948,71 +1111,87 @@ int eval_impl(celeste_ctx* ctx, const celeste_batch* b, const double* theta, dou
     px_weight = 1.0 / keep_prob;
   }
   EvalBufs B;
-  if (noalloc) {
+  if (noalloc)
     CHK(scratch_bufs(ctx, &P, grad ? (hess ? NACC : NGRAD) : 1, &B));
-    const int rc = prepare_in(ctx, b, &P, &B, st, true);
-    if (B.lfact_ready) scratch_lfact_filled(ctx->device);
-    CHK(rc);
-  } else {
+  else
     CHK(ctx_bufs(ctx, &P, &B));
-    const int rc = prepare_in(ctx, b, &P, &B, st, true);
-    ctx->lfact_ready = ctx->lfact_ready || B.lfact_ready;
-    CHK(rc);
-  }
   const int* kept = nullptr;
   if (keep) {
     CHK(ensure(ctx->kept, sizeof(int) * std::max<size_t>(1, kept_rows.size())));
-    if (!kept_rows.empty())
-      HIPCHK(hipMemcpyAsync(ctx->kept.p, kept_rows.data(), sizeof(int) * kept_rows.size(), hipMemcpyHostToDevice, st));
     kept = as<int>(ctx->kept);
   }
+  // results of a host batch: one device block, read back through pinned memory (of at most OUT_STAGE bytes)
+  const size_t n_out = S * (1 + (grad ? NP : 0) + (hess ? NP * NP : 0));
+  const bool pinned = on_host && n_out * sizeof(double) <= OUT_STAGE;
   double *d_elbo = elbo, *d_grad = grad, *d_hess = hess;
-  if (b->mem_kind == CELESTE_MEM_HOST) {
-    CHK(ensure(ctx->o_elbo, sizeof(double) * S));
+  if (on_host) {
+    CHK(ensure(ctx->o_elbo, sizeof(double) * n_out));
+    if (pinned) CHK(ensure_host(ctx->h_out, sizeof(double) * n_out));
     d_elbo = as<double>(ctx->o_elbo);
-    if (grad) {
-      CHK(ensure(ctx->o_grad, sizeof(double) * NP * S));
-      d_grad = as<double>(ctx->o_grad);
-    }
-    if (hess) {
-      CHK(ensure(ctx->o_hess, sizeof(double) * NP * NP * S));
-      d_hess = as<double>(ctx->o_hess);
-    }
+    if (grad) d_grad = d_elbo + S;
+    if (hess) d_hess = d_grad + S * NP;
   }
+  CHK(upload_in(ctx, b, &P, &B, st, true, check_on_device ? th_dev : nullptr));
+  if (!kept_rows.empty())
+    HIPCHK(hipMemcpyAsync(ctx->kept.p, kept_rows.data(), sizeof(int) * kept_rows.size(), hipMemcpyHostToDevice, st));
   PhaseTimer T;
   CHK(T.init(ctx->profile != 0 && !noalloc));   // events are not created on the no-allocation path
   T.mark(0, st);
   HIPCHK(launch_setup(B.imgs, P.n_img, th_dev, nullptr, P.prof, B.tables, P.tstride, st));
   T.mark(1, st);
+  int64_t* launches = nullptr;
   if (grad && hess) {
     HIPCHK(launch_eval_full(B.items, P.n_items, B.imgs, B.tables, P.tstride, P.prof.n_exp, P.prof.n_dev, nullptr,
                             B.partials, ctx->block, full_variant(ctx), ctx->tile_log2, ctx->e_zero, st, kept));
     T.mark(2, st);
     HIPCHK(launch_reduce_full(B.srcs, P.n_src, B.imgs, B.partials, B.img_const, th_dev, P.prior, nullptr, d_elbo,
-                              d_grad, d_hess, ctr_full(ctx), st, px_weight));
-    ctx->stats.full_launches += 1;
+                              d_grad, d_hess, ctr_full(ctx), st, px_weight, B.flag));
+    launches = &ctx->stats.full_launches;
   } else if (grad) {
     HIPCHK(launch_eval_grad(B.items, P.n_items, B.imgs, B.tables, P.tstride, P.prof.n_exp, P.prof.n_dev, nullptr,
                             B.partials, ctx->block, full_variant(ctx), ctx->tile_log2, ctx->e_zero, st, kept));
     T.mark(2, st);
     HIPCHK(launch_reduce_grad(B.srcs, P.n_src, B.imgs, B.partials, B.img_const, th_dev, P.prior, nullptr, d_elbo,
-                              d_grad, ctr_grad(ctx), st, px_weight));
-    ctx->stats.grad_launches += 1;
+                              d_grad, ctr_grad(ctx), st, px_weight, B.flag));
+    launches = &ctx->stats.grad_launches;
   } else {
     HIPCHK(launch_eval_value(B.items, P.n_items, B.imgs, B.tables, P.tstride, P.prof.n_exp, P.prof.n_dev, nullptr,
                              B.partials, ctx->vblock, ctx->variant, ctx->vtile_log2, ctx->e_zero, st, kept));
     T.mark(2, st);
     HIPCHK(launch_reduce_value(B.srcs, P.n_src, B.imgs, B.partials, B.img_const, th_dev, P.prior, nullptr, d_elbo,
-                               ctr_value(ctx), st, px_weight));
-    ctx->stats.value_launches += 1;
+                               ctr_value(ctx), st, px_weight, B.flag));
+    launches = &ctx->stats.value_launches;
   }
   T.mark(3, st);
-  if (b->mem_kind == CELESTE_MEM_HOST) {
+  int bad = 0;
+  HIPCHK(hipMemcpyAsync(&bad, B.flag, sizeof(int), hipMemcpyDeviceToHost, st));
+  if (pinned) HIPCHK(hipMemcpyAsync(ctx->h_out.p, d_elbo, sizeof(double) * n_out, hipMemcpyDeviceToHost, st));
+  HIPCHK(hipStreamSynchronize(st));
+  if (noalloc) {
+    if (B.lfact_ready) scratch_lfact_filled(ctx->device);
+  } else {
+    ctx->lfact_ready = ctx->lfact_ready || B.lfact_ready;
+  }
+  if (bad & FLAG_THETA) {   // read them back for the message
+    th_host.resize(NP * S);
+    HIPCHK(hipMemcpyAsync(th_host.data(), theta, sizeof(double) * NP * S, hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
+    CHK(check_thetas(th_host.data(), (int64_t)S));
+    return fail(CELESTE_E_INVALID, "theta out of range");
+  }
+  if (bad) return pixel_error();
+  *launches += 1;
+  if (pinned) {
+    const double* h = as<double>(ctx->h_out);
+    std::memcpy(elbo, h, sizeof(double) * S);
+    if (grad) std::memcpy(grad, h + S, sizeof(double) * S * NP);
+    if (hess) std::memcpy(hess, h + S + S * NP, sizeof(double) * S * NP * NP);
+  } else if (on_host) {
     HIPCHK(hipMemcpyAsync(elbo, d_elbo, sizeof(double) * S, hipMemcpyDeviceToHost, st));
     if (grad) HIPCHK(hipMemcpyAsync(grad, d_grad, sizeof(double) * NP * S, hipMemcpyDeviceToHost, st));
     if (hess) HIPCHK(hipMemcpyAsync(hess, d_hess, sizeof(double) * NP * NP * S, hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
   }
-  HIPCHK(hipStreamSynchronize(st));
   if (T.on) {
     ctx->stats.ms_setup += T.span(0, 1);
     (hess ? ctx->stats.ms_full : grad ? ctx->stats.ms_grad : ctx->stats.ms_value) += T.span(1, 2);
@@ -1057,8 +1236,6 @@ int scratch_init(int device) {
   return CELESTE_OK;
 }
 
-size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
-
 // The buffers of one evaluation carved from the device's scratch array: the log n! table
 // first (filled once per device, never written by anything else), then the call's own
 // regions.  E_NOMEM when the batch does not fit.
@@ -1078,10 +1255,7 @@ int scratch_bufs(celeste_ctx* ctx, const Packed* P, int per_item, EvalBufs* B) {
     return o;
   };
   const size_t o_lfact = carve(sizeof(double) * LFACT_N);
-  const size_t o_flag = carve(sizeof(int) * 4);
-  const size_t o_imgs = carve(sizeof(ImgDev) * P->n_img);
-  const size_t o_items = carve(sizeof(WorkItem) * P->n_items);
-  const size_t o_srcs = carve(sizeof(SrcDev) * P->n_src);
+  const size_t o_meta = carve(P->bytes);
   const size_t o_const = carve(sizeof(double) * P->n_img);
   const size_t o_tables = carve(sizeof(float) * (size_t)P->tstride * P->n_img);
   const size_t o_part = carve(sizeof(double) * (size_t)per_item * P->n_items);
@@ -1092,10 +1266,7 @@ int scratch_bufs(celeste_ctx* ctx, const Packed* P, int per_item, EvalBufs* B) {
                 P->n_src, P->n_img, P->n_items, off, (size_t)CELESTE_NOALLOC_SCRATCH_BYTES);
   unsigned char* base = sl.ptr;
   B->lfact = reinterpret_cast<double*>(base + o_lfact);
-  B->flag = reinterpret_cast<int*>(base + o_flag);
-  B->imgs = reinterpret_cast<ImgDev*>(base + o_imgs);
-  B->items = reinterpret_cast<WorkItem*>(base + o_items);
-  B->srcs = reinterpret_cast<SrcDev*>(base + o_srcs);
+  B->place(*P, base + o_meta);
   B->img_const = reinterpret_cast<double*>(base + o_const);
   B->tables = reinterpret_cast<float*>(base + o_tables);
   B->partials = reinterpret_cast<double*>(base + o_part);
@@ -1600,12 +1771,11 @@ int run_fit_sampled(celeste_ctx* ctx, const celeste_batch* b, double* theta_inou
   CHK(fit_begin(ctx, b, theta_inout, o->init_mode, fp, st, stage, &P, &F, &th));
   // the subsampled pack: the dense image records (pixels already staged) with work items over
   // the kept blocks only
-  HostPack hs;
-  hs.imgs.assign(P.imgs, P.imgs + P.n_img);
-  hs.srcs.assign(P.srcs, P.srcs + P.n_src);
+  std::vector<ImgDev> img_copy(P.imgs, P.imgs + P.n_img);
+  std::vector<SrcDev> src_copy(P.srcs, P.srcs + P.n_src);
   Packed Ps = P;
-  Ps.imgs = hs.imgs.data();
-  Ps.srcs = hs.srcs.data();
+  Ps.imgs = img_copy.data();
+  Ps.srcs = src_copy.data();
   std::vector<int> kept_rows;
   CHK(subsample_items(ctx, b, &Ps, keep, keep_off, kept_rows));
   CHK(ensure(ctx->imgs_s, sizeof(ImgDev) * Ps.n_img));
@@ -1883,7 +2053,7 @@ int celeste_ctx_set_surrogate(celeste_ctx* ctx, celeste_net* net) {
 
 int celeste_make_patches(celeste_ctx* ctx, const celeste_batch* b, const double* theta, void* out) {
   Packed P;
-  CHK(validate_and_pack(ctx, b, &P));
+  CHK(validate_and_pack(ctx, b, &P, nullptr, Pack::kNoItems));
   if (!theta || !out) return fail(CELESTE_E_INVALID, "theta and out must not be NULL");
   HIPCHK(hipSetDevice(ctx->device));
   const hipStream_t st = ctx->stream;
@@ -1975,58 +2145,133 @@ int source_boxes(const celeste_batch* b, std::vector<Box>* out) {
   return CELESTE_OK;
 }
 
-// No two images of the batch on the same field may overlap (single writer per field pixel).
-int check_disjoint(const celeste_batch* b, const celeste_fields* f) {
-  const int64_t n = b->image_offsets[b->n_sources];
-  std::unordered_map<int64_t, std::vector<int64_t>> grid;
-  for (int64_t i = 0; i < n; ++i) {
-    const celeste_image& a = b->images[i];
-    const int64_t ax = (int64_t)a.origin[0], ay = (int64_t)a.origin[1];
-    const int64_t fkey = (int64_t)f->img_field[i] << 40;
-    for (int64_t cy = ay / CELL; cy <= (ay + a.h - 1) / CELL; ++cy)
-      for (int64_t cx = ax / CELL; cx <= (ax + a.w - 1) / CELL; ++cx) {
-        auto& v = grid[fkey ^ (cx << 20) ^ cy];
-        for (int64_t j : v) {
-          const celeste_image& c = b->images[j];
-          const int64_t bx = (int64_t)c.origin[0], by = (int64_t)c.origin[1];
-          if (f->img_field[j] == f->img_field[i] && ax < bx + c.w && bx < ax + a.w && ay < by + c.h && by < ay + a.h)
-            return fail(CELESTE_E_INVALID, "images %lld and %lld overlap in field %d", (long long)j, (long long)i,
-                        f->img_field[i]);
+// An image's patch in its field.
+struct Patch {
+  int field, x, y, w, h;
+};
+
+// No two images of the batch on the same field may overlap (single writer per field pixel).  The fields are shared
+// out over host threads; each files its patches in a grid of CELL-sided cells, in image order, a chain per cell.
+int check_disjoint(const std::vector<Patch>& pt, int n_fields) {
+  const int64_t n = (int64_t)pt.size();
+  struct Hit {
+    int64_t i = INT64_MAX, j = 0;
+  };
+  Hit hit[16];
+  team(std::min(team_size(8 * n), n_fields), [&](int t, int nt, Barrier&) {
+    const int f0 = (int)((int64_t)n_fields * t / nt), f1 = (int)((int64_t)n_fields * (t + 1) / nt);
+    struct Node {
+      int img, next;
+    };
+    std::vector<Node> nodes;
+    std::unordered_map<int64_t, int> last;   // newest node of a cell
+    last.reserve((size_t)(4 * n / nt));
+    for (int64_t i = 0; i < n && hit[t].i == INT64_MAX; ++i) {
+      const Patch& a = pt[i];
+      if (a.field < f0 || a.field >= f1) continue;
+      const int64_t fkey = (int64_t)a.field << 40;
+      for (int64_t cy = a.y / CELL; cy <= (a.y + a.h - 1) / CELL; ++cy)
+        for (int64_t cx = a.x / CELL; cx <= (a.x + a.w - 1) / CELL && hit[t].i == INT64_MAX; ++cx) {
+          auto e = last.emplace(fkey ^ (cx << 20) ^ cy, -1).first;
+          for (int k = e->second; k >= 0; k = nodes[k].next) {   // newest first: the last match is the first image
+            const Patch& c = pt[nodes[k].img];
+            if (c.field == a.field && a.x < c.x + c.w && c.x < a.x + a.w && a.y < c.y + c.h && c.y < a.y + a.h)
+              hit[t] = Hit{i, nodes[k].img};
+          }
+          nodes.push_back(Node{(int)i, e->second});
+          e->second = (int)nodes.size() - 1;
         }
-        v.push_back(i);
-      }
-  }
+    }
+  });
+  const Hit* h = std::min_element(hit, hit + 16, [](const Hit& a, const Hit& b) { return a.i < b.i; });
+  if (h->i != INT64_MAX)
+    return fail(CELESTE_E_INVALID, "images %lld and %lld overlap in field %d", (long long)h->j, (long long)h->i,
+                pt[h->i].field);
   return CELESTE_OK;
 }
 
-int check_fields(const celeste_batch* b, const Packed& P, const celeste_fields* f) {
+int check_patch(const celeste_batch* b, const celeste_fields* f, int64_t i) {
+  const celeste_image& im = b->images[i];
+  const int fi = f->img_field[i];
+  if (fi < 0 || fi >= f->n_fields) return fail(CELESTE_E_INVALID, "image %lld: field index out of range", (long long)i);
+  const double ox = im.origin[0], oy = im.origin[1];
+  if (ox != std::floor(ox) || oy != std::floor(oy))
+    return fail(CELESTE_E_INVALID, "image %lld: origin not integer", (long long)i);
+  if (ox < 0 || oy < 0 || ox + im.w > f->width || oy + im.h > f->height)
+    return fail(CELESTE_E_INVALID, "image %lld: patch outside its field", (long long)i);
+  return CELESTE_OK;
+}
+
+// patches (may be null) receives where the images lie.
+int check_fields(const celeste_batch* b, const Packed& P, const celeste_fields* f, std::vector<Patch>* patches) {
   if (!f || !f->img_field || !f->mean || !f->var) return fail(CELESTE_E_INVALID, "fields and its arrays must not be NULL");
   if (b->mem_kind != CELESTE_MEM_DEVICE) return fail(CELESTE_E_INVALID, "crowded fields need CELESTE_MEM_DEVICE");
   if (f->n_fields < 1 || f->height < 1 || f->width < 1 || f->reserved != 0)
     return fail(CELESTE_E_INVALID, "bad field dimensions");
-  for (int i = 0; i < P.n_img; ++i) {
+  if (patches) patches->resize((size_t)P.n_img);
+  const int64_t bad = first_failure(P.n_img, [&](int64_t i) {
+    if (check_patch(b, f, i) != CELESTE_OK) return false;
     const celeste_image& im = b->images[i];
-    const int fi = f->img_field[i];
-    if (fi < 0 || fi >= f->n_fields) return fail(CELESTE_E_INVALID, "image %d: field index out of range", i);
-    const double ox = im.origin[0], oy = im.origin[1];
-    if (ox != std::floor(ox) || oy != std::floor(oy)) return fail(CELESTE_E_INVALID, "image %d: origin not integer", i);
-    if (ox < 0 || oy < 0 || ox + im.w > f->width || oy + im.h > f->height)
-      return fail(CELESTE_E_INVALID, "image %d: patch outside its field", i);
-  }
-  return CELESTE_OK;
+    if (patches) (*patches)[i] = Patch{f->img_field[i], (int)im.origin[0], (int)im.origin[1], im.w, im.h};
+    return true;
+  });
+  return bad < P.n_img ? check_patch(b, f, bad) : CELESTE_OK;
 }
 
-int upload_theta(celeste_ctx* ctx, const celeste_batch* b, const Packed& P, const double* theta, const double** out,
-                 hipStream_t st) {
+// Device memory estimates, read back and checked.
+int check_device_theta(celeste_ctx* ctx, const Packed& P, const double* theta, hipStream_t st) {
   if (!theta) return fail(CELESTE_E_INVALID, "theta is NULL");
-  std::vector<double> h(NP * (size_t)P.n_src);
-  HIPCHK(hipMemcpyAsync(h.data(), theta, sizeof(double) * h.size(), hipMemcpyDeviceToHost, st));
+  const size_t bytes = sizeof(double) * NP * (size_t)P.n_src;
+  CHK(ensure_host(ctx->h_theta, bytes));
+  HIPCHK(hipMemcpyAsync(ctx->h_theta.p, theta, bytes, hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
-  for (int s = 0; s < P.n_src; ++s) CHK(check_theta(h.data() + (size_t)s * NP, s));
-  *out = theta;
-  (void)ctx;
-  (void)b;
-  return CELESTE_OK;
+  return check_thetas(as<double>(ctx->h_theta), P.n_src);
+}
+
+// The images whose patch meets each RT x RT tile of the fields, in image order: offsets (n_tiles + 1) and, behind
+// them, the lists, in the context's pinned buffer.  The fields are shared out over host threads.
+constexpr int RT = 32;
+int tile_lists(celeste_ctx* ctx, const std::vector<Patch>& pt, int n_fields, int tx, int tpf, int64_t* n_ints) {
+  const int64_t n = (int64_t)pt.size();
+  const int n_tiles = tpf * n_fields;
+  std::vector<int> pos((size_t)n_tiles, 0);   // counts, then the next place of each tile
+  int* out = nullptr;
+  int rc = CELESTE_OK;
+  team(std::min(team_size(8 * n), n_fields), [&](int t, int nt, Barrier& bar) {
+    const int f0 = (int)((int64_t)n_fields * t / nt), f1 = (int)((int64_t)n_fields * (t + 1) / nt);
+    const auto each = [&](auto fn) {
+      for (int64_t i = 0; i < n; ++i) {
+        const Patch& p = pt[i];
+        if (p.field < f0 || p.field >= f1) continue;
+        for (int yy = p.y / RT; yy <= (p.y + p.h - 1) / RT; ++yy)
+          for (int xx = p.x / RT; xx <= (p.x + p.w - 1) / RT; ++xx) fn(p.field * tpf + yy * tx + xx, (int)i);
+      }
+    };
+    each([&](int tile, int) { pos[tile] += 1; });
+    bar.wait();
+    if (t == 0) {
+      int64_t total = 0;
+      for (int k = 0; k < n_tiles; ++k) total += pos[k];
+      if (total > INT32_MAX)
+        rc = fail(CELESTE_E_INVALID, "too many patch tiles");
+      else
+        rc = ensure_host(ctx->h_out, sizeof(int) * (size_t)(n_tiles + 1 + total));
+      if (rc == CELESTE_OK) {
+        out = as<int>(ctx->h_out);
+        int at = 0;
+        for (int k = 0; k < n_tiles; ++k) {
+          out[k] = at;
+          at += pos[k];
+          pos[k] = out[k];
+        }
+        out[n_tiles] = at;
+        *n_ints = n_tiles + 1 + total;
+      }
+    }
+    bar.wait();
+    if (rc == CELESTE_OK) each([&](int tile, int i) { out[n_tiles + 1 + pos[tile]++] = i; });
+  });
+  return rc;
 }
 
 }  // namespace
@@ -2035,44 +2280,29 @@ extern "C" {
 
 int celeste_render_fields(celeste_ctx* ctx, const celeste_batch* b, const double* theta, const celeste_fields* f) {
   Packed P;
-  CHK(validate_and_pack(ctx, b, &P));
-  CHK(check_fields(b, P, f));
+  std::vector<Patch> patches;
+  CHK(validate_and_pack(ctx, b, &P, nullptr, Pack::kNoItems));
+  CHK(check_fields(b, P, f, &patches));
   HIPCHK(hipSetDevice(ctx->device));
   const hipStream_t st = ctx->stream;
-  const double* th = nullptr;
-  CHK(upload_theta(ctx, b, P, theta, &th, st));
+  CHK(check_device_theta(ctx, P, theta, st));
+  const int tx = (f->width + RT - 1) / RT, ty = (f->height + RT - 1) / RT;
+  const int64_t n_tiles64 = (int64_t)tx * ty * f->n_fields;
+  if ((int64_t)tx * ty > INT32_MAX || n_tiles64 > INT32_MAX / 2) return fail(CELESTE_E_INVALID, "too many tiles");
+  const int n_tiles = (int)n_tiles64, tpf = tx * ty;
+  // the metadata and the setup tables are under way while the lists are formed
   CHK(prepare(ctx, b, &P, st, false));
-  // tile -> images index (counting sort, images in source order within a tile)
-  const int tx = (f->width + 31) / 32, ty = (f->height + 31) / 32;
-  const int tpf = tx * ty;
-  const int64_t n_tiles64 = (int64_t)tpf * f->n_fields;
-  if (n_tiles64 > INT32_MAX / 2) return fail(CELESTE_E_INVALID, "too many tiles");
-  const int n_tiles = (int)n_tiles64;
-  std::vector<int> cnt(n_tiles + 1, 0);
-  for (int i = 0; i < P.n_img; ++i) {
-    const celeste_image& im = b->images[i];
-    const int c0 = (int)im.origin[0], r0 = (int)im.origin[1];
-    const int base = f->img_field[i] * tpf;
-    for (int yy = r0 / 32; yy <= (r0 + im.h - 1) / 32; ++yy)
-      for (int xx = c0 / 32; xx <= (c0 + im.w - 1) / 32; ++xx) cnt[base + yy * tx + xx + 1] += 1;
+  HIPCHK(launch_setup(as<ImgDev>(ctx->imgs), P.n_img, theta, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st));
+  int64_t n_ints = 0;
+  int rc = tile_lists(ctx, patches, f->n_fields, tx, tpf, &n_ints);
+  if (rc == CELESTE_OK) rc = ensure(ctx->tile_off, sizeof(int) * (size_t)n_ints);
+  if (rc != CELESTE_OK) {
+    (void)hipStreamSynchronize(st);   // the pinned metadata is free again
+    return rc;
   }
-  for (int t = 0; t < n_tiles; ++t) cnt[t + 1] += cnt[t];
-  std::vector<int> pos(cnt.begin(), cnt.end() - 1), lst((size_t)cnt[n_tiles]);
-  for (int i = 0; i < P.n_img; ++i) {
-    const celeste_image& im = b->images[i];
-    const int c0 = (int)im.origin[0], r0 = (int)im.origin[1];
-    const int base = f->img_field[i] * tpf;
-    for (int yy = r0 / 32; yy <= (r0 + im.h - 1) / 32; ++yy)
-      for (int xx = c0 / 32; xx <= (c0 + im.w - 1) / 32; ++xx) lst[pos[base + yy * tx + xx]++] = i;
-  }
-  CHK(ensure(ctx->tile_off, sizeof(int) * cnt.size()));
-  CHK(ensure(ctx->tile_img, sizeof(int) * std::max<size_t>(1, lst.size())));
-  HIPCHK(hipMemcpyAsync(ctx->tile_off.p, cnt.data(), sizeof(int) * cnt.size(), hipMemcpyHostToDevice, st));
-  if (!lst.empty())
-    HIPCHK(hipMemcpyAsync(ctx->tile_img.p, lst.data(), sizeof(int) * lst.size(), hipMemcpyHostToDevice, st));
-  const ImgDev* imgs = as<ImgDev>(ctx->imgs);
-  HIPCHK(launch_setup(imgs, P.n_img, th, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st));
-  HIPCHK(launch_render(as<int>(ctx->tile_off), as<int>(ctx->tile_img), n_tiles, imgs, as<float>(ctx->tables),
+  int* off = as<int>(ctx->tile_off);
+  HIPCHK(hipMemcpyAsync(off, ctx->h_out.p, sizeof(int) * (size_t)n_ints, hipMemcpyHostToDevice, st));
+  HIPCHK(launch_render(off, off + n_tiles + 1, n_tiles, as<ImgDev>(ctx->imgs), as<float>(ctx->tables),
                        P.tstride, P.prof.n_exp, P.prof.n_dev, f->height, f->width, tx, tpf, ctx->e_zero, f->mean,
                        f->var, st));
   HIPCHK(hipStreamSynchronize(st));
@@ -2082,22 +2312,21 @@ int celeste_render_fields(celeste_ctx* ctx, const celeste_batch* b, const double
 int celeste_neighbour_arrays(celeste_ctx* ctx, const celeste_batch* b, const double* theta, const celeste_fields* f,
                              const int64_t* nbr_off, float* nbr_mean, float* nbr_var) {
   Packed P;
-  CHK(validate_and_pack(ctx, b, &P));
-  CHK(check_fields(b, P, f));
+  CHK(validate_and_pack(ctx, b, &P, nullptr, Pack::kNoItems));
+  CHK(check_fields(b, P, f, nullptr));
   if (!nbr_off || !nbr_mean || !nbr_var) return fail(CELESTE_E_INVALID, "neighbour arrays must not be NULL");
   for (int i = 0; i < P.n_img; ++i)
     if (nbr_off[i] < 0) return fail(CELESTE_E_INVALID, "negative neighbour offset");
   HIPCHK(hipSetDevice(ctx->device));
   const hipStream_t st = ctx->stream;
-  const double* th = nullptr;
-  CHK(upload_theta(ctx, b, P, theta, &th, st));
-  CHK(prepare(ctx, b, &P, st, false));
+  CHK(check_device_theta(ctx, P, theta, st));
   CHK(ensure(ctx->img_field, sizeof(int) * P.n_img));
   CHK(ensure(ctx->nbr_off, sizeof(long long) * P.n_img));
+  CHK(prepare(ctx, b, &P, st, false));
   HIPCHK(hipMemcpyAsync(ctx->img_field.p, f->img_field, sizeof(int) * P.n_img, hipMemcpyHostToDevice, st));
   HIPCHK(hipMemcpyAsync(ctx->nbr_off.p, nbr_off, sizeof(long long) * P.n_img, hipMemcpyHostToDevice, st));
   const ImgDev* imgs = as<ImgDev>(ctx->imgs);
-  HIPCHK(launch_setup(imgs, P.n_img, th, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st));
+  HIPCHK(launch_setup(imgs, P.n_img, theta, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st));
   HIPCHK(launch_neighbours(imgs, P.n_img, as<int>(ctx->img_field), as<float>(ctx->tables), P.tstride, P.prof.n_exp,
                            P.prof.n_dev, f->height, f->width, ctx->e_zero, f->mean, f->var,
                            as<long long>(ctx->nbr_off), nbr_mean, nbr_var, st));
@@ -2141,21 +2370,21 @@ int celeste_colour_sources(const celeste_batch* b, int32_t* colour, int32_t* n_c
 int celeste_update_fields(celeste_ctx* ctx, const celeste_batch* b, const double* theta_old, const double* theta_new,
                           const celeste_fields* f) {
   Packed P;
-  CHK(validate_and_pack(ctx, b, &P));
-  CHK(check_fields(b, P, f));
-  CHK(check_disjoint(b, f));
+  std::vector<Patch> patches;
+  CHK(validate_and_pack(ctx, b, &P, nullptr, Pack::kNoItems));
+  CHK(check_fields(b, P, f, &patches));
+  CHK(check_disjoint(patches, f->n_fields));
   HIPCHK(hipSetDevice(ctx->device));
   const hipStream_t st = ctx->stream;
-  const double *th_old = nullptr, *th_new = nullptr;
-  CHK(upload_theta(ctx, b, P, theta_old, &th_old, st));
-  CHK(upload_theta(ctx, b, P, theta_new, &th_new, st));
-  CHK(prepare(ctx, b, &P, st, false));
+  CHK(check_device_theta(ctx, P, theta_old, st));
+  CHK(check_device_theta(ctx, P, theta_new, st));
   CHK(ensure(ctx->tables2, sizeof(float) * (size_t)P.tstride * P.n_img));
   CHK(ensure(ctx->img_field, sizeof(int) * P.n_img));
+  CHK(prepare(ctx, b, &P, st, false));
   HIPCHK(hipMemcpyAsync(ctx->img_field.p, f->img_field, sizeof(int) * P.n_img, hipMemcpyHostToDevice, st));
   const ImgDev* imgs = as<ImgDev>(ctx->imgs);
-  HIPCHK(launch_setup(imgs, P.n_img, th_old, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st));
-  HIPCHK(launch_setup(imgs, P.n_img, th_new, nullptr, P.prof, as<float>(ctx->tables2), P.tstride, st));
+  HIPCHK(launch_setup(imgs, P.n_img, theta_old, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st));
+  HIPCHK(launch_setup(imgs, P.n_img, theta_new, nullptr, P.prof, as<float>(ctx->tables2), P.tstride, st));
   HIPCHK(launch_update_fields(imgs, P.n_img, as<int>(ctx->img_field), as<float>(ctx->tables),
                               as<float>(ctx->tables2), P.tstride, P.prof.n_exp, P.prof.n_dev, f->height, f->width,
                               ctx->e_zero, f->mean, f->var, st));
@@ -2166,8 +2395,8 @@ int celeste_update_fields(celeste_ctx* ctx, const celeste_batch* b, const double
 int celeste_field_elbo(celeste_ctx* ctx, const celeste_batch* b, const double* theta, const celeste_fields* f,
                        const float* field_pixels, const double* field_sky, double* elbo_out) {
   Packed P;
-  CHK(validate_and_pack(ctx, b, &P));
-  CHK(check_fields(b, P, f));
+  CHK(validate_and_pack(ctx, b, &P, nullptr, Pack::kCheck));
+  CHK(check_fields(b, P, f, nullptr));
   if (!field_pixels || !field_sky || !elbo_out)
     return fail(CELESTE_E_INVALID, "field_pixels, field_sky and elbo_out must not be NULL");
   for (int k = 0; k < f->n_fields; ++k)
@@ -2175,8 +2404,7 @@ int celeste_field_elbo(celeste_ctx* ctx, const celeste_batch* b, const double* t
       return fail(CELESTE_E_INVALID, "field %d: sky must be finite and > 0", k);
   HIPCHK(hipSetDevice(ctx->device));
   const hipStream_t st = ctx->stream;
-  const double* th = nullptr;
-  CHK(upload_theta(ctx, b, P, theta, &th, st));
+  CHK(check_device_theta(ctx, P, theta, st));
   const int S = P.n_src;
   const int64_t n = (int64_t)f->n_fields * f->height * f->width;
   const int per_block = 8192;
@@ -2187,7 +2415,7 @@ int celeste_field_elbo(celeste_ctx* ctx, const celeste_batch* b, const double* t
   CHK(ensure(ctx->o_elbo, sizeof(double) * S));
   CHK(ensure(ctx->partials, sizeof(double) * (size_t)nb));
   HIPCHK(hipMemcpyAsync(ctx->fsky.p, field_sky, sizeof(double) * f->n_fields, hipMemcpyHostToDevice, st));
-  HIPCHK(launch_prior_term(th, S, P.prior, as<double>(ctx->o_elbo), st));
+  HIPCHK(launch_prior_term(theta, S, P.prior, as<double>(ctx->o_elbo), st));
   HIPCHK(launch_field_terms(field_pixels, f->mean, f->var, as<double>(ctx->fsky), f->height, f->width, f->n_fields,
                             per_block, nb, as<double>(ctx->partials), st));
   std::vector<double> pri(S), part(nb);

@@ -121,11 +121,13 @@ hipError_t launch_setup(const ImgDev* imgs, int n_img, const double* theta, cons
                         ProfDev prof, float* tables, int tstride, hipStream_t st);
 // log n! table for the theta-independent pixel constants (LFACT_N doubles), and the pass that
 // checks every pixel / neighbour value (bad |= 1 on a negative or non-finite one) and writes
-// each image's constant sum x log E_bg - E_bg - log x!.
+// each image's constant sum x log E_bg - E_bg - log x!.  With theta (n_src x NP, device memory) its rows are
+// checked too (bad |= 2 where one is not finite or out of range).
+constexpr int FLAG_PIXELS = 1, FLAG_THETA = 2;
 constexpr int LFACT_N = 1 << 16;
 hipError_t launch_lfact(double* table, hipStream_t st);
 hipError_t launch_check_const(const ImgDev* imgs, int n_img, const double* lfact, double* img_const, int* bad,
-                              hipStream_t st);
+                              hipStream_t st, const double* theta = nullptr, int n_src = 0);
 // tw_log2: log2 of the pixel-tile width (3..6; tiles hold 64 pixels).  kept: nullptr for
 // dense work items; for a pixel subsample, the first rows of the kept 8-row blocks, and each
 // item's [row_begin, row_end) indexes this list instead of rows.
@@ -160,16 +162,16 @@ hipError_t launch_eval_value(const WorkItem* items, int n_items, const ImgDev* i
 hipError_t launch_reduce_full(const SrcDev* srcs, int n_src, const ImgDev* imgs, const double* partials,
                               const double* img_const, const double* theta, PriorDev prior, const int* src_flag,
                               double* elbo, double* grad, double* hess, unsigned long long* px_ctr,
-                              hipStream_t st, double px_weight = 1.0);
+                              hipStream_t st, double px_weight = 1.0, const int* bad = nullptr);
 // Value and natural gradient per source from gradient partials (NGRAD per work item).
 hipError_t launch_reduce_grad(const SrcDev* srcs, int n_src, const ImgDev* imgs, const double* partials,
                               const double* img_const, const double* theta, PriorDev prior, const int* src_flag,
                               double* elbo, double* grad, unsigned long long* px_ctr, hipStream_t st,
-                              double px_weight = 1.0);
+                              double px_weight = 1.0, const int* bad = nullptr);
 hipError_t launch_reduce_value(const SrcDev* srcs, int n_src, const ImgDev* imgs, const double* partials,
                                const double* img_const, const double* theta, PriorDev prior, const int* src_flag,
                                double* elbo, unsigned long long* px_ctr, hipStream_t st,
-                               double px_weight = 1.0);
+                               double px_weight = 1.0, const int* bad = nullptr);
 
 hipError_t launch_render(const int* tile_off, const int* tile_img, int n_tiles, const ImgDev* imgs,
                          const float* tables, int tstride, int n_exp, int n_dev, int H, int W, int tiles_x,

@@ -155,7 +155,8 @@ __global__ __launch_bounds__(RB) void k_reduce_full(const SrcDev* __restrict__ s
                                                     const double* __restrict__ theta, PriorDev prior,
                                                     const int* __restrict__ src_flag, double* __restrict__ elbo,
                                                     double* __restrict__ grad, double* __restrict__ hess,
-                                                    unsigned long long* __restrict__ px_ctr, double px_weight) {
+                                                    unsigned long long* __restrict__ px_ctr, double px_weight,
+                                                    const int* __restrict__ bad) {
   __shared__ double tmp[NACC];
   __shared__ double grp[5][NACC];
   __shared__ double isum[ICH][NACC];
@@ -165,7 +166,7 @@ __global__ __launch_bounds__(RB) void k_reduce_full(const SrcDev* __restrict__ s
   __shared__ double vt;
   __shared__ KL kl;
   const int s = blockIdx.x;
-  if (src_flag && !src_flag[s]) return;
+  if ((src_flag && !src_flag[s]) || (bad && *bad)) return;
   const int t = threadIdx.x;
   const double* th = theta + (size_t)s * NP;
   for (int k = t; k < NP * NP; k += RB) Ht[k] = 0.0;
@@ -235,11 +236,11 @@ __global__ __launch_bounds__(64) void k_reduce_grad(const SrcDev* __restrict__ s
                                                     const double* __restrict__ theta, PriorDev prior,
                                                     const int* __restrict__ src_flag, double* __restrict__ elbo,
                                                     double* __restrict__ grad, unsigned long long* __restrict__ px_ctr,
-                                                    double px_weight) {
+                                                    double px_weight, const int* __restrict__ bad) {
   __shared__ double tmp[NGRAD];
   __shared__ KL kl;
   const int s = blockIdx.x;
-  if (src_flag && !src_flag[s]) return;
+  if ((src_flag && !src_flag[s]) || (bad && *bad)) return;
   const int t = threadIdx.x;
   const SrcDev sr = srcs[s];
   double gt = 0.0, vt = 0.0;
@@ -276,10 +277,11 @@ __global__ __launch_bounds__(64) void k_reduce_value_t(const SrcDev* __restrict_
                                                        const double* __restrict__ img_const,
                                                        const double* __restrict__ theta, PriorDev prior,
                                                        const int* __restrict__ src_flag, double* __restrict__ elbo,
-                                                       unsigned long long* __restrict__ px_ctr, double px_weight) {
+                                                       unsigned long long* __restrict__ px_ctr, double px_weight,
+                                                    const int* __restrict__ bad) {
   const int s = blockIdx.x * 64 + threadIdx.x;
   if (s >= n_src) return;
-  if (src_flag && !src_flag[s]) return;
+  if ((src_flag && !src_flag[s]) || (bad && *bad)) return;
   const SrcDev sr = srcs[s];
   double v = 0.0;
   for (int i = sr.img_begin; i < sr.img_end; ++i) {
@@ -315,29 +317,29 @@ hipError_t launch_prior_term(const double* theta, int n_src, PriorDev prior, dou
 hipError_t launch_reduce_full(const SrcDev* srcs, int n_src, const ImgDev* imgs, const double* partials,
                               const double* img_const, const double* theta, PriorDev prior, const int* src_flag,
                               double* elbo, double* grad, double* hess, unsigned long long* px_ctr,
-                              hipStream_t st, double px_weight) {
+                              hipStream_t st, double px_weight, const int* bad) {
   if (n_src <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_reduce_full, dim3(n_src), dim3(RB), 0, st, srcs, imgs, partials, img_const, theta, prior,
-                     src_flag, elbo, grad, hess, px_ctr, px_weight);
+                     src_flag, elbo, grad, hess, px_ctr, px_weight, bad);
   return hipGetLastError();
 }
 
 hipError_t launch_reduce_grad(const SrcDev* srcs, int n_src, const ImgDev* imgs, const double* partials,
                               const double* img_const, const double* theta, PriorDev prior, const int* src_flag,
                               double* elbo, double* grad, unsigned long long* px_ctr, hipStream_t st,
-                              double px_weight) {
+                              double px_weight, const int* bad) {
   if (n_src <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_reduce_grad, dim3(n_src), dim3(64), 0, st, srcs, imgs, partials, img_const, theta, prior,
-                     src_flag, elbo, grad, px_ctr, px_weight);
+                     src_flag, elbo, grad, px_ctr, px_weight, bad);
   return hipGetLastError();
 }
 
 hipError_t launch_reduce_value(const SrcDev* srcs, int n_src, const ImgDev* imgs, const double* partials,
                                const double* img_const, const double* theta, PriorDev prior, const int* src_flag,
-                               double* elbo, unsigned long long* px_ctr, hipStream_t st, double px_weight) {
+                               double* elbo, unsigned long long* px_ctr, hipStream_t st, double px_weight, const int* bad) {
   if (n_src <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_reduce_value_t, dim3((n_src + 63) / 64), dim3(64), 0, st, srcs, n_src, imgs, partials,
-                     img_const, theta, prior, src_flag, elbo, px_ctr, px_weight);
+                     img_const, theta, prior, src_flag, elbo, px_ctr, px_weight, bad);
   return hipGetLastError();
 }
 

@@ -241,6 +241,16 @@ __device__ __forceinline__ int table_index(float x) {
   return (float)n == x && (unsigned)n < (unsigned)LFACT_N ? n : -1;
 }
 
+// The host's conditions on a source's estimate (the C entry's check of theta).
+__device__ __forceinline__ bool theta_in_range(const double* __restrict__ th) {
+  bool ok = true;
+  for (int i = 0; i < NP; ++i) ok = ok && fabs(th[i]) < INFINITY;   // false for NaN
+  ok = ok && th[2] > 0.0 && th[2] < 1.0 && th[3] >= 0.0 && th[3] <= 1.0 && th[4] > 0.0 && th[4] <= 1.0 && th[6] > 0.0 &&
+       th[9] > 0.0 && th[10] > 0.0;
+  for (int i = 19; i < NP; ++i) ok = ok && th[i] > 0.0;
+  return ok;
+}
+
 // One pass over every pixel of an image (one block per image): flags any negative or
 // non-finite pixel / neighbour value, and sums the theta-independent part of the pixel term,
 // x log E_bg - E_bg - log x!, E_bg = sky + neighbour mean.  log x! of an integer count below
@@ -258,10 +268,16 @@ __device__ __forceinline__ int table_index(float x) {
 // pixels per thread in flight, a division each and lgamma in the loop; 310 us at the rate of a large
 // copy.  1.4e8 px with neighbour arrays: 507 us (1,580).
 __global__ __launch_bounds__(256, 8) void k_check_const(const ImgDev* __restrict__ imgs, const double* __restrict__ lfact,
-                                                     double* __restrict__ out, int* __restrict__ bad) {
+                                                     double* __restrict__ out, int* __restrict__ bad, int n_img,
+                                                     const double* __restrict__ theta, int n_src) {
   typedef float V4 __attribute__((ext_vector_type(4), aligned(4)));
   typedef const __attribute__((address_space(1))) V4* GlobalV4;
   __shared__ double sh[4];
+  if ((int)blockIdx.x >= n_img) {   // the blocks behind the images': 256 sources' estimates each
+    const int s = ((int)blockIdx.x - n_img) * 256 + threadIdx.x;
+    if (s < n_src && !theta_in_range(theta + (size_t)s * NP)) atomicOr(bad, FLAG_THETA);
+    return;
+  }
   const ImgDev& im = imgs[blockIdx.x];
   const int w = im.w, n = im.h * w, pitch = im.pitch, npitch = im.nbr_pitch;
   const GlobalF px = global(im.pix), ne = global(im.nbr_mean), nv = global(im.nbr_var);
@@ -387,7 +403,7 @@ __global__ __launch_bounds__(256, 8) void k_check_const(const ImgDev* __restrict
   }
   const double tot = block_sum<256>(acc, sh);
   if (t == 0) out[blockIdx.x] = one_sky ? tot - (double)n * sky : tot;
-  if (flag) atomicOr(bad, 1);
+  if (flag) atomicOr(bad, FLAG_PIXELS);
 }
 
 // Plain start: aperture flux (radius 3 px around the catalog position) in the
@@ -460,9 +476,10 @@ hipError_t launch_lfact(double* table, hipStream_t st) {
 }
 
 hipError_t launch_check_const(const ImgDev* imgs, int n_img, const double* lfact, double* img_const, int* bad,
-                              hipStream_t st) {
+                              hipStream_t st, const double* theta, int n_src) {
   if (n_img <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_check_const, dim3(n_img), dim3(256), 0, st, imgs, lfact, img_const, bad);
+  hipLaunchKernelGGL(k_check_const, dim3(n_img + (n_src + 255) / 256), dim3(256), 0, st, imgs, lfact, img_const, bad,
+                     n_img, theta, n_src);
   return hipGetLastError();
 }
 
