@@ -805,91 +805,85 @@ __global__ void k_zero(int* p, int n) {
 
 // ---------------------------------------------------------------- linear-response covariance
 // Sigma = D (-H_psi)^{-1} D at a fitted theta, H_psi = D H D + diag(D' g) in the fit's
-// unconstrained coordinates (D = d theta / d psi, diagonal), one wavefront per source, FP64:
-// Cholesky factor L of -H_psi in LDS (right-looking, one column per step, the trailing
-// update spread over the lanes), L^{-1} by forward substitution (one column per lane), and
-// Sigma_psi = L^{-T} L^{-1} summed in the same order for (a, b) and (b, a), so the result is
-// exactly symmetric.  status: 0, 1 when a pivot is not positive (-H_psi not positive
+// unconstrained coordinates (D = d theta / d psi, diagonal), one wavefront per source, FP64, a row (then a
+// column) per lane in registers: Cholesky factor L of -H_psi (right-looking), L^{-1} by forward
+// substitution, and Sigma_psi = L^{-T} L^{-1} summed in the same order for (a, b) and (b, a), so the
+// result is exactly symmetric.  status: 0, 1 when a pivot is not positive (-H_psi not positive
 // definite), 2 for a non-finite input; cov is NaN where status != 0.
-__global__ __launch_bounds__(64) void k_lr_cov(const double* __restrict__ theta, const double* __restrict__ u0s,
-                                               double u_box, const double* __restrict__ grad,
-                                               const double* __restrict__ hess, double* __restrict__ cov,
-                                               int* __restrict__ status) {
-  __shared__ double M[NP][NP + 1];
-  __shared__ double W[NP][NP + 1];
-  __shared__ double d1s[NP];
-  __shared__ int bad;
-  const int s = blockIdx.x, t = threadIdx.x;
-  const double* th = theta + (size_t)s * NP;
-  const double* g = grad + (size_t)s * NP;
+//
+// Bound by the chain of 27 pivots' square roots and divisions and by issue: every product's other factor is
+// another lane's, read into a scalar register (two lane reads an FP64 multiply-add), with no
+// barrier and no LDS access between.  5,000 sources: 65 us (169 us with the matrices in LDS, 729 entries
+// over the lanes for each column and a barrier after each part; the Hessians' and covariances' traffic: 12 us).
+__global__ __launch_bounds__(64, 4) void k_lr_cov(const double* __restrict__ theta, const double* __restrict__ u0s,
+                                                  double u_box, const double* __restrict__ grad,
+                                                  const double* __restrict__ hess, double* __restrict__ cov,
+                                                  int* __restrict__ status) {
+  __shared__ double buf[NP * NP];
+  const int s = blockIdx.x, t = threadIdx.x, row = min(t, NP - 1);   // the lanes past the last row repeat it
   const double* H = hess + (size_t)s * NP * NP;
-  if (t == 0) bad = 0;
+  double* out = cov + (size_t)s * NP * NP;
+  for (int k = t; k < NP * NP; k += 64) buf[k] = H[k];
+  bool finite_in;
+  double d1, d2g;
+  {
+    const double u0[2] = {u0s[2 * s], u0s[2 * s + 1]}, th = theta[(size_t)s * NP + row], g = grad[(size_t)s * NP + row];
+    const Box b = box_of(row, u0, u_box);
+    double d2;
+    to_theta1(to_psi1(th, b), b, &d1, &d2);
+    d2g = d2 * g;
+    finite_in = isfinite(th) && isfinite(g) && isfinite(u0[0]) && isfinite(u0[1]);
+  }
+  asm volatile("" : "+v"(d2g));   // rounded by itself, not fused with the subtraction below
   __syncthreads();
-  double d2g = 0.0;
-  if (t < NP) {
-    const double u0[2] = {u0s[2 * s], u0s[2 * s + 1]};
-    const Box b = box_of(t, u0, u_box);
-    double d1, d2;
-    to_theta1(to_psi1(th[t], b), b, &d1, &d2);
-    d1s[t] = d1;
-    d2g = d2 * g[t];
-    if (!isfinite(th[t]) || !isfinite(g[t]) || !isfinite(u0[0]) || !isfinite(u0[1])) atomicOr(&bad, 2);
+  double m[NP];
+#pragma unroll
+  for (int c = 0; c < NP; ++c) {
+    const double h = 0.5 * (buf[row * NP + c] + buf[c * NP + row]);
+    finite_in = finite_in && isfinite(h);
+    m[c] = -(d1 * h * lane_value(d1, c));
+    asm volatile("" : "+v"(m[c]));
+    if (c == row) m[c] -= d2g;
   }
   __syncthreads();
-  for (int k = t; k < NP * NP; k += 64) {
-    const int r = k / NP, c = k - r * NP;
-    const double h = 0.5 * (H[r * NP + c] + H[c * NP + r]);
-    if (!isfinite(h)) atomicOr(&bad, 2);
-    M[r][c] = -(d1s[r] * h * d1s[c]);
-  }
-  __syncthreads();
-  if (t < NP) M[t][t] -= d2g;
-  __syncthreads();
-  if (bad == 0) {
+  int bad = __ballot(!finite_in) ? 2 : 0;
+  if (!bad) {
+#pragma unroll
     for (int k = 0; k < NP; ++k) {
-      const double piv = M[k][k];
-      if (!(piv > 0.0) || !isfinite(piv)) {   // the same value on every lane: a uniform exit
-        if (t == 0) bad = 1;
+      const double piv = lane_value(m[k], k);
+      if (!(piv > 0.0) || !isfinite(piv)) {
+        bad = 1;
         break;
       }
       const double lkk = sqrt(piv);
-      __syncthreads();
-      if (t == k) M[k][k] = lkk;
-      if (t > k && t < NP) M[t][k] /= lkk;
-      __syncthreads();
-      for (int e = t; e < NP * NP; e += 64) {
-        const int i = e / NP, j = e - i * NP;
-        if (j > k && i >= j) M[i][j] -= M[i][k] * M[j][k];
-      }
-      __syncthreads();
+      m[k] = k == row ? lkk : m[k] / lkk;
+#pragma unroll
+      for (int j = k + 1; j < NP; ++j) m[j] = fma(-m[k], lane_value(m[k], j), m[j]);
     }
   }
-  __syncthreads();
-  double* out = cov + (size_t)s * NP * NP;
-  if (bad != 0) {
+  if (bad) {
     for (int k = t; k < NP * NP; k += 64) out[k] = __builtin_nan("");
     if (t == 0) status[s] = bad;
     return;
   }
-  if (t < NP) {
-    const int j = t;
-    for (int i = 0; i < NP; ++i) {
-      if (i < j) {
-        W[i][j] = 0.0;
-        continue;
-      }
-      double acc = i == j ? 1.0 : 0.0;
-      for (int k = j; k < i; ++k) acc -= M[i][k] * W[k][j];
-      W[i][j] = acc / M[i][i];
-    }
+  double w[NP];   // column `row` of L^{-1}; its entries above the diagonal come out as 0
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    double acc = i == row ? 1.0 : 0.0;
+#pragma unroll
+    for (int k = 0; k < i; ++k) acc = fma(-lane_value(m[k], i), w[k], acc);
+    w[i] = acc / lane_value(m[i], i);
+  }
+#pragma unroll
+  for (int b = 0; b < NP; ++b) {
+    double acc = 0.0;
+#pragma unroll
+    for (int k = b; k < NP; ++k) acc = fma(w[k], lane_value(w[k], b), acc);
+    const double v = acc * (d1 * lane_value(d1, b));   // the same rounding for (a, b) and (b, a)
+    if (t < NP) buf[t * NP + b] = v;
   }
   __syncthreads();
-  for (int e = t; e < NP * NP; e += 64) {
-    const int a = e / NP, b = e - a * NP;
-    double acc = 0.0;
-    for (int k = a > b ? a : b; k < NP; ++k) acc += W[k][a] * W[k][b];
-    out[e] = acc * (d1s[a] * d1s[b]);   // the same rounding for (a, b) and (b, a)
-  }
+  for (int k = t; k < NP * NP; k += 64) out[k] = buf[k];
   if (t == 0) status[s] = 0;
 }
 
