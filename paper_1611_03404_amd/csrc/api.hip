@@ -1388,7 +1388,6 @@ int enqueue_iteration(celeste_ctx* ctx, const Packed& P, const FitDev& F, const 
   HIPCHK(launch_reduce_full(srcs, P.n_src, imgs, parts, ic, F.theta, P.prior, F.need_full, F.f_full, F.g, F.H,
                             ctr_full(ctx), st));
   T->mark(3, st);
-  HIPCHK(launch_zero_int(F.n_active, 1, st));
   HIPCHK(launch_tr_step(F, P.n_src, fp, st));
   T->mark(4, st);
   HIPCHK(launch_setup(imgs, P.n_img, F.theta_trial, F.active, P.prof, tables, P.tstride, st));
@@ -1432,7 +1431,6 @@ int enqueue_iteration_td(celeste_ctx* ctx, const Packed& P, const FitDev& F, con
   const ImgDev* imgs = as<ImgDev>(ctx->imgs);
   double* parts = as<double>(ctx->partials);
   T->mark(0, st);
-  HIPCHK(launch_zero_int(F.n_active, 1, st));
   HIPCHK(launch_tr_step(F, P.n_src, fp, st));
   T->mark(1, st);
   if (Q) HIPCHK(launch_build_queue(*Q, P.n_src, F.active, st));
@@ -1446,7 +1444,6 @@ int enqueue_iteration_td(celeste_ctx* ctx, const Packed& P, const FitDev& F, con
                             F.theta_trial, P.prior, F.active, F.f_trial, F.g_trial, F.H_trial, ctr_trial(ctx), st));
   T->mark(4, st);
   HIPCHK(launch_accept(F, P.n_src, fp, st));
-  HIPCHK(launch_take_trial(F, P.n_src, st));
   T->mark(5, st);
   return CELESTE_OK;
 }
@@ -1707,7 +1704,8 @@ int run_fit(celeste_ctx* ctx, const celeste_batch* b, double* theta_inout, const
     CHK(fit_queue(ctx, P, &Q));
     CHK(fit_grid(ctx, P));
   }
-  const WorkQueue* Qp = ctx->persistent ? &Q : nullptr;
+  // items that all run at once need no list to be drawn from (its launch: 4.6 us an iteration)
+  const WorkQueue* Qp = ctx->persistent && P.n_items > ctx->pgrid ? &Q : nullptr;
   if (fp.trial_derivs) {
     // the start's gradient and Hessian, then iterations that evaluate them at every trial point
     CHK(enqueue_current_derivs(ctx, P, F, st, &T, Qp));
@@ -1825,7 +1823,6 @@ int run_fit_sampled(celeste_ctx* ctx, const celeste_batch* b, double* theta_inou
     HIPCHK(launch_reduce_full(srcs_s, S, imgs_s, parts_s, ic, F.theta, P.prior, F.fb, F.f_full, F.g, F.H,
                               ctr_full(ctx), st, w));
     t->mark(3, st);
-    HIPCHK(launch_zero_int(F.n_active, 1, st));
     HIPCHK(launch_tr_step(F, S, fp, st));
     t->mark(4, st);
     HIPCHK(launch_split(F.active, F.samp, F.fa, F.fb, S, st));

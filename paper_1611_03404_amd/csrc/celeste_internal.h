@@ -159,6 +159,7 @@ hipError_t launch_eval_value(const WorkItem* items, int n_items, const ImgDev* i
                              const int* kept = nullptr);
 // px_weight scales every image's pixel partials (not its theta-free constant): 1/p for a
 // pixel subsample whose work items cover only the kept rows.
+// bad (all reductions; may be null): nothing is written where it points to a non-zero flag.
 hipError_t launch_reduce_full(const SrcDev* srcs, int n_src, const ImgDev* imgs, const double* partials,
                               const double* img_const, const double* theta, PriorDev prior, const int* src_flag,
                               double* elbo, double* grad, double* hess, unsigned long long* px_ctr,
@@ -209,7 +210,7 @@ struct FitDev {
   int* status;          // S
   int* active;          // S  1 while the source is being fitted
   int* need_full;       // S  1 when g/H must be computed at theta (with trial derivatives: from an
-                        //    accepted step until k_take_trial hands over the trial point's g/H)
+                        //    accepted step until k_accept hands over the trial point's g/H)
   int* n_full;          // S value+gradient+Hessian evaluations
   int* n_acc;           // S accepted steps
   int* flags;           // S  CELESTE_FLAG_* bits
@@ -227,7 +228,7 @@ struct FitParams {
   double switch_rtol;   // subsampled phase: move to the full objective when pred <= switch_rtol max(1, |L|)
   int tr_chol;          // solve the subproblem by Cholesky factorisations where B is positive definite
   int trial_derivs;     // the gradient and Hessian are evaluated at every trial point (k_accept counts
-                        // each trial evaluation; launch_take_trial moves them to an accepted point)
+                        // each trial evaluation and moves them to an accepted point)
   const SrcDev* srcs;   // with trial_derivs: the sources (pixel counts) ...
   unsigned long long* taken_px;   // ... and the pixels of accepted steps whose trial derivatives are taken
   unsigned long long* tr_ctr;   // subproblems solved: [0] interior step, [1] boundary step by Cholesky,
@@ -280,11 +281,11 @@ hipError_t launch_patches(const SrcDev* srcs, int n_src, const ImgDev* imgs, con
                           hipStream_t st);
 hipError_t launch_plain_init(const SrcDev* srcs, int n_src, const ImgDev* imgs, PriorDev prior, double* theta,
                              hipStream_t s);
+// The subproblem's step and trial point; clears n_active, which launch_accept counts into.
 hipError_t launch_tr_step(FitDev st, int n_src, FitParams fp, hipStream_t s);
+// Ratio test; with trial derivatives an accepted source takes the gradient and Hessian of its trial point
+// (g_trial, H_trial).
 hipError_t launch_accept(FitDev st, int n_src, FitParams fp, hipStream_t s);
-// Trial derivatives: sources whose step was just accepted take the gradient and Hessian of their
-// trial point (g_trial, H_trial) and clear need_full.
-hipError_t launch_take_trial(FitDev st, int n_src, hipStream_t s);
 hipError_t launch_zero_int(int* p, int n, hipStream_t s);
 hipError_t launch_fill_int(int* p, int n, int value, hipStream_t s);
 // fa[s] = flag[s] && !samp[s], fb[s] = flag[s] && samp[s] for every source

@@ -11,13 +11,18 @@
 #include <math.h>
 
 #include "celeste_internal.h"
+#include "wave.h"
 
 namespace celeste {
 
 namespace {
 
-__device__ __constant__ double kSigns[5][4] = {
-    {-1.0, -1.0, 0.0, 0.0}, {0.0, -1.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 1.0, 0.0}, {0.0, 0.0, 1.0, 1.0}};
+// Signs of the colours in a band's log brightness: bands 0, 1 below and 3, 4 above the reference band 2.
+// (Formed, not looked up: a table indexed per lane is a load from memory in every map below.)
+__device__ __forceinline__ double sign_of(int band, int j) {
+  if ((band == 0 && j < 2) || (band == 1 && j == 1)) return -1.0;
+  return (band == 3 && j == 2) || (band == 4 && j >= 2) ? 1.0 : 0.0;
+}
 
 constexpr int tri(int i, int j) { return i * NZ - (i * (i - 1)) / 2 + (j - i); }
 
@@ -36,9 +41,9 @@ __device__ inline int theta_to_z(int i, int band, const double* wcs, int* za, do
   if (i == 8) { za[0] = 3; ca[0] = 1.0; return 1; }
   if (i == 9) { za[0] = 2; ca[0] = 1.0; return 1; }
   if (i == 10) { za[0] = 4; ca[0] = 1.0; return 1; }
-  if (i < 15) { za[0] = 1; ca[0] = kSigns[band][i - 11]; return 1; }
-  if (i < 19) { za[0] = 3; ca[0] = kSigns[band][i - 15]; return 1; }
-  const double s = kSigns[band][(i - 19) & 3];
+  if (i < 15) { za[0] = 1; ca[0] = sign_of(band, i - 11); return 1; }
+  if (i < 19) { za[0] = 3; ca[0] = sign_of(band, i - 15); return 1; }
+  const double s = sign_of(band, (i - 19) & 3);
   za[0] = i < 23 ? 2 : 4;
   ca[0] = s * s;
   return 1;
@@ -54,40 +59,66 @@ struct KL {
   double d2kla;
 };
 
-__device__ void kl_value_grad(const double* th, const PriorDev& pr, KL& k) {
-  const double a = th[2], phi = pr.p_star;
+// The arguments of kl_value_grad's logarithms: a / phi, (1 - a) / (1 - phi), r2 / s2 of the two types, their c2.
+constexpr int KL_LOGS = 12;
+__device__ __forceinline__ double kl_log_arg(const double* th, const PriorDev& pr, int i) {
+  if (i == 0) return th[2] / pr.p_star;
+  if (i == 1) return (1.0 - th[2]) / (1.0 - pr.p_star);
+  if (i < 4) return th[9 + (i - 2)] / pr.r_var[i - 2];
+  return th[19 + (i - 4)];
+}
+
+// LOG(i): the i-th of them.  U: 1 keeps the loops rolled (less code to fetch where one block runs), 8 unrolls them.
+template <int U, class LOG>
+__device__ __forceinline__ void kl_value_grad(const double* th, const PriorDev& pr, KL& k, LOG lg) {
+  const double a = th[2];
+#pragma unroll U
   for (int i = 0; i < NP; ++i) k.dks[i] = k.dkg[i] = 0.0;
-  const double kla = a * log(a / phi) + (1.0 - a) * log((1.0 - a) / (1.0 - phi));
-  const double dkla = log(a / phi) - log((1.0 - a) / (1.0 - phi));
+  const double kla = a * lg(0) + (1.0 - a) * lg(1);
+  const double dkla = lg(0) - lg(1);
   k.d2kla = 1.0 / a + 1.0 / (1.0 - a);
   k.a = a;
   double ktype[2];
+#pragma unroll U
   for (int t = 0; t < 2; ++t) {
     double* dk = t == 0 ? k.dks : k.dkg;
     const int ir1 = 7 + t, ir2 = 9 + t, ic1 = 11 + 4 * t, ic2 = 19 + 4 * t;
     const double r1 = th[ir1], r2 = th[ir2];
     const double mu = pr.r_mean[t], s2 = pr.r_var[t];
-    double kv = 0.5 * ((r2 + (r1 - mu) * (r1 - mu)) / s2 - 1.0 - log(r2 / s2));
+    double kv = 0.5 * ((r2 + (r1 - mu) * (r1 - mu)) / s2 - 1.0 - lg(2 + t));
     dk[ir1] = (r1 - mu) / s2;
     dk[ir2] = 0.5 * (1.0 / s2 - 1.0 / r2);
-    double dc[4];
-    for (int j = 0; j < 4; ++j) dc[j] = th[ic1 + j] - pr.c_mean[t][j];
     double quad = 0.0, tr = 0.0, slog = 0.0;
+#pragma unroll U
     for (int j = 0; j < 4; ++j) {
       double row = 0.0;
-      for (int l = 0; l < 4; ++l) row += pr.c_inv[t][j][l] * dc[l];
-      quad += dc[j] * row;
+      for (int l = 0; l < 4; ++l) row += pr.c_inv[t][j][l] * (th[ic1 + l] - pr.c_mean[t][l]);
+      quad += (th[ic1 + j] - pr.c_mean[t][j]) * row;
       dk[ic1 + j] = row;
       tr += pr.c_inv[t][j][j] * th[ic2 + j];
-      slog += log(th[ic2 + j]);
+      slog += lg(4 + 4 * t + j);
       dk[ic2 + j] = 0.5 * (pr.c_inv[t][j][j] - 1.0 / th[ic2 + j]);
     }
     kv += 0.5 * (tr + quad - 4.0 + pr.c_logdet[t] - slog);
     ktype[t] = kv;
   }
   k.val = -kla - a * ktype[0] - (1.0 - a) * ktype[1];
+#pragma unroll U
   for (int i = 0; i < NP; ++i) k.g[i] = -a * k.dks[i] - (1.0 - a) * k.dkg[i];
   k.g[2] += -dkla - ktype[0] + ktype[1];
+}
+
+__device__ void kl_value_grad(const double* th, const PriorDev& pr, KL& k) {
+  double l[KL_LOGS];
+#pragma unroll
+  for (int i = 0; i < KL_LOGS; ++i) l[i] = log(kl_log_arg(th, pr, i));
+  kl_value_grad<8>(th, pr, k, [&](int i) { return l[i]; });
+}
+
+// ... by a wavefront, a logarithm per lane (one lane's chain of 14 took a third of a small batch's reduction).
+__device__ __forceinline__ void kl_value_grad_wave(const double* th, const PriorDev& pr, KL& k, int lane) {
+  const double l = log(kl_log_arg(th, pr, min(lane, KL_LOGS - 1)));
+  kl_value_grad<1>(th, pr, k, [&](int i) { return lane_value(l, i); });
 }
 
 // Second derivative of a single-type KL (r and c terms) in natural coordinates.
@@ -108,47 +139,70 @@ __device__ inline double kl_hess(const double* th, const PriorDev& pr, const KL&
   return h;
 }
 
-constexpr int RB = 256;
+constexpr int RB = 320;
 constexpr int RSLOT = 80;              // threads per image slot in k_reduce_full (NACC of them busy)
 constexpr int NSLOT = RB / RSLOT;      // images whose partials are summed at once
 constexpr int ICH = 24;                // images per chunk of per-image sums held in LDS
 
-// Adds one z-space sum (tmp: value, 11 gradient, 66 Hessian entries, in LDS) mapped to the 27
-// natural parameters through the map of (band, WCS matrix) to Ht / gt.  All threads; tmp
-// must be complete on entry (barrier before the call); ends with a barrier.
-__device__ inline void project_add(const double* tmp, int band, const double* wcs, double* Hz, double* Ht,
-                                   double* gt) {
-  const int t = threadIdx.x;
-  if (t < NZ * NZ) {
-    const int a = t / NZ, b = t - a * NZ;
-    Hz[t] = tmp[1 + NZ + (a <= b ? tri(a, b) : tri(b, a))];
+// The map theta -> z of all bands for one WCS matrix, in LDS: theta_i feeds entry z[i] with factor c[band][i],
+// the positions (i = 0, 1) the entries 5 and 6 with the matrix's.
+struct ZMap {
+  double c[5][NP];
+  int z[NP];
+};
+__device__ __forceinline__ void fill_zmap(ZMap& m, int t) {
+  if (t < 5 * NP) {
+    const int b = t / NP, i = t - b * NP;
+    const double no_wcs[6] = {};
+    int za[2];
+    double ca[2];
+    theta_to_z(i, b, no_wcs, za, ca);
+    m.c[b][i] = ca[0];
+    if (b == 0) m.z[i] = za[0];
   }
-  __syncthreads();
+}
+
+// Adds one z-space sum (value, 11 gradient, 66 Hessian entries, in LDS) mapped to the 27 natural parameters
+// through the map of (band, WCS matrix) to Ht / gt, each thread its own entries.
+__device__ __forceinline__ void project_add(const double* sum, const ZMap& m, int band, const double* wcs, double* Ht,
+                                            double* gt) {
+  const int t = threadIdx.x;
+  const auto coef = [&](int i, int u) { return i < 2 ? wcs[2 * u + i] : m.c[band][i]; };
+  const auto entry = [&](int i, int u) { return i < 2 ? 5 + u : m.z[i]; };
+#pragma unroll 3
   for (int k = t; k < NP * NP; k += RB) {
     const int r = k / NP, c = k - r * NP;
-    int zr[2], zc[2];
-    double cr[2], cc[2];
-    const int nr = theta_to_z(r, band, wcs, zr, cr);
-    const int nc = theta_to_z(c, band, wcs, zc, cc);
+    const int nr = r < 2 ? 2 : 1, nc = c < 2 ? 2 : 1;
     double h = 0.0;
-    for (int u = 0; u < nr; ++u)
-      for (int v = 0; v < nc; ++v) h += cr[u] * cc[v] * Hz[zr[u] * NZ + zc[v]];
+#pragma unroll 1
+    for (int u = 0; u < nr; ++u) {
+      const double cr = coef(r, u);
+      const int a = entry(r, u);
+#pragma unroll 1
+      for (int v = 0; v < nc; ++v) {
+        const int b = entry(c, v);
+        h += cr * coef(c, v) * sum[1 + NZ + tri(min(a, b), max(a, b))];
+      }
+    }
     Ht[k] += h;
   }
   if (t < NP) {
-    int zr[2];
-    double cr[2];
-    const int nr = theta_to_z(t, band, wcs, zr, cr);
     double g = 0.0;
-    for (int u = 0; u < nr; ++u) g += cr[u] * tmp[1 + zr[u]];
+#pragma unroll 1
+    for (int u = 0; u < (t < 2 ? 2 : 1); ++u) g += coef(t, u) * sum[1 + entry(t, u)];
     gt[t] += g;
   }
-  __syncthreads();
 }
 
 // The map theta -> z of an image depends only on its band and the linear part of its WCS, so
 // the z-space sums of the images that share the source's first WCS matrix are added per band
 // first and mapped once per band; images with another WCS matrix are mapped one by one.
+// A block's time is latency, of the loads of the partials (the items' in order, four in flight; four images
+// at once) and, for a single source, of fetching its own code: the loops are kept rolled, the maps' factors
+// are formed once for all bands, each thread applies the maps to its own entries without barriers, and the
+// last wavefront forms the prior terms meanwhile, a logarithm per lane.  One source of five images: 20 us (28.9 us
+// with 20 KB of code, three barriers a map, a table of signs in memory and the prior terms on one lane at the
+// end; unrolled and in registers, 25 KB: 24.9 us); 4,000 uneven sources: 234 us (278 us).
 __global__ __launch_bounds__(RB) void k_reduce_full(const SrcDev* __restrict__ srcs, const ImgDev* __restrict__ imgs,
                                                     const double* __restrict__ partials,
                                                     const double* __restrict__ img_const,
@@ -157,24 +211,25 @@ __global__ __launch_bounds__(RB) void k_reduce_full(const SrcDev* __restrict__ s
                                                     double* __restrict__ grad, double* __restrict__ hess,
                                                     unsigned long long* __restrict__ px_ctr, double px_weight,
                                                     const int* __restrict__ bad) {
-  __shared__ double tmp[NACC];
   __shared__ double grp[5][NACC];
   __shared__ double isum[ICH][NACC];
-  __shared__ double Hz[NZ * NZ];
-  __shared__ double Ht[NP * NP];
+  __shared__ double Ht[NP * NP];   // each thread reads and writes its own entries (of gt too)
   __shared__ double gt[NP];
-  __shared__ double vt;
+  __shared__ ZMap zmap;
   __shared__ KL kl;
   const int s = blockIdx.x;
   if ((src_flag && !src_flag[s]) || (bad && *bad)) return;
   const int t = threadIdx.x;
   const double* th = theta + (size_t)s * NP;
+  double vt = 0.0;   // thread 0
+#pragma unroll 1
   for (int k = t; k < NP * NP; k += RB) Ht[k] = 0.0;
   if (t < NP) gt[t] = 0.0;
+  fill_zmap(zmap, t);
   if (t < NACC)
+#pragma unroll 1
     for (int b = 0; b < 5; ++b) grp[b][t] = 0.0;
-  if (t == 0) vt = 0.0;
-  __syncthreads();
+  if (t >= RB - 64) kl_value_grad_wave(th, prior, kl, t & 63);
   const SrcDev sr = srcs[s];
   const double* wref = imgs[sr.img_begin].wcs;
   unsigned used = 0;   // bands with images in grp (the same on every thread)
@@ -183,14 +238,24 @@ __global__ __launch_bounds__(RB) void k_reduce_full(const SrcDev* __restrict__ s
     const int c1 = min(sr.img_end, c0 + ICH);
     // the chunk's per-image sums of the work items' partials (items in order), NSLOT images at a
     // time, so that the loads of several images are in flight together
-    if (slot < NSLOT && e < NACC)
+    if (e < NACC)
       for (int i = c0 + slot; i < c1; i += NSLOT) {
         const ImgDev& im = imgs[i];
+        const int it1 = im.item_end;
         double acc = 0.0;
-        for (int it = im.item_begin; it < im.item_end; ++it) acc += partials[(size_t)it * NACC + e];
+#pragma unroll 1
+        for (int it = im.item_begin; it < it1; it += 4) {
+          double v[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) v[j] = partials[(size_t)min(it + j, it1 - 1) * NACC + e];
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (it + j < it1) acc += v[j];
+        }
         isum[i - c0][e] = acc * px_weight;
       }
     __syncthreads();
+#pragma unroll 1
     for (int i = c0; i < c1; ++i) {
       const ImgDev& im = imgs[i];
       const double* acc = isum[i - c0];
@@ -201,26 +266,24 @@ __global__ __launch_bounds__(RB) void k_reduce_full(const SrcDev* __restrict__ s
         used |= 1u << im.band;
       } else {
         if (t == 0) vt += acc[0];
-        project_add(acc, im.band, im.wcs, Hz, Ht, gt);
+        project_add(acc, zmap, im.band, im.wcs, Ht, gt);
       }
     }
     __syncthreads();   // the chunk's sums are read before the next chunk overwrites them
   }
+#pragma unroll 1
   for (int b = 0; b < 5; ++b) {
     if (!(used & (1u << b))) continue;
-    if (t < NACC) tmp[t] = grp[b][t];
-    __syncthreads();
-    if (t == 0) vt += tmp[0];
-    project_add(tmp, b, wref, Hz, Ht, gt);
+    if (t == 0) vt += grp[b][0];
+    project_add(grp[b], zmap, b, wref, Ht, gt);
   }
-  if (t == 0) kl_value_grad(th, prior, kl);
-  __syncthreads();
   if (t == 0) {
     elbo[s] = vt + kl.val;
     if (px_ctr) atomicAdd(px_ctr, (unsigned long long)sr.npix);
   }
   if (grad && t < NP) grad[(size_t)s * NP + t] = gt[t] + kl.g[t];
   if (hess) {
+#pragma unroll 3
     for (int k = t; k < NP * NP; k += RB) {
       const int r = k / NP, c = k - r * NP;
       hess[(size_t)s * NP * NP + k] = Ht[k] + kl_hess(th, prior, kl, r, c);
@@ -270,30 +333,39 @@ __global__ __launch_bounds__(64) void k_reduce_grad(const SrcDev* __restrict__ s
   if (t < NP) grad[(size_t)s * NP + t] = gt + kl.g[t];
 }
 
-// One thread per source: fixed-order sum of the source's value partials.
-__global__ __launch_bounds__(64) void k_reduce_value_t(const SrcDev* __restrict__ srcs, int n_src,
-                                                       const ImgDev* __restrict__ imgs,
-                                                       const double* __restrict__ partials,
-                                                       const double* __restrict__ img_const,
-                                                       const double* __restrict__ theta, PriorDev prior,
-                                                       const int* __restrict__ src_flag, double* __restrict__ elbo,
-                                                       unsigned long long* __restrict__ px_ctr, double px_weight,
-                                                    const int* __restrict__ bad) {
-  const int s = blockIdx.x * 64 + threadIdx.x;
+// One wavefront per source: an image's value partials summed per lane (items in order), then the images in order.
+// A thread per source left 1,500 uneven sources' sums to 24 wavefronts' chains of loads: 88 us, 30 us so.
+__global__ __launch_bounds__(256) void k_reduce_value(const SrcDev* __restrict__ srcs, int n_src,
+                                                        const ImgDev* __restrict__ imgs,
+                                                        const double* __restrict__ partials,
+                                                        const double* __restrict__ img_const,
+                                                        const double* __restrict__ theta, PriorDev prior,
+                                                        const int* __restrict__ src_flag, double* __restrict__ elbo,
+                                                        unsigned long long* __restrict__ px_ctr, double px_weight,
+                                                        const int* __restrict__ bad) {
+  __shared__ KL kl[4];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int s = blockIdx.x * 4 + wv;
   if (s >= n_src) return;
   if ((src_flag && !src_flag[s]) || (bad && *bad)) return;
+  kl_value_grad_wave(theta + (size_t)s * NP, prior, kl[wv], lane);
   const SrcDev sr = srcs[s];
   double v = 0.0;
-  for (int i = sr.img_begin; i < sr.img_end; ++i) {
-    const ImgDev& im = imgs[i];
-    double a = 0.0;
-    for (int it = im.item_begin; it < im.item_end; ++it) a += partials[it];
-    v += a * px_weight + img_const[i];
+  for (int i0 = sr.img_begin; i0 < sr.img_end; i0 += 64) {
+    const int n = min(64, sr.img_end - i0);
+    double x = 0.0;
+    if (lane < n) {
+      const ImgDev& im = imgs[i0 + lane];
+      double a = 0.0;
+      for (int it = im.item_begin; it < im.item_end; ++it) a += partials[it];
+      x = a * px_weight + img_const[i0 + lane];
+    }
+    for (int k = 0; k < n; ++k) v += lane_value(x, k);
   }
-  KL k;
-  kl_value_grad(theta + (size_t)s * NP, prior, k);
-  elbo[s] = v + k.val;
-  if (px_ctr) atomicAdd(px_ctr, (unsigned long long)sr.npix);
+  if (lane == 0) {
+    elbo[s] = v + kl[wv].val;
+    if (px_ctr) atomicAdd(px_ctr, (unsigned long long)sr.npix);
+  }
 }
 
 // Prior part of the ELBO (minus the KL terms) per source.
@@ -338,7 +410,7 @@ hipError_t launch_reduce_value(const SrcDev* srcs, int n_src, const ImgDev* imgs
                                const double* img_const, const double* theta, PriorDev prior, const int* src_flag,
                                double* elbo, unsigned long long* px_ctr, hipStream_t st, double px_weight, const int* bad) {
   if (n_src <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_reduce_value_t, dim3((n_src + 63) / 64), dim3(64), 0, st, srcs, n_src, imgs, partials,
+  hipLaunchKernelGGL(k_reduce_value, dim3((n_src + 3) / 4), dim3(256), 0, st, srcs, n_src, imgs, partials,
                      img_const, theta, prior, src_flag, elbo, px_ctr, px_weight, bad);
   return hipGetLastError();
 }
