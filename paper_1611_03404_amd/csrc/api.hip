@@ -106,7 +106,8 @@ struct celeste_ctx {
   DevBuf qbuf;                                     // the fits' device work queue
   bool lfact_ready = false;
   DevBuf h_meta, h_items, h_out, h_pix, h_theta;   // pinned host staging: packed metadata, a subsample's items,
-                                                   // results, pixels of host batches, estimates
+                                                   // results, pixels of host batches, estimates,
+  DevBuf h_poll;                                   // active counts of a fit's last two polls
 };
 
 namespace {
@@ -892,7 +893,7 @@ void celeste_ctx_destroy(celeste_ctx* c) {
                     &c->lfact, &c->lb_buf, &c->imgs_s, &c->items_s, &c->srcs_s, &c->partials_s, &c->qbuf};
   for (DevBuf* b : bufs)
     if (b->p) (void)hipFree(b->p);
-  for (DevBuf* b : {&c->h_meta, &c->h_items, &c->h_out, &c->h_pix, &c->h_theta})
+  for (DevBuf* b : {&c->h_meta, &c->h_items, &c->h_out, &c->h_pix, &c->h_theta, &c->h_poll})
     if (b->p) (void)hipHostFree(b->p);
   (void)hipStreamDestroy(c->stream);
   delete c;
@@ -1599,7 +1600,7 @@ int fit_results(celeste_ctx* ctx, const celeste_batch* b, const FitDev& F, int S
 }
 
 // Replays (graph) or enqueues (eager) `iteration` until no source is active or max_loops loop
-// steps; the host reads the device's active count every `poll` steps.
+// steps; the host reads the device's active count of every `poll` steps.
 // count(stats) records the launches of one executed step (replayed or enqueued).
 template <class Iter, class Count>
 int run_loop(celeste_ctx* ctx, hipStream_t st, int max_loops, int poll, bool use_graph, const int* n_active_dev,
@@ -1618,9 +1619,32 @@ int run_loop(celeste_ctx* ctx, hipStream_t st, int max_loops, int poll, bool use
     HIPCHK(e2);
     HIPCHK(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
   }
-  int rc = CELESTE_OK;
-  int n_active = 1;
-  for (int it = 0; it < max_loops && n_active > 0; ++it) {
+  // The count is read one poll behind the launches, so that the device always has iterations to run: reading it
+  // before the next launch left the device idle for 40 us an iteration of a single source's fit (of 185).
+  // The iterations launched past the one that left nothing active find every source inactive.  With phase
+  // times (T.on, one iteration's events) each iteration is waited for.
+  int rc = ensure_host(ctx->h_poll, 2 * sizeof(int));
+  volatile int* slot = as<int>(ctx->h_poll);
+  hipEvent_t ev[2] = {};
+  for (auto& e : ev)
+    if (rc == CELESTE_OK && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess)
+      rc = fail(CELESTE_E_DEVICE, "event creation failed");
+  int polls = 0, since = 0, covered[2] = {};
+  bool active = true;
+  const auto read_poll = [&](int k) {   // waits for poll k; its iterations are counted
+    const hipError_t e = hipEventSynchronize(ev[k & 1]);
+    if (e != hipSuccess) {
+      rc = fail(CELESTE_E_DEVICE, "active-count readback: %s", hipGetErrorString(e));
+      return;
+    }
+    for (int i = 0; i < covered[k & 1]; ++i) {
+      ctx->stats.iterations += 1;
+      count(ctx->stats);
+    }
+    account(ctx, T);
+    active = slot[k & 1] > 0;
+  };
+  for (int it = 0; it < max_loops && active && rc == CELESTE_OK; ++it) {
     if (exec) {
       hipError_t e = hipGraphLaunch(exec, st);
       if (e != hipSuccess) {
@@ -1631,19 +1655,27 @@ int run_loop(celeste_ctx* ctx, hipStream_t st, int max_loops, int poll, bool use
       rc = iteration(&T);
       if (rc != CELESTE_OK) break;
     }
-    ctx->stats.iterations += 1;
-    count(ctx->stats);
-    if ((it + 1) % poll == 0 || it + 1 == max_loops) {
-      hipError_t e = hipMemcpyAsync(&n_active, n_active_dev, sizeof(int), hipMemcpyDeviceToHost, st);
-      if (e == hipSuccess) e = hipStreamSynchronize(st);
-      if (e != hipSuccess) {
-        rc = fail(CELESTE_E_DEVICE, "active-count readback: %s", hipGetErrorString(e));
-        break;
-      }
-      account(ctx, T);
+    ++since;
+    if ((it + 1) % poll != 0 && it + 1 != max_loops) continue;
+    hipError_t e = hipMemcpyAsync(const_cast<int*>(slot) + (polls & 1), n_active_dev, sizeof(int), hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipEventRecord(ev[polls & 1], st);
+    if (e != hipSuccess) {
+      rc = fail(CELESTE_E_DEVICE, "active-count readback: %s", hipGetErrorString(e));
+      break;
     }
+    covered[polls & 1] = since;
+    since = 0;
+    ++polls;
+    const bool last = it + 1 == max_loops;
+    if (polls > 1 && !T.on) read_poll(polls - 2);
+    if (rc == CELESTE_OK && active && (last || T.on)) read_poll(polls - 1);
   }
-  if (exec) (void)hipGraphExecDestroy(exec);
+  for (auto& e : ev)
+    if (e) (void)hipEventDestroy(e);
+  if (exec) {   // not while a launch of it runs
+    (void)hipStreamSynchronize(st);
+    (void)hipGraphExecDestroy(exec);
+  }
   if (graph) (void)hipGraphDestroy(graph);
   return rc;
 }
