@@ -1138,7 +1138,7 @@ int eval_impl(celeste_ctx* ctx, const celeste_batch* b, const double* theta, dou
   PhaseTimer T;
   CHK(T.init(ctx->profile != 0 && !noalloc));   // events are not created on the no-allocation path
   T.mark(0, st);
-  HIPCHK(launch_setup(B.imgs, P.n_img, th_dev, nullptr, P.prof, B.tables, P.tstride, st));
+  HIPCHK(launch_setup(B.imgs, P.n_img, th_dev, nullptr, P.prof, B.tables, P.tstride, st, grad != nullptr));
   T.mark(1, st);
   int64_t* launches = nullptr;
   if (grad && hess) {
@@ -1391,7 +1391,7 @@ int enqueue_iteration(celeste_ctx* ctx, const Packed& P, const FitDev& F, const 
   T->mark(3, st);
   HIPCHK(launch_tr_step(F, P.n_src, fp, st));
   T->mark(4, st);
-  HIPCHK(launch_setup(imgs, P.n_img, F.theta_trial, F.active, P.prof, tables, P.tstride, st));
+  HIPCHK(launch_setup(imgs, P.n_img, F.theta_trial, F.active, P.prof, tables, P.tstride, st, false));
   T->mark(5, st);
   HIPCHK(launch_eval_value(items, P.n_items, imgs, tables, P.tstride, P.prof.n_exp, P.prof.n_dev, F.active, parts,
                            ctx->vblock, ctx->variant, ctx->vtile_log2, ctx->e_zero, st));
@@ -1532,7 +1532,7 @@ int fit_begin(celeste_ctx* ctx, const celeste_batch* b, const double* theta_inou
     HIPCHK(launch_plain_init(as<SrcDev>(ctx->srcs), S, imgs0, P.prior, F.theta, st));
     for (int k = 0; k < 2; ++k) {
       double* tk = k == 0 ? F.theta : F.theta_trial;
-      HIPCHK(launch_setup(imgs0, P.n_img, tk, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st));
+      HIPCHK(launch_setup(imgs0, P.n_img, tk, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st, false));
       HIPCHK(launch_eval_value(as<WorkItem>(ctx->items), P.n_items, imgs0, as<float>(ctx->tables), P.tstride,
                                P.prof.n_exp, P.prof.n_dev, nullptr, as<double>(ctx->partials), ctx->vblock, ctx->variant,
                              ctx->vtile_log2, ctx->e_zero, st));
@@ -1551,7 +1551,7 @@ int fit_begin(celeste_ctx* ctx, const celeste_batch* b, const double* theta_inou
     // inside the boxes, where the transform round trip of the fit set-up moves a parameter by
     // rounding, or by at most 1e-9 of its box where a start sits on the box edge)
     const ImgDev* imgs = as<ImgDev>(ctx->imgs);
-    HIPCHK(launch_setup(imgs, P.n_img, F.theta, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st));
+    HIPCHK(launch_setup(imgs, P.n_img, F.theta, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st, false));
     HIPCHK(launch_eval_value(as<WorkItem>(ctx->items), P.n_items, imgs, as<float>(ctx->tables), P.tstride,
                              P.prof.n_exp, P.prof.n_dev, nullptr, as<double>(ctx->partials), ctx->vblock,
                              ctx->variant, ctx->vtile_log2, ctx->e_zero, st));
@@ -1834,7 +1834,7 @@ int run_fit_sampled(celeste_ctx* ctx, const celeste_batch* b, double* theta_inou
   // every fitted source starts on the subsampled objective: its value there at the start
   HIPCHK(launch_fill_int(F.samp, S, 1, st));
   HIPCHK(launch_split(F.active, F.samp, F.fa, F.fb, S, st));
-  HIPCHK(launch_setup(imgs, P.n_img, F.theta, F.fb, P.prof, tables, P.tstride, st));
+  HIPCHK(launch_setup(imgs, P.n_img, F.theta, F.fb, P.prof, tables, P.tstride, st, false));
   HIPCHK(launch_eval_value(items_s, Ps.n_items, imgs_s, tables, P.tstride, P.prof.n_exp, P.prof.n_dev, F.fb, parts_s,
                            ctx->vblock, ctx->variant, ctx->vtile_log2, ctx->e_zero, st, kept));
   HIPCHK(launch_reduce_value(srcs_s, S, imgs_s, parts_s, ic, F.theta, P.prior, F.fb, F.f, ctr_value(ctx), st, w));
@@ -1858,7 +1858,7 @@ int run_fit_sampled(celeste_ctx* ctx, const celeste_batch* b, double* theta_inou
     HIPCHK(launch_tr_step(F, S, fp, st));
     t->mark(4, st);
     HIPCHK(launch_split(F.active, F.samp, F.fa, F.fb, S, st));
-    HIPCHK(launch_setup(imgs, P.n_img, F.theta_trial, F.active, P.prof, tables, P.tstride, st));
+    HIPCHK(launch_setup(imgs, P.n_img, F.theta_trial, F.active, P.prof, tables, P.tstride, st, false));
     t->mark(5, st);
     HIPCHK(launch_eval_value(items, P.n_items, imgs, tables, P.tstride, P.prof.n_exp, P.prof.n_dev, F.fa, parts,
                              ctx->vblock, ctx->variant, ctx->vtile_log2, ctx->e_zero, st));
@@ -1980,7 +1980,7 @@ int run_lbfgs(celeste_ctx* ctx, const celeste_batch* b, double* theta_inout, con
     HIPCHK(launch_zero_int(F.n_active, 1, st));
     HIPCHK(launch_lbfgs_dir(F, X, P.n_src, lp, st));
     t->mark(4, st);
-    HIPCHK(launch_setup(imgs, P.n_img, F.theta_trial, X.in_ls, P.prof, tables, P.tstride, st));
+    HIPCHK(launch_setup(imgs, P.n_img, F.theta_trial, X.in_ls, P.prof, tables, P.tstride, st, false));
     t->mark(5, st);
     HIPCHK(launch_eval_value(items, P.n_items, imgs, tables, P.tstride, P.prof.n_exp, P.prof.n_dev, X.in_ls, parts,
                              ctx->vblock, ctx->variant, ctx->vtile_log2, ctx->e_zero, st));
@@ -2321,7 +2321,7 @@ int celeste_render_fields(celeste_ctx* ctx, const celeste_batch* b, const double
   const int n_tiles = (int)n_tiles64, tpf = tx * ty;
   // the metadata and the setup tables are under way while the lists are formed
   CHK(prepare(ctx, b, &P, st, false));
-  HIPCHK(launch_setup(as<ImgDev>(ctx->imgs), P.n_img, theta, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st));
+  HIPCHK(launch_setup(as<ImgDev>(ctx->imgs), P.n_img, theta, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st, false));
   int64_t n_ints = 0;
   int rc = tile_lists(ctx, patches, f->n_fields, tx, tpf, &n_ints);
   if (rc == CELESTE_OK) rc = ensure(ctx->tile_off, sizeof(int) * (size_t)n_ints);
@@ -2355,7 +2355,7 @@ int celeste_neighbour_arrays(celeste_ctx* ctx, const celeste_batch* b, const dou
   HIPCHK(hipMemcpyAsync(ctx->img_field.p, f->img_field, sizeof(int) * P.n_img, hipMemcpyHostToDevice, st));
   HIPCHK(hipMemcpyAsync(ctx->nbr_off.p, nbr_off, sizeof(long long) * P.n_img, hipMemcpyHostToDevice, st));
   const ImgDev* imgs = as<ImgDev>(ctx->imgs);
-  HIPCHK(launch_setup(imgs, P.n_img, theta, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st));
+  HIPCHK(launch_setup(imgs, P.n_img, theta, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st, false));
   HIPCHK(launch_neighbours(imgs, P.n_img, as<int>(ctx->img_field), as<float>(ctx->tables), P.tstride, P.prof.n_exp,
                            P.prof.n_dev, f->height, f->width, ctx->e_zero, f->mean, f->var,
                            as<long long>(ctx->nbr_off), nbr_mean, nbr_var, st));
@@ -2412,8 +2412,8 @@ int celeste_update_fields(celeste_ctx* ctx, const celeste_batch* b, const double
   CHK(prepare(ctx, b, &P, st, false));
   HIPCHK(hipMemcpyAsync(ctx->img_field.p, f->img_field, sizeof(int) * P.n_img, hipMemcpyHostToDevice, st));
   const ImgDev* imgs = as<ImgDev>(ctx->imgs);
-  HIPCHK(launch_setup(imgs, P.n_img, theta_old, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st));
-  HIPCHK(launch_setup(imgs, P.n_img, theta_new, nullptr, P.prof, as<float>(ctx->tables2), P.tstride, st));
+  HIPCHK(launch_setup(imgs, P.n_img, theta_old, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st, false));
+  HIPCHK(launch_setup(imgs, P.n_img, theta_new, nullptr, P.prof, as<float>(ctx->tables2), P.tstride, st, false));
   HIPCHK(launch_update_fields(imgs, P.n_img, as<int>(ctx->img_field), as<float>(ctx->tables),
                               as<float>(ctx->tables2), P.tstride, P.prof.n_exp, P.prof.n_dev, f->height, f->width,
                               ctx->e_zero, f->mean, f->var, st));

@@ -117,8 +117,9 @@ __device__ __forceinline__ int queue_next(const WorkQueue& q) {
 }
 
 // ---------------------------------------------------------------- launch wrappers
+// derivs: false leaves out what only gradients and Hessians read (values and field rates come next).
 hipError_t launch_setup(const ImgDev* imgs, int n_img, const double* theta, const int* src_flag,
-                        ProfDev prof, float* tables, int tstride, hipStream_t st);
+                        ProfDev prof, float* tables, int tstride, hipStream_t st, bool derivs = true);
 // log n! table for the theta-independent pixel constants (LFACT_N doubles), and the pass that
 // checks every pixel / neighbour value (bad |= 1 on a negative or non-finite one) and writes
 // each image's constant sum x log E_bg - E_bg - log x!.  With theta (n_src x NP, device memory) its rows are
