@@ -8,6 +8,8 @@
 // their contributions in FP64 per pixel.  The neighbour array of a source is the rendered
 // field minus the source's own contribution, computed by the same per-pixel routine (Mixture::rates, whose
 // operations are written out so that every kernel rounds them alike).
+#include <algorithm>
+
 #include "celeste_internal.h"
 #include "tiles.h"
 
@@ -149,14 +151,14 @@ template <int NE, int ND, int Q>
 __global__ __launch_bounds__(256) void k_render(const int* __restrict__ tile_off, const int* __restrict__ tile_img,
                                                 const ImgDev* __restrict__ imgs, const float* __restrict__ tables,
                                                 int tstride, int n_exp, int n_dev, int H, int W, int tiles_x,
-                                                int tiles_per_field, int n_blocks, float e_zero,
+                                                int tiles_per_field, int tile0, int n_blocks, float e_zero,
                                                 float* __restrict__ mean, float* __restrict__ var) {
   constexpr int QX = Q >= 2 ? 2 : 1, QY = Q / QX;       // squares of a wavefront
   constexpr int BX = RTILE / (16 * QX), BY = RTILE / (16 * QY);   // blocks of a tile
   const int per_xcd = (int)gridDim.x >> 3;
   const int blk = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);   // neighbouring tiles on one XCD
   if (blk >= n_blocks) return;
-  const int tile = blk / (BX * BY), part = blk - tile * (BX * BY);
+  const int local = blk / (BX * BY), part = blk - local * (BX * BY), tile = tile0 + local;
   const int f = tile / tiles_per_field, tt = tile - f * tiles_per_field;
   const int ty = tt / tiles_x, tx = tt - ty * tiles_x;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -337,10 +339,16 @@ hipError_t launch_render(const int* tile_off, const int* tile_img, int n_tiles, 
                          int tiles_per_field, float e_zero, float* mean, float* var, hipStream_t st) {
   if (n_tiles <= 0) return hipSuccess;
   const auto k = unrolled(n_exp, n_dev) ? &k_render<6, 8, RQ> : &k_render<0, 0, RQ>;
-  const int n_blocks = n_tiles * (4 / RQ);
-  hipLaunchKernelGGL(k, dim3((n_blocks + 7) / 8 * 8), dim3(256), 0, st, tile_off, tile_img, imgs, tables, tstride,
-                     n_exp, n_dev, H, W, tiles_x, tiles_per_field, n_blocks, e_zero, mean, var);
-  return hipGetLastError();
+  // A launch holds fewer than 2^32 threads; one with more runs some of its blocks only, without an error.
+  constexpr int PER_LAUNCH = 1 << 22;
+  for (int t0 = 0; t0 < n_tiles; t0 += std::min(PER_LAUNCH, n_tiles - t0)) {
+    const int n_blocks = std::min(PER_LAUNCH, n_tiles - t0) * (4 / RQ);
+    hipLaunchKernelGGL(k, dim3((n_blocks + 7) / 8 * 8), dim3(256), 0, st, tile_off, tile_img, imgs, tables, tstride,
+                       n_exp, n_dev, H, W, tiles_x, tiles_per_field, t0, n_blocks, e_zero, mean, var);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_neighbours(const ImgDev* imgs, int n_img, const int* img_field, const float* tables, int tstride,

@@ -489,10 +489,16 @@ hipError_t launch_lfact(double* table, hipStream_t st) {
 
 hipError_t launch_check_const(const ImgDev* imgs, int n_img, const double* lfact, double* img_const, int* bad,
                               hipStream_t st, const double* theta, int n_src) {
-  if (n_img <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_check_const, dim3(n_img + (n_src + 255) / 256), dim3(256), 0, st, imgs, lfact, img_const, bad,
-                     n_img, theta, n_src);
-  return hipGetLastError();
+  const auto launch = [&](int ni, int ns) {
+    const int blocks = ni + (ns + 255) / 256;
+    if (blocks > 0)
+      hipLaunchKernelGGL(k_check_const, dim3(blocks), dim3(256), 0, st, imgs, lfact, img_const, bad, ni, theta, ns);
+    return hipGetLastError();
+  };
+  // the estimates by themselves where the launch would otherwise hold 2^32 threads
+  if (n_img + (n_src + 255) / 256 < 1 << 24) return launch(n_img, n_src);
+  const hipError_t e = launch(n_img, 0);
+  return e != hipSuccess ? e : launch(0, n_src);
 }
 
 hipError_t launch_plain_init(const SrcDev* srcs, int n_src, const ImgDev* imgs, PriorDev prior, double* theta,
