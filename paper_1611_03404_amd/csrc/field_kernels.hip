@@ -45,7 +45,7 @@ struct Mixture {
     const int c = min(lane, n_gal - 1), k = lane - n_gal;
     const bool star = k >= 0;
     const float* sr = T + STAR + STAR_REC * (star ? min(k, npsf - 1) : c / ncomp);
-    skip = skip_test(star ? sr : T + EXPO + c * EXPO_REC, sr);
+    skip = skip_test(star ? sr : T + EXPO + c * EXPO_REC, sr, 0.f);
   }
 
   __device__ __forceinline__ TileHits split(unsigned long long hits) const {

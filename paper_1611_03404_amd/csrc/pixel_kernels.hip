@@ -56,7 +56,6 @@ __device__ __forceinline__ float log1p_pos(float u) {
 // Exact-zero threshold on log2 of a component's density, a launch argument: -160 in general
 // (2^-160 lies below the smallest FP32 subnormal), -127 where v_exp_f32 flushes results below
 // 2^-126 to zero, which the library checks on the device when a context is created.
-constexpr float FAR = 1.0e4f;      // offset used by lanes outside the image
 constexpr int FLUSH = 16;          // tile steps of lane sums in FP32 before a butterfly into FP64
 constexpr int JFLUSH = 8;          // tile steps of matrix-core sums in FP32 before FP64
 constexpr int JP = 68;             // LDS row pitch (floats) of the staged J^T W J operands
@@ -329,7 +328,7 @@ __global__ __launch_bounds__(BLOCK, MINW) void k_eval_full(const WorkItem* __res
   TileMap<PK, BLOCK / 64> tm(wi, w, im.h, tw_log2, kept, wv);
   const int n_gal = npsf * ncomp;   // at most 64
   const float* __restrict__ G = T + gal_at(n_gal);
-  if (threadIdx.x < n_gal) skip[threadIdx.x] = skip_test_of(T, threadIdx.x, ncomp);
+  if (threadIdx.x < n_gal) skip[threadIdx.x] = skip_test_of(T, threadIdx.x, ncomp, reach_of(im, psx, psy));
   touch_table(T, gal_at(n_gal) + n_gal * GAL_REC);
   __syncthreads();
   const SkipTest& my_skip = skip[min(lane, n_gal - 1)];
@@ -387,7 +386,9 @@ __global__ __launch_bounds__(BLOCK, MINW) void k_eval_full(const WorkItem* __res
     const float dx0 = live ? (float)col - psx : FAR, dy0 = live ? (float)row - psy : FAR;
 
     // galaxy components that may be non-zero on the tile
-    unsigned long long hits = tile_hits(my_skip, tm, col, first, psx, psy, e_zero) & gal_lanes;
+    unsigned long long odd, hits = tile_hits(my_skip, tm, col, first, psx, psy, e_zero, &odd) & gal_lanes;
+    odd &= gal_lanes;
+    if (__builtin_expect(odd != 0ull, 0)) hits = (hits & ~odd) | odd_hits(odd, T, ncomp, dx0, dy0, e_zero);
     bool hit = hits != 0ull;   // some component is not exactly 0 on this tile (wavefront-uniform)
 
     // ---- star: N, dN/dp, d2N/dp2; galaxy: Hermite moments per profile type.  The galaxy's hits are
@@ -786,7 +787,7 @@ __global__ __launch_bounds__(BLOCK) void k_eval_value(const WorkItem* __restrict
   TileMap<PK, BLOCK / 64> tm(wi, w, im.h, tw_log2, kept, wv);
   const int n_gal = npsf * ncomp;   // at most 64
   const float* __restrict__ E = T + EXPO;
-  if (threadIdx.x < n_gal) skip[threadIdx.x] = skip_test_of(T, threadIdx.x, ncomp);
+  if (threadIdx.x < n_gal) skip[threadIdx.x] = skip_test_of(T, threadIdx.x, ncomp, 0.f);
   touch_table(T, gal_at(n_gal));
   __syncthreads();
   const SkipTest my_skip = skip[min(lane, n_gal - 1)];
@@ -922,7 +923,7 @@ __global__ __launch_bounds__(BLOCK) void k_eval_grad(const WorkItem* __restrict_
   TileMap<PK, BLOCK / 64> tm(wi, w, im.h, tw_log2, kept, wv);
   const int n_gal = npsf * ncomp;   // at most 64
   const float* __restrict__ G = T + gal_at(n_gal);
-  if (threadIdx.x < n_gal) skip[threadIdx.x] = skip_test_of(T, threadIdx.x, ncomp);
+  if (threadIdx.x < n_gal) skip[threadIdx.x] = skip_test_of(T, threadIdx.x, ncomp, reach_of(im, psx, psy));
   touch_table(T, gal_at(n_gal) + n_gal * GAL_REC);
   __syncthreads();
   const SkipTest& my_skip = skip[min(lane, n_gal - 1)];
@@ -939,7 +940,9 @@ __global__ __launch_bounds__(BLOCK) void k_eval_grad(const WorkItem* __restrict_
     const float x = live ? xp : 0.f, ebg = sky + (live ? en : 0.f), vbg = live ? vn : 0.f;
     const float dx0 = live ? (float)col - psx : FAR, dy0 = live ? (float)row - psy : FAR;
 
-    unsigned long long hits = tile_hits(my_skip, tm, col, first, psx, psy, e_zero) & gal_lanes;
+    unsigned long long odd, hits = tile_hits(my_skip, tm, col, first, psx, psy, e_zero, &odd) & gal_lanes;
+    odd &= gal_lanes;
+    if (__builtin_expect(odd != 0ull, 0)) hits = (hits & ~odd) | odd_hits(odd, T, ncomp, dx0, dy0, e_zero);
     bool hit = hits != 0ull;
     float s0 = 0.f, s1x = 0.f, s1y = 0.f;
     GalAcc1 X = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, D = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};

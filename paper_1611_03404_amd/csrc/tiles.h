@@ -234,29 +234,48 @@ __device__ __forceinline__ void comp_value(const ValRec& r, float dxx, float dxy
 // Against a test of every component's exponent on the tile's pixels (3 FMAs, a compare and a branch
 // each) this takes about 30 vector instructions for all components, and the hits are known before
 // their records are read, so the next hit's scalar loads are in flight while one is evaluated.
+//
+// The box says nothing of a component whose constants are not finite or not positive (an estimate's scale or a
+// WCS beyond FP32), nor may one be evaluated on pixels where it is 0 if it is so narrow, or so far off, that
+// its derivatives' polynomials overflow there (0 times infinity; a PSF of 1e-5 px).  Such a component is odd: it may
+// be non-zero on every tile, and a kernel of derivatives then tests it on the tile's pixels (odd_hits).
 struct SkipTest {
-  float4 form;     // c0, A, B, C
+  float4 form;     // c0, A, B, C; an odd component: infinity, 0, 0, 0
   float4 geo;      // centre offset x, y (the PSF component's), B / 2C, B / 2A
 };
 
-// Test of the component with the constants at r, of the PSF component with the star record sr.
-__device__ __forceinline__ SkipTest skip_test(const float* __restrict__ r, const float* __restrict__ sr) {
+constexpr float FAR = 1.0e4f;      // offset used by lanes outside the image
+
+// Test of the component with the constants at r, of the PSF component with the star record sr.  reach: the
+// largest offset from the source at which its derivatives are formed, 0 where none are.  (With P <= 1.39 times the
+// larger of A and C, |P d| stays below 4 * 7e8 and its fourth power below 7e37.)
+__device__ __forceinline__ SkipTest skip_test(const float* __restrict__ r, const float* __restrict__ sr, float reach) {
   using namespace tab;
   SkipTest s;
   s.form = make_float4(r[R_C0], -r[R_QXX], -r[R_QXY], -r[R_QYY]);
+  const float far = reach + fabsf(sr[S_XIX]) + fabsf(sr[S_XIY]);
+  const bool ok = s.form.x < 1e30f && s.form.y >= 0.f && s.form.w >= 0.f && s.form.y * far < 7e8f &&
+                  s.form.w * far < 7e8f && fabsf(s.form.z) * far < 1.4e9f;   // false for NaN and infinities
+  if (!ok) s.form = make_float4(INFINITY, 0.f, 0.f, 0.f);
   s.geo = make_float4(sr[S_XIX], sr[S_XIY], s.form.w > 0.f ? 0.5f * s.form.z / s.form.w : 0.f,
                       s.form.y > 0.f ? 0.5f * s.form.z / s.form.y : 0.f);
   return s;
 }
 
 // ... of galaxy component c
-__device__ __forceinline__ SkipTest skip_test_of(const float* __restrict__ T, int c, int ncomp) {
+__device__ __forceinline__ SkipTest skip_test_of(const float* __restrict__ T, int c, int ncomp, float reach) {
   using namespace tab;
-  return skip_test(T + EXPO + c * EXPO_REC, T + STAR + (c / ncomp) * STAR_REC);
+  return skip_test(T + EXPO + c * EXPO_REC, T + STAR + (c / ncomp) * STAR_REC, reach);
 }
 
-// True on the lanes whose component may be non-zero on the box (psx, psy: the source's position).
-__device__ __forceinline__ bool may_hit(const SkipTest& s, const TileBox& b, float psx, float psy, float e_zero) {
+// The largest offset from the source on an image's lanes.
+__device__ __forceinline__ float reach_of(const ImgDev& im, float psx, float psy) {
+  return FAR + (float)max(im.w, im.h) + fabsf(psx) + fabsf(psy);
+}
+
+// Upper bound of this lane's component's exponent on the box (psx, psy: the source's position); infinite or NaN
+// for an odd component, and NaN where the position is beyond FP32.
+__device__ __forceinline__ float exponent_bound(const SkipTest& s, const TileBox& b, float psx, float psy) {
   const float xl = ((float)b.x0 - psx) - s.geo.x, xh = ((float)b.x1 - psx) - s.geo.x;
   const float yl = ((float)b.y0 - psy) - s.geo.y, yh = ((float)b.y1 - psy) - s.geo.y;
   const float A = s.form.y, B = s.form.z, C = s.form.w;
@@ -267,7 +286,12 @@ __device__ __forceinline__ bool may_hit(const SkipTest& s, const TileBox& b, flo
   const float q2 = fmaf(C * yn, yn, xs * fmaf(B, yn, A * xs));
   const float X = fmaxf(fabsf(xl), fabsf(xh)), Y = fmaxf(fabsf(yl), fabsf(yh));
   const float M = fmaf(X, fmaf(A, X, fabsf(B) * Y), C * Y * Y);
-  return (s.form.x - fminf(q1, q2)) + fmaf(M, 0x1p-20f, 0.01f) >= e_zero;
+  return (s.form.x - fminf(q1, q2)) + fmaf(M, 0x1p-20f, 0.01f);
+}
+
+// True on the lanes whose component must be evaluated on the box: one that may be non-zero, or NaN.
+__device__ __forceinline__ bool may_hit(const SkipTest& s, const TileBox& b, float psx, float psy, float e_zero) {
+  return !(exponent_bound(s, b, psx, psy) < e_zero);
 }
 
 // Brings an image's whole table (n floats) into the cache behind the scalar loads that will read it,
@@ -286,14 +310,34 @@ __device__ __forceinline__ int low_bit(unsigned long long m) { return m ? __buil
 // The lanes below n (n <= 64).
 __device__ __forceinline__ unsigned long long lane_mask(int n) { return n >= 64 ? ~0ull : (1ull << n) - 1; }
 
-// Components (bit = the lane holding the component's test) that may be non-zero on tm's tile; col and
-// first are this lane's from tm.pixel.
+// Components (bit = the lane holding the component's test) that must be evaluated on tm's tile; col and
+// first are this lane's from tm.pixel.  *odd (where asked for): the odd ones, whose bound is not finite.
 template <class MAP>
 __device__ __forceinline__ unsigned long long tile_hits(const SkipTest& s, const MAP& tm, int col, int first,
-                                                        float psx, float psy, float e_zero) {
+                                                        float psx, float psy, float e_zero,
+                                                        unsigned long long* odd = nullptr) {
   bool two;
-  unsigned long long hits = __ballot(may_hit(s, tm.box(col, first, false, &two), psx, psy, e_zero));
+  const float e = exponent_bound(s, tm.box(col, first, false, &two), psx, psy);
+  unsigned long long hits = __ballot(!(e < e_zero));
+  if (odd) *odd = __ballot(!(e < INFINITY));
   if (two) hits |= __ballot(may_hit(s, tm.box(col, first, true, &two), psx, psy, e_zero));
+  return hits;
+}
+
+// Odd components whose exponent reaches the threshold on some pixel of the tile (derivative kernels; dx0, dy0: this
+// lane's offset from the source).
+__device__ __forceinline__ unsigned long long odd_hits(unsigned long long odd, const float* __restrict__ T, int ncomp,
+                                                       float dx0, float dy0, float e_zero) {
+  using namespace tab;
+  unsigned long long hits = 0ull;
+  for (; odd; odd &= odd - 1) {
+    const int c = __builtin_ctzll(odd);
+    const float* __restrict__ sr = T + STAR + (c / ncomp) * STAR_REC;
+    const ValRec r = load_val(T + EXPO + c * EXPO_REC);
+    const float dx = dx0 - sr[S_XIX], dy = dy0 - sr[S_XIY];
+    const float e = fmaf(r.qxx, dx * dx, fmaf(r.qxy, dx * dy, fmaf(r.qyy, dy * dy, r.c0)));
+    if (__ballot(e >= e_zero)) hits |= 1ull << c;
+  }
   return hits;
 }
 
