@@ -252,6 +252,45 @@ __device__ __forceinline__ int table_index(float x) {
   return (float)n == x && (unsigned)n < (unsigned)LFACT_N ? n : -1;
 }
 
+// log x! = log Gamma(z), z = x + 1, of a finite value x >= 0 that the table does not hold; the library's lgamma, which
+// also serves negative arguments, takes three times the registers.  From z = 16 on Stirling's series
+// (Abramowitz & Stegun 6.1.41; its first term left out, 691 / 360360 z^-11, is 1.1e-16 there); below, the series about 2
+// (6.1.33: log Gamma(2 + f) = (1 - gamma) f + sum over k >= 2 of (-1)^k (zeta(k) - 1) f^k / k, kLog2f its
+// coefficients from k = 2 on) at |f| <= 1/2 and the recurrence.  Error against 80 bits, rms: 9.3e-16
+// for x in 1..15 (the C library's 1.5e-15), 1.8e-14 in 15..100 (2.1e-14), 2.3e-13 in 100..1,000 (2.8e-13), below
+// 2e-17 from 0 to 1.5.
+__device__ __constant__ double kLog2f[] = {
+    0.3224670334241132, -0.0673523010531981, 0.020580808427784546, -0.007385551028673986, 0.0028905103307415234,
+    -0.001192753911703261, 0.0005096695247430425, -0.00022315475845357939, 9.945751278180853e-05,
+    -4.492623673813314e-05, 2.050721277567069e-05, -9.439488275268397e-06, 4.374866789907488e-06,
+    -2.039215753801366e-06, 9.55141213040742e-07, -4.492469198764566e-07, 2.1207184805554665e-07,
+    -1.0043224823968099e-07, 4.7698101693639804e-08, -2.2711094608943164e-08, 1.0838659214896955e-08,
+    -5.183475041970047e-09, 2.4836745438024785e-09, -1.1921401405860912e-09, 5.731367241678862e-10,
+    -2.7595228851242334e-10};
+__device__ __noinline__ double log_factorial(float x) {
+  const double z = (double)x + 1.0;
+  if (z < 16.0) {
+    const bool low = z < 1.5;
+    const double m = low ? -1.0 : rint(z) - 2.0, f = z - (m + 2.0);
+    double p = z, y = z;   // low: Gamma(z) = Gamma(z + 1) / z; otherwise (z - 1) ... (z - m) Gamma(z - m)
+    if (!low) p = 1.0;
+    for (int i = 0; i < 14 && i < (int)m; ++i) {
+      y -= 1.0;
+      p *= y;
+    }
+    constexpr int K = sizeof(kLog2f) / sizeof(double);
+    double q = kLog2f[K - 1];
+#pragma unroll 1   // (unrolled, the coefficients are held in registers across the pixels: 111 spills)
+    for (int k = K - 2; k >= 0; --k) q = fma(q, f, kLog2f[k]);
+    const double v = f * fma(f, q, 0.4227843350984671), l = log(p);
+    return low ? v - l : v + l;
+  }
+  const double r = 1.0 / z, r2 = r * r;
+  const double series =
+      r * fma(r2, fma(r2, fma(r2, fma(r2, 1.0 / 1188.0, -1.0 / 1680.0), 1.0 / 1260.0), -1.0 / 360.0), 1.0 / 12.0);
+  return fma(z - 0.5, log(z) - 1.0, series + 0.41893853320467274);   // (z - 1/2) log z - z + log(2 pi) / 2 + series
+}
+
 // The host's conditions on a source's estimate (the C entry's check of theta).
 __device__ __forceinline__ bool theta_in_range(const double* __restrict__ th) {
   bool ok = true;
@@ -271,13 +310,15 @@ __device__ __forceinline__ bool theta_in_range(const double* __restrict__ th) {
 // An image of the usual sizes is one or two passes of the block, so the loads of a pass are issued
 // together: rows that follow each other without gaps are read as one run of 16-byte pieces (4,096 px at
 // once; 1,024 px and their neighbour arrays), which need the 4-byte alignment of the pixels only; others pixel by
-// pixel, their row and column carried along instead of divided out.  What the table does not hold is
-// left to a second pass over the image, taken only where there is such a pixel (the library's lgamma
-// inside the unrolled loops took 219 registers), which also finds the negative and non-finite ones.
-// The registers are held to eight waves per SIMD (176 and two waves otherwise, for the second pass's lgamma,
-// whose spills only that pass meets: 1,180 us).  3.6e8 px of 4,000 uneven sources: 436 us; 1,950 us with 4
-// pixels per thread in flight, a division each and lgamma in the loop; 310 us at the rate of a large
-// copy.  1.4e8 px with neighbour arrays: 507 us (1,580).
+// pixel, their row and column carried along instead of divided out.  Pixels that are no count of the
+// table (calibrated images: every one) are left to a second pass over the image, taken only where there is one.
+// It reads the pixels in the same pieces and adds their log x!.  The registers allow eight waves per SIMD; log_factorial
+// is called, since inlined its registers came on top of the main pass's (counts in rows with gaps: 53 us).
+// 3.6e8 px of 4,000 uneven sources: 436 us; 1,950 us with 4 pixels per thread in flight, a division each
+// and lgamma in the loop; 310 us at the rate of a large copy.  1.4e8 px with neighbour arrays: 507 us (1,580).
+// 1.8e7 px of 2,000 sources, counts 32 us (110 before the second pass was split off), fractional values 108 (199;
+// 369 with the library's lgamma there, a division a pixel and one load in flight); in rows with gaps 37 and
+// 247 (109 and 308; 687); with neighbour arrays 81 and 161 (210 and 298; 443).
 __global__ __launch_bounds__(256, 8) void k_check_const(const ImgDev* __restrict__ imgs, const double* __restrict__ lfact,
                                                      double* __restrict__ out, int* __restrict__ bad, int n_img,
                                                      const double* __restrict__ theta, int n_src) {
@@ -295,7 +336,7 @@ __global__ __launch_bounds__(256, 8) void k_check_const(const ImgDev* __restrict
   const double sky = im.sky;
   const int t = threadIdx.x;
   double acc = 0.0;      // - log x!, and with neighbour arrays x log E_bg - E_bg
-  double sx = 0.0;       // without a neighbour mean: sum of x over the counts of the table
+  double sx = 0.0;       // without neighbour arrays: sum of x
   bool rare = false;     // a pixel that is no count of the table
   bool flag = false;     // a pixel or neighbour value out of range
   if (!ne && !nv) {
@@ -359,7 +400,7 @@ __global__ __launch_bounds__(256, 8) void k_check_const(const ImgDev* __restrict
       rare |= k < 0;
       flag |= !(e >= 0.f) || !(e < INFINITY) || !(v >= 0.f) || !(v < INFINITY);
       const double ebg = sky + (double)e;
-      acc += (k < 0 ? 0.0 : (double)x) * log(ebg) - ebg - lfact[max(k, 0)];
+      acc += (double)x * log(ebg) - ebg - lfact[max(k, 0)];
     };
     if (pitch == w && npitch == w) {
       const int n4 = n >> 2;
@@ -400,18 +441,52 @@ __global__ __launch_bounds__(256, 8) void k_check_const(const ImgDev* __restrict
     }
   }
   const bool one_sky = !ne && !nv;
-  if (one_sky) acc += log(sky) * sx;
   if (__syncthreads_or(rare)) {
+    const auto more = [&](float x) {
+      if (table_index(x) >= 0) return;
+      const bool ok = x >= 0.f && x < INFINITY;
+      flag |= !ok;
+      sx += (double)x;   // (with neighbour arrays the main pass has x's other term)
+      acc -= log_factorial(ok ? x : 0.f);
+    };
+    if (pitch == w) {
+      const int n4 = n >> 2;
 #pragma unroll 1
-    for (int m = t; m < n; m += 256) {
-      const int r = m / w, c = m - r * w;
-      const float x = px[(int64_t)r * pitch + c];
-      if (table_index(x) >= 0) continue;
-      flag |= !(x >= 0.f) || !(x < INFINITY);
-      const double ebg = sky + (ne ? (double)ne[(int64_t)r * npitch + c] : 0.0);
-      acc += (double)x * log(ebg) - lgamma((double)x + 1.0);
+      for (int m = t; m < n4; m += 256) {
+        V4 x = ((GlobalV4)px)[m];
+#pragma unroll 1
+        for (int j = 0; j < 4; ++j) {
+          more(x.x);
+          x = V4{x.y, x.z, x.w, x.x};
+        }
+      }
+      const int m = 4 * n4 + t;
+      if (m < n) more(px[m]);
+    } else {
+      const int dr = 256 / w, dc = 256 - dr * w;
+      int r = t / w, c = t - r * w;
+#pragma unroll 1
+      for (int m0 = t; m0 < n; m0 += 4 * 256) {
+        V4 x;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          x[u] = m0 + u * 256 < n ? px[(int64_t)r * pitch + c] : 0.f;
+          r += dr;
+          c += dc;
+          if (c >= w) {
+            c -= w;
+            ++r;
+          }
+        }
+#pragma unroll 1
+        for (int u = 0; u < 4; ++u) {
+          more(x.x);
+          x = V4{x.y, x.z, x.w, x.x};
+        }
+      }
     }
   }
+  if (one_sky) acc += log(sky) * sx;
   const double tot = block_sum<256>(acc, sh);
   if (t == 0) out[blockIdx.x] = one_sky ? tot - (double)n * sky : tot;
   if (flag) atomicOr(bad, FLAG_PIXELS);
