@@ -105,9 +105,13 @@ struct celeste_ctx {
   int n_cu = 0;                                    // compute units of the device
   DevBuf qbuf;                                     // the fits' device work queue
   bool lfact_ready = false;
-  DevBuf h_meta, h_items, h_out, h_pix, h_theta;   // pinned host staging: packed metadata, a subsample's items,
-                                                   // results, pixels of host batches, estimates,
+  DevBuf h_meta, h_items, h_out, h_theta;          // pinned host staging: packed metadata, a subsample's items,
+                                                   // tile lists, estimates,
   DevBuf h_poll;                                   // active counts of a fit's last two polls
+  DevBuf h_ring;                                   // pixels and results of host batches on their way: two pieces
+  hipEvent_t ring_ev[2] = {};                      // a piece's last copy, and whether there was one
+  bool ring_used[2] = {};
+  size_t ring_mapped = 0;                          // bytes of it, from its start, that have been used before
 };
 
 namespace {
@@ -608,17 +612,128 @@ int subsample_items(celeste_ctx* ctx, const celeste_batch* b, Packed* P, const u
   return rc;
 }
 
-// Copies host pixel arrays into one device staging buffer and repoints the images, through a pinned buffer
-// of at most PIX_STAGE bytes (a larger batch in as many turns).
-constexpr size_t PIX_STAGE = (size_t)64 << 20;
+// Host data on its way to or from the device goes through two pinned pieces taking turns, so that one is packed (or
+// emptied) while the other is copied.  A copy costs about 10 us beside its bytes, so that pieces of 1 MB are the best
+// for a few MB; but the first use of pinned memory costs 0.37 us a KB, its pages being mapped one by one, which
+// made a context's first call on 100 sources' pixels (3.5 MB) take 1,430 us with one pinned buffer
+// for all of them (670 us through pageable memory).  So the pieces begin with 256 KB each, or a 32nd of a
+// large transfer, and while a call waits for its kernels it maps more of the ring, which the next calls use:
+// 620 us for the first, 315 us in steady state (370 with one buffer, 420 pageable).
+constexpr size_t PIECE_MIN = (size_t)256 << 10, PIECE_MAX = (size_t)4 << 20;
 
+// The ring for a transfer of `bytes`, its pieces free: *piece bytes each, the second behind the first.
+int ring_for(celeste_ctx* ctx, size_t bytes, size_t* piece) {
+  for (int k = 0; k < 2; ++k) {
+    if (!ctx->ring_ev[k]) HIPCHK(hipEventCreateWithFlags(&ctx->ring_ev[k], hipEventDisableTiming));
+    if (ctx->ring_used[k]) HIPCHK(hipEventSynchronize(ctx->ring_ev[k]));   // (left by a call that failed)
+    ctx->ring_used[k] = false;
+  }
+  size_t p = PIECE_MIN;
+  while (p < PIECE_MAX && p * 4 < bytes) p *= 2;
+  if (2 * p > ctx->h_ring.cap) {
+    if (ctx->h_ring.p) (void)hipHostFree(ctx->h_ring.p);
+    ctx->h_ring = DevBuf{};
+    ctx->ring_mapped = 0;
+    CHK(ensure_host(ctx->h_ring, 2 * p));
+  }
+  const size_t least = std::max(PIECE_MIN, std::min(PIECE_MAX, bytes / 32 & ~(size_t)4095));
+  *piece = bytes <= 2 * PIECE_MIN ? 2 * PIECE_MIN : std::max(least, ctx->ring_mapped / 2 & ~(size_t)4095);
+  ctx->ring_mapped = std::max(ctx->ring_mapped, std::min(bytes, 2 * least));
+  return CELESTE_OK;
+}
+
+// Maps more of the ring for as long as the stream has work.
+void ring_map_more(celeste_ctx* ctx, hipStream_t st) {
+  const volatile unsigned char* p = as<unsigned char>(ctx->h_ring);
+  while (ctx->ring_mapped >= 2 * PIECE_MIN && ctx->ring_mapped < ctx->h_ring.cap && hipStreamQuery(st) == hipErrorNotReady) {
+    for (int k = 0; k < 8 && ctx->ring_mapped < ctx->h_ring.cap; ++k, ctx->ring_mapped += 4096) (void)p[ctx->ring_mapped];
+  }
+}
+
+int ring_mark(celeste_ctx* ctx, int k, hipStream_t st) {
+  HIPCHK(hipEventRecord(ctx->ring_ev[k], st));
+  ctx->ring_used[k] = true;
+  return CELESTE_OK;
+}
+
+int ring_wait(celeste_ctx* ctx, int k) {
+  if (ctx->ring_used[k]) HIPCHK(hipEventSynchronize(ctx->ring_ev[k]));
+  ctx->ring_used[k] = false;
+  return CELESTE_OK;
+}
+
+// A host array of h rows of w 4-byte elements, `pitch` elements apart, that goes to element `off` of a device buffer.
+struct Part {
+  const void* src;
+  size_t pitch, off;
+  int h, w;
+};
+
+// Copies the parts, in the order of their offsets and without gaps, to dst (`total` elements).  The copies are in the
+// stream when this returns.
+int ring_upload(celeste_ctx* ctx, const std::vector<Part>& parts, size_t total, void* dst, hipStream_t st) {
+  size_t piece;
+  CHK(ring_for(ctx, 4 * total, &piece));
+  piece /= 4;
+  const int n_pieces = (int)((total + piece - 1) / piece);
+  int rc = CELESTE_OK;             // the calling thread's
+  bool stop[2] = {false, false};   // whether it failed, as all threads see it behind piece q's barrier: stop[q & 1]
+  team(team_size((int64_t)(total / 512)), [&](int t, int nt, Barrier& bar) {   // a thread packs 4 MB in 60 us
+    for (int q = 0; q < n_pieces; ++q) {
+      const size_t p0 = q * piece, n = std::min(total - p0, piece);
+      unsigned char* buf = as<unsigned char>(ctx->h_ring) + (q & 1) * 4 * piece;
+      const size_t a = p0 + n * t / nt, e = p0 + n * (t + 1) / nt;   // this thread's elements
+      size_t k = std::upper_bound(parts.begin(), parts.end(), a, [](size_t v, const Part& p) { return v < p.off; }) -
+                 parts.begin() - 1;
+      for (size_t at = a; at < e; ++k) {
+        const Part& p = parts[k];
+        const size_t end = std::min(e, p.off + (size_t)p.h * p.w), r = (at - p.off) / p.w;
+        const unsigned char* row = static_cast<const unsigned char*>(p.src) + 4 * r * p.pitch;
+        for (size_t c = (at - p.off) - r * p.w; at < end; c = 0, row += 4 * p.pitch) {
+          const size_t m = std::min(end - at, (size_t)p.w - c);
+          std::memcpy(buf + 4 * (at - p0), row + 4 * c, 4 * m);
+          at += m;
+        }
+      }
+      if (t == 0) {
+        if (rc == CELESTE_OK && q + 1 < n_pieces) rc = ring_wait(ctx, (q + 1) & 1);
+        stop[q & 1] = rc != CELESTE_OK;
+      }
+      bar.wait();   // the piece is packed, and the next one free
+      if (stop[q & 1]) return;
+      if (t == 0) {
+        const hipError_t err = hipMemcpyAsync(static_cast<unsigned char*>(dst) + 4 * p0, buf, 4 * n, hipMemcpyHostToDevice, st);
+        rc = err != hipSuccess ? fail(CELESTE_E_DEVICE, "copy to the device: %s", hipGetErrorString(err))
+             : n_pieces > 1   ? ring_mark(ctx, q & 1, st)
+                              : CELESTE_OK;
+      }
+    }
+  });
+  return rc;
+}
+
+// Copies n doubles from src (device memory) to the host, piece by piece: give(values, first, count).
+template <class F>
+int ring_download(celeste_ctx* ctx, const double* src, size_t n, hipStream_t st, F give) {
+  size_t piece;
+  CHK(ring_for(ctx, sizeof(double) * n, &piece));
+  const size_t per = piece / sizeof(double), n_pieces = (n + per - 1) / per;
+  for (size_t q = 0; q <= n_pieces; ++q) {
+    if (q < n_pieces) {
+      HIPCHK(hipMemcpyAsync(as<unsigned char>(ctx->h_ring) + (q & 1) * piece, src + q * per,
+                            sizeof(double) * std::min(per, n - q * per), hipMemcpyDeviceToHost, st));
+      CHK(ring_mark(ctx, q & 1, st));
+    }
+    if (q == 0) continue;
+    const size_t at = (q - 1) * per;
+    CHK(ring_wait(ctx, (q - 1) & 1));
+    give(reinterpret_cast<const double*>(as<unsigned char>(ctx->h_ring) + ((q - 1) & 1) * piece), at, std::min(per, n - at));
+  }
+  return CELESTE_OK;
+}
+
+// Copies host pixel arrays into one device staging buffer and repoints the images.
 int stage_host_pixels(celeste_ctx* ctx, const celeste_batch* b, Packed* P, hipStream_t st) {
-  // the arrays in their order, each as h rows of w pixels
-  struct Part {
-    const float* src;
-    size_t pitch, off;   // off: first pixel in the staging buffer
-    int h, w;
-  };
   std::vector<Part> parts;
   parts.reserve((size_t)P->n_img);
   size_t total = 0;
@@ -627,35 +742,15 @@ int stage_host_pixels(celeste_ctx* ctx, const celeste_batch* b, Packed* P, hipSt
     const float* srcs[3] = {im.pixels, im.nbr_mean, im.nbr_var};
     for (int k = 0; k < 3; ++k) {
       if (!srcs[k]) continue;
-      parts.push_back(Part{srcs[k], k == 0 ? (size_t)im.pitch : (size_t)(im.nbr_pitch ? im.nbr_pitch : im.pitch), total,
-                           im.h, im.w});
+      const int pitch = k == 0 || !im.nbr_pitch ? im.pitch : im.nbr_pitch;
+      const bool gaps = pitch != im.w;   // rows without them are packed as one
+      parts.push_back(Part{srcs[k], (size_t)pitch, total, gaps ? im.h : 1, gaps ? im.w : im.h * im.w});
       total += (size_t)im.h * im.w;
     }
   }
   CHK(ensure(ctx->staging, total * sizeof(float)));
   float* base = as<float>(ctx->staging);
-  const size_t cap = std::min(total, PIX_STAGE / sizeof(float));   // pixels per turn
-  CHK(ensure_host(ctx->h_pix, cap * sizeof(float)));
-  float* pin = as<float>(ctx->h_pix);
-  for (size_t p0 = 0; p0 < total; p0 += cap) {
-    const size_t p1 = std::min(total, p0 + cap);
-    if (p0 > 0) HIPCHK(hipStreamSynchronize(st));   // the pinned buffer is free again
-    team(team_size((int64_t)((p1 - p0) / 64)), [&](int t, int nt, Barrier&) {
-      const size_t a = p0 + (p1 - p0) * t / nt, e = p0 + (p1 - p0) * (t + 1) / nt;   // this thread's pixels
-      size_t k = std::upper_bound(parts.begin(), parts.end(), a, [](size_t v, const Part& p) { return v < p.off; }) -
-                 parts.begin() - 1;
-      for (size_t at = a; at < e; ++k) {
-        const Part& p = parts[k];
-        const size_t end = std::min(e, p.off + (size_t)p.h * p.w);
-        while (at < end) {
-          const size_t r = (at - p.off) / p.w, c = (at - p.off) - r * p.w, n = std::min(end - at, (size_t)p.w - c);
-          std::memcpy(pin + (at - p0), p.src + r * p.pitch + c, sizeof(float) * n);
-          at += n;
-        }
-      }
-    });
-    HIPCHK(hipMemcpyAsync(base + p0, pin, (p1 - p0) * sizeof(float), hipMemcpyHostToDevice, st));
-  }
+  CHK(ring_upload(ctx, parts, total, base, st));
   size_t k = 0;
   for (int i = 0; i < P->n_img; ++i) {
     const celeste_image& im = b->images[i];
@@ -893,8 +988,10 @@ void celeste_ctx_destroy(celeste_ctx* c) {
                     &c->lfact, &c->lb_buf, &c->imgs_s, &c->items_s, &c->srcs_s, &c->partials_s, &c->qbuf};
   for (DevBuf* b : bufs)
     if (b->p) (void)hipFree(b->p);
-  for (DevBuf* b : {&c->h_meta, &c->h_items, &c->h_out, &c->h_pix, &c->h_theta, &c->h_poll})
+  for (DevBuf* b : {&c->h_meta, &c->h_items, &c->h_out, &c->h_theta, &c->h_poll, &c->h_ring})
     if (b->p) (void)hipHostFree(b->p);
+  for (hipEvent_t e : c->ring_ev)
+    if (e) (void)hipEventDestroy(e);
   (void)hipStreamDestroy(c->stream);
   delete c;
 }
@@ -1070,7 +1167,6 @@ int celeste_lr_covariance(celeste_ctx* ctx, const celeste_batch* b, const double
 namespace {
 
 int scratch_bufs(celeste_ctx* ctx, const Packed* P, int per_item, EvalBufs* B);
-constexpr size_t OUT_STAGE = (size_t)16 << 20;
 void scratch_lfact_filled(int device);
 
 int eval_impl(celeste_ctx* ctx, const celeste_batch* b, const double* theta, double* elbo, double* grad,
@@ -1121,13 +1217,11 @@ int eval_impl(celeste_ctx* ctx, const celeste_batch* b, const double* theta, dou
     CHK(ensure(ctx->kept, sizeof(int) * std::max<size_t>(1, kept_rows.size())));
     kept = as<int>(ctx->kept);
   }
-  // results of a host batch: one device block, read back through pinned memory (of at most OUT_STAGE bytes)
+  // results of a host batch: one device block, read back through the ring
   const size_t n_out = S * (1 + (grad ? NP : 0) + (hess ? NP * NP : 0));
-  const bool pinned = on_host && n_out * sizeof(double) <= OUT_STAGE;
   double *d_elbo = elbo, *d_grad = grad, *d_hess = hess;
   if (on_host) {
     CHK(ensure(ctx->o_elbo, sizeof(double) * n_out));
-    if (pinned) CHK(ensure_host(ctx->h_out, sizeof(double) * n_out));
     d_elbo = as<double>(ctx->o_elbo);
     if (grad) d_grad = d_elbo + S;
     if (hess) d_hess = d_grad + S * NP;
@@ -1164,9 +1258,12 @@ int eval_impl(celeste_ctx* ctx, const celeste_batch* b, const double* theta, dou
     launches = &ctx->stats.value_launches;
   }
   T.mark(3, st);
+  if (on_host) ring_map_more(ctx, st);
   int bad = 0;
   HIPCHK(hipMemcpyAsync(&bad, B.flag, sizeof(int), hipMemcpyDeviceToHost, st));
-  if (pinned) HIPCHK(hipMemcpyAsync(ctx->h_out.p, d_elbo, sizeof(double) * n_out, hipMemcpyDeviceToHost, st));
+  // (the pixels' copies out of the ring are ahead in the stream)
+  const bool one_copy = on_host && sizeof(double) * n_out <= ctx->ring_mapped;
+  if (one_copy) HIPCHK(hipMemcpyAsync(ctx->h_ring.p, d_elbo, sizeof(double) * n_out, hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
   if (noalloc) {
     if (B.lfact_ready) scratch_lfact_filled(ctx->device);
@@ -1182,16 +1279,20 @@ int eval_impl(celeste_ctx* ctx, const celeste_batch* b, const double* theta, dou
   }
   if (bad) return pixel_error();
   *launches += 1;
-  if (pinned) {
-    const double* h = as<double>(ctx->h_out);
-    std::memcpy(elbo, h, sizeof(double) * S);
-    if (grad) std::memcpy(grad, h + S, sizeof(double) * S * NP);
-    if (hess) std::memcpy(hess, h + S + S * NP, sizeof(double) * S * NP * NP);
-  } else if (on_host) {
-    HIPCHK(hipMemcpyAsync(elbo, d_elbo, sizeof(double) * S, hipMemcpyDeviceToHost, st));
-    if (grad) HIPCHK(hipMemcpyAsync(grad, d_grad, sizeof(double) * NP * S, hipMemcpyDeviceToHost, st));
-    if (hess) HIPCHK(hipMemcpyAsync(hess, d_hess, sizeof(double) * NP * NP * S, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
+  if (on_host) {
+    // entries [at, at + n) of the results at src to the caller's arrays
+    const auto give = [&](const double* src, size_t at, size_t n) {
+      const size_t sizes[3] = {S, grad ? S * NP : 0, hess ? S * NP * NP : 0};
+      double* const to[3] = {elbo, grad, hess};
+      for (size_t k = 0, first = 0; k < 3; first += sizes[k++]) {
+        const size_t b0 = std::max(at, first), b1 = std::min(at + n, first + sizes[k]);
+        if (b0 < b1) std::memcpy(to[k] + (b0 - first), src + (b0 - at), sizeof(double) * (b1 - b0));
+      }
+    };
+    if (one_copy)
+      give(as<double>(ctx->h_ring), 0, n_out);
+    else
+      CHK(ring_download(ctx, d_elbo, n_out, st, give));
   }
   if (T.on) {
     ctx->stats.ms_setup += T.span(0, 1);
