@@ -10,6 +10,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -90,7 +91,7 @@ struct celeste_ctx {
   celeste_net* net = nullptr;   // surrogate network (not owned)
   DevBuf sur;                   // surrogate predictions (float, S x 27)
   DevBuf tile_off, img_field, nbr_off;             // crowded-field index buffers
-  DevBuf tables2, fsky;                            // second setup table (field updates), field skies
+  DevBuf tables2, fsky, theta_flag;                // second setup table (field updates), field skies, estimates' check
   DevBuf kept;                                     // first rows of the kept blocks of a pixel subsample
   DevBuf lr_in, lr_cov, lr_status, lr_eval;        // linear-response covariance staging
   DevBuf lfact;                                    // log n! table of the pixel constants
@@ -105,9 +106,9 @@ struct celeste_ctx {
   int n_cu = 0;                                    // compute units of the device
   DevBuf qbuf;                                     // the fits' device work queue
   bool lfact_ready = false;
-  DevBuf h_meta, h_items, h_out, h_theta;          // pinned host staging: packed metadata, a subsample's items,
-                                                   // tile lists, estimates,
-  DevBuf h_poll;                                   // active counts of a fit's last two polls
+  DevBuf h_meta, h_items, h_lists;                 // pinned host staging: packed metadata, a subsample's items,
+                                                   // tile lists,
+  DevBuf h_poll, h_flags;                          // active counts of a fit's last two polls; theta_flag read back
   DevBuf h_ring;                                   // pixels and results of host batches on their way: two pieces
   hipEvent_t ring_ev[2] = {};                      // a piece's last copy, and whether there was one
   bool ring_used[2] = {};
@@ -825,6 +826,15 @@ int upload_in(celeste_ctx* ctx, const celeste_batch* b, Packed* P, EvalBufs* B, 
   return CELESTE_OK;
 }
 
+// The error of estimates (device memory) of which the device found one out of range.
+int theta_error(const double* theta, size_t n, hipStream_t st) {
+  std::vector<double> h(NP * n);
+  HIPCHK(hipMemcpyAsync(h.data(), theta, sizeof(double) * NP * n, hipMemcpyDeviceToHost, st));
+  HIPCHK(hipStreamSynchronize(st));
+  CHK(check_thetas(h.data(), (int64_t)n));
+  return fail(CELESTE_E_INVALID, "theta out of range");
+}
+
 int pixel_error() { return fail(CELESTE_E_INVALID, "pixel or neighbour arrays hold negative or non-finite values"); }
 
 // upload_in on the context's own buffers; waits for the check of the pixels.
@@ -983,12 +993,12 @@ void celeste_ctx_destroy(celeste_ctx* c) {
   (void)hipStreamSynchronize(c->stream);
   DevBuf* bufs[] = {&c->meta, &c->items_kept, &c->tables, &c->partials, &c->img_const, &c->staging,
                     &c->theta, &c->o_elbo, &c->o_grad, &c->o_hess, &c->st_buf, &c->ctr, &c->sur,
-                    &c->tile_off, &c->img_field, &c->nbr_off, &c->tables2, &c->fsky,
+                    &c->tile_off, &c->img_field, &c->nbr_off, &c->tables2, &c->fsky, &c->theta_flag,
                     &c->kept, &c->lr_in, &c->lr_cov, &c->lr_status, &c->lr_eval,
                     &c->lfact, &c->lb_buf, &c->imgs_s, &c->items_s, &c->srcs_s, &c->partials_s, &c->qbuf};
   for (DevBuf* b : bufs)
     if (b->p) (void)hipFree(b->p);
-  for (DevBuf* b : {&c->h_meta, &c->h_items, &c->h_out, &c->h_theta, &c->h_poll, &c->h_ring})
+  for (DevBuf* b : {&c->h_meta, &c->h_items, &c->h_lists, &c->h_poll, &c->h_flags, &c->h_ring})
     if (b->p) (void)hipHostFree(b->p);
   for (hipEvent_t e : c->ring_ev)
     if (e) (void)hipEventDestroy(e);
@@ -1270,13 +1280,7 @@ int eval_impl(celeste_ctx* ctx, const celeste_batch* b, const double* theta, dou
   } else {
     ctx->lfact_ready = ctx->lfact_ready || B.lfact_ready;
   }
-  if (bad & FLAG_THETA) {   // read them back for the message
-    th_host.resize(NP * S);
-    HIPCHK(hipMemcpyAsync(th_host.data(), theta, sizeof(double) * NP * S, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
-    CHK(check_thetas(th_host.data(), (int64_t)S));
-    return fail(CELESTE_E_INVALID, "theta out of range");
-  }
+  if (bad & FLAG_THETA) return theta_error(theta, S, st);
   if (bad) return pixel_error();
   *launches += 1;
   if (on_host) {
@@ -2348,23 +2352,36 @@ int check_fields(const celeste_batch* b, const Packed& P, const celeste_fields* 
   return bad < P.n_img ? check_patch(b, f, bad) : CELESTE_OK;
 }
 
-// Device memory estimates, read back and checked.
-int check_device_theta(celeste_ctx* ctx, const Packed& P, const double* theta, hipStream_t st) {
-  if (!theta) return fail(CELESTE_E_INVALID, "theta is NULL");
-  const size_t bytes = sizeof(double) * NP * (size_t)P.n_src;
-  CHK(ensure_host(ctx->h_theta, bytes));
-  HIPCHK(hipMemcpyAsync(ctx->h_theta.p, theta, bytes, hipMemcpyDeviceToHost, st));
+// Checks estimates in device memory there (th2: a second array, or null); they are read back for the message where
+// one is out of range.  The flags are 0 between calls.
+int check_device_theta(celeste_ctx* ctx, const Packed& P, const double* th1, const double* th2, hipStream_t st) {
+  const double* th[2] = {th1, th2};
+  if (!ctx->theta_flag.p) {
+    CHK(ensure(ctx->theta_flag, sizeof(int) * 2));
+    HIPCHK(launch_zero_int(as<int>(ctx->theta_flag), 2, st));
+  }
+  CHK(ensure_host(ctx->h_flags, sizeof(int) * 2));
+  for (int k = 0; k < 2; ++k)
+    if (th[k]) HIPCHK(launch_check_theta(th[k], P.n_src, as<int>(ctx->theta_flag) + k, st));
+  HIPCHK(hipMemcpyAsync(ctx->h_flags.p, ctx->theta_flag.p, sizeof(int) * 2, hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
-  return check_thetas(as<double>(ctx->h_theta), P.n_src);
+  const int* bad = as<int>(ctx->h_flags);
+  if (!bad[0] && !bad[1]) return CELESTE_OK;
+  HIPCHK(launch_zero_int(as<int>(ctx->theta_flag), 2, st));
+  return theta_error(bad[0] ? th1 : th2, (size_t)P.n_src, st);
 }
 
 // The images whose patch meets each RT x RT tile of the fields, in image order: offsets (n_tiles + 1) and, behind
-// them, the lists, in the context's pinned buffer.  The fields are shared out over host threads.
+// them, the lists, into ctx->tile_off.  The fields are shared out over host threads.  Lists of up to LIST_PINNED
+// bytes are formed in the context's pinned memory; larger ones on the heap, for this call.
 constexpr int RT = 32;
-int tile_lists(celeste_ctx* ctx, const std::vector<Patch>& pt, int n_fields, int tx, int tpf, int64_t* n_ints) {
+constexpr size_t LIST_PINNED = (size_t)8 << 20;
+int tile_lists(celeste_ctx* ctx, const std::vector<Patch>& pt, int n_fields, int tx, int tpf, hipStream_t st) {
   const int64_t n = (int64_t)pt.size();
   const int n_tiles = tpf * n_fields;
   std::vector<int> pos((size_t)n_tiles, 0);   // counts, then the next place of each tile
+  std::unique_ptr<int[]> heap;
+  size_t n_ints = 0;
   int* out = nullptr;
   int rc = CELESTE_OK;
   team(std::min(team_size(8 * n), n_fields), [&](int t, int nt, Barrier& bar) {
@@ -2382,12 +2399,18 @@ int tile_lists(celeste_ctx* ctx, const std::vector<Patch>& pt, int n_fields, int
     if (t == 0) {
       int64_t total = 0;
       for (int k = 0; k < n_tiles; ++k) total += pos[k];
-      if (total > INT32_MAX)
+      n_ints = (size_t)n_tiles + 1 + (size_t)total;
+      if (total > INT32_MAX) {
         rc = fail(CELESTE_E_INVALID, "too many patch tiles");
-      else
-        rc = ensure_host(ctx->h_out, sizeof(int) * (size_t)(n_tiles + 1 + total));
+      } else if (n_ints * sizeof(int) <= LIST_PINNED) {
+        rc = ensure_host(ctx->h_lists, n_ints * sizeof(int));
+        out = as<int>(ctx->h_lists);
+      } else {
+        heap.reset(new (std::nothrow) int[n_ints]);
+        out = heap.get();
+        if (!out) rc = fail(CELESTE_E_NOMEM, "host allocation of %zu bytes failed", n_ints * sizeof(int));
+      }
       if (rc == CELESTE_OK) {
-        out = as<int>(ctx->h_out);
         int at = 0;
         for (int k = 0; k < n_tiles; ++k) {
           out[k] = at;
@@ -2395,13 +2418,23 @@ int tile_lists(celeste_ctx* ctx, const std::vector<Patch>& pt, int n_fields, int
           pos[k] = out[k];
         }
         out[n_tiles] = at;
-        *n_ints = n_tiles + 1 + total;
       }
     }
     bar.wait();
-    if (rc == CELESTE_OK) each([&](int tile, int i) { out[n_tiles + 1 + pos[tile]++] = i; });
+    if (rc == CELESTE_OK) each([&](int tile, int i) { out[(size_t)n_tiles + 1 + pos[tile]++] = i; });
   });
-  return rc;
+  CHK(rc);
+  CHK(ensure(ctx->tile_off, n_ints * sizeof(int)));
+  if (heap) {
+    constexpr size_t W = (size_t)1 << 20;
+    const size_t rows = n_ints / W;
+    std::vector<Part> parts;
+    if (rows) parts.push_back(Part{out, W, 0, (int)rows, (int)W});
+    if (n_ints % W) parts.push_back(Part{out + rows * W, W, rows * W, 1, (int)(n_ints % W)});
+    return ring_upload(ctx, parts, n_ints, ctx->tile_off.p, st);
+  }
+  HIPCHK(hipMemcpyAsync(ctx->tile_off.p, out, n_ints * sizeof(int), hipMemcpyHostToDevice, st));
+  return CELESTE_OK;
 }
 
 }  // namespace
@@ -2415,7 +2448,8 @@ int celeste_render_fields(celeste_ctx* ctx, const celeste_batch* b, const double
   CHK(check_fields(b, P, f, &patches));
   HIPCHK(hipSetDevice(ctx->device));
   const hipStream_t st = ctx->stream;
-  CHK(check_device_theta(ctx, P, theta, st));
+  if (!theta) return fail(CELESTE_E_INVALID, "theta is NULL");
+  CHK(check_device_theta(ctx, P, theta, nullptr, st));
   const int tx = (f->width + RT - 1) / RT, ty = (f->height + RT - 1) / RT;
   const int64_t n_tiles64 = (int64_t)tx * ty * f->n_fields;
   if ((int64_t)tx * ty > INT32_MAX || n_tiles64 > INT32_MAX / 2) return fail(CELESTE_E_INVALID, "too many tiles");
@@ -2423,15 +2457,12 @@ int celeste_render_fields(celeste_ctx* ctx, const celeste_batch* b, const double
   // the metadata and the setup tables are under way while the lists are formed
   CHK(prepare(ctx, b, &P, st, false));
   HIPCHK(launch_setup(as<ImgDev>(ctx->imgs), P.n_img, theta, nullptr, P.prof, as<float>(ctx->tables), P.tstride, st, false));
-  int64_t n_ints = 0;
-  int rc = tile_lists(ctx, patches, f->n_fields, tx, tpf, &n_ints);
-  if (rc == CELESTE_OK) rc = ensure(ctx->tile_off, sizeof(int) * (size_t)n_ints);
+  const int rc = tile_lists(ctx, patches, f->n_fields, tx, tpf, st);
   if (rc != CELESTE_OK) {
     (void)hipStreamSynchronize(st);   // the pinned metadata is free again
     return rc;
   }
-  int* off = as<int>(ctx->tile_off);
-  HIPCHK(hipMemcpyAsync(off, ctx->h_out.p, sizeof(int) * (size_t)n_ints, hipMemcpyHostToDevice, st));
+  const int* off = as<int>(ctx->tile_off);
   HIPCHK(launch_render(off, off + n_tiles + 1, n_tiles, as<ImgDev>(ctx->imgs), as<float>(ctx->tables),
                        P.tstride, P.prof.n_exp, P.prof.n_dev, f->height, f->width, tx, tpf, ctx->e_zero, f->mean,
                        f->var, st));
@@ -2449,7 +2480,8 @@ int celeste_neighbour_arrays(celeste_ctx* ctx, const celeste_batch* b, const dou
     if (nbr_off[i] < 0) return fail(CELESTE_E_INVALID, "negative neighbour offset");
   HIPCHK(hipSetDevice(ctx->device));
   const hipStream_t st = ctx->stream;
-  CHK(check_device_theta(ctx, P, theta, st));
+  if (!theta) return fail(CELESTE_E_INVALID, "theta is NULL");
+  CHK(check_device_theta(ctx, P, theta, nullptr, st));
   CHK(ensure(ctx->img_field, sizeof(int) * P.n_img));
   CHK(ensure(ctx->nbr_off, sizeof(long long) * P.n_img));
   CHK(prepare(ctx, b, &P, st, false));
@@ -2506,8 +2538,9 @@ int celeste_update_fields(celeste_ctx* ctx, const celeste_batch* b, const double
   CHK(check_disjoint(patches, f->n_fields));
   HIPCHK(hipSetDevice(ctx->device));
   const hipStream_t st = ctx->stream;
-  CHK(check_device_theta(ctx, P, theta_old, st));
-  CHK(check_device_theta(ctx, P, theta_new, st));
+  if (theta_old && !theta_new) CHK(check_device_theta(ctx, P, theta_old, nullptr, st));   // its error comes first
+  if (!theta_old || !theta_new) return fail(CELESTE_E_INVALID, "theta is NULL");
+  CHK(check_device_theta(ctx, P, theta_old, theta_new, st));
   CHK(ensure(ctx->tables2, sizeof(float) * (size_t)P.tstride * P.n_img));
   CHK(ensure(ctx->img_field, sizeof(int) * P.n_img));
   CHK(prepare(ctx, b, &P, st, false));
@@ -2534,7 +2567,8 @@ int celeste_field_elbo(celeste_ctx* ctx, const celeste_batch* b, const double* t
       return fail(CELESTE_E_INVALID, "field %d: sky must be finite and > 0", k);
   HIPCHK(hipSetDevice(ctx->device));
   const hipStream_t st = ctx->stream;
-  CHK(check_device_theta(ctx, P, theta, st));
+  if (!theta) return fail(CELESTE_E_INVALID, "theta is NULL");
+  CHK(check_device_theta(ctx, P, theta, nullptr, st));
   const int S = P.n_src;
   const int64_t n = (int64_t)f->n_fields * f->height * f->width;
   const int per_block = 8192;

@@ -129,6 +129,8 @@ constexpr int LFACT_N = 1 << 16;
 hipError_t launch_lfact(double* table, hipStream_t st);
 hipError_t launch_check_const(const ImgDev* imgs, int n_img, const double* lfact, double* img_const, int* bad,
                               hipStream_t st, const double* theta = nullptr, int n_src = 0);
+// ... of theta alone
+hipError_t launch_check_theta(const double* theta, int n_src, int* bad, hipStream_t st);
 // tw_log2: log2 of the pixel-tile width (3..6; tiles hold 64 pixels).  kept: nullptr for
 // dense work items; for a pixel subsample, the first rows of the kept 8-row blocks, and each
 // item's [row_begin, row_end) indexes this list instead of rows.

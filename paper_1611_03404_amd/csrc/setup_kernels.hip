@@ -576,6 +576,13 @@ hipError_t launch_check_const(const ImgDev* imgs, int n_img, const double* lfact
   return e != hipSuccess ? e : launch(0, n_src);
 }
 
+hipError_t launch_check_theta(const double* theta, int n_src, int* bad, hipStream_t st) {
+  if (n_src <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_check_const, dim3((n_src + 255) / 256), dim3(256), 0, st, nullptr, nullptr, nullptr, bad, 0, theta,
+                     n_src);
+  return hipGetLastError();
+}
+
 hipError_t launch_plain_init(const SrcDev* srcs, int n_src, const ImgDev* imgs, PriorDev prior, double* theta,
                              hipStream_t s) {
   if (n_src <= 0) return hipSuccess;
