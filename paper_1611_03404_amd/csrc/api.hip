@@ -80,7 +80,7 @@ struct celeste_ctx {
   bool exp2_flushes = false;   // the device's exp2 returns 0 below 2^-126 (checked at creation)
   int vblock = 256;      // value kernel block size
   int vtile_log2 = 3;    // log2 tile width of the value kernel
-  DevBuf meta, items_kept;                // packed metadata (one upload); a subsample's work items
+  DevBuf meta, items_kept;                // packed metadata (one upload); a subsample's work items and kept rows
   DevBuf imgs, items, srcs, flag;         // where the last pack's parts lie in them (views, not owned)
   DevBuf tables, partials, img_const, staging, theta, o_elbo, o_grad, o_hess;
   DevBuf st_buf;   // all trust-region state in one allocation
@@ -92,7 +92,6 @@ struct celeste_ctx {
   DevBuf sur;                   // surrogate predictions (float, S x 27)
   DevBuf tile_off, img_field, nbr_off;             // crowded-field index buffers
   DevBuf tables2, fsky, theta_flag;                // second setup table (field updates), field skies, estimates' check
-  DevBuf kept;                                     // first rows of the kept blocks of a pixel subsample
   DevBuf lr_in, lr_cov, lr_status, lr_eval;        // linear-response covariance staging
   DevBuf lfact;                                    // log n! table of the pixel constants
   DevBuf lb_buf;                                   // L-BFGS state beyond the fit state
@@ -301,7 +300,10 @@ struct Packed {
   WorkItem* items = nullptr;
   unsigned char* block = nullptr;
   size_t o_srcs = 0, o_items = 0, o_flag = 0, bytes = 0;   // parts of the block
-  bool own_items = false;                                  // the items lie outside it (a pixel subsample)
+  // a pixel subsample's items lie in a block of their own, [work items | first rows of the kept blocks]
+  bool own_items = false;
+  int* kept_rows = nullptr;
+  size_t o_kept = 0, items_bytes = 0;
   PriorDev prior;
   ProfDev prof;
   int tstride = 0;
@@ -526,7 +528,7 @@ int validate_and_pack(celeste_ctx* ctx, const celeste_batch* b, Packed* P, HostP
 // adjacent), and its [row_begin, row_end) indexes kept_rows.  The item ranges of the images
 // and sources and the sources' pixel counts follow.  keep / keep_off: host arrays.
 int subsample_items(celeste_ctx* ctx, const celeste_batch* b, Packed* P, const uint8_t* keep,
-                    const int64_t* keep_off, std::vector<int>& kept_rows) {
+                    const int64_t* keep_off) {
   if (keep_off[0] != 0) return fail(CELESTE_E_INVALID, "keep_off[0] must be 0");
   const int64_t off_bad = first_failure(
       P->n_img, [&](int64_t i) { return keep_off[i + 1] - keep_off[i] == (b->images[i].h + 7) / 8; });
@@ -567,20 +569,16 @@ int subsample_items(celeste_ctx* ctx, const celeste_batch* b, Packed* P, const u
         all.rows += sl[k].rows;
         all.items += sl[k].items;
       }
+      P->o_kept = align256(sizeof(WorkItem) * (size_t)all.items);
+      P->items_bytes = P->o_kept + sizeof(int) * (size_t)all.rows;
       if (all.rows > (int64_t)INT32_MAX / 2)
         rc = fail(CELESTE_E_INVALID, "too many kept blocks");
       else if (all.items > (int64_t)INT32_MAX / 2)
         rc = fail(CELESTE_E_INVALID, "too many work items");
       else
-        rc = ensure_host(ctx->h_items, sizeof(WorkItem) * std::max<int64_t>(1, all.items));
-      if (rc == CELESTE_OK) {
-        try {
-          kept_rows.resize((size_t)all.rows);
-        } catch (const std::bad_alloc&) {
-          rc = fail(CELESTE_E_NOMEM, "host allocation of the kept blocks failed");
-        }
-      }
+        rc = ensure_host(ctx->h_items, P->items_bytes);
       P->items = as<WorkItem>(ctx->h_items);
+      P->kept_rows = reinterpret_cast<int*>(as<unsigned char>(ctx->h_items) + P->o_kept);
       P->own_items = true;
       P->n_items = (int)all.items;
     }
@@ -599,7 +597,7 @@ int subsample_items(celeste_ctx* ctx, const celeste_batch* b, Packed* P, const u
         const int64_t first = row;
         for (int j = 0; j < nb; ++j)
           if (k[j]) {
-            kept_rows[row++] = TILE * j;
+            P->kept_rows[row++] = TILE * j;
             sd.npix += (int64_t)(std::min(im.h, TILE * (j + 1)) - TILE * j) * im.w;
           }
         d.item_begin = (int)it;
@@ -789,7 +787,7 @@ struct EvalBufs {
 // The context's own buffers, grown to the batch.
 int ctx_bufs(celeste_ctx* ctx, const Packed* P, EvalBufs* B) {
   CHK(ensure(ctx->meta, P->bytes));
-  if (P->own_items) CHK(ensure(ctx->items_kept, sizeof(WorkItem) * P->n_items));
+  if (P->own_items) CHK(ensure(ctx->items_kept, P->items_bytes));
   CHK(ensure(ctx->img_const, sizeof(double) * P->n_img));
   CHK(ensure(ctx->tables, sizeof(float) * (size_t)P->tstride * P->n_img));
   CHK(ensure(ctx->partials, sizeof(double) * (size_t)NACC * P->n_items));
@@ -816,7 +814,7 @@ int upload_in(celeste_ctx* ctx, const celeste_batch* b, Packed* P, EvalBufs* B, 
   if (b->mem_kind == CELESTE_MEM_HOST) CHK(stage_host_pixels(ctx, b, P, st));
   HIPCHK(hipMemcpyAsync(B->imgs, P->block, P->bytes, hipMemcpyHostToDevice, st));
   if (P->own_items && P->n_items > 0)
-    HIPCHK(hipMemcpyAsync(B->items, P->items, sizeof(WorkItem) * P->n_items, hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(B->items, P->items, P->items_bytes, hipMemcpyHostToDevice, st));
   if (!pixels) return CELESTE_OK;
   if (!B->lfact_ready) {
     HIPCHK(launch_lfact(B->lfact, st));
@@ -994,7 +992,7 @@ void celeste_ctx_destroy(celeste_ctx* c) {
   DevBuf* bufs[] = {&c->meta, &c->items_kept, &c->tables, &c->partials, &c->img_const, &c->staging,
                     &c->theta, &c->o_elbo, &c->o_grad, &c->o_hess, &c->st_buf, &c->ctr, &c->sur,
                     &c->tile_off, &c->img_field, &c->nbr_off, &c->tables2, &c->fsky, &c->theta_flag,
-                    &c->kept, &c->lr_in, &c->lr_cov, &c->lr_status, &c->lr_eval,
+                    &c->lr_in, &c->lr_cov, &c->lr_status, &c->lr_eval,
                     &c->lfact, &c->lb_buf, &c->imgs_s, &c->items_s, &c->srcs_s, &c->partials_s, &c->qbuf};
   for (DevBuf* b : bufs)
     if (b->p) (void)hipFree(b->p);
@@ -1212,9 +1210,8 @@ int eval_impl(celeste_ctx* ctx, const celeste_batch* b, const double* theta, dou
     CHK(check_thetas(th_host.data(), (int64_t)S));
   }
   double px_weight = 1.0;
-  std::vector<int> kept_rows;
   if (keep) {
-    CHK(subsample_items(ctx, b, &P, keep, keep_off, kept_rows));
+    CHK(subsample_items(ctx, b, &P, keep, keep_off));
     px_weight = 1.0 / keep_prob;
   }
   EvalBufs B;
@@ -1222,11 +1219,7 @@ int eval_impl(celeste_ctx* ctx, const celeste_batch* b, const double* theta, dou
     CHK(scratch_bufs(ctx, &P, grad ? (hess ? NACC : NGRAD) : 1, &B));
   else
     CHK(ctx_bufs(ctx, &P, &B));
-  const int* kept = nullptr;
-  if (keep) {
-    CHK(ensure(ctx->kept, sizeof(int) * std::max<size_t>(1, kept_rows.size())));
-    kept = as<int>(ctx->kept);
-  }
+  const int* kept = keep ? reinterpret_cast<int*>(as<unsigned char>(ctx->items_kept) + P.o_kept) : nullptr;
   // results of a host batch: one device block, read back through the ring
   const size_t n_out = S * (1 + (grad ? NP : 0) + (hess ? NP * NP : 0));
   double *d_elbo = elbo, *d_grad = grad, *d_hess = hess;
@@ -1237,8 +1230,6 @@ int eval_impl(celeste_ctx* ctx, const celeste_batch* b, const double* theta, dou
     if (hess) d_hess = d_grad + S * NP;
   }
   CHK(upload_in(ctx, b, &P, &B, st, true, check_on_device ? th_dev : nullptr));
-  if (!kept_rows.empty())
-    HIPCHK(hipMemcpyAsync(ctx->kept.p, kept_rows.data(), sizeof(int) * kept_rows.size(), hipMemcpyHostToDevice, st));
   PhaseTimer T;
   CHK(T.init(ctx->profile != 0 && !noalloc));   // events are not created on the no-allocation path
   T.mark(0, st);
@@ -1911,26 +1902,22 @@ int run_fit_sampled(celeste_ctx* ctx, const celeste_batch* b, double* theta_inou
   Packed Ps = P;
   Ps.imgs = img_copy.data();
   Ps.srcs = src_copy.data();
-  std::vector<int> kept_rows;
-  CHK(subsample_items(ctx, b, &Ps, keep, keep_off, kept_rows));
+  CHK(subsample_items(ctx, b, &Ps, keep, keep_off));
   CHK(ensure(ctx->imgs_s, sizeof(ImgDev) * Ps.n_img));
-  CHK(ensure(ctx->items_s, sizeof(WorkItem) * std::max(1, Ps.n_items)));
+  CHK(ensure(ctx->items_s, Ps.items_bytes));
   CHK(ensure(ctx->srcs_s, sizeof(SrcDev) * Ps.n_src));
   CHK(ensure(ctx->partials_s, sizeof(double) * (size_t)NACC * std::max(1, Ps.n_items)));
-  CHK(ensure(ctx->kept, sizeof(int) * std::max<size_t>(1, kept_rows.size())));
   HIPCHK(hipMemcpyAsync(ctx->imgs_s.p, Ps.imgs, sizeof(ImgDev) * Ps.n_img, hipMemcpyHostToDevice, st));
   if (Ps.n_items > 0)
-    HIPCHK(hipMemcpyAsync(ctx->items_s.p, Ps.items, sizeof(WorkItem) * Ps.n_items, hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(ctx->items_s.p, Ps.items, Ps.items_bytes, hipMemcpyHostToDevice, st));
   HIPCHK(hipMemcpyAsync(ctx->srcs_s.p, Ps.srcs, sizeof(SrcDev) * Ps.n_src, hipMemcpyHostToDevice, st));
-  if (!kept_rows.empty())
-    HIPCHK(hipMemcpyAsync(ctx->kept.p, kept_rows.data(), sizeof(int) * kept_rows.size(), hipMemcpyHostToDevice, st));
   const ImgDev* imgs = as<ImgDev>(ctx->imgs);
   const WorkItem* items = as<WorkItem>(ctx->items);
   const SrcDev* srcs = as<SrcDev>(ctx->srcs);
   const ImgDev* imgs_s = as<ImgDev>(ctx->imgs_s);
   const WorkItem* items_s = as<WorkItem>(ctx->items_s);
   const SrcDev* srcs_s = as<SrcDev>(ctx->srcs_s);
-  const int* kept = as<int>(ctx->kept);
+  const int* kept = reinterpret_cast<int*>(as<unsigned char>(ctx->items_s) + Ps.o_kept);
   float* tables = as<float>(ctx->tables);
   double* parts = as<double>(ctx->partials);
   double* parts_s = as<double>(ctx->partials_s);
