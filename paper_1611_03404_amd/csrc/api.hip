@@ -627,7 +627,7 @@ int ring_for(celeste_ctx* ctx, size_t bytes, size_t* piece) {
     if (ctx->ring_used[k]) HIPCHK(hipEventSynchronize(ctx->ring_ev[k]));   // (left by a call that failed)
     ctx->ring_used[k] = false;
   }
-  size_t p = PIECE_MIN;
+  size_t p = bytes <= 2 * PIECE_MIN ? PIECE_MIN : 4 * PIECE_MIN;
   while (p < PIECE_MAX && p * 4 < bytes) p *= 2;
   if (2 * p > ctx->h_ring.cap) {
     if (ctx->h_ring.p) (void)hipHostFree(ctx->h_ring.p);
