@@ -333,6 +333,7 @@ __global__ __launch_bounds__(BLOCK, MINW) void k_eval_full(const WorkItem* __res
   __syncthreads();
   const SkipTest& my_skip = skip[min(lane, n_gal - 1)];
   const unsigned long long gal_lanes = lane_mask(n_gal);
+  const float e_min = mark_odd(e_zero, my_skip, gal_lanes);
   double val = 0.0;                 // ELBO value, per lane
   // FP64 wavefront sums of the derivative entries, in LDS between flushes (ten registers a lane
   // otherwise): the first lane of each quad holds 5 of them
@@ -386,9 +387,8 @@ __global__ __launch_bounds__(BLOCK, MINW) void k_eval_full(const WorkItem* __res
     const float dx0 = live ? (float)col - psx : FAR, dy0 = live ? (float)row - psy : FAR;
 
     // galaxy components that may be non-zero on the tile
-    unsigned long long odd, hits = tile_hits(my_skip, tm, col, first, psx, psy, e_zero, &odd) & gal_lanes;
-    odd &= gal_lanes;
-    if (__builtin_expect(odd != 0ull, 0)) hits = (hits & ~odd) | odd_hits(odd, T, ncomp, dx0, dy0, e_zero);
+    unsigned long long hits = tile_hits(my_skip, tm, col, first, psx, psy, e_min) & gal_lanes;
+    hits = drop_odd(hits, my_skip, T, ncomp, dx0, dy0, e_min);
     bool hit = hits != 0ull;   // some component is not exactly 0 on this tile (wavefront-uniform)
 
     // ---- star: N, dN/dp, d2N/dp2; galaxy: Hermite moments per profile type.  The galaxy's hits are
@@ -417,7 +417,7 @@ __global__ __launch_bounds__(BLOCK, MINW) void k_eval_full(const WorkItem* __res
       const float dx = dx0 - r[S_XIX], dy = dy0 - r[S_XIY];
       const float dxx = dx * dx, dxy = dx * dy, dyy = dy * dy;
       const float e = fmaf(r[R_QXX], dxx, fmaf(r[R_QXY], dxy, fmaf(r[R_QYY], dyy, r[R_C0])));
-      if (wave_any(e >= e_zero)) {
+      if (wave_any(e >= e_min)) {
         hit = true;
         const float N = ex2(e);
         const float bx = fmaf(r[R_PXX], dx, r[R_PXY] * dy), by = fmaf(r[R_PXY], dx, r[R_PYY] * dy);
@@ -928,6 +928,7 @@ __global__ __launch_bounds__(BLOCK) void k_eval_grad(const WorkItem* __restrict_
   __syncthreads();
   const SkipTest& my_skip = skip[min(lane, n_gal - 1)];
   const unsigned long long gal_lanes = lane_mask(n_gal);
+  const float e_min = mark_odd(e_zero, my_skip, gal_lanes);
   double acc[NG];
 #pragma unroll
   for (int j = 0; j < NG; ++j) acc[j] = 0.0;
@@ -940,9 +941,8 @@ __global__ __launch_bounds__(BLOCK) void k_eval_grad(const WorkItem* __restrict_
     const float x = live ? xp : 0.f, ebg = sky + (live ? en : 0.f), vbg = live ? vn : 0.f;
     const float dx0 = live ? (float)col - psx : FAR, dy0 = live ? (float)row - psy : FAR;
 
-    unsigned long long odd, hits = tile_hits(my_skip, tm, col, first, psx, psy, e_zero, &odd) & gal_lanes;
-    odd &= gal_lanes;
-    if (__builtin_expect(odd != 0ull, 0)) hits = (hits & ~odd) | odd_hits(odd, T, ncomp, dx0, dy0, e_zero);
+    unsigned long long hits = tile_hits(my_skip, tm, col, first, psx, psy, e_min) & gal_lanes;
+    hits = drop_odd(hits, my_skip, T, ncomp, dx0, dy0, e_min);
     bool hit = hits != 0ull;
     float s0 = 0.f, s1x = 0.f, s1y = 0.f;
     GalAcc1 X = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, D = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -965,7 +965,7 @@ __global__ __launch_bounds__(BLOCK) void k_eval_grad(const WorkItem* __restrict_
       const float dx = dx0 - r[S_XIX], dy = dy0 - r[S_XIY];
       const float dxx = dx * dx, dxy = dx * dy, dyy = dy * dy;
       const float e = fmaf(r[R_QXX], dxx, fmaf(r[R_QXY], dxy, fmaf(r[R_QYY], dyy, r[R_C0])));
-      if (wave_any(e >= e_zero)) {
+      if (wave_any(e >= e_min)) {
         hit = true;
         const float N = ex2(e);
         s0 += N;

@@ -238,10 +238,11 @@ __device__ __forceinline__ void comp_value(const ValRec& r, float dxx, float dxy
 // The box says nothing of a component whose constants are not finite or not positive (an estimate's scale or a
 // WCS beyond FP32), nor may one be evaluated on pixels where it is 0 if it is so narrow, or so far off, that
 // its derivatives' polynomials overflow there (0 times infinity; a PSF of 1e-5 px).  Such a component is odd: it may
-// be non-zero on every tile, and a kernel of derivatives then tests it on the tile's pixels (odd_hits).
+// be non-zero on every tile, and a kernel of derivatives then tests it on the tile's pixels (drop_odd).
 struct SkipTest {
   float4 form;     // c0, A, B, C; an odd component: infinity, 0, 0, 0
   float4 geo;      // centre offset x, y (the PSF component's), B / 2C, B / 2A
+  __device__ __forceinline__ bool odd() const { return form.x == INFINITY; }
 };
 
 constexpr float FAR = 1.0e4f;      // offset used by lanes outside the image
@@ -311,32 +312,40 @@ __device__ __forceinline__ int low_bit(unsigned long long m) { return m ? __buil
 __device__ __forceinline__ unsigned long long lane_mask(int n) { return n >= 64 ? ~0ull : (1ull << n) - 1; }
 
 // Components (bit = the lane holding the component's test) that must be evaluated on tm's tile; col and
-// first are this lane's from tm.pixel.  *odd (where asked for): the odd ones, whose bound is not finite.
+// first are this lane's from tm.pixel.
 template <class MAP>
 __device__ __forceinline__ unsigned long long tile_hits(const SkipTest& s, const MAP& tm, int col, int first,
-                                                        float psx, float psy, float e_zero,
-                                                        unsigned long long* odd = nullptr) {
+                                                        float psx, float psy, float e_zero) {
   bool two;
-  const float e = exponent_bound(s, tm.box(col, first, false, &two), psx, psy);
-  unsigned long long hits = __ballot(!(e < e_zero));
-  if (odd) *odd = __ballot(!(e < INFINITY));
+  unsigned long long hits = __ballot(may_hit(s, tm.box(col, first, false, &two), psx, psy, e_zero));
   if (two) hits |= __ballot(may_hit(s, tm.box(col, first, true, &two), psx, psy, e_zero));
   return hits;
 }
 
-// Odd components whose exponent reaches the threshold on some pixel of the tile (derivative kernels; dx0, dy0: this
-// lane's offset from the source).
-__device__ __forceinline__ unsigned long long odd_hits(unsigned long long odd, const float* __restrict__ T, int ncomp,
-                                                       float dx0, float dy0, float e_zero) {
+// The threshold of a work item of the derivative kernels, with its last bit set where the item has an odd component (lanes:
+// the components' lanes).  A mark in a scalar that the tile loop holds anyway: one more of them, or a vector
+// comparison a tile, cost the value+gradient+Hessian kernel 2%.
+__device__ __forceinline__ float mark_odd(float e_zero, const SkipTest& s, unsigned long long lanes) {
+  const bool odd = (__ballot(s.odd()) & lanes) != 0ull;
+  // slightly lower, which skips no more; -infinity becomes the lowest finite value
+  return odd ? __uint_as_float(e_zero == -INFINITY ? 0xff7fffffu : __float_as_uint(e_zero) | 1u) : e_zero;
+}
+
+// hits without the odd components whose exponent reaches the threshold on no pixel of the tile (dx0, dy0: this
+// lane's offset from the source); where e_zero bears no mark, hits.
+__device__ __forceinline__ unsigned long long drop_odd(unsigned long long hits, const SkipTest& s,
+                                                       const float* __restrict__ T, int ncomp, float dx0, float dy0,
+                                                       float e_zero) {
   using namespace tab;
-  unsigned long long hits = 0ull;
-  for (; odd; odd &= odd - 1) {
-    const int c = __builtin_ctzll(odd);
-    const float* __restrict__ sr = T + STAR + (c / ncomp) * STAR_REC;
-    const ValRec r = load_val(T + EXPO + c * EXPO_REC);
-    const float dx = dx0 - sr[S_XIX], dy = dy0 - sr[S_XIY];
-    const float e = fmaf(r.qxx, dx * dx, fmaf(r.qxy, dx * dy, fmaf(r.qyy, dy * dy, r.c0)));
-    if (__ballot(e >= e_zero)) hits |= 1ull << c;
+  if (__builtin_expect(__float_as_uint(e_zero) & 1u, 0)) {
+    for (unsigned long long odd = __ballot(s.odd()) & hits; odd; odd &= odd - 1) {
+      const int c = __builtin_ctzll(odd);
+      const float* __restrict__ sr = T + STAR + (c / ncomp) * STAR_REC;
+      const ValRec r = load_val(T + EXPO + c * EXPO_REC);
+      const float dx = dx0 - sr[S_XIX], dy = dy0 - sr[S_XIY];
+      const float e = fmaf(r.qxx, dx * dx, fmaf(r.qxy, dx * dy, fmaf(r.qyy, dy * dy, r.c0)));
+      if (!__ballot(e >= e_zero)) hits &= ~(1ull << c);
+    }
   }
   return hits;
 }
