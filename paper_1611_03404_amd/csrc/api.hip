@@ -4,7 +4,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdarg>
@@ -14,12 +13,11 @@
 #include <mutex>
 #include <new>
 #include <string>
-#include <system_error>
-#include <thread>
 #include <unordered_map>
 #include <vector>
 
 #include "celeste_internal.h"
+#include "host_team.h"
 
 using namespace celeste;
 
@@ -311,75 +309,8 @@ struct Packed {
 };
 typedef std::vector<unsigned char> HostPack;
 
-// Host threads of one pass over a batch: fn(t, n, barrier) on n threads, the calling one among them.  A pass
-// costs about 50 ns an item and a thread about 10 us to start, so a thread is taken for every 2,048 items,
-// up to 16 (20,000 images packed: 10 threads; with one per 8,192, two).  Where a thread
-// cannot be started the pass runs on those that were.
-class Barrier {
- public:
-  void wait() {
-    const int g = gen_.load(std::memory_order_acquire);
-    if (in_.fetch_add(1, std::memory_order_acq_rel) + 1 == total_) {
-      in_.store(0, std::memory_order_relaxed);
-      gen_.fetch_add(1, std::memory_order_release);
-    } else {
-      while (gen_.load(std::memory_order_acquire) == g) std::this_thread::yield();
-    }
-  }
-  void set(int n) { total_ = n; }
-
- private:
-  int total_ = 1;
-  std::atomic<int> in_{0}, gen_{0};
-};
-
-int team_size(int64_t n) {
-  const int nt = (int)std::min<int64_t>(16, std::max<int64_t>(1, n / 2048));
-  return std::min<int>(nt, std::max(1u, std::thread::hardware_concurrency()));
-}
-
-template <class F>
-void team(int nt, F fn) {
-  Barrier bar;
-  std::atomic<int> go{0};   // the number of threads, once all have been started
-  std::vector<std::thread> th;
-  th.reserve(nt);
-  for (int t = 1; t < nt; ++t) {
-    try {
-      th.emplace_back([&, t] {
-        int n;
-        while ((n = go.load(std::memory_order_acquire)) == 0) std::this_thread::yield();
-        fn(t, n, bar);
-      });
-    } catch (const std::system_error&) {
-      break;
-    }
-  }
-  const int n = (int)th.size() + 1;
-  bar.set(n);
-  go.store(n, std::memory_order_release);
-  fn(0, n, bar);
-  for (auto& x : th) x.join();
-}
-
-// The first index of [0, n) for which ok(i) is false, or n.
-template <class F>
-int64_t first_failure(int64_t n, F ok) {
-  std::atomic<int64_t> bad{n};
-  team(team_size(n), [&](int t, int nt, Barrier&) {
-    for (int64_t i = n * t / nt; i < n * (t + 1) / nt; ++i)
-      if (!ok(i)) {
-        int64_t cur = bad.load();
-        while (i < cur && !bad.compare_exchange_weak(cur, i)) {
-        }
-        break;
-      }
-  });
-  return bad.load();
-}
-
 int check_thetas(const double* th, int64_t n) {
-  const int64_t bad = first_failure(n, [&](int64_t s) { return check_theta(th + s * NP, s) == CELESTE_OK; });
+  const int64_t bad = first_failure(n, 20, [&](int64_t s) { return check_theta(th + s * NP, s) == CELESTE_OK; });
   return bad < n ? check_theta(th + bad * NP, bad) : CELESTE_OK;
 }
 
@@ -423,10 +354,10 @@ int validate_and_pack(celeste_ctx* ctx, const celeste_batch* b, Packed* P, HostP
     int64_t bad = INT64_MAX, items = 0;
     int max_psf = 1;
   };
-  Slice sl[16];
+  Slice sl[TEAM_MAX];
   int rc = CELESTE_OK;
   int64_t bad = INT64_MAX, n_items = 0;
-  team(team_size(n_img), [&](int t, int nt, Barrier& bar) {
+  team(team_size(n_img, what == Pack::kCheck ? 8 : 20), [&](int t, int nt, Barrier& bar) {
     // sources whose first image lies in this thread's share of the images
     const auto first_src = [&](int k) {
       return k == nt ? S : (int)(std::lower_bound(b->image_offsets, b->image_offsets + S, n_img * k / nt) - b->image_offsets);
@@ -531,7 +462,7 @@ int subsample_items(celeste_ctx* ctx, const celeste_batch* b, Packed* P, const u
                     const int64_t* keep_off) {
   if (keep_off[0] != 0) return fail(CELESTE_E_INVALID, "keep_off[0] must be 0");
   const int64_t off_bad = first_failure(
-      P->n_img, [&](int64_t i) { return keep_off[i + 1] - keep_off[i] == (b->images[i].h + 7) / 8; });
+      P->n_img, 3, [&](int64_t i) { return keep_off[i + 1] - keep_off[i] == (b->images[i].h + 7) / 8; });
   if (off_bad < P->n_img)
     return fail(CELESTE_E_INVALID, "image %lld: keep_off must give (h + 7) / 8 blocks", (long long)off_bad);
   const int chunk = std::max(64, ctx->chunk_px), S = P->n_src;
@@ -539,9 +470,9 @@ int subsample_items(celeste_ctx* ctx, const celeste_batch* b, Packed* P, const u
   struct Slice {
     int64_t rows = 0, items = 0;
   };
-  Slice sl[16];
+  Slice sl[TEAM_MAX];
   int rc = CELESTE_OK;
-  team(team_size(n_img), [&](int t, int nt, Barrier& bar) {
+  team(team_size(n_img, 40), [&](int t, int nt, Barrier& bar) {
     const auto first_src = [&](int k) {
       return k == nt ? S : (int)(std::lower_bound(b->image_offsets, b->image_offsets + S, n_img * k / nt) - b->image_offsets);
     };
@@ -677,7 +608,7 @@ int ring_upload(celeste_ctx* ctx, const std::vector<Part>& parts, size_t total, 
   const int n_pieces = (int)((total + piece - 1) / piece);
   int rc = CELESTE_OK;             // the calling thread's
   bool stop[2] = {false, false};   // whether it failed, as all threads see it behind piece q's barrier: stop[q & 1]
-  team(team_size((int64_t)(total / 512)), [&](int t, int nt, Barrier& bar) {   // a thread packs 4 MB in 60 us
+  team(team_size((int64_t)(total / 1024), 60), [&](int t, int nt, Barrier& bar) {   // a thread packs 4 MB in 60 us
     for (int q = 0; q < n_pieces; ++q) {
       const size_t p0 = q * piece, n = std::min(total - p0, piece);
       unsigned char* buf = as<unsigned char>(ctx->h_ring) + (q & 1) * 4 * piece;
@@ -2278,33 +2209,37 @@ int check_disjoint(const std::vector<Patch>& pt, int n_fields) {
   struct Hit {
     int64_t i = INT64_MAX, j = 0;
   };
-  Hit hit[16];
-  team(std::min(team_size(8 * n), n_fields), [&](int t, int nt, Barrier&) {
-    const int f0 = (int)((int64_t)n_fields * t / nt), f1 = (int)((int64_t)n_fields * (t + 1) / nt);
-    struct Node {
-      int img, next;
-    };
-    std::vector<Node> nodes;
-    std::unordered_map<int64_t, int> last;   // newest node of a cell
-    last.reserve((size_t)(4 * n / nt));
-    for (int64_t i = 0; i < n && hit[t].i == INT64_MAX; ++i) {
-      const Patch& a = pt[i];
-      if (a.field < f0 || a.field >= f1) continue;
-      const int64_t fkey = (int64_t)a.field << 40;
-      for (int64_t cy = a.y / CELL; cy <= (a.y + a.h - 1) / CELL; ++cy)
-        for (int64_t cx = a.x / CELL; cx <= (a.x + a.w - 1) / CELL && hit[t].i == INT64_MAX; ++cx) {
-          auto e = last.emplace(fkey ^ (cx << 20) ^ cy, -1).first;
-          for (int k = e->second; k >= 0; k = nodes[k].next) {   // newest first: the last match is the first image
-            const Patch& c = pt[nodes[k].img];
-            if (c.field == a.field && a.x < c.x + c.w && c.x < a.x + a.w && a.y < c.y + c.h && c.y < a.y + a.h)
-              hit[t] = Hit{i, nodes[k].img};
+  Hit hit[TEAM_MAX];
+  try {
+    team(std::min(team_size(n, 35), n_fields), [&](int t, int nt, Barrier&) {
+      const int f0 = (int)((int64_t)n_fields * t / nt), f1 = (int)((int64_t)n_fields * (t + 1) / nt);
+      struct Node {
+        int img, next;
+      };
+      std::vector<Node> nodes;
+      std::unordered_map<int64_t, int> last;   // newest node of a cell
+      last.reserve((size_t)(4 * n / nt));
+      for (int64_t i = 0; i < n && hit[t].i == INT64_MAX; ++i) {
+        const Patch& a = pt[i];
+        if (a.field < f0 || a.field >= f1) continue;
+        const int64_t fkey = (int64_t)a.field << 40;
+        for (int64_t cy = a.y / CELL; cy <= (a.y + a.h - 1) / CELL; ++cy)
+          for (int64_t cx = a.x / CELL; cx <= (a.x + a.w - 1) / CELL && hit[t].i == INT64_MAX; ++cx) {
+            auto e = last.emplace(fkey ^ (cx << 20) ^ cy, -1).first;
+            for (int k = e->second; k >= 0; k = nodes[k].next) {   // newest first: the last match is the first image
+              const Patch& c = pt[nodes[k].img];
+              if (c.field == a.field && a.x < c.x + c.w && c.x < a.x + a.w && a.y < c.y + c.h && c.y < a.y + a.h)
+                hit[t] = Hit{i, nodes[k].img};
+            }
+            nodes.push_back(Node{(int)i, e->second});
+            e->second = (int)nodes.size() - 1;
           }
-          nodes.push_back(Node{(int)i, e->second});
-          e->second = (int)nodes.size() - 1;
-        }
-    }
-  });
-  const Hit* h = std::min_element(hit, hit + 16, [](const Hit& a, const Hit& b) { return a.i < b.i; });
+      }
+    });
+  } catch (const std::bad_alloc&) {
+    return fail(CELESTE_E_NOMEM, "host allocation of the patches' grid failed");
+  }
+  const Hit* h = std::min_element(hit, hit + TEAM_MAX, [](const Hit& a, const Hit& b) { return a.i < b.i; });
   if (h->i != INT64_MAX)
     return fail(CELESTE_E_INVALID, "images %lld and %lld overlap in field %d", (long long)h->j, (long long)h->i,
                 pt[h->i].field);
@@ -2330,7 +2265,7 @@ int check_fields(const celeste_batch* b, const Packed& P, const celeste_fields* 
   if (f->n_fields < 1 || f->height < 1 || f->width < 1 || f->reserved != 0)
     return fail(CELESTE_E_INVALID, "bad field dimensions");
   if (patches) patches->resize((size_t)P.n_img);
-  const int64_t bad = first_failure(P.n_img, [&](int64_t i) {
+  const int64_t bad = first_failure(P.n_img, 4, [&](int64_t i) {
     if (check_patch(b, f, i) != CELESTE_OK) return false;
     const celeste_image& im = b->images[i];
     if (patches) (*patches)[i] = Patch{f->img_field[i], (int)im.origin[0], (int)im.origin[1], im.w, im.h};
@@ -2371,7 +2306,7 @@ int tile_lists(celeste_ctx* ctx, const std::vector<Patch>& pt, int n_fields, int
   size_t n_ints = 0;
   int* out = nullptr;
   int rc = CELESTE_OK;
-  team(std::min(team_size(8 * n), n_fields), [&](int t, int nt, Barrier& bar) {
+  team(std::min(team_size(n, 80), n_fields), [&](int t, int nt, Barrier& bar) {
     const int f0 = (int)((int64_t)n_fields * t / nt), f1 = (int)((int64_t)n_fields * (t + 1) / nt);
     const auto each = [&](auto fn) {
       for (int64_t i = 0; i < n; ++i) {
