@@ -106,6 +106,8 @@ enum {                          /* context options (celeste_ctx_set_option) */
                                    still being fitted are compacted into a device list, and a
                                    persistent grid of the pixel kernel draws them in turn (grids do
                                    not shrink otherwise: blocks of finished sources exit at once).
+                                   A fit of no more work items than the grid has blocks, which all run
+                                   at once, takes one block per work item and no list.
                                    n in 1..16 = n blocks per compute unit; -1 (default) = as many
                                    blocks per compute unit as the launched kernel instance keeps
                                    resident (its register budget, CELESTE_OPT_VARIANT bit 0);
@@ -139,9 +141,12 @@ enum {                          /* context options (celeste_ctx_set_option) */
 typedef struct celeste_stats {
   int64_t full_px;              /* pixel evaluations by the value+gradient+Hessian kernel */
   int64_t value_px;             /* pixel evaluations by the value-only kernel */
-  int64_t full_launches;        /* launches of the value+gradient+Hessian pixel kernel */
-  int64_t value_launches;       /* launches of the value-only pixel kernel */
-  int64_t iterations;           /* trust-region iterations enqueued (all sources together) */
+  int64_t full_launches;        /* launches of the value+gradient+Hessian pixel kernel (of a fit: those of
+                                   the iterations counted below) */
+  int64_t value_launches;       /* launches of the value-only pixel kernel (likewise) */
+  int64_t iterations;           /* trust-region iterations (all sources together), up to the poll that found
+                                   every source done; those enqueued behind it while its count was on
+                                   the way, which find nothing to do, are not counted */
   /* milliseconds per phase, measured with HIP events on the library's stream; only
    * accumulated while CELESTE_OPT_PROFILE is set */
   double ms_setup, ms_full, ms_reduce_full, ms_tr, ms_value, ms_reduce_value, ms_accept;
@@ -169,8 +174,8 @@ typedef struct celeste_stats {
   /* Jacobi sweeps of the eigendecomposition solves, the solves that reached the 40-sweep cap, and
    * Newton steps on the multiplier of the boundary solves by Cholesky */
   int64_t tr_sweeps, tr_sweep_cap, tr_newton_steps;
-  /* blocks of the last trust-region fit's persistent value+gradient+Hessian grid (0: one block per
-   * work item; CELESTE_OPT_PERSISTENT) */
+  /* blocks of the persistent value+gradient+Hessian grid of the last trust-region fit (0 with
+   * CELESTE_OPT_PERSISTENT 0); a fit of no more work items than that ran one block per item */
   int64_t fit_grid_blocks;
   /* with CELESTE_OPT_TRIAL_DERIVATIVES: pixel evaluations of the value+gradient+Hessian passes at
    * trial points (included in full_px), and the pixels of the sources at each accepted step (the

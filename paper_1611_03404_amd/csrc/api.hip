@@ -1628,7 +1628,7 @@ int fit_results(celeste_ctx* ctx, const celeste_batch* b, const FitDev& F, int S
 
 // Replays (graph) or enqueues (eager) `iteration` until no source is active or max_loops loop
 // steps; the host reads the device's active count of every `poll` steps.
-// count(stats) records the launches of one executed step (replayed or enqueued).
+// count(stats) records the launches of one step (replayed or enqueued) up to the poll that ends the loop.
 template <class Iter, class Count>
 int run_loop(celeste_ctx* ctx, hipStream_t st, int max_loops, int poll, bool use_graph, const int* n_active_dev,
              PhaseTimer& T, Iter iteration, Count count, void (*account)(celeste_ctx*, PhaseTimer&)) {
