@@ -108,11 +108,12 @@ __device__ __forceinline__ void kl_value_grad(const double* th, const PriorDev& 
   k.g[2] += -dkla - ktype[0] + ktype[1];
 }
 
+template <int U = 8>
 __device__ void kl_value_grad(const double* th, const PriorDev& pr, KL& k) {
   double l[KL_LOGS];
 #pragma unroll
   for (int i = 0; i < KL_LOGS; ++i) l[i] = log(kl_log_arg(th, pr, i));
-  kl_value_grad<8>(th, pr, k, [&](int i) { return l[i]; });
+  kl_value_grad<U>(th, pr, k, [&](int i) { return l[i]; });
 }
 
 // ... by a wavefront, a logarithm per lane (one lane's chain of 14 took a third of a small batch's reduction).
@@ -373,8 +374,8 @@ __global__ __launch_bounds__(64) void k_prior_term(const double* __restrict__ th
                                                    double* __restrict__ out) {
   const int s = blockIdx.x * 64 + threadIdx.x;
   if (s >= n_src) return;
-  KL k;
-  kl_value_grad(theta + (size_t)s * NP, prior, k);
+  KL k;   // its value alone is used: with every loop unrolled its arrays are left out (680 bytes of scratch a lane otherwise)
+  kl_value_grad<NP>(theta + (size_t)s * NP, prior, k);
   out[s] = k.val;
 }
 
