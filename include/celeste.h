@@ -299,9 +299,10 @@ void celeste_fit_opts_default(celeste_fit_opts* opts);
  *           value+gradient pixel kernel runs (no Hessian work), with neither the value kernel
  *   stream: hipStream_t to run on, or NULL for the context's stream.  The call
  *           returns after the results are written (host or device memory).
- * Pixel arrays are checked on the device first: any negative or non-finite pixel or
- * neighbour value makes the call fail with E_INVALID before any evaluation.
- * Errors: E_INVALID (validation; nothing is launched), E_DEVICE, E_NOMEM. */
+ * Pixel arrays and estimates are checked: any negative or non-finite pixel or neighbour value,
+ * and any theta out of its range, makes the call fail with E_INVALID.  Device memory is
+ * checked on the device, in the stream of the evaluation, whose results are not written then.
+ * Errors: E_INVALID (validation; no output is written), E_DEVICE, E_NOMEM. */
 int celeste_elbo_eval(celeste_ctx* ctx, const celeste_batch* batch, const double* theta,
                       double* elbo, double* grad, double* hess, void* stream);
 

@@ -79,8 +79,8 @@ struct celeste_ctx {
   int vblock = 256;      // value kernel block size
   int vtile_log2 = 3;    // log2 tile width of the value kernel
   DevBuf meta, items_kept;                // packed metadata (one upload); a subsample's work items and kept rows
-  DevBuf imgs, items, srcs, flag;         // where the last pack's parts lie in them (views, not owned)
-  DevBuf tables, partials, img_const, staging, theta, o_elbo, o_grad, o_hess;
+  DevBuf imgs, items, srcs;               // where the last pack's parts lie in them (views, not owned)
+  DevBuf tables, partials, img_const, staging, theta, o_elbo;
   DevBuf st_buf;   // all trust-region state in one allocation
   DevBuf ctr;      // device counters: pixel evaluations [full, value, grad], subproblem paths and work [3..8]
   int profile = 0;
@@ -728,7 +728,6 @@ int ctx_bufs(celeste_ctx* ctx, const Packed* P, EvalBufs* B) {
   ctx->imgs.p = B->imgs;
   ctx->srcs.p = B->srcs;
   ctx->items.p = B->items;
-  ctx->flag.p = B->flag;
   B->img_const = as<double>(ctx->img_const);
   B->tables = as<float>(ctx->tables);
   B->partials = as<double>(ctx->partials);
@@ -921,7 +920,7 @@ void celeste_ctx_destroy(celeste_ctx* c) {
   (void)hipSetDevice(c->device);
   (void)hipStreamSynchronize(c->stream);
   DevBuf* bufs[] = {&c->meta, &c->items_kept, &c->tables, &c->partials, &c->img_const, &c->staging,
-                    &c->theta, &c->o_elbo, &c->o_grad, &c->o_hess, &c->st_buf, &c->ctr, &c->sur,
+                    &c->theta, &c->o_elbo, &c->st_buf, &c->ctr, &c->sur,
                     &c->tile_off, &c->img_field, &c->nbr_off, &c->tables2, &c->fsky, &c->theta_flag,
                     &c->lr_in, &c->lr_cov, &c->lr_status, &c->lr_eval,
                     &c->lfact, &c->lb_buf, &c->imgs_s, &c->items_s, &c->srcs_s, &c->partials_s, &c->qbuf};

@@ -18,8 +18,8 @@
 //
 // Work that is exactly zero is skipped, never approximated: a mixture component whose
 // exponent is below the exact-zero threshold on every lane of a wavefront has density exactly 0 in
-// FP32 there, so all its contributions are exactly 0.  For the galaxy components of k_eval_full that is
-// decided before any is evaluated, one component per lane, from the tile's box (tiles.h).  Lanes of a
+// FP32 there, so all its contributions are exactly 0.  For the galaxy components that is decided before any
+// is evaluated, one component per lane, from the tile's box (tiles.h).  Lanes of a
 // tile that fall outside the image evaluate a point far from every component with a zero count and zero
 // background variance, which makes every one of their terms exactly 0 as well.
 //

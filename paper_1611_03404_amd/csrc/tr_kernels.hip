@@ -1,15 +1,15 @@
 // Trust-region Newton state machine on the device (section III-B: Newton's method
 // with updates constrained by a trust region, dense hand-derived Hessian, per
-// source).  One wavefront per active source solves the 27x27 FP64 subproblem
+// source).  A block of four wavefronts per active source solves the 27x27 FP64 subproblem
 //     maximise g'p + p'Hp/2  subject to |p| <= Delta     (unconstrained coordinates)
 // through a cyclic Jacobi eigendecomposition of B = -H (parallel round-robin
-// ordering, 14 disjoint rotations per round applied to B in LDS by 2x2 blocks, one
-// barrier after the rotation parameters and one after the update), followed by the secular
+// ordering, 14 disjoint rotations per round, applied to B in LDS by 2x2 blocks and to the
+// eigenvectors in registers while the next round's are formed, one barrier a round), followed by the secular
 // equation |(B + sI)^{-1} g| = Delta solved by safeguarded Newton on 1/|p(s)|
 // (More-Sorensen), including the hard case.  Where B is positive definite, Cholesky
 // factorisations of B + lam I give the step instead (the interior Newton step, or the
 // boundary step by Newton's method on lam).  A separate kernel applies the
-// ratio test and updates the radius, one thread per source.
+// ratio test, updates the radius and takes an accepted step over, one wavefront per source.
 #include <math.h>
 
 #include "celeste_internal.h"
