@@ -576,6 +576,7 @@ int ring_for(celeste_ctx* ctx, size_t bytes, size_t* piece) {
 void ring_map_more(celeste_ctx* ctx, hipStream_t st) {
   const volatile unsigned char* p = as<unsigned char>(ctx->h_ring);
   while (ctx->ring_mapped >= 2 * PIECE_MIN && ctx->ring_mapped < ctx->h_ring.cap && hipStreamQuery(st) == hipErrorNotReady) {
+    (void)hipGetLastError();   // "not ready" is no error of a later launch
     for (int k = 0; k < 8 && ctx->ring_mapped < ctx->h_ring.cap; ++k, ctx->ring_mapped += 4096) (void)p[ctx->ring_mapped];
   }
 }

@@ -78,3 +78,16 @@ def test_results_in_pieces(cb):
             many.append(m)
         _same(ctx, *many, th, "hess")
     ctx.close()
+
+
+def test_no_error_is_left_behind(cb):
+    """While a call waits for its kernels it asks the stream whether it is done: the answer "not yet" must not
+    come up as the error of somebody's next launch."""
+    ctx = cb.Context(0)
+    host, _, th = _batches(cb, 300, 64, 64, False, 1)
+    hip_last_error = cb.load().hipGetLastError
+    for k in range(6):
+        print("call", k, flush=True)
+        ctx.elbo_eval(host, th, want="hess")
+        assert hip_last_error() == 0
+    ctx.close()
