@@ -138,12 +138,9 @@ struct TileMap {
       }
       const bool full = b < nb - 1 || hl == 8;
       // q / hl in the last band: (q + 1/2) / hl is at least 1/14 from an integer, so its floor is
-      // exact where the quotient's FP32 rounding is below that
+      // exact where the quotient's FP32 rounding is below that (at a width of 3e7 it is off by up to 3)
       int cl = (int)(((float)q + 0.5f) * inv_hl);
-      if (w > 65536) {
-        cl -= (cl * hl > q) ? 1 : 0;
-        cl += ((cl + 1) * hl <= q) ? 1 : 0;
-      }
+      if (w > 65536) cl = (int)((unsigned)q / (unsigned)hl);
       col = full ? q >> 3 : cl;
       row = first + (full ? (q & 7) : q - cl * hl);
     } else {
