@@ -548,7 +548,7 @@ int subsample_items(celeste_ctx* ctx, const celeste_batch* b, Packed* P, const u
 // made a context's first call on 100 sources' pixels (3.5 MB) take 1,430 us with one pinned buffer
 // for all of them (670 us through pageable memory).  So the pieces begin with 256 KB each, or a 32nd of a
 // large transfer, and while a call waits for its kernels it maps more of the ring, which the next calls use:
-// 620 us for the first, 315 us in steady state (370 with one buffer, 420 pageable).
+// 640 us for the first, 330 us in steady state (370 with one buffer, 420 pageable).
 constexpr size_t PIECE_MIN = (size_t)256 << 10, PIECE_MAX = (size_t)4 << 20;
 
 // The ring for a transfer of `bytes`, its pieces free: *piece bytes each, the second behind the first.
