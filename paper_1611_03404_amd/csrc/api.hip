@@ -1193,8 +1193,9 @@ int eval_impl(celeste_ctx* ctx, const celeste_batch* b, const double* theta, dou
   if (on_host) ring_map_more(ctx, st);
   int bad = 0;
   HIPCHK(hipMemcpyAsync(&bad, B.flag, sizeof(int), hipMemcpyDeviceToHost, st));
-  // (the pixels' copies out of the ring are ahead in the stream)
-  const bool one_copy = on_host && sizeof(double) * n_out <= ctx->ring_mapped;
+  // results that fit in what the ring has used, or in 256 KB of it (it holds at least two such pieces), come with the
+  // flag; the pixels' copies out of the ring are ahead in the stream
+  const bool one_copy = on_host && sizeof(double) * n_out <= std::max(ctx->ring_mapped, PIECE_MIN);
   if (one_copy) HIPCHK(hipMemcpyAsync(ctx->h_ring.p, d_elbo, sizeof(double) * n_out, hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
   if (noalloc) {
