@@ -551,8 +551,9 @@ int subsample_items(celeste_ctx* ctx, const celeste_batch* b, Packed* P, const u
 // 640 us for the first, 330 us in steady state (370 with one buffer, 420 pageable).
 constexpr size_t PIECE_MIN = (size_t)256 << 10, PIECE_MAX = (size_t)4 << 20;
 
-// The ring for a transfer of `bytes`, its pieces free: *piece bytes each, the second behind the first.
-int ring_for(celeste_ctx* ctx, size_t bytes, size_t* piece) {
+// The ring for a transfer of `bytes`, its pieces free: *piece bytes each, the second behind the first.  Where it exists
+// and is small, it is made larger only if `grow`.
+int ring_for(celeste_ctx* ctx, size_t bytes, bool grow, size_t* piece) {
   for (int k = 0; k < 2; ++k) {
     if (!ctx->ring_ev[k]) HIPCHK(hipEventCreateWithFlags(&ctx->ring_ev[k], hipEventDisableTiming));
     if (ctx->ring_used[k]) HIPCHK(hipEventSynchronize(ctx->ring_ev[k]));   // (left by a call that failed)
@@ -560,25 +561,29 @@ int ring_for(celeste_ctx* ctx, size_t bytes, size_t* piece) {
   }
   size_t p = bytes <= 2 * PIECE_MIN ? PIECE_MIN : 4 * PIECE_MIN;
   while (p < PIECE_MAX && p * 4 < bytes) p *= 2;
-  if (2 * p > ctx->h_ring.cap) {
+  if (2 * p > ctx->h_ring.cap && (grow || !ctx->h_ring.p)) {
     if (ctx->h_ring.p) (void)hipHostFree(ctx->h_ring.p);
     ctx->h_ring = DevBuf{};
     ctx->ring_mapped = 0;
     CHK(ensure_host(ctx->h_ring, 2 * p));
   }
-  const size_t least = std::max(PIECE_MIN, std::min(PIECE_MAX, bytes / 32 & ~(size_t)4095));
+  const size_t most = std::min(PIECE_MAX, ctx->h_ring.cap / 2 & ~(size_t)4095);
+  const size_t least = std::max(PIECE_MIN, std::min(most, bytes / 32 & ~(size_t)4095));
   *piece = bytes <= 2 * PIECE_MIN ? 2 * PIECE_MIN : std::max(least, ctx->ring_mapped / 2 & ~(size_t)4095);
   ctx->ring_mapped = std::max(ctx->ring_mapped, std::min(bytes, 2 * least));
   return CELESTE_OK;
 }
 
-// Maps more of the ring for as long as the stream has work.
-void ring_map_more(celeste_ctx* ctx, hipStream_t st) {
+// Maps more of the ring for as long as the stream has work, where the context moves more than 256 KB: pixels, or the
+// results of `bytes`.
+void ring_map_more(celeste_ctx* ctx, size_t bytes, hipStream_t st) {
   const volatile unsigned char* p = as<unsigned char>(ctx->h_ring);
-  while (ctx->ring_mapped >= 2 * PIECE_MIN && ctx->ring_mapped < ctx->h_ring.cap && hipStreamQuery(st) == hipErrorNotReady) {
+  if (ctx->ring_mapped < 2 * PIECE_MIN && bytes <= PIECE_MIN) return;
+  while (ctx->ring_mapped < ctx->h_ring.cap && hipStreamQuery(st) == hipErrorNotReady) {
     (void)hipGetLastError();   // "not ready" is no error of a later launch
     for (int k = 0; k < 8 && ctx->ring_mapped < ctx->h_ring.cap; ++k, ctx->ring_mapped += 4096) (void)p[ctx->ring_mapped];
   }
+  ctx->ring_mapped = std::min(ctx->ring_mapped, ctx->h_ring.cap);   // (it need not begin at a page)
 }
 
 int ring_mark(celeste_ctx* ctx, int k, hipStream_t st) {
@@ -604,7 +609,7 @@ struct Part {
 // stream when this returns.
 int ring_upload(celeste_ctx* ctx, const std::vector<Part>& parts, size_t total, void* dst, hipStream_t st) {
   size_t piece;
-  CHK(ring_for(ctx, 4 * total, &piece));
+  CHK(ring_for(ctx, 4 * total, true, &piece));
   piece /= 4;
   const int n_pieces = (int)((total + piece - 1) / piece);
   int rc = CELESTE_OK;             // the calling thread's
@@ -647,7 +652,7 @@ int ring_upload(celeste_ctx* ctx, const std::vector<Part>& parts, size_t total, 
 template <class F>
 int ring_download(celeste_ctx* ctx, const double* src, size_t n, hipStream_t st, F give) {
   size_t piece;
-  CHK(ring_for(ctx, sizeof(double) * n, &piece));
+  CHK(ring_for(ctx, sizeof(double) * n, false, &piece));
   const size_t per = piece / sizeof(double), n_pieces = (n + per - 1) / per;
   for (size_t q = 0; q <= n_pieces; ++q) {
     if (q < n_pieces) {
@@ -1190,7 +1195,7 @@ int eval_impl(celeste_ctx* ctx, const celeste_batch* b, const double* theta, dou
     launches = &ctx->stats.value_launches;
   }
   T.mark(3, st);
-  if (on_host) ring_map_more(ctx, st);
+  if (on_host) ring_map_more(ctx, sizeof(double) * n_out, st);
   int bad = 0;
   HIPCHK(hipMemcpyAsync(&bad, B.flag, sizeof(int), hipMemcpyDeviceToHost, st));
   // results that fit in what the ring has used, or in 256 KB of it (it holds at least two such pieces), come with the
@@ -1216,10 +1221,18 @@ int eval_impl(celeste_ctx* ctx, const celeste_batch* b, const double* theta, dou
         if (b0 < b1) std::memcpy(to[k] + (b0 - first), src + (b0 - at), sizeof(double) * (b1 - b0));
       }
     };
-    if (one_copy)
+    if (one_copy) {
       give(as<double>(ctx->h_ring), 0, n_out);
-    else
+    } else if (ctx->ring_mapped >= 2 * PIECE_MIN || sizeof(double) * n_out <= 4 * PIECE_MIN) {
       CHK(ring_download(ctx, d_elbo, n_out, st, give));
+    } else {
+      // a new ring, or the first use of what there is of one, costs more than pageable copies from about 1 MB: first
+      // Hessians of 300 sources of 5 x 5 pixels 400 us, 920 through a ring made for them; 330 and 304 later on
+      HIPCHK(hipMemcpyAsync(elbo, d_elbo, sizeof(double) * S, hipMemcpyDeviceToHost, st));
+      if (grad) HIPCHK(hipMemcpyAsync(grad, d_grad, sizeof(double) * S * NP, hipMemcpyDeviceToHost, st));
+      if (hess) HIPCHK(hipMemcpyAsync(hess, d_hess, sizeof(double) * S * NP * NP, hipMemcpyDeviceToHost, st));
+      HIPCHK(hipStreamSynchronize(st));
+    }
   }
   if (T.on) {
     ctx->stats.ms_setup += T.span(0, 1);

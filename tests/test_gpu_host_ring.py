@@ -80,6 +80,20 @@ def test_results_in_pieces(cb):
     ctx.close()
 
 
+@pytest.mark.parametrize("n", [46, 47, 93, 94, 186, 187, 400])
+def test_results_beside_few_pixels(cb, n):
+    """Hessians (5,624 bytes a source) of one image of 5 x 5 pixels each, on either side of 256 KB, 512 KB and 1 MB, in a
+    new context and in one whose ring has come to be mapped whole meanwhile."""
+    ctx = cb.Context(0)
+    host, dev, th = _batches(cb, 1, 5, 5, False, n)
+    th = perturb_theta(np.repeat(th, n, axis=0), n)
+    host, dev = (b.subset(np.zeros(n, np.int64))[0] for b in (host, dev))
+    for k in range(8):
+        print("few pixels", n, k, flush=True)
+        _same(ctx, host, dev, th, "hess")
+    ctx.close()
+
+
 def test_no_error_is_left_behind(cb):
     """While a call waits for its kernels it asks the stream whether it is done: the answer "not yet" must not
     come up as the error of somebody's next launch."""
